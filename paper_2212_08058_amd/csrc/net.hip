@@ -8,7 +8,7 @@
 // the matrix cores (v_mfma_f32_16x16x16_bf16): per wavefront a 16-channel x
 // 16-voxel output block accumulates 27 taps of (16 out x 16 in) weights times
 // (16 in x 16 voxels) inputs; so do their weight gradients (wgrad16_kernel,
-// a sum over voxels of 16 x 16 outer products per tap). The 1 -> 16 and
+// a sum over voxels of 16 x 16 outer products per tap, 32 voxels an instruction). The 1 -> 16 and
 // 16 -> 1 layers and their weight gradients are VALU kernels (their shapes fit
 // the matrix cores badly).
 //
@@ -97,6 +97,17 @@ struct Dims {
 __device__ __forceinline__ bool inside(const Dims &d, int t, int y, int x) {
     return (unsigned)t < (unsigned)d.T && (unsigned)y < (unsigned)d.H && (unsigned)x < (unsigned)d.W;
 }
+
+// Work unit of a workgroup: consecutive units share an XCD (workgroups are
+// dealt round-robin over the 8 XCDs), so neighbours find each other's rows in
+// the same L2. -1 for workgroups past the last unit.
+constexpr int XCDS = 8;
+__device__ __forceinline__ int net_unit(int block, int n) {
+    const int per = (n + XCDS - 1) / XCDS;
+    const int u = (block % XCDS) * per + block / XCDS;
+    return u < n ? u : -1;
+}
+inline int net_grid(int n) { return (n + XCDS - 1) / XCDS * XCDS; }
 
 // Raw buffer loads over a channels-last activation volume: an out-of-range
 // byte offset reads 0, so the loads of the zero padding need no branch (and
@@ -362,58 +373,170 @@ __global__ __launch_bounds__(256) void out_bwd_kernel(Dims d, const float *gy, c
 
 // Weight and bias gradients of a 16 -> 16 layer on the matrix cores. For each
 // tap, dW_tap[co][ci] = sum_v g[v][co] a[v + tap][ci] is a (16 x V) x (V x 16)
-// product: v_mfma_f32_16x16x4f32 takes 4 voxels per instruction, lane l
-// holding g[v0 + l/16][co = l%16] (A) and a[v0 + l/16 + tap][ci = l%16] (B),
-// so a wavefront's loads are contiguous runs of the channels-last volumes.
-// Operands are the stored bfloat16 values widened exactly to float, so the
-// products and FP32 sums are those of a bfloat16 matrix product with FP32
-// accumulation. Each workgroup writes its partial sums ([co][ci * 27 + tap],
-// then the bias of co); wgrad_reduce sums them.
-__global__ __launch_bounds__(256, 2) void wgrad16_kernel(Dims d, const short *a, const short *g, float *partials) {
+// product: v_mfma_f32_16x16x32_bf16 takes 32 voxels of a row per instruction,
+// lane l holding 8 consecutive voxels of channel l % 16 of g (A) and of a (B).
+// The volumes are channels-last, so rows are transposed on their way into LDS
+// (blocks of 4 voxels x 8 channels per thread, byte permutes in registers).
+// A workgroup walks down a WG_XC-voxel wide strip of one frame: per row step
+// it stages one row of a of the three frames t - 1 .. t + 1 (a ring of four
+// rows per frame) and one row of g, and each wavefront forms all 27 taps of
+// 32 voxels: the three x shifts are taken on g (12 fragment reads for 27
+// products), the nine (t, y) shifts are the staged rows of a. Rows, columns
+// and frames outside the volume are staged as zeros. The strips' row steps
+// are dealt out as equal contiguous ranges, one per workgroup.
+// Operands are the stored bfloat16 values, products are exact, sums FP32. Each
+// workgroup writes its partial sums ([co][ci * 27 + tap], then the bias of
+// co); wgrad_reduce sums them.
+// Bound by the matrix cores and the LDS reads (27 products per 12 reads). The
+// form with one 16-bit load per (voxel, tap) and K = 4 float products it
+// replaces took 606 us at 16x240x432; this takes 51.5 us (two reads of 53 MB).
+constexpr int WG_XC = 128;              // strip width: 32 voxels per wavefront
+constexpr int WG_AP = WG_XC + 8;        // halves per transposed row of a (conflict-free 16-byte reads)
+constexpr int WG_GP = WG_XC + 24;       // the same for g, with its neighbours at x - 1 and x + WG_XC
+constexpr int WG_GO = 8;                // index of the strip's first voxel in a row of g
+constexpr int WG_ROW_A = C * WG_AP, WG_ROW_G = C * WG_GP;
+
+__device__ __forceinline__ uint4 load_b128(__amdgpu_buffer_rsrc_t r, uint32_t boff) {
+    return __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, boff, 0, 0));
+}
+
+// One thread's block of a channels-last row: 4 consecutive voxels (from byte
+// offset row + 32 x of the volume) x 8 channels (half 0 or 1).
+struct Block4x8 {
+    uint4 v[4];
+};
+__device__ __forceinline__ void load_block(Block4x8 &b, __amdgpu_buffer_rsrc_t r, bool rowok, uint32_t row, int x,
+                                           int W, int half) {
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+        b.v[j] = load_b128(r, rowok && x + j < W ? row + (uint32_t)(x + j) * (C * 2) + 16 * half : OOB_OFF);
+}
+// Writes it transposed: channel 8 half + c at dst + (8 half + c) * pitch.
+__device__ __forceinline__ void store_block(const Block4x8 &b, short *dst, int pitch, int half) {
+    const uint32_t w[4][4] = {{b.v[0].x, b.v[0].y, b.v[0].z, b.v[0].w},
+                              {b.v[1].x, b.v[1].y, b.v[1].z, b.v[1].w},
+                              {b.v[2].x, b.v[2].y, b.v[2].z, b.v[2].w},
+                              {b.v[3].x, b.v[3].y, b.v[3].z, b.v[3].w}};
+#pragma unroll
+    for (int c = 0; c < 8; ++c) {
+        const uint32_t sel = (c & 1) ? 0x07060302u : 0x05040100u;
+        uint2 o;
+        o.x = __builtin_amdgcn_perm(w[1][c / 2], w[0][c / 2], sel);
+        o.y = __builtin_amdgcn_perm(w[3][c / 2], w[2][c / 2], sel);
+        *reinterpret_cast<uint2 *>(dst + (8 * half + c) * pitch) = o;
+    }
+}
+
+// Row steps of the weight-gradient strips: index r is row y of strip xc of
+// frame t, r = (t * nxc + xc) * H + y; workgroup `unit` of n owns an equal share.
+__device__ __forceinline__ int strip_count(const Dims &d) { return (d.W + WG_XC - 1) / WG_XC; }
+__device__ __forceinline__ int share_begin(const Dims &d, int unit, int n) {
+    return (int)((int64_t)unit * d.T * strip_count(d) * d.H / n);
+}
+
+// Fragment of 8 consecutive voxels shifted by one: elements -1 .. 6 or 1 .. 8
+// around the aligned block m (prev and next hold the neighbouring pairs).
+__device__ __forceinline__ bf16v8 shift_up(const uint4 &m, uint32_t prev) {
+    const uint4 r = {__builtin_amdgcn_alignbit(m.x, prev, 16), __builtin_amdgcn_alignbit(m.y, m.x, 16),
+                     __builtin_amdgcn_alignbit(m.z, m.y, 16), __builtin_amdgcn_alignbit(m.w, m.z, 16)};
+    return __builtin_bit_cast(bf16v8, r);
+}
+__device__ __forceinline__ bf16v8 shift_down(const uint4 &m, uint32_t next) {
+    const uint4 r = {__builtin_amdgcn_alignbit(m.y, m.x, 16), __builtin_amdgcn_alignbit(m.z, m.y, 16),
+                     __builtin_amdgcn_alignbit(m.w, m.z, 16), __builtin_amdgcn_alignbit(next, m.w, 16)};
+    return __builtin_bit_cast(bf16v8, r);
+}
+__device__ __forceinline__ bf16v8 ones_frag() {
+    const uint4 r = {0x3f803f80u, 0x3f803f80u, 0x3f803f80u, 0x3f803f80u};
+    return __builtin_bit_cast(bf16v8, r);
+}
+
+__global__ __launch_bounds__(256, 2) void wgrad16_kernel(Dims d, const short *a, const short *g, int nunits,
+                                                         float *partials) {
     constexpr int NP = C * (C * NT + 1);
-    __shared__ float red[NP];
-    const int lane = threadIdx.x & 63;
-    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wave = blockIdx.x * 4 + wid;
-    const int nwaves = gridDim.x * 4;
+    constexpr int STAGE = 12 * WG_ROW_A + 2 * WG_ROW_G;  // halves
+    constexpr int LDS_BYTES = STAGE * 2 > NP * 4 ? STAGE * 2 : NP * 4;
+    __shared__ __align__(16) char lds[LDS_BYTES];
+    short *const La = reinterpret_cast<short *>(lds);  // [frame 3][row ring 4][C][WG_AP]
+    short *const Lg = La + 12 * WG_ROW_A;              // [2][C][WG_GP]
+    const int unit = net_unit(blockIdx.x, nunits);
+    if (unit < 0) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int ch = lane % 16, kv = lane / 16;
-    const size_t V = (size_t)d.T * d.H * d.W;
-    const size_t nq = (V + 3) / 4;
     const auto ra = act_rsrc(a, d), rg = act_rsrc(g, d);
-    f32x4 acc[NT];
+    // staging: wavefront 0 .. 2 the row of frame t - 1 .. t + 1 of a, wavefront 3 the row of g
+    const int half = lane & 1, bx = 4 * (lane >> 1);
+    f32x4 acc[NT], bacc = {0.f, 0.f, 0.f, 0.f};
 #pragma unroll
     for (int tap = 0; tap < NT; ++tap) acc[tap] = f32x4{0.f, 0.f, 0.f, 0.f};
-    float bacc = 0.0f;
-    // two quads of voxels per pass: their 56 loads are in flight together
-    for (size_t q0 = (size_t)wave * 2; q0 < nq; q0 += (size_t)nwaves * 2) {
-        float gv[2], av[2][NT];
-#pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const size_t v = (q0 + h) * 4 + kv;
-            const bool vin = v < V;
-            const int x = vin ? (int)(v % d.W) : 0, y = vin ? (int)((v / d.W) % d.H) : 0;
-            const int t = vin ? (int)(v / ((size_t)d.W * d.H)) : 0;
-            gv[h] = bf2f(load_b16(rg, vin ? (uint32_t)(v * C + ch) * 2 : OOB_OFF));
-#pragma unroll
-            for (int tap = 0; tap < NT; ++tap) {
-                const int tt = t + tap / 9 - 1, yy = y + (tap / 3) % 3 - 1, xx = x + tap % 3 - 1;
-                const uint32_t off = (uint32_t)((((size_t)tt * d.H + yy) * d.W + xx) * C + ch) * 2;
-                av[h][tap] = bf2f(load_b16(ra, vin && inside(d, tt, yy, xx) ? off : OOB_OFF));
+    const int nxc = strip_count(d);
+    const int rend = share_begin(d, unit + 1, nunits);
+    int r = share_begin(d, unit, nunits);
+    while (r < rend) {
+        const int strip = r / d.H, ys = r - strip * d.H;
+        const int t = strip / nxc, X0 = (strip - t * nxc) * WG_XC;
+        const int ye = ys + (rend - r) < d.H ? ys + (rend - r) : d.H;
+        Block4x8 blk;
+        short edge = 0;
+        // loads of row ya of a (three frames) and row yg of g
+        auto load_rows = [&](int ya, int yg) __attribute__((always_inline)) {
+            const int tt = wid < 3 ? t + wid - 1 : t, yy = wid < 3 ? ya : yg;
+            const bool ok = tt >= 0 && tt < d.T && yy >= 0 && yy < d.H;
+            const uint32_t row = (uint32_t)(((size_t)(ok ? tt : 0) * d.H + (ok ? yy : 0)) * d.W) * (C * 2);
+            load_block(blk, wid < 3 ? ra : rg, ok, row, X0 + bx, d.W, half);
+            if (wid == 3) {  // the strip's neighbours of g: lanes 0 .. 15 x - 1, 16 .. 31 x + WG_XC
+                const int xe = lane < 16 ? X0 - 1 : X0 + WG_XC;
+                edge = load_b16(rg, ok && lane < 32 && xe >= 0 && xe < d.W ? row + (uint32_t)xe * (C * 2) + 2 * ch
+                                                                          : OOB_OFF);
             }
-        }
+        };
+        auto store_rows = [&](int ya, int yg) __attribute__((always_inline)) {
+            if (wid < 3) {
+                store_block(blk, La + (wid * 4 + (ya & 3)) * WG_ROW_A + bx, WG_AP, half);
+            } else {
+                short *dst = Lg + (yg & 1) * WG_ROW_G;
+                store_block(blk, dst + WG_GO + bx, WG_GP, half);
+                if (lane < 32) dst[ch * WG_GP + (lane < 16 ? WG_GO - 1 : WG_GO + WG_XC)] = edge;
+            }
+        };
+        // rows ys - 1, ys, ys + 1 of a and row ys of g (rows of g outside the range are never read)
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            bacc += gv[h];
-#pragma unroll
-            for (int tap = 0; tap < NT; ++tap)
-                acc[tap] = __builtin_amdgcn_mfma_f32_16x16x4f32(gv[h], av[h][tap], acc[tap], 0, 0, 0);
+        for (int k = 0; k < 3; ++k) {
+            load_rows(ys - 1 + k, ys);
+            store_rows(ys - 1 + k, ys);
         }
+        __syncthreads();
+        for (int y = ys; y < ye; ++y) {
+            const bool more = y + 1 < ye;
+            if (more) load_rows(y + 2, y + 1);
+            if (X0 + 32 * wid < d.W) {
+                const short *gp = Lg + (y & 1) * WG_ROW_G + ch * WG_GP + WG_GO + 32 * wid + 8 * kv;
+                const uint4 m = *reinterpret_cast<const uint4 *>(gp);
+                const uint32_t prev = *reinterpret_cast<const uint32_t *>(gp - 2);
+                const uint32_t next = *reinterpret_cast<const uint32_t *>(gp + 8);
+                // a at u = v + off: for x shift dx the voxel of g is u - dx
+                const bf16v8 gf[3] = {shift_down(m, next), __builtin_bit_cast(bf16v8, m), shift_up(m, prev)};
+                bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf[1], ones_frag(), bacc, 0, 0, 0);
+#pragma unroll
+                for (int k = 0; k < 9; ++k) {
+                    const int slot = (k / 3) * 4 + ((y + k % 3 - 1) & 3);
+                    const bf16v8 af = *reinterpret_cast<const bf16v8 *>(La + slot * WG_ROW_A + ch * WG_AP +
+                                                                        32 * wid + 8 * kv);
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx)
+                        acc[3 * k + dx] =
+                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf[dx], af, acc[3 * k + dx], 0, 0, 0);
+                }
+            }
+            if (more) store_rows(y + 2, y + 1);
+            __syncthreads();
+        }
+        r += ye - ys;
     }
-    // bias: lanes ch, ch + 16, ch + 32, ch + 48 hold the four voxel rows of channel ch
-    float b = bacc + __shfl_xor(bacc, 16, 64);
-    b += __shfl_xor(b, 32, 64);
     // the workgroup's four wavefronts add into LDS in turn (lane holds
     // dW_tap[co = 4 kv + j][ci = ch]), then one partial per workgroup
+    float *red = reinterpret_cast<float *>(lds);
     for (int w = 0; w < 4; ++w) {
         if (wid == w) {
 #pragma unroll
@@ -423,15 +546,18 @@ __global__ __launch_bounds__(256, 2) void wgrad16_kernel(Dims d, const short *a,
                     const int k = (4 * kv + j) * (C * NT + 1) + ch * NT + tap;
                     red[k] = (w == 0 ? 0.0f : red[k]) + acc[tap][j];
                 }
-            if (kv == 0) {
-                const int k = ch * (C * NT + 1) + C * NT;
-                red[k] = (w == 0 ? 0.0f : red[k]) + b;
+            if (ch == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k = (4 * kv + j) * (C * NT + 1) + C * NT;
+                    red[k] = (w == 0 ? 0.0f : red[k]) + bacc[j];
+                }
             }
         }
         __syncthreads();
     }
-    float *out = partials + (size_t)blockIdx.x * NP;
-    for (int k = threadIdx.x; k < NP; k += 256) out[k] = red[k];
+    float *out = partials + (size_t)unit * NP;
+    for (int k = tid; k < NP; k += 256) out[k] = red[k];
 }
 
 // Weight and bias gradients of the one-channel layers on the matrix cores
@@ -528,19 +654,27 @@ __global__ __launch_bounds__(256, 2) void wgrad1_kernel(Dims d, const short *x16
 constexpr int WG16_BLOCKS = 512;  // x 4 wavefronts (two per SIMD): one partial per workgroup
 
 // Sums the workgroup partials of one layer into the gradient buffer (same
-// layout as the masters): dW[co][ci][tap] at w_off, db[co] at b_off. One
-// workgroup per entry: threads add strided partials in double, then the
-// fixed block tree.
+// layout as the masters): dW[co][ci][tap] at w_off, db[co] at b_off. A
+// workgroup takes 64 consecutive entries (the partials are read in whole
+// lines; one workgroup per entry read 4 bytes of each line and took 20 us for
+// 512 partials of a 16 -> 16 layer, this 4.8 us): each of its 16 wavefronts adds
+// every 16th partial in double, then the 16 sums are added in order.
 template <int CI, int CO>
-__global__ __launch_bounds__(256) void wgrad_reduce(int nblocks, const float *partials, float *grad, int w_off,
-                                                    int b_off) {
+__global__ __launch_bounds__(1024) void wgrad_reduce(int nblocks, const float *partials, float *grad, int w_off,
+                                                     int b_off) {
     constexpr int NP = CO * (CI * NT + 1);
-    __shared__ double red[256 / 64];
-    const int i = blockIdx.x;
+    __shared__ double red[16][64];
+    const int lane = threadIdx.x & 63, part = threadIdx.x >> 6;
+    const int i = blockIdx.x * 64 + lane;
     double s = 0.0;
-    for (int b = threadIdx.x; b < nblocks; b += 256) s += (double)partials[(size_t)b * NP + i];
-    s = block_sum<256>(s, red);
-    if (threadIdx.x == 0) {
+    if (i < NP) {
+#pragma unroll 8
+        for (int b = part; b < nblocks; b += 16) s += (double)partials[(size_t)b * NP + i];
+    }
+    red[part][lane] = s;
+    __syncthreads();
+    if (part == 0 && i < NP) {
+        for (int k = 1; k < 16; ++k) s += red[k][lane];
         const int co = i / (CI * NT + 1), r = i % (CI * NT + 1);
         if (r < CI * NT)
             grad[w_off + co * CI * NT + r] = (float)s;
@@ -627,6 +761,13 @@ static NetWs net_ws(const stpi_problem *p, void *ws) {
     return n;
 }
 
+// Workgroups of a weight-gradient launch: two per CU, and at least six row
+// steps each (a share starts by staging three rows).
+static int wgrad_units(const stpi_problem *p) {
+    const int64_t rows = (int64_t)p->T * ((p->W + WG_XC - 1) / WG_XC) * p->H;
+    return (int)std::min<int64_t>(WG16_BLOCKS, std::max<int64_t>(1, rows / 6));
+}
+
 static int conv16_grid(const stpi_problem *p) {
     const long groups = (long)p->T * ((p->H + CONV_RB - 1) / CONV_RB) * ((p->W + 15) / 16);
     const long blocks = (groups + 3) / 4;
@@ -664,30 +805,31 @@ int stpi_net_backward(const stpi_problem *p, const float *f, const void *prep, c
     hipStream_t s = (hipStream_t)stream;
     const Dims d{p->T, p->H, p->W};
     const size_t V = (size_t)p->T * p->H * p->W;
+    const int nw = wgrad_units(p);
     hipLaunchKernelGGL(mse_kernel, dim3(2048), dim3(256), 0, s, V, y, x_star, std::sqrt((double)V), n.gy, n.lpart);
     hipLaunchKernelGGL(mse_finalize, dim3(1), dim3(256), 0, s, 2048, V, n.lpart, loss);
     // layer 4
     hipLaunchKernelGGL(wgrad1_kernel<4>, dim3(WG1_BLOCKS), dim3(256), 0, s, d, (const short *)n.act3,
                        (const float *)n.gy, n.wpart);
-    hipLaunchKernelGGL((wgrad_reduce<C, 1>), dim3(C * NT + 1), dim3(256), 0, s, WG1_BLOCKS, n.wpart, grad, OFF_W4, OFF_B4);
+    hipLaunchKernelGGL((wgrad_reduce<C, 1>), dim3((C * NT + 1 + 63) / 64), dim3(1024), 0, s, WG1_BLOCKS, n.wpart, grad, OFF_W4, OFF_B4);
     hipLaunchKernelGGL(out_bwd_kernel, dim3(2048), dim3(256), 0, s, d, n.gy, n.act3, P, n.g_a);  // g at pre3
     // layer 3
-    hipLaunchKernelGGL(wgrad16_kernel, dim3(WG16_BLOCKS), dim3(256), 0, s, d, (const short *)n.act2, n.g_a,
-                       n.wpart);
-    hipLaunchKernelGGL((wgrad_reduce<C, C>), dim3(C * (C * NT + 1)), dim3(256), 0, s,
-                       WG16_BLOCKS, n.wpart, grad, OFF_W3, OFF_B3);
+    hipLaunchKernelGGL(wgrad16_kernel, dim3(net_grid(nw)), dim3(256), 0, s, d, (const short *)n.act2,
+                       (const short *)n.g_a, nw, n.wpart);
+    hipLaunchKernelGGL((wgrad_reduce<C, C>), dim3((C * (C * NT + 1) + 63) / 64), dim3(1024), 0, s, nw,
+                       n.wpart, grad, OFF_W3, OFF_B3);
     hipLaunchKernelGGL(conv16_kernel<1>, dim3(conv16_grid(p)), dim3(256), 0, s, d, n.g_a, P->a3d,
                        (const float *)nullptr, n.act2, n.g_b);  // g at pre2
     // layer 2
-    hipLaunchKernelGGL(wgrad16_kernel, dim3(WG16_BLOCKS), dim3(256), 0, s, d, (const short *)n.act1, n.g_b,
-                       n.wpart);
-    hipLaunchKernelGGL((wgrad_reduce<C, C>), dim3(C * (C * NT + 1)), dim3(256), 0, s,
-                       WG16_BLOCKS, n.wpart, grad, OFF_W2, OFF_B2);
+    hipLaunchKernelGGL(wgrad16_kernel, dim3(net_grid(nw)), dim3(256), 0, s, d, (const short *)n.act1,
+                       (const short *)n.g_b, nw, n.wpart);
+    hipLaunchKernelGGL((wgrad_reduce<C, C>), dim3((C * (C * NT + 1) + 63) / 64), dim3(1024), 0, s, nw,
+                       n.wpart, grad, OFF_W2, OFF_B2);
     hipLaunchKernelGGL(conv16_kernel<1>, dim3(conv16_grid(p)), dim3(256), 0, s, d, n.g_b, P->a2d,
                        (const float *)nullptr, n.act1, n.g_a);  // g at pre1
     // layer 1
     hipLaunchKernelGGL(wgrad1_kernel<1>, dim3(WG1_BLOCKS), dim3(256), 0, s, d, (const short *)n.g_a, f, n.wpart);
-    hipLaunchKernelGGL((wgrad_reduce<1, C>), dim3(C * (NT + 1)), dim3(256), 0, s, WG1_BLOCKS, n.wpart, grad, OFF_W1, OFF_B1);
+    hipLaunchKernelGGL((wgrad_reduce<1, C>), dim3((C * (NT + 1) + 63) / 64), dim3(1024), 0, s, WG1_BLOCKS, n.wpart, grad, OFF_W1, OFF_B1);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? STPI_OK : hip_fail(e, "net backward");
 }

@@ -92,6 +92,41 @@ def test_backward_matches_oracle(W):
         off += n + gb.size
 
 
+@pytest.mark.parametrize("shape", [(1, 1, 1), (2, 7, 31), (3, 18, 33), (2, 17, 127), (2, 5, 128), (3, 9, 130), (1, 3, 260)])
+def test_backward_at_tile_edges(W, shape):
+    """The loss gradient is nonzero only in columns and rows around the kernels'
+    tile edges, so a dropped or doubled edge shows in full. Rounding: the layer
+    gradients are stored in bfloat16 (2^-9 relative each, at most three on a
+    path), the sums cancel by a small factor: 2e-2 of each layer's gradient."""
+    T, H, Wd = shape
+    rng = np.random.default_rng(T * 1000 + Wd)
+    f = rng.uniform(0, 1, shape).astype(np.float32)
+    net = W.WarmStartNet(_random_params(W, 11))
+    fd = torch.from_numpy(f).to(DEV)
+    y = net.forward(fd)
+    yh = y.double().cpu().numpy()
+    off = np.zeros(shape)
+    for x in (0, 15, 16, 31, 32, 63, 64, 127, 128, 129, Wd - 1):
+        if x < Wd:
+            off[:, :, x] = rng.uniform(0.5, 1.5, (T, H))
+    for yy in (0, 15, 16, H - 1):
+        if yy < H:
+            off[:, yy, ::7] = rng.uniform(-1.5, -0.5, off[:, yy, ::7].shape)
+    n = f.size
+    xs = ((yh - off) / np.sqrt(n)).astype(np.float32)
+    net.backward(fd, y, torch.from_numpy(xs).to(DEV))
+    g = net.grad.double().cpu().numpy()
+    _, cache = oracle.net_forward(f, W.unflatten(net.params), bf16=True)
+    grads = oracle.net_backward(cache, 2.0 * (yh - xs.astype(np.float64) * np.sqrt(n)) / n)
+    o = 0
+    for li, (gw, gb) in enumerate(grads):
+        for name, ref in (("w", gw.reshape(-1)), ("b", gb)):
+            err = rel(g[o:o + ref.size], ref)
+            print(shape, "layer", li + 1, name, err)
+            assert err < 2e-2, (li, name, err)
+            o += ref.size
+
+
 def test_training_lowers_loss(W):
     from paper_2212_08058_amd import Kernel, power_iterate
     kern = Kernel(4.0, 1.5, 8, 3)
