@@ -287,28 +287,114 @@ __global__ __launch_bounds__(256, 3) void conv16_kernel(Dims d, const short *in,
     }
 }
 
-// Layer 4 (16 -> 1), no activation: y = b4 + sum w4 * act3.
-__global__ __launch_bounds__(256) void conv_out_kernel(Dims d, const short *act, const Prep *p, float *y) {
-    __shared__ float w[C][NT];
-    for (int i = threadIdx.x; i < C * NT; i += blockDim.x) w[i / NT][i % NT] = p->w4[i / NT][i % NT];
-    __syncthreads();
+// Tile of the layer kernels that stream a tile's frames: CT_H x CT_W voxels,
+// staged with the one-voxel rim their taps reach. A unit is a range of frames
+// of one tile ("segment"); neighbouring tiles of a segment share an XCD.
+constexpr int CT_H = 16, CT_W = 32, CT_C = CT_W + 2, CT_V = (CT_H + 2) * CT_C;
+struct TileUnit {
+    int x0, y0, t0, t1;
+};
+__device__ __forceinline__ bool tile_unit(const Dims &d, int nseg, TileUnit &u) {
+    const int nbx = (d.W + CT_W - 1) / CT_W, ntiles = nbx * ((d.H + CT_H - 1) / CT_H);
+    const int k = net_unit(blockIdx.x, ntiles * nseg);
+    if (k < 0) return false;
+    const int tile = k % ntiles, seg = k / ntiles;
+    u.x0 = (tile % nbx) * CT_W;
+    u.y0 = (tile / nbx) * CT_H;
+    u.t0 = (int)((int64_t)seg * d.T / nseg);
+    u.t1 = (int)((int64_t)(seg + 1) * d.T / nseg);
+    return true;
+}
+// One frame of a channels-last volume (an empty range outside the clip: loads return 0).
+__device__ __forceinline__ __amdgpu_buffer_rsrc_t frame_rsrc(const short *base, const Dims &d, int t) {
+    const bool ok = t >= 0 && t < d.T;
+    const size_t plane = (size_t)d.H * d.W * C;
+    return __builtin_amdgcn_make_buffer_rsrc(const_cast<short *>(base + (ok ? t : 0) * plane), (short)0,
+                                             ok ? (int)(plane * sizeof(short)) : 0, 0x00020000);
+}
+
+// Layer 4 (16 -> 1), no activation: y = b4 + sum w4 * act3. One output channel
+// leaves an output-by-voxel product 15 of 16 rows empty, so the product is
+// turned around: v_mfma_f32_32x32x16_bf16 forms, for 32 voxels u at a time,
+// P[tap][u] = sum_ci w4[ci][tap] act3[u][ci] (27 of 32 rows used), and every
+// output adds the 27 entries P[tap][v + off(tap)] in float. A workgroup streams
+// the frames of a tile: per frame the P of its 612 voxels goes through LDS, and
+// each thread adds 9 entries to each of the three output frames in flight.
+// Bound by the read of act3 (32 bytes a voxel, 1.2 times with the rims): the
+// per-voxel gather of 432 products it replaces took 651 us at 32x480x854;
+// this takes 148 us.
+constexpr int CO_PV = 616;  // floats per tap: 4 * CO_PV is half the banks, so a wavefront's two tap rows do not collide
+static_assert(CO_PV >= CT_V && CO_PV % 16 == 8, "P row pitch");
+typedef float f32x16 __attribute__((ext_vector_type(16)));
+
+__global__ __launch_bounds__(256, 2) void conv_out_kernel(Dims d, const short *act, const Prep *p, float *y, int nseg) {
+    __shared__ float P[NT * CO_PV];
+    TileUnit u;
+    if (!tile_unit(d, nseg, u)) return;
+    const int tid = threadIdx.x, lane = tid & 63, wid = tid >> 6;
+    const int n = lane % 32, hf = lane / 32;
+    // A operand: lane holds tap n, channels 8 hf .. + 7; B: voxel n of the block, the same channels
+    bf16x8 aw;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) aw[j] = n < NT ? bfbits(p->w4[8 * hf + j][n]) : (short)0;
     const float b4 = p->b4;
-    const size_t V = (size_t)d.T * d.H * d.W;
-    for (size_t v = (size_t)blockIdx.x * blockDim.x + threadIdx.x; v < V; v += (size_t)gridDim.x * blockDim.x) {
-        const int x = (int)(v % d.W), yy0 = (int)((v / d.W) % d.H), t = (int)(v / ((size_t)d.W * d.H));
-        float s = b4;
-        for (int tap = 0; tap < NT; ++tap) {
-            const int tt = t + tap / 9 - 1, yy = yy0 + (tap / 3) % 3 - 1, xx = x + tap % 3 - 1;
-            if (!inside(d, tt, yy, xx)) continue;
-            const bf16x4 *src = reinterpret_cast<const bf16x4 *>(act + (((size_t)tt * d.H + yy) * d.W + xx) * C);
+    constexpr int NB = (CT_V + 127) / 128;  // 32-voxel blocks per wavefront
+    uint32_t off[NB];
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {
-                const bf16x4 a = src[q];
+    for (int m = 0; m < NB; ++m) {
+        const int v = 32 * (wid + 4 * m) + n;
+        const int gy = u.y0 - 1 + v / CT_C, gx = u.x0 - 1 + v % CT_C;
+        const bool ok = v < CT_V && (unsigned)gy < (unsigned)d.H && (unsigned)gx < (unsigned)d.W;
+        off[m] = ok ? (uint32_t)(gy * d.W + gx) * (C * 2) + 16 * hf : OOB_OFF;
+    }
+    uint4 b[NB];
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+        const auto r = frame_rsrc(act, d, t);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) s = fmaf(w[4 * q + j][tap], bf2f(a[j]), s);
+        for (int m = 0; m < NB; ++m) b[m] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, off[m], 0, 0));
+    };
+    fetch(u.t0 - 1);
+    constexpr int NO = CT_H * CT_W / 256;  // outputs per thread
+    float a1[NO], a2[NO];                  // frames t and t - 1 in flight
+#pragma unroll
+    for (int k = 0; k < NO; ++k) a1[k] = a2[k] = b4;
+    for (int t = u.t0 - 1; t <= u.t1; ++t) {
+#pragma unroll
+        for (int m = 0; m < NB; ++m) {
+            f32x16 z;
+#pragma unroll
+            for (int i = 0; i < 16; ++i) z[i] = 0.f;
+            const f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(bf16v8, aw),
+                                                                       __builtin_bit_cast(bf16v8, b[m]), z, 0, 0, 0);
+            const int v = 32 * (wid + 4 * m) + n;
+            if (v < CT_V) {
+#pragma unroll
+                for (int i = 0; i < 16; ++i) {
+                    const int tap = i % 4 + 8 * (i / 4) + 4 * hf;  // D row of element i
+                    if (tap < NT) P[tap * CO_PV + v] = acc[i];
+                }
             }
         }
-        y[v] = s;
+        if (t < u.t1) fetch(t + 1);
+        __syncthreads();
+#pragma unroll
+        for (int k = 0; k < NO; ++k) {
+            const int o = tid + 256 * k, row = o / CT_W, col = o % CT_W;
+            const float *q = P + row * CT_C + col;
+            float a0 = b4;
+#pragma unroll
+            for (int i = 0; i < 9; ++i) {
+                const int at = (i / 3) * CT_C + i % 3;
+                a0 += q[i * CO_PV + at];
+                a1[k] += q[(9 + i) * CO_PV + at];
+                a2[k] += q[(18 + i) * CO_PV + at];
+            }
+            const int gy = u.y0 + row, gx = u.x0 + col;
+            if (t - 1 >= u.t0 && gy < d.H && gx < d.W) y[((size_t)(t - 1) * d.H + gy) * d.W + gx] = a2[k];
+            a2[k] = a1[k];
+            a1[k] = a0;
+        }
+        __syncthreads();
     }
 }
 
@@ -761,6 +847,26 @@ static NetWs net_ws(const stpi_problem *p, void *ws) {
     return n;
 }
 
+static int net_tiles(const stpi_problem *p) { return ((p->W + CT_W - 1) / CT_W) * ((p->H + CT_H - 1) / CT_H); }
+
+// Frame segments of the streamed layer kernels (two workgroups per CU): a
+// segment costs its frames plus three (two rim frames and the start), and the
+// chip takes the units in rounds of its resident workgroups, so the split with
+// the fewest frame steps over all rounds.
+static int tile_segments(const stpi_problem *p) {
+    const int64_t tiles = net_tiles(p), slots = 2 * (int64_t)device_cus();
+    int best = 1;
+    int64_t cost = INT64_MAX;
+    for (int k = 1; k <= p->T && k <= 64; ++k) {
+        const int64_t c = (tiles * k + slots - 1) / slots * ((p->T + k - 1) / k + 3);
+        if (c < cost) {
+            cost = c;
+            best = k;
+        }
+    }
+    return best;
+}
+
 // Workgroups of a weight-gradient launch: two per CU, and at least six row
 // steps each (a share starts by staging three rows).
 static int wgrad_units(const stpi_problem *p) {
@@ -789,7 +895,9 @@ int stpi_net_forward(const stpi_problem *p, const float *f, const void *prep, fl
                        (const short *)nullptr, n.act2);
     hipLaunchKernelGGL(conv16_kernel<0>, dim3(conv16_grid(p)), dim3(256), 0, s, d, n.act2, P->a3, P->b3,
                        (const short *)nullptr, n.act3);
-    hipLaunchKernelGGL(conv_out_kernel, dim3(2048), dim3(256), 0, s, d, n.act3, P, y);
+    const int nseg = tile_segments(p);
+    hipLaunchKernelGGL(conv_out_kernel, dim3(net_grid(net_tiles(p) * nseg)), dim3(256), 0, s, d,
+                       (const short *)n.act3, P, y, nseg);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? STPI_OK : hip_fail(e, "net forward");
 }
