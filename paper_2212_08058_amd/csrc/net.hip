@@ -5,9 +5,9 @@
 // Weights and activations are bfloat16, accumulation is FP32. Hidden
 // activations are stored channels-last ([voxel][16], 32 bytes per voxel).
 // The two 16 -> 16 layers, and their input gradients, run as implicit GEMMs on
-// the matrix cores (v_mfma_f32_16x16x16_bf16): per wavefront a 16-channel x
+// the matrix cores (v_mfma_f32_16x16x32_bf16): per wavefront a 16-channel x
 // 16-voxel output block accumulates 27 taps of (16 out x 16 in) weights times
-// (16 in x 16 voxels) inputs; so do their weight gradients (wgrad16_kernel,
+// (16 in x 16 voxels) inputs, two taps an instruction; so do their weight gradients (wgrad16_kernel,
 // a sum over voxels of 16 x 16 outer products per tap, 32 voxels an instruction). The 1 -> 16 and
 // 16 -> 1 layers and their weight gradients are VALU kernels (their shapes fit
 // the matrix cores badly).
@@ -118,9 +118,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t act_rsrc(const short *base, co
     const int bytes = (int)((size_t)d.T * d.H * d.W * C * sizeof(short));
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<short *>(base), (short)0, bytes, 0x00020000);
 }
-__device__ __forceinline__ bf16x4 load_b64(__amdgpu_buffer_rsrc_t r, uint32_t boff) {
-    return __builtin_bit_cast(bf16x4, __builtin_amdgcn_raw_buffer_load_b64(r, boff, 0, 0));
-}
 __device__ __forceinline__ short load_b16(__amdgpu_buffer_rsrc_t r, uint32_t boff) {
     return (short)__builtin_amdgcn_raw_buffer_load_b16(r, boff, 0, 0);
 }
@@ -189,104 +186,6 @@ __global__ __launch_bounds__(256) void conv_in_kernel(Dims d, const float *f, co
     }
 }
 
-// Lane n of each 16-lane row takes src from lane n + 1 (ROW_SHL1) or n - 1
-// (ROW_SHR1) of the same row; lanes whose source lies outside the row keep
-// `old` (the neighbouring tile's edge voxel).
-constexpr int DPP_ROW_SHL1 = 0x101, DPP_ROW_SHR1 = 0x111;
-template <int CTRL>
-__device__ __forceinline__ bf16x4 row_shift(bf16x4 src, bf16x4 old) {
-    union U {
-        bf16x4 v;
-        int i[2];
-    } s, o, r;
-    s.v = src;
-    o.v = old;
-    r.i[0] = __builtin_amdgcn_update_dpp(o.i[0], s.i[0], CTRL, 0xF, 0xF, false);
-    r.i[1] = __builtin_amdgcn_update_dpp(o.i[1], s.i[1], CTRL, 0xF, 0xF, false);
-    return r.v;
-}
-
-constexpr int CONV_RB = 4;  // output rows per wavefront
-
-// 16 -> 16 convolution on the matrix cores. mode 0: out = relu(conv + bias);
-// mode 1 (input gradient of a ReLU layer): out = conv(g, flipped W^T) masked
-// by mask > 0. One wavefront per 16 consecutive voxels of CONV_RB rows: each
-// input row (per frame offset) is loaded once, as 16 voxels plus the two edge
-// voxels (one load: lane 0 takes x0 - 1, lane 15 x0 + 16), and feeds up to
-// three output rows; the x-1 and x+1 taps take the
-// row's registers shifted by one lane (DPP), so every activation is read
-// from memory about (CONV_RB + 2) / CONV_RB * 3 times instead of 27. A
-// group's 3 (CONV_RB + 2) row loads are all issued before its MFMAs.
-template <int MODE>
-__global__ __launch_bounds__(256, 3) void conv16_kernel(Dims d, const short *in, const bf16x4 (*A)[64],
-                                                     const float *bias, const short *mask, short *out) {
-    const int lane = threadIdx.x & 63;
-    const int wave = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-    const int gx = (d.W + 15) / 16, gy = (d.H + CONV_RB - 1) / CONV_RB;
-    const int ngroups = d.T * gy * gx;
-    const int nwaves = gridDim.x * (blockDim.x / 64);
-    const int n = lane % 16, kq = lane / 16;  // voxel column of B, channel quad
-    const auto rs = act_rsrc(in, d);
-    bf16x4 a[NT];
-#pragma unroll
-    for (int tap = 0; tap < NT; ++tap) a[tap] = A[tap][lane];
-    for (int g = wave; g < ngroups; g += nwaves) {
-        const int xg = g % gx, yb = (g / gx) % gy, t = g / (gx * gy);
-        const int x0 = xg * 16, y0 = yb * CONV_RB, x = x0 + n;
-        f32x4 acc[CONV_RB];
-#pragma unroll
-        for (int r = 0; r < CONV_RB; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
-        // all the group's input rows are loaded first (rows and frames outside
-        // the volume read as zero), so their latencies overlap
-        constexpr int NR = 3 * (CONV_RB + 2);
-        // b0: the lane's voxel; be: the row's edge voxel the shifts bring in
-        // (x0 - 1 for lane 0, x0 + 16 for lane 15; other lanes never use it)
-        const int xe = n == 0 ? x0 - 1 : x0 + 16;
-        const bool eok = xe >= 0 && xe < d.W;
-        bf16x4 b0[NR], be[NR];
-#pragma unroll
-        for (int k = 0; k < NR; ++k) {
-            const int tt = t + k / (CONV_RB + 2) - 1, yy = y0 - 1 + k % (CONV_RB + 2);
-            const bool rowok = tt >= 0 && tt < d.T && yy >= 0 && yy < d.H;
-            const uint32_t row = (uint32_t)(((size_t)tt * d.H + yy) * d.W) * (C * 2) + 8 * kq;
-            b0[k] = load_b64(rs, rowok && x < d.W ? row + (uint32_t)x * (C * 2) : OOB_OFF);
-            be[k] = load_b64(rs, rowok && eok ? row + (uint32_t)xe * (C * 2) : OOB_OFF);
-        }
-#pragma unroll
-        for (int k = 0; k < NR; ++k) {
-            const int dt = k / (CONV_RB + 2) - 1, ry = k % (CONV_RB + 2);
-            const bf16x4 bl = row_shift<DPP_ROW_SHR1>(b0[k], be[k]);  // voxel x - 1 (lane 0 keeps be)
-            const bf16x4 br = row_shift<DPP_ROW_SHL1>(b0[k], be[k]);  // voxel x + 1 (lane 15 keeps be)
-#pragma unroll
-            for (int dy = -1; dy <= 1; ++dy) {
-                const int r = ry - 1 - dy;  // output row fed by this input row through dy
-                if (r < 0 || r >= CONV_RB) continue;
-                const int tap = (dt + 1) * 9 + (dy + 1) * 3;
-                acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[tap], bl, acc[r], 0, 0, 0);
-                acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[tap + 1], b0[k], acc[r], 0, 0, 0);
-                acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a[tap + 2], br, acc[r], 0, 0, 0);
-            }
-        }
-        // lane holds out[co = 4 kq + j][voxel n] of each row
-#pragma unroll
-        for (int r = 0; r < CONV_RB; ++r) {
-            const int y = y0 + r;
-            if (y >= d.H || x >= d.W) continue;
-            const size_t v = ((size_t)t * d.H + y) * d.W + x;
-            bf16x4 o;
-            if (MODE == 0) {
-#pragma unroll
-                for (int j = 0; j < 4; ++j) o[j] = bfbits(fmaxf(acc[r][j] + bias[4 * kq + j], 0.0f));
-            } else {
-                const bf16x4 mk = *reinterpret_cast<const bf16x4 *>(mask + v * C + 4 * kq);
-#pragma unroll
-                for (int j = 0; j < 4; ++j) o[j] = bf2f(mk[j]) > 0.0f ? bfbits(acc[r][j]) : (short)0;
-            }
-            *reinterpret_cast<bf16x4 *>(out + v * C + 4 * kq) = o;
-        }
-    }
-}
-
 // Tile of the layer kernels that stream a tile's frames: CT_H x CT_W voxels,
 // staged with the one-voxel rim their taps reach. A unit is a range of frames
 // of one tile ("segment"); neighbouring tiles of a segment share an XCD.
@@ -311,6 +210,187 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t frame_rsrc(const short *base, 
     const size_t plane = (size_t)d.H * d.W * C;
     return __builtin_amdgcn_make_buffer_rsrc(const_cast<short *>(base + (ok ? t : 0) * plane), (short)0,
                                              ok ? (int)(plane * sizeof(short)) : 0, 0x00020000);
+}
+
+// 16 -> 16 convolution on the matrix cores. MODE 0: out = relu(conv + bias);
+// MODE 1 (input gradient of a ReLU layer): out = conv(g, flipped W^T) masked
+// by mask > 0. A workgroup streams the frames of a CT_H x CT_W tile through a
+// ring of four staged frames (the rim included; the frame after the next is
+// loaded while one is computed, one barrier per frame). In LDS the two channel
+// halves of a voxel lie in planes of their own, so what a lane reads is next to
+// its neighbours'. Each wavefront owns 8 rows x 16 columns; a staged fragment
+// feeds up to three output rows, and the weights stay in registers.
+// MODE 0 takes one tap an instruction (v_mfma_f32_16x16x16_bf16) in the taps'
+// order: its results are rounded to bfloat16 and feed three further layers, so
+// the order of its float sums is part of the network's arithmetic. MODE 1
+// takes two taps an instruction (K = 32): the nine (frame, x) taps of an input
+// row make four pairs and one single, whose upper half is zero in both
+// operands (no product of another K is mixed in: back-to-back K = 16 and
+// K = 32 products on one accumulator came out wrong).
+// Bound by memory (32 bytes a voxel read, 1.2 times with the rims, and 32
+// written) beside the matrix cores. The form it replaces (a wavefront per 16 x
+// 4 voxels, every row loaded from memory three times and shifted by lane
+// moves) took 502 us at 32x480x854 and 64 (MODE 0) and 67 us (MODE 1) at
+// 16x240x432; this takes 302, 44 and 48 us.
+constexpr int CV_PLANE = CT_V * 8;     // halves of one channel half of a staged frame
+constexpr int CV_FRAME = 2 * CV_PLANE;
+constexpr int CV_ROWS = 8;             // output rows per wavefront
+
+template <int MODE>
+__global__ __launch_bounds__(256, 2) void conv16_kernel(Dims d, const short *in, const bf16x4 (*A)[64],
+                                                        const float *bias, const short *mask, short *out, int nseg) {
+    __shared__ __align__(16) short lds[4 * CV_FRAME];
+    TileUnit u;
+    if (!tile_unit(d, nseg, u)) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane % 16, kq = lane / 16;
+    // MODE 0: tap operands as prepared (channels 4 kq .. + 3 of one tap).
+    // MODE 1: tap order of an input row q = 3 (dt + 1) + (dx + 1). Pair p holds
+    // taps 2 p (lanes kq 0, 1) and 2 p + 1 (kq 2, 3), channels 8 (kq % 2) .. + 7;
+    // pair 4 is the single q = 8 (kq 0, 1).
+    constexpr bool PAIR = MODE == 1;
+    const bool lower = kq < 2;
+    bf16x4 a1[PAIR ? 1 : NT];
+    bf16v8 ap[3][5];
+    if constexpr (PAIR) {
+#pragma unroll
+        for (int dy = 0; dy < 3; ++dy)
+#pragma unroll
+            for (int p = 0; p < 5; ++p) {
+                const int q = p < 4 ? 2 * p + kq / 2 : 8, tap = (q / 3) * 9 + dy * 3 + q % 3;
+                union {
+                    bf16x4 h[2];
+                    bf16v8 v;
+                } w;
+                w.h[0] = A[tap][n + 32 * (kq % 2)];
+                w.h[1] = A[tap][n + 32 * (kq % 2) + 16];
+                if (p == 4 && !lower) w.h[0] = w.h[1] = bf16x4{0, 0, 0, 0};
+                ap[dy][p] = w.v;
+            }
+    } else {
+#pragma unroll
+        for (int tap = 0; tap < NT; ++tap) a1[tap] = A[tap][lane];
+    }
+    float bv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bv[j] = MODE == 0 ? bias[4 * kq + j] : 0.f;
+    // staging: item it = 16 bytes (voxel it / 2 of the rimmed tile, channel half it % 2)
+    constexpr int NIT = 2 * CT_V, NST = (NIT + 255) / 256;
+    uint32_t soff[NST];
+#pragma unroll
+    for (int m = 0; m < NST; ++m) {
+        const int it = tid + 256 * m, v = it >> 1;
+        const int gy = u.y0 - 1 + v / CT_C, gx = u.x0 - 1 + v % CT_C;
+        const bool ok = it < NIT && (unsigned)gy < (unsigned)d.H && (unsigned)gx < (unsigned)d.W;
+        soff[m] = ok ? (uint32_t)(gy * d.W + gx) * (C * 2) + 16 * (it & 1) : OOB_OFF;
+    }
+    uint4 st[NST];
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+        const auto r = frame_rsrc(in, d, t);
+#pragma unroll
+        for (int m = 0; m < NST; ++m) st[m] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, soff[m], 0, 0));
+    };
+    auto stage = [&](int t) __attribute__((always_inline)) {
+        short *f = lds + (t & 3) * CV_FRAME;
+#pragma unroll
+        for (int m = 0; m < NST; ++m) {
+            const int it = tid + 256 * m;
+            if (NIT % 256 == 0 || m < NST - 1 || it < NIT)
+                *reinterpret_cast<uint4 *>(f + (it & 1) * CV_PLANE + (it >> 1) * 8) = st[m];
+        }
+    };
+    const int r0 = CV_ROWS * (wid >> 1), c0 = 16 * (wid & 1);  // the wavefront's rows and columns of the tile
+    // fragment addresses within a staged frame, row r0 - 1 of the tile (pairs: by this lane's tap)
+    int poff[5], pdt[5];
+#pragma unroll
+    for (int p = 0; p < 5; ++p) {
+        const int q = p < 4 ? 2 * p + kq / 2 : 8;
+        pdt[p] = q / 3;
+        poff[p] = (kq % 2) * CV_PLANE + (r0 * CT_C + c0 + n + q % 3) * 8;
+    }
+    const int off1 = (kq / 2) * CV_PLANE + (r0 * CT_C + c0 + n) * 8 + 4 * (kq % 2);
+    const int x = u.x0 + c0 + n;
+#pragma unroll
+    for (int k = -1; k <= 1; ++k) {
+        fetch(u.t0 + k);
+        stage(u.t0 + k);
+    }
+    __syncthreads();
+    for (int t = u.t0; t < u.t1; ++t) {
+        const bool more = t + 1 < u.t1;
+        if (more) fetch(t + 2);
+        f32x4 acc[CV_ROWS];
+#pragma unroll
+        for (int r = 0; r < CV_ROWS; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+        if constexpr (PAIR) {
+            const short *pp[5];
+#pragma unroll
+            for (int p = 0; p < 5; ++p) pp[p] = lds + ((t - 1 + pdt[p]) & 3) * CV_FRAME + poff[p];
+#pragma unroll
+            for (int ry = 0; ry < CV_ROWS + 2; ++ry) {  // input row r0 - 1 + ry of the tile
+                bf16v8 b[5];
+#pragma unroll
+                for (int p = 0; p < 5; ++p) {
+                    uint4 w = *reinterpret_cast<const uint4 *>(pp[p] + ry * CT_C * 8);
+                    if (p == 4) {
+                        w.x = lower ? w.x : 0u;
+                        w.y = lower ? w.y : 0u;
+                        w.z = lower ? w.z : 0u;
+                        w.w = lower ? w.w : 0u;
+                    }
+                    b[p] = __builtin_bit_cast(bf16v8, w);
+                }
+#pragma unroll
+                for (int dy = 0; dy < 3; ++dy) {
+                    const int r = ry - dy;  // output row fed through tap row dy
+                    if (r < 0 || r >= CV_ROWS) continue;
+#pragma unroll
+                    for (int p = 0; p < 5; ++p)
+                        acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[dy][p], b[p], acc[r], 0, 0, 0);
+                }
+            }
+        } else {
+#pragma unroll
+            for (int dt = 0; dt < 3; ++dt) {
+                const short *q = lds + ((t - 1 + dt) & 3) * CV_FRAME + off1;
+#pragma unroll
+                for (int ry = 0; ry < CV_ROWS + 2; ++ry) {
+                    bf16x4 b[3];
+#pragma unroll
+                    for (int dx = 0; dx < 3; ++dx) b[dx] = *reinterpret_cast<const bf16x4 *>(q + (ry * CT_C + dx) * 8);
+#pragma unroll
+                    for (int dy = 0; dy < 3; ++dy) {
+                        const int r = ry - dy;
+                        if (r < 0 || r >= CV_ROWS) continue;
+#pragma unroll
+                        for (int dx = 0; dx < 3; ++dx)
+                            acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1[dt * 9 + dy * 3 + dx], b[dx], acc[r], 0,
+                                                                               0, 0);
+                    }
+                }
+            }
+        }
+        // lane holds out[co = 4 kq + j][column n] of each row
+#pragma unroll
+        for (int r = 0; r < CV_ROWS; ++r) {
+            const int y = u.y0 + r0 + r;
+            if (y >= d.H || x >= d.W) continue;
+            const size_t v = ((size_t)t * d.H + y) * d.W + x;
+            bf16x4 o;
+            if (MODE == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[j] = bfbits(fmaxf(acc[r][j] + bv[j], 0.0f));
+            } else {
+                const bf16x4 mk = *reinterpret_cast<const bf16x4 *>(mask + v * C + 4 * kq);
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[j] = bf2f(mk[j]) > 0.0f ? bfbits(acc[r][j]) : (short)0;
+            }
+            *reinterpret_cast<bf16x4 *>(out + v * C + 4 * kq) = o;
+        }
+        if (more) stage(t + 2);
+        __syncthreads();
+    }
 }
 
 // Layer 4 (16 -> 1), no activation: y = b4 + sum w4 * act3. One output channel
@@ -875,7 +955,7 @@ static int wgrad_units(const stpi_problem *p) {
 }
 
 static int conv16_grid(const stpi_problem *p) {
-    const long groups = (long)p->T * ((p->H + CONV_RB - 1) / CONV_RB) * ((p->W + 15) / 16);
+    const long groups = (long)p->T * ((p->H + 3) / 4) * ((p->W + 15) / 16);
     const long blocks = (groups + 3) / 4;
     return (int)(blocks < 8192 ? blocks : 8192);
 }
@@ -890,13 +970,13 @@ int stpi_net_forward(const stpi_problem *p, const float *f, const void *prep, fl
     NetWs n = net_ws(p, ws);
     hipStream_t s = (hipStream_t)stream;
     const Dims d{p->T, p->H, p->W};
+    const int nseg = tile_segments(p), grid = net_grid(net_tiles(p) * nseg);
     hipLaunchKernelGGL(conv_in_kernel, dim3(conv16_grid(p)), dim3(256), 0, s, d, f, P, n.act1);
-    hipLaunchKernelGGL(conv16_kernel<0>, dim3(conv16_grid(p)), dim3(256), 0, s, d, n.act1, P->a2, P->b2,
-                       (const short *)nullptr, n.act2);
-    hipLaunchKernelGGL(conv16_kernel<0>, dim3(conv16_grid(p)), dim3(256), 0, s, d, n.act2, P->a3, P->b3,
-                       (const short *)nullptr, n.act3);
-    const int nseg = tile_segments(p);
-    hipLaunchKernelGGL(conv_out_kernel, dim3(net_grid(net_tiles(p) * nseg)), dim3(256), 0, s, d,
+    hipLaunchKernelGGL(conv16_kernel<0>, dim3(grid), dim3(256), 0, s, d, (const short *)n.act1, P->a2, P->b2,
+                       (const short *)nullptr, n.act2, nseg);
+    hipLaunchKernelGGL(conv16_kernel<0>, dim3(grid), dim3(256), 0, s, d, (const short *)n.act2, P->a3, P->b3,
+                       (const short *)nullptr, n.act3, nseg);
+    hipLaunchKernelGGL(conv_out_kernel, dim3(grid), dim3(256), 0, s, d,
                        (const short *)n.act3, P, y, nseg);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? STPI_OK : hip_fail(e, "net forward");
@@ -913,7 +993,7 @@ int stpi_net_backward(const stpi_problem *p, const float *f, const void *prep, c
     hipStream_t s = (hipStream_t)stream;
     const Dims d{p->T, p->H, p->W};
     const size_t V = (size_t)p->T * p->H * p->W;
-    const int nw = wgrad_units(p);
+    const int nw = wgrad_units(p), nseg = tile_segments(p), grid = net_grid(net_tiles(p) * nseg);
     hipLaunchKernelGGL(mse_kernel, dim3(2048), dim3(256), 0, s, V, y, x_star, std::sqrt((double)V), n.gy, n.lpart);
     hipLaunchKernelGGL(mse_finalize, dim3(1), dim3(256), 0, s, 2048, V, n.lpart, loss);
     // layer 4
@@ -926,15 +1006,15 @@ int stpi_net_backward(const stpi_problem *p, const float *f, const void *prep, c
                        (const short *)n.g_a, nw, n.wpart);
     hipLaunchKernelGGL((wgrad_reduce<C, C>), dim3((C * (C * NT + 1) + 63) / 64), dim3(1024), 0, s, nw,
                        n.wpart, grad, OFF_W3, OFF_B3);
-    hipLaunchKernelGGL(conv16_kernel<1>, dim3(conv16_grid(p)), dim3(256), 0, s, d, n.g_a, P->a3d,
-                       (const float *)nullptr, n.act2, n.g_b);  // g at pre2
+    hipLaunchKernelGGL(conv16_kernel<1>, dim3(grid), dim3(256), 0, s, d, (const short *)n.g_a, P->a3d,
+                       (const float *)nullptr, (const short *)n.act2, n.g_b, nseg);  // g at pre2
     // layer 2
     hipLaunchKernelGGL(wgrad16_kernel, dim3(net_grid(nw)), dim3(256), 0, s, d, (const short *)n.act1,
                        (const short *)n.g_b, nw, n.wpart);
     hipLaunchKernelGGL((wgrad_reduce<C, C>), dim3((C * (C * NT + 1) + 63) / 64), dim3(1024), 0, s, nw,
                        n.wpart, grad, OFF_W2, OFF_B2);
-    hipLaunchKernelGGL(conv16_kernel<1>, dim3(conv16_grid(p)), dim3(256), 0, s, d, n.g_b, P->a2d,
-                       (const float *)nullptr, n.act1, n.g_a);  // g at pre1
+    hipLaunchKernelGGL(conv16_kernel<1>, dim3(grid), dim3(256), 0, s, d, (const short *)n.g_b, P->a2d,
+                       (const float *)nullptr, (const short *)n.act1, n.g_a, nseg);  // g at pre1
     // layer 1
     hipLaunchKernelGGL(wgrad1_kernel<1>, dim3(WG1_BLOCKS), dim3(256), 0, s, d, (const short *)n.g_a, f, n.wpart);
     hipLaunchKernelGGL((wgrad_reduce<1, C>), dim3((C * (NT + 1) + 63) / 64), dim3(1024), 0, s, WG1_BLOCKS, n.wpart, grad, OFF_W1, OFF_B1);
