@@ -125,67 +125,6 @@ __device__ __forceinline__ short load_b16(__amdgpu_buffer_rsrc_t r, uint32_t bof
 typedef short bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
 
-// Layer 1 (1 -> 16), ReLU. f is FP32 and enters rounded to bfloat16. One
-// v_mfma_f32_16x16x32_bf16 per 16 voxels of a row: A = W1 [co][tap] with the
-// 27 taps padded to K = 32 (lane l holds co = l % 16, taps 8 (l / 16) .. + 7),
-// B = the voxels' 27 neighbours (lane l: voxel l % 16, the same taps),
-// gathered with buffer loads whose out-of-range offsets read the zero padding.
-__global__ __launch_bounds__(256) void conv_in_kernel(Dims d, const float *f, const Prep *p, short *act) {
-    const int lane = threadIdx.x & 63;
-    const int wave = blockIdx.x * (blockDim.x / 64) + (threadIdx.x >> 6);
-    const int nwaves = gridDim.x * (blockDim.x / 64);
-    const int n = lane % 16, kq = lane / 16;
-    bf16x8 aw;
-#pragma unroll
-    for (int j = 0; j < 8; ++j) {
-        const int tap = 8 * kq + j;
-        aw[j] = tap < NT ? bfbits(p->w1[n][tap]) : (short)0;  // the masters are already bfloat16 values
-    }
-    float bias[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) bias[j] = p->b1[4 * kq + j];
-    const int bytes = (int)((size_t)d.T * d.H * d.W * sizeof(float));
-    const auto rf = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(f), (short)0, bytes, 0x00020000);
-    const int gx = (d.W + 15) / 16;
-    const int ngroups = d.T * d.H * gx;
-    constexpr int GB = 4;  // groups whose gathers are in flight together
-    for (int g0 = wave * GB; g0 < ngroups; g0 += nwaves * GB) {
-        bf16x8 bv[GB];
-#pragma unroll
-        for (int h = 0; h < GB; ++h) {
-            const int g = g0 + h < ngroups ? g0 + h : ngroups - 1;
-            const int xg = g % gx, y = (g / gx) % d.H, t = g / (gx * d.H);
-            const int x = xg * 16 + n;
-#pragma unroll
-            for (int j = 0; j < 8; ++j) {
-                const int tap = 8 * kq + j;
-                const int tt = t + tap / 9 - 1, yy = y + (tap / 3) % 3 - 1, xx = x + tap % 3 - 1;
-                const bool ok = tap < NT && inside(d, tt, yy, xx);
-                const uint32_t off = (uint32_t)(((size_t)tt * d.H + yy) * d.W + xx) * 4;
-                bv[h][j] = bfbits(__uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rf, ok ? off : OOB_OFF, 0, 0)));
-            }
-        }
-#pragma unroll
-        for (int h = 0; h < GB; ++h) {
-            const int g = g0 + h;
-            if (g >= ngroups) break;
-            const int xg = g % gx, y = (g / gx) % d.H, t = g / (gx * d.H);
-            const int x = xg * 16 + n;
-            f32x4 acc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16v8, aw),
-                                                                __builtin_bit_cast(bf16v8, bv[h]),
-                                                                f32x4{0.f, 0.f, 0.f, 0.f}, 0, 0, 0);
-            // lane holds pre-activation[co = 4 kq + j][voxel n]
-            if (x < d.W) {
-                const size_t v = ((size_t)t * d.H + y) * d.W + x;
-                bf16x4 o;
-#pragma unroll
-                for (int j = 0; j < 4; ++j) o[j] = bfbits(fmaxf(acc[j] + bias[j], 0.0f));
-                *reinterpret_cast<bf16x4 *>(act + v * C + 4 * kq) = o;
-            }
-        }
-    }
-}
-
 // Tile of the layer kernels that stream a tile's frames: CT_H x CT_W voxels,
 // staged with the one-voxel rim their taps reach. A unit is a range of frames
 // of one tile ("segment"); neighbouring tiles of a segment share an XCD.
@@ -212,6 +151,172 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t frame_rsrc(const short *base, 
                                              ok ? (int)(plane * sizeof(short)) : 0, 0x00020000);
 }
 
+// The layers with one input channel. MODE 0: layer 1, act = relu(conv(f) + b1),
+// f rounded to bfloat16. MODE 1: the input gradient of layer 4 masked by layer
+// 3's ReLU, g3[v][ci] = (act3[v][ci] > 0) sum_tap w4[ci][tap] g_y[v - off(tap)],
+// g_y in float: split exactly into three bfloat16 parts, one product each.
+// One v_mfma_f32_16x16x32_bf16 per 16 voxels of a row: A = weights [channel]
+// [tap] with the 27 taps padded to K = 32 (lane l holds channel l % 16, taps
+// 8 (l / 16) .. + 7), B = the voxels' 27 neighbours in the same order. A
+// workgroup streams the frames of a tile as the 16 -> 16 layers do; a staged
+// element is the pair (f[x], f[x + 1]), so any two neighbours of a row are one
+// aligned 4-byte read, and a lane's 8 taps (8 consecutive of the row triples
+// in tap order) are four such pairs, some made of two reads by a byte permute.
+// Bound by the 32 bytes a voxel written. The gathers they replace (8 element
+// loads per lane and 16 voxels; a scalar sum of 27 x 16 terms per voxel) took
+// 296 us at 32x480x854 (layer 1) and 127 us at 16x240x432 (the gradient; layer
+// 1 there 46); these take 121 and 42 us (20).
+template <int MODE>
+__global__ __launch_bounds__(256) void one_channel_kernel(Dims d, const float *f, const Prep *p, const short *mask,
+                                                          short *out, int nseg) {
+    constexpr int PARTS = MODE == 0 ? 1 : 3;
+    __shared__ uint32_t lds[4 * PARTS * CT_V];  // [frame ring 4][part][row][column]
+    TileUnit u;
+    if (!tile_unit(d, nseg, u)) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    const int n = lane % 16, kq = lane / 16;
+    bf16x8 aw;
+#pragma unroll
+    for (int j = 0; j < 8; ++j) {
+        const int tap = 8 * kq + j;  // MODE 1 reads v - off(tap) = v + off(26 - tap)
+        const float w = tap >= NT ? 0.f : (MODE == 0 ? p->w1[n][tap] : p->w4[n][NT - 1 - tap]);
+        aw[j] = bfbits(w);  // the prepared weights are already bfloat16 values
+    }
+    float bv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) bv[j] = MODE == 0 ? p->b1[4 * kq + j] : 0.f;
+    // This lane's taps 8 kq .. + 7 as four pairs: pair i is (element a) alone, or
+    // the low halves of elements a and b. An element is named by its row R =
+    // 3 (dt + 1) + (dy + 1) and its column offset from the voxel's left neighbour.
+    constexpr uint32_t WHOLE = 0x03020100u, LOWS = 0x05040100u, LOW0 = 0x0c0c0100u, ZERO = 0x0c0c0c0cu;
+    constexpr int RA[4][4] = {{0, 0, 1, 2}, {2, 3, 4, 4}, {5, 6, 6, 7}, {8, 8, 8, 8}};
+    constexpr int CA[4][4] = {{0, 2, 1, 0}, {2, 1, 0, 2}, {1, 0, 2, 1}, {0, 2, 0, 0}};
+    constexpr int RB[4][4] = {{0, 1, 1, 2}, {3, 3, 4, 5}, {5, 6, 7, 7}, {8, 8, 8, 8}};  // column offset 0
+    constexpr uint32_t SEL[4][4] = {{WHOLE, LOWS, WHOLE, WHOLE},
+                                    {LOWS, WHOLE, WHOLE, LOWS},
+                                    {WHOLE, WHOLE, LOWS, WHOLE},
+                                    {WHOLE, LOW0, ZERO, ZERO}};
+    const int r0 = 8 * (wid >> 1), c0 = 16 * (wid & 1);
+    int fa[4], fb[4], oa[4], ob[4];
+    uint32_t sel[4];
+#pragma unroll
+    for (int i = 0; i < 4; ++i) {
+        int ra = 0, ca = 0, rb = 0;
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+            if (kq == q) {
+                ra = RA[q][i];
+                ca = CA[q][i];
+                rb = RB[q][i];
+                sel[i] = SEL[q][i];
+            }
+        fa[i] = ra / 3;
+        oa[i] = (r0 + ra % 3) * CT_C + c0 + n + ca;
+        fb[i] = rb / 3;
+        ob[i] = (r0 + rb % 3) * CT_C + c0 + n;
+    }
+    constexpr int NST = (CT_V + 255) / 256;
+    uint32_t s0[NST], s1[NST];  // byte offsets of f[x], f[x + 1] in a frame
+#pragma unroll
+    for (int m = 0; m < NST; ++m) {
+        const int v = tid + 256 * m, gy = u.y0 - 1 + v / CT_C, gx = u.x0 - 1 + v % CT_C;
+        const bool ok = v < CT_V && (unsigned)gy < (unsigned)d.H;
+        s0[m] = ok && (unsigned)gx < (unsigned)d.W ? (uint32_t)(gy * d.W + gx) * 4 : OOB_OFF;
+        s1[m] = ok && (unsigned)(gx + 1) < (unsigned)d.W ? (uint32_t)(gy * d.W + gx + 1) * 4 : OOB_OFF;
+    }
+    float e0[NST], e1[NST];
+    auto fetch = [&](int t) __attribute__((always_inline)) {
+        const bool ok = t >= 0 && t < d.T;
+        const size_t plane = (size_t)d.H * d.W;
+        const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(f + (ok ? t : 0) * plane), (short)0,
+                                                         ok ? (int)(plane * sizeof(float)) : 0, 0x00020000);
+#pragma unroll
+        for (int m = 0; m < NST; ++m) {
+            e0[m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, s0[m], 0, 0));
+            e1[m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, s1[m], 0, 0));
+        }
+    };
+    auto stage = [&](int t) __attribute__((always_inline)) {
+        uint32_t *q = lds + (t & 3) * PARTS * CT_V;
+#pragma unroll
+        for (int m = 0; m < NST; ++m) {
+            const int v = tid + 256 * m;
+            if (CT_V % 256 == 0 || m < NST - 1 || v < CT_V) {
+                float a = e0[m], b = e1[m];
+#pragma unroll
+                for (int k = 0; k < PARTS; ++k) {
+                    const uint32_t w = f32x2_to_bf16x2_bits(a, b);
+                    q[k * CT_V + v] = w;
+                    a -= __uint_as_float(w << 16);  // exact remainder
+                    b -= __uint_as_float(w & 0xffff0000u);
+                }
+            }
+        }
+    };
+    const int x = u.x0 + c0 + n;
+#pragma unroll
+    for (int k = -1; k <= 1; ++k) {
+        fetch(u.t0 + k);
+        stage(u.t0 + k);
+    }
+    __syncthreads();
+    for (int t = u.t0; t < u.t1; ++t) {
+        const bool more = t + 1 < u.t1;
+        if (more) fetch(t + 2);
+        bf16x4 mk[MODE == 0 ? 1 : 8];  // the mask of the step's outputs, in flight beside the products
+        if constexpr (MODE == 1) {
+#pragma unroll
+            for (int r = 0; r < 8; ++r) {
+                const int y = u.y0 + r0 + r;
+                mk[r] = bf16x4{0, 0, 0, 0};
+                if (y < d.H && x < d.W)
+                    mk[r] = *reinterpret_cast<const bf16x4 *>(mask + (((size_t)t * d.H + y) * d.W + x) * C + 4 * kq);
+            }
+        }
+        const uint32_t *qa[4], *qb[4];
+#pragma unroll
+        for (int i = 0; i < 4; ++i) {
+            qa[i] = lds + ((t - 1 + fa[i]) & 3) * PARTS * CT_V + oa[i];
+            qb[i] = lds + ((t - 1 + fb[i]) & 3) * PARTS * CT_V + ob[i];
+        }
+        f32x4 acc[8];
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int k = PARTS - 1; k >= 0; --k) {  // smallest part first
+                uint4 b;
+                const int at = k * CT_V + r * CT_C;
+                b.x = __builtin_amdgcn_perm(qb[0][at], qa[0][at], sel[0]);
+                b.y = __builtin_amdgcn_perm(qb[1][at], qa[1][at], sel[1]);
+                b.z = __builtin_amdgcn_perm(qb[2][at], qa[2][at], sel[2]);
+                b.w = __builtin_amdgcn_perm(qb[3][at], qa[3][at], sel[3]);
+                acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16v8, aw),
+                                                                 __builtin_bit_cast(bf16v8, b), acc[r], 0, 0, 0);
+            }
+        }
+        // lane holds out[channel 4 kq + j][column n] of each row
+#pragma unroll
+        for (int r = 0; r < 8; ++r) {
+            const int y = u.y0 + r0 + r;
+            if (y >= d.H || x >= d.W) continue;
+            const size_t v = ((size_t)t * d.H + y) * d.W + x;
+            bf16x4 o;
+            if (MODE == 0) {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[j] = bfbits(fmaxf(acc[r][j] + bv[j], 0.0f));
+            } else {
+#pragma unroll
+                for (int j = 0; j < 4; ++j) o[j] = bf2f(mk[r][j]) > 0.0f ? bfbits(acc[r][j]) : (short)0;
+            }
+            *reinterpret_cast<bf16x4 *>(out + v * C + 4 * kq) = o;
+        }
+        if (more) stage(t + 2);
+        __syncthreads();
+    }
+}
+
 // 16 -> 16 convolution on the matrix cores. MODE 0: out = relu(conv + bias);
 // MODE 1 (input gradient of a ReLU layer): out = conv(g, flipped W^T) masked
 // by mask > 0. A workgroup streams the frames of a CT_H x CT_W tile through a
@@ -231,7 +336,7 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t frame_rsrc(const short *base, 
 // written) beside the matrix cores. The form it replaces (a wavefront per 16 x
 // 4 voxels, every row loaded from memory three times and shifted by lane
 // moves) took 502 us at 32x480x854 and 64 (MODE 0) and 67 us (MODE 1) at
-// 16x240x432; this takes 302, 44 and 48 us.
+// 16x240x432; this takes 302, 44 and 42 us.
 constexpr int CV_PLANE = CT_V * 8;     // halves of one channel half of a staged frame
 constexpr int CV_FRAME = 2 * CV_PLANE;
 constexpr int CV_ROWS = 8;             // output rows per wavefront
@@ -320,6 +425,16 @@ __global__ __launch_bounds__(256, 2) void conv16_kernel(Dims d, const short *in,
     for (int t = u.t0; t < u.t1; ++t) {
         const bool more = t + 1 < u.t1;
         if (more) fetch(t + 2);
+        bf16x4 mk[MODE == 0 ? 1 : CV_ROWS];  // the mask of the step's outputs, in flight beside the products
+        if constexpr (MODE == 1) {
+#pragma unroll
+            for (int r = 0; r < CV_ROWS; ++r) {
+                const int y = u.y0 + r0 + r;
+                mk[r] = bf16x4{0, 0, 0, 0};
+                if (y < d.H && x < d.W)
+                    mk[r] = *reinterpret_cast<const bf16x4 *>(mask + (((size_t)t * d.H + y) * d.W + x) * C + 4 * kq);
+            }
+        }
         f32x4 acc[CV_ROWS];
 #pragma unroll
         for (int r = 0; r < CV_ROWS; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
@@ -382,9 +497,8 @@ __global__ __launch_bounds__(256, 2) void conv16_kernel(Dims d, const short *in,
 #pragma unroll
                 for (int j = 0; j < 4; ++j) o[j] = bfbits(fmaxf(acc[r][j] + bv[j], 0.0f));
             } else {
-                const bf16x4 mk = *reinterpret_cast<const bf16x4 *>(mask + v * C + 4 * kq);
 #pragma unroll
-                for (int j = 0; j < 4; ++j) o[j] = bf2f(mk[j]) > 0.0f ? bfbits(acc[r][j]) : (short)0;
+                for (int j = 0; j < 4; ++j) o[j] = bf2f(mk[r][j]) > 0.0f ? bfbits(acc[r][j]) : (short)0;
             }
             *reinterpret_cast<bf16x4 *>(out + v * C + 4 * kq) = o;
         }
@@ -502,40 +616,6 @@ __global__ __launch_bounds__(256) void mse_finalize(int nb, size_t V, const doub
     s = block_sum<256>(s, red);
     if (threadIdx.x == 0) *loss = s / (double)V;
 }
-
-// Input gradient of layer 4, masked by layer 3's ReLU:
-// g3[v][ci] = (act3[v][ci] > 0) * sum_tap w4[ci][tap] * g_y[v - tap]
-__global__ __launch_bounds__(256) void out_bwd_kernel(Dims d, const float *gy, const short *act3, const Prep *p, short *g3) {
-    __shared__ float w[C][NT];
-    for (int i = threadIdx.x; i < C * NT; i += blockDim.x) w[i / NT][i % NT] = p->w4[i / NT][i % NT];
-    __syncthreads();
-    const size_t V = (size_t)d.T * d.H * d.W;
-    for (size_t v = (size_t)blockIdx.x * blockDim.x + threadIdx.x; v < V; v += (size_t)gridDim.x * blockDim.x) {
-        const int x = (int)(v % d.W), y = (int)((v / d.W) % d.H), t = (int)(v / ((size_t)d.W * d.H));
-        float g[NT];
-#pragma unroll
-        for (int tap = 0; tap < NT; ++tap) {
-            const int tt = t - (tap / 9 - 1), yy = y - ((tap / 3) % 3 - 1), xx = x - (tap % 3 - 1);
-            g[tap] = inside(d, tt, yy, xx) ? gy[((size_t)tt * d.H + yy) * d.W + xx] : 0.0f;
-        }
-        const bf16x4 *ap = reinterpret_cast<const bf16x4 *>(act3 + v * C);
-        bf16x4 *dst = reinterpret_cast<bf16x4 *>(g3 + v * C);
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-            const bf16x4 a = ap[q];
-            bf16x4 o;
-#pragma unroll
-            for (int j = 0; j < 4; ++j) {
-                float s = 0.0f;
-#pragma unroll
-                for (int tap = 0; tap < NT; ++tap) s = fmaf(w[4 * q + j][tap], g[tap], s);
-                o[j] = bf2f(a[j]) > 0.0f ? bfbits(s) : (short)0;
-            }
-            dst[q] = o;
-        }
-    }
-}
-
 
 // Weight and bias gradients of a 16 -> 16 layer on the matrix cores. For each
 // tap, dW_tap[co][ci] = sum_v g[v][co] a[v + tap][ci] is a (16 x V) x (V x 16)
@@ -954,12 +1034,6 @@ static int wgrad_units(const stpi_problem *p) {
     return (int)std::min<int64_t>(WG16_BLOCKS, std::max<int64_t>(1, rows / 6));
 }
 
-static int conv16_grid(const stpi_problem *p) {
-    const long groups = (long)p->T * ((p->H + 3) / 4) * ((p->W + 15) / 16);
-    const long blocks = (groups + 3) / 4;
-    return (int)(blocks < 8192 ? blocks : 8192);
-}
-
 int stpi_net_forward(const stpi_problem *p, const float *f, const void *prep, float *y, void *ws, size_t ws_bytes,
                      void *stream) {
     clear_error();
@@ -971,7 +1045,7 @@ int stpi_net_forward(const stpi_problem *p, const float *f, const void *prep, fl
     hipStream_t s = (hipStream_t)stream;
     const Dims d{p->T, p->H, p->W};
     const int nseg = tile_segments(p), grid = net_grid(net_tiles(p) * nseg);
-    hipLaunchKernelGGL(conv_in_kernel, dim3(conv16_grid(p)), dim3(256), 0, s, d, f, P, n.act1);
+    hipLaunchKernelGGL(one_channel_kernel<0>, dim3(grid), dim3(256), 0, s, d, f, P, (const short *)nullptr, n.act1, nseg);
     hipLaunchKernelGGL(conv16_kernel<0>, dim3(grid), dim3(256), 0, s, d, (const short *)n.act1, P->a2, P->b2,
                        (const short *)nullptr, n.act2, nseg);
     hipLaunchKernelGGL(conv16_kernel<0>, dim3(grid), dim3(256), 0, s, d, (const short *)n.act2, P->a3, P->b3,
@@ -1000,7 +1074,8 @@ int stpi_net_backward(const stpi_problem *p, const float *f, const void *prep, c
     hipLaunchKernelGGL(wgrad1_kernel<4>, dim3(WG1_BLOCKS), dim3(256), 0, s, d, (const short *)n.act3,
                        (const float *)n.gy, n.wpart);
     hipLaunchKernelGGL((wgrad_reduce<C, 1>), dim3((C * NT + 1 + 63) / 64), dim3(1024), 0, s, WG1_BLOCKS, n.wpart, grad, OFF_W4, OFF_B4);
-    hipLaunchKernelGGL(out_bwd_kernel, dim3(2048), dim3(256), 0, s, d, n.gy, n.act3, P, n.g_a);  // g at pre3
+    hipLaunchKernelGGL(one_channel_kernel<1>, dim3(grid), dim3(256), 0, s, d, (const float *)n.gy, P,
+                       (const short *)n.act3, n.g_a, nseg);  // g at pre3
     // layer 3
     hipLaunchKernelGGL(wgrad16_kernel, dim3(net_grid(nw)), dim3(256), 0, s, d, (const short *)n.act2,
                        (const short *)n.g_a, nw, n.wpart);
