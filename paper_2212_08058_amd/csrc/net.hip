@@ -94,10 +94,6 @@ struct Dims {
     int T, H, W;
 };
 
-__device__ __forceinline__ bool inside(const Dims &d, int t, int y, int x) {
-    return (unsigned)t < (unsigned)d.T && (unsigned)y < (unsigned)d.H && (unsigned)x < (unsigned)d.W;
-}
-
 // Work unit of a workgroup: consecutive units share an XCD (workgroups are
 // dealt round-robin over the 8 XCDs), so neighbours find each other's rows in
 // the same L2. -1 for workgroups past the last unit.
@@ -806,74 +802,127 @@ __global__ __launch_bounds__(256, 2) void wgrad16_kernel(Dims d, const short *a,
     for (int k = tid; k < NP; k += 256) out[k] = red[k];
 }
 
-// Weight and bias gradients of the one-channel layers on the matrix cores
-// (v_mfma_f32_16x16x4f32, four voxels per instruction, taps in two blocks of
-// 16 columns):
+// Weight and bias gradients of the one-channel layers on the matrix cores:
 //   MODE 1 (layer 1): D[co][tap] = sum_v g[v][co] bf16(f[v + off(tap)]),
 //                     db1[co] = sum_v g[v][co]; X = g (channels-last), Z = f;
 //   MODE 4 (layer 4): D[ci][tap] = sum_u act3[u][ci] g_y[u - off(tap)]
 //                     (the same sum as over v = u - off), db4 = sum_v g_y[v];
-//                     X = act3, Z = g_y.
-// Lane l holds X[voxel l / 16][channel l % 16] (A operand) and Z at that
-// voxel shifted by tap 16 blk + l % 16 (B operand); terms whose shifted voxel
-// lies outside the volume read zero through out-of-range buffer offsets.
-// Partial sums per workgroup: [co][ci * 27 + tap] then the bias of co (CI x 27 + 1 per co).
+//                     X = act3, Z = g_y, split exactly into three bfloat16 parts.
+// Strips, row steps and shares as wgrad16_kernel: X rows are staged transposed,
+// 32 voxels of a row per instruction, the 27 taps as two blocks of 16 columns.
+// Z rows of the three frames lie in LDS three times, shifted by x = -1, 0, 1, so
+// that a lane's 8 consecutive voxels at its own tap are one aligned read.
+// Bound by the read of X (32 bytes a voxel) and the row steps' latency. The
+// element-wise gathers with K = 4 float products it replaces took 104 (layer 1)
+// and 102 us (layer 4) at 16x240x432; this takes 22 and 28 us.
 template <int MODE>
-__global__ __launch_bounds__(256, 2) void wgrad1_kernel(Dims d, const short *x16, const float *z1, float *partials) {
+__global__ __launch_bounds__(256) void wgrad1_kernel(Dims d, const short *x16, const float *z1, int nunits,
+                                                     float *partials) {
+    constexpr int PARTS = MODE == 1 ? 1 : 3;
     constexpr int NPR = MODE == 1 ? C * (NT + 1) : C * NT + 1;
+    constexpr int ZROWS = 3 * 3 * 4;  // [x shift][frame][row ring]
+    __shared__ __align__(16) short lds[2 * WG_ROW_A + PARTS * ZROWS * WG_AP];
     __shared__ float red[NPR];
-    const int lane = threadIdx.x & 63;
-    const int wid = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-    const int wave = blockIdx.x * 4 + wid;
-    const int nwaves = gridDim.x * 4;
+    short *const Lx = lds;                 // [2][C][WG_AP]
+    short *const Lz = lds + 2 * WG_ROW_A;  // [part][shift][frame][4][WG_AP]
+    const int unit = net_unit(blockIdx.x, nunits);
+    if (unit < 0) return;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
     const int c = lane % 16, kv = lane / 16;
-    const size_t V = (size_t)d.T * d.H * d.W;
-    const size_t nq = (V + 3) / 4;
     const auto rx = act_rsrc(x16, d);
-    const auto rz = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(z1), (short)0, (int)(V * sizeof(float)),
-                                                      0x00020000);
-    int sdt[2], sdy[2], sdx[2];
+    const auto rz = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(z1), (short)0,
+                                                      (int)((size_t)d.T * d.H * d.W * sizeof(float)), 0x00020000);
+    // this lane's tap columns: Z at off(tap) (MODE 1) or at -off(tap) = off(26 - tap) (MODE 4)
     bool tapok[2];
+    int zoff[2], zdy[2];
 #pragma unroll
     for (int blk = 0; blk < 2; ++blk) {
         const int tap = 16 * blk + c;
         tapok[blk] = tap < NT;
-        const int s = MODE == 1 ? 1 : -1;  // layer 4 reads Z at u - off
-        sdt[blk] = s * (tap / 9 - 1);
-        sdy[blk] = s * ((tap / 3) % 3 - 1);
-        sdx[blk] = s * (tap % 3 - 1);
+        const int s = !tapok[blk] ? 0 : (MODE == 1 ? tap : NT - 1 - tap);
+        zoff[blk] = ((s % 3) * 3 + s / 9) * 4 * WG_AP + 32 * wid + 8 * kv;
+        zdy[blk] = (s / 3) % 3 - 1;
     }
-    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}};
-    float bacc = 0.0f;
-    for (size_t q0 = (size_t)wave * 2; q0 < nq; q0 += (size_t)nwaves * 2) {
-        float xa[2], zb[2][2];
+    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}}, bacc = {0.f, 0.f, 0.f, 0.f};
+    const int nxc = strip_count(d);
+    const int rend = share_begin(d, unit + 1, nunits);
+    int r = share_begin(d, unit, nunits);
+    while (r < rend) {
+        const int strip = r / d.H, ys = r - strip * d.H;
+        const int t = strip / nxc, X0 = (strip - t * nxc) * WG_XC;
+        const int ye = ys + (rend - r) < d.H ? ys + (rend - r) : d.H;
+        Block4x8 blk;
+        float z[3];
+        // wavefront 0 stages a row of X, wavefronts 1 .. 3 a row of Z of the
+        // frames t - 1 .. t + 1 (columns X0 - 1 .. X0 + WG_XC)
+        auto load_rows = [&](int yx, int yz) __attribute__((always_inline)) {
+            const int tt = wid == 0 ? t : t + wid - 2, yy = wid == 0 ? yx : yz;
+            const bool ok = tt >= 0 && tt < d.T && yy >= 0 && yy < d.H;
+            const size_t row = ((size_t)(ok ? tt : 0) * d.H + (ok ? yy : 0)) * d.W;
+            if (wid == 0) {
+                load_block(blk, rx, ok, (uint32_t)row * (C * 2), X0 + 4 * (lane >> 1), d.W, lane & 1);
+            } else {
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            const size_t v = (q0 + h) * 4 + kv;
-            const bool vin = v < V;
-            const int x = vin ? (int)(v % d.W) : 0, y = vin ? (int)((v / d.W) % d.H) : 0;
-            const int t = vin ? (int)(v / ((size_t)d.W * d.H)) : 0;
-            xa[h] = bf2f(load_b16(rx, vin ? (uint32_t)(v * C + c) * 2 : OOB_OFF));
-#pragma unroll
-            for (int blk = 0; blk < 2; ++blk) {
-                const int tt = t + sdt[blk], yy = y + sdy[blk], xx = x + sdx[blk];
-                const bool ok = vin && tapok[blk] && inside(d, tt, yy, xx);
-                const uint32_t off = (uint32_t)(((size_t)tt * d.H + yy) * d.W + xx) * 4;
-                const float zv = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(rz, ok ? off : OOB_OFF, 0, 0));
-                zb[h][blk] = MODE == 1 ? bfr(zv) : zv;
+                for (int k = 0; k < 3; ++k) {
+                    const int e = lane + 64 * k, xe = X0 - 1 + e;
+                    z[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                        rz, ok && e < WG_XC + 2 && xe >= 0 && xe < d.W ? (uint32_t)(row + xe) * 4 : OOB_OFF, 0, 0));
+                }
             }
-        }
+        };
+        auto store_rows = [&](int yx, int yz) __attribute__((always_inline)) {
+            if (wid == 0) {
+                store_block(blk, Lx + (yx & 1) * WG_ROW_A + 4 * (lane >> 1), WG_AP, lane & 1);
+            } else {
+                short *dst = Lz + ((wid - 1) * 4 + (yz & 3)) * WG_AP;
 #pragma unroll
-        for (int h = 0; h < 2; ++h) {
-            bacc += MODE == 1 ? xa[h] : (c == 13 ? zb[h][0] : 0.0f);  // tap 13 is the centre
+                for (int k = 0; k < 3; ++k) {
+                    const int e = lane + 64 * k;  // column X0 - 1 + e: index e - s of the plane shifted by s - 1
+                    float rest = z[k];
 #pragma unroll
-            for (int blk = 0; blk < 2; ++blk)
-                acc[blk] = __builtin_amdgcn_mfma_f32_16x16x4f32(xa[h], zb[h][blk], acc[blk], 0, 0, 0);
+                    for (int q = 0; q < PARTS; ++q) {
+                        const short b = bfbits(rest);
+                        rest -= bf2f(b);
+#pragma unroll
+                        for (int s = 0; s < 3; ++s)
+                            if (e >= s && e - s < WG_XC) dst[(q * 9 + s * 3) * 4 * WG_AP + e - s] = b;
+                    }
+                }
+            }
+        };
+#pragma unroll
+        for (int k = 0; k < 3; ++k) {
+            load_rows(ys, ys - 1 + k);
+            store_rows(ys, ys - 1 + k);
         }
+        __syncthreads();
+        for (int y = ys; y < ye; ++y) {
+            const bool more = y + 1 < ye;
+            if (more) load_rows(y + 1, y + 2);
+            if (X0 + 32 * wid < d.W) {
+                const bf16v8 xf =
+                    *reinterpret_cast<const bf16v8 *>(Lx + (y & 1) * WG_ROW_A + c * WG_AP + 32 * wid + 8 * kv);
+                if constexpr (MODE == 1) bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, ones_frag(), bacc, 0, 0, 0);
+#pragma unroll
+                for (int q = PARTS - 1; q >= 0; --q) {  // smallest part first
+                    bf16v8 zf[2];
+#pragma unroll
+                    for (int b = 0; b < 2; ++b)
+                        zf[b] = *reinterpret_cast<const bf16v8 *>(Lz + q * ZROWS * WG_AP + zoff[b] +
+                                                                  ((y + zdy[b]) & 3) * WG_AP);
+                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, zf[0], acc[0], 0, 0, 0);
+                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, zf[1], acc[1], 0, 0, 0);
+                    // column 13 of block 0 is the centre tap
+                    if constexpr (MODE == 4)
+                        bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_frag(), zf[0], bacc, 0, 0, 0);
+                }
+            }
+            if (more) store_rows(y + 1, y + 2);
+            __syncthreads();
+        }
+        r += ye - ys;
     }
-    // bias over the four voxel rows: lanes c, c + 16, c + 32, c + 48
-    float b = bacc + __shfl_xor(bacc, 16, 64);
-    b += __shfl_xor(b, 32, 64);
     // lane holds D[channel 4 kv + j][tap 16 blk + c]; the four wavefronts add into LDS in turn
     for (int w = 0; w < 4; ++w) {
         if (wid == w) {
@@ -886,15 +935,18 @@ __global__ __launch_bounds__(256, 2) void wgrad1_kernel(Dims d, const short *x16
                     const int k = MODE == 1 ? ch * (NT + 1) + tap : ch * NT + tap;
                     red[k] = (w == 0 ? 0.0f : red[k]) + acc[blk][j];
                 }
-            if (kv == 0 && (MODE == 1 || c == 13)) {
-                const int k = MODE == 1 ? c * (NT + 1) + NT : C * NT;
-                red[k] = (w == 0 ? 0.0f : red[k]) + b;
+            if (MODE == 1 ? c == 0 : lane == 13) {
+#pragma unroll
+                for (int j = 0; j < (MODE == 1 ? 4 : 1); ++j) {
+                    const int k = MODE == 1 ? (4 * kv + j) * (NT + 1) + NT : C * NT;
+                    red[k] = (w == 0 ? 0.0f : red[k]) + bacc[j];
+                }
             }
         }
         __syncthreads();
     }
-    float *out = partials + (size_t)blockIdx.x * NPR;
-    for (int k = threadIdx.x; k < NPR; k += 256) out[k] = red[k];
+    float *out = partials + (size_t)unit * NPR;
+    for (int k = tid; k < NPR; k += 256) out[k] = red[k];
 }
 
 constexpr int WG16_BLOCKS = 512;  // x 4 wavefronts (two per SIMD): one partial per workgroup
@@ -935,7 +987,7 @@ __global__ void warm_x0_kernel(size_t V, const float *y, float eps, float *x0) {
         x0[v] = fmaxf(y[v], 0.0f) + eps;
 }
 
-constexpr int WG1_BLOCKS = 2048;  // x 4 wavefronts: wgrad1_kernel's partial sums (448 floats each)
+constexpr int WG1_BLOCKS = 1024;  // x 4 wavefronts: wgrad1_kernel's partial sums (448 floats each)
 
 }  // namespace net
 
@@ -1027,11 +1079,12 @@ static int tile_segments(const stpi_problem *p) {
     return best;
 }
 
-// Workgroups of a weight-gradient launch: two per CU, and at least six row
-// steps each (a share starts by staging three rows).
-static int wgrad_units(const stpi_problem *p) {
+// Workgroups of a weight-gradient launch: as many as fit at once (two per CU
+// of wgrad16_kernel, four of wgrad1_kernel), and at least six row steps each (a
+// share starts by staging three rows).
+static int wgrad_units(const stpi_problem *p, int most) {
     const int64_t rows = (int64_t)p->T * ((p->W + WG_XC - 1) / WG_XC) * p->H;
-    return (int)std::min<int64_t>(WG16_BLOCKS, std::max<int64_t>(1, rows / 6));
+    return (int)std::min<int64_t>(most, std::max<int64_t>(1, rows / 6));
 }
 
 int stpi_net_forward(const stpi_problem *p, const float *f, const void *prep, float *y, void *ws, size_t ws_bytes,
@@ -1067,13 +1120,13 @@ int stpi_net_backward(const stpi_problem *p, const float *f, const void *prep, c
     hipStream_t s = (hipStream_t)stream;
     const Dims d{p->T, p->H, p->W};
     const size_t V = (size_t)p->T * p->H * p->W;
-    const int nw = wgrad_units(p), nseg = tile_segments(p), grid = net_grid(net_tiles(p) * nseg);
+    const int nw = wgrad_units(p, WG16_BLOCKS), nw1 = wgrad_units(p, WG1_BLOCKS), nseg = tile_segments(p), grid = net_grid(net_tiles(p) * nseg);
     hipLaunchKernelGGL(mse_kernel, dim3(2048), dim3(256), 0, s, V, y, x_star, std::sqrt((double)V), n.gy, n.lpart);
     hipLaunchKernelGGL(mse_finalize, dim3(1), dim3(256), 0, s, 2048, V, n.lpart, loss);
     // layer 4
-    hipLaunchKernelGGL(wgrad1_kernel<4>, dim3(WG1_BLOCKS), dim3(256), 0, s, d, (const short *)n.act3,
-                       (const float *)n.gy, n.wpart);
-    hipLaunchKernelGGL((wgrad_reduce<C, 1>), dim3((C * NT + 1 + 63) / 64), dim3(1024), 0, s, WG1_BLOCKS, n.wpart, grad, OFF_W4, OFF_B4);
+    hipLaunchKernelGGL(wgrad1_kernel<4>, dim3(net_grid(nw1)), dim3(256), 0, s, d, (const short *)n.act3,
+                       (const float *)n.gy, nw1, n.wpart);
+    hipLaunchKernelGGL((wgrad_reduce<C, 1>), dim3((C * NT + 1 + 63) / 64), dim3(1024), 0, s, nw1, n.wpart, grad, OFF_W4, OFF_B4);
     hipLaunchKernelGGL(one_channel_kernel<1>, dim3(grid), dim3(256), 0, s, d, (const float *)n.gy, P,
                        (const short *)n.act3, n.g_a, nseg);  // g at pre3
     // layer 3
@@ -1091,8 +1144,8 @@ int stpi_net_backward(const stpi_problem *p, const float *f, const void *prep, c
     hipLaunchKernelGGL(conv16_kernel<1>, dim3(grid), dim3(256), 0, s, d, (const short *)n.g_b, P->a2d,
                        (const float *)nullptr, (const short *)n.act1, n.g_a, nseg);  // g at pre1
     // layer 1
-    hipLaunchKernelGGL(wgrad1_kernel<1>, dim3(WG1_BLOCKS), dim3(256), 0, s, d, (const short *)n.g_a, f, n.wpart);
-    hipLaunchKernelGGL((wgrad_reduce<1, C>), dim3((C * (NT + 1) + 63) / 64), dim3(1024), 0, s, WG1_BLOCKS, n.wpart, grad, OFF_W1, OFF_B1);
+    hipLaunchKernelGGL(wgrad1_kernel<1>, dim3(net_grid(nw1)), dim3(256), 0, s, d, (const short *)n.g_a, f, nw1, n.wpart);
+    hipLaunchKernelGGL((wgrad_reduce<1, C>), dim3((C * (NT + 1) + 63) / 64), dim3(1024), 0, s, nw1, n.wpart, grad, OFF_W1, OFF_B1);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? STPI_OK : hip_fail(e, "net backward");
 }
