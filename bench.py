@@ -41,7 +41,7 @@ def log(msg):
 STEP_SOURCES = ["paper_2212_08058_amd/csrc/common.hpp", "paper_2212_08058_amd/csrc/stencil.hpp",
                 "paper_2212_08058_amd/csrc/stencil_mfma.hpp", "paper_2212_08058_amd/csrc/forward.hpp",
                 "paper_2212_08058_amd/csrc/kernels_f32.hip", "paper_2212_08058_amd/csrc/host.cpp"]
-LOOP_KIND = {0: "plain", 1: "pipelined", 2: "straight-line", 3: "matrix-core"}
+LOOP_KIND = {0: "plain", 1: "pipelined", 2: "straight-line", 3: "matrix-core", 4: "all frames at once"}
 
 
 def profiled_traffic(tag: str):

@@ -22,6 +22,45 @@ __device__ __forceinline__ void sum_pairs(const double *partials, int n, double 
     s1 = block_sum<CHAIN_THREADS>(b, red);
 }
 
+// 16 bytes of stored elements, for streaming passes.
+template <class ST>
+union Chunk16 {
+    uint4 u;
+    ST e[16 / sizeof(ST)];
+};
+
+// State of a new chain (see DevState).
+__device__ __forceinline__ void init_state(DevState *s, double scale, double tol, int max_iters, int check_rise,
+                                           int pform) {
+    DevState v = {};
+    v.scale = scale;
+    v.tol = tol;
+    v.done = max_iters <= 0 ? 1 : 0;
+    v.max_iters = max_iters;
+    v.check_rise = check_rise;
+    v.pform = pform;
+    *s = v;
+}
+
+// Uniform start of a plain-form chain: x <- 1 and the state.
+template <class ST>
+__global__ void uniform_start_kernel(ST *x, size_t n, DevState *s, double scale, double tol, int max_iters) {
+    using CT = typename Compute<ST>::type;
+    if (blockIdx.x == 0 && threadIdx.x == 0) init_state(s, scale, tol, max_iters, 0, 0);
+    constexpr int VEC = 16 / (int)sizeof(ST);
+    const size_t stride = (size_t)gridDim.x * blockDim.x, tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
+    size_t head = 0;
+    if (((uintptr_t)x & 15) == 0) {
+        Chunk16<ST> c;
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) st(&c.e[e], CT(1));
+        const size_t nv = n / VEC;
+        for (size_t i = tid; i < nv; i += stride) reinterpret_cast<uint4 *>(x)[i] = c.u;
+        head = nv * VEC;
+    }
+    for (size_t i = head + tid; i < n; i += stride) st(x + i, CT(1));
+}
+
 template <class ST>
 __global__ void fill_ones_kernel(ST *x, size_t n) {
     using CT = typename Compute<ST>::type;
@@ -45,19 +84,19 @@ __global__ void sumsq_kernel(const ST *x, size_t n, double *partials) {
 }
 
 // x <- scale * (current iterate), written into the caller's buffer.
-// 16 bytes of stored elements, for streaming passes.
+// nparts > 0: the chain's last finalisation is formed here first (resolve_state)
+// and the final state written to s_out; otherwise *s is final and copied there
+// (s_out may be null).
 template <class ST>
-union Chunk16 {
-    uint4 u;
-    ST e[16 / sizeof(ST)];
-};
-
-template <class ST>
-__global__ void normalize_kernel(ST *x, const ST *buf1, size_t n, const DevState *s) {
+__global__ __launch_bounds__(256) void normalize_kernel(ST *x, const ST *buf1, size_t n, const DevState *s,
+                                                        StepPartials part, int nparts, DevState *s_out) {
     using CT = typename Compute<ST>::type;
     constexpr int VEC = 16 / (int)sizeof(ST);
-    const ST *src = s->cur ? buf1 : x;
-    const CT scale = (CT)s->scale;
+    __shared__ DevState fin;
+    __shared__ double red[3 * FINAL_THREADS / 64];
+    resolve_state<256>(s, part, nparts, &fin, red, s_out, 0);
+    const ST *src = fin.cur ? buf1 : x;
+    const CT scale = (CT)fin.scale;
     const size_t stride = (size_t)gridDim.x * blockDim.x, tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     size_t head = 0;
     if ((((uintptr_t)x | (uintptr_t)src) & 15) == 0) {
@@ -102,9 +141,15 @@ __global__ void to_product_kernel(const ST *f, const ST *x, ST *w, size_t n, Dev
 // iterate being w / (f g) (0 where f = 0), computed in double as the step's
 // sums are; before any step of a uniform start it is the constant 1.
 template <class ST>
-__global__ void from_product_kernel(ST *x, const ST *buf1, const ST *f, size_t n, const DevState *s) {
+__global__ __launch_bounds__(256) void from_product_kernel(ST *x, const ST *buf1, const ST *f, size_t n,
+                                                           const DevState *s0, StepPartials part, int nparts,
+                                                           DevState *s_out) {
     using CT = typename Compute<ST>::type;
     constexpr int VEC = 16 / (int)sizeof(ST);
+    __shared__ DevState fin;
+    __shared__ double red[3 * FINAL_THREADS / 64];
+    resolve_state<256>(s0, part, nparts, &fin, red, s_out, 0);
+    const DevState *s = &fin;
     const size_t stride = (size_t)gridDim.x * blockDim.x, tid = (size_t)blockIdx.x * blockDim.x + threadIdx.x;
     if (s->pform == 2) {
         const CT c = (CT)s->scale;

@@ -6,25 +6,7 @@
 namespace stpi {
 
 __global__ void state_init_kernel(DevState *s, double scale, double tol, int max_iters, int check_rise, int pform) {
-    if (threadIdx.x == 0 && blockIdx.x == 0) {
-        s->scale = scale;
-        s->residual = 0.0;
-        s->lambda = 0.0;
-        s->rayleigh = 0.0;
-        s->tol = tol;
-        s->iters = 0;
-        s->done = max_iters <= 0 ? 1 : 0;
-        s->cur = 0;
-        s->flags = 0u;
-        s->max_iters = max_iters;
-        s->converged = 0;
-        s->arrive = 0u;
-        s->ubound = 0u;
-        s->wmax[0] = s->wmax[1] = 0u;
-        s->first_res[0] = s->first_res[1] = 0.0;
-        s->check_rise = check_rise;
-        s->pform = pform;
-    }
+    if (threadIdx.x == 0 && blockIdx.x == 0) init_state(s, scale, tol, max_iters, check_rise, pform);
 }
 
 // Empties the partial-sum slots of a chain whose steps finalise themselves.
@@ -59,11 +41,13 @@ __global__ void state_from_norm_kernel(const double *partials, int n, DevState *
 // After a step wrote z = A x_k (x_k unit) and block partials
 // (sum z * x_stored, sum z^2):  n = ||z||, x_{k+1} = z / n,
 // cos = <x_{k+1}, x_k> = scale * P1 / n, residual = sqrt(2 - 2 cos).
-__global__ void finalize_kernel(const double *partials, int n, DevState *s) {
+__global__ __launch_bounds__(CHAIN_THREADS) void finalize_kernel(StepPartials part, int n, DevState *s) {
     if (s->done) return;
+    __shared__ double red[3 * FINAL_THREADS / 64];
     double p1, p2;
-    sum_pairs(partials, n, p1, p2);
-    if (threadIdx.x == 0) step_finalize(s, p1, p2);
+    uint32_t wm;
+    sum_partials<CHAIN_THREADS>(part.sums, part.wmax, n, red, p1, p2, wm);
+    if (threadIdx.x == 0) step_finalize(s, p1, p2, wm);
 }
 
 // Single-step mode: d_sums = (sum z^2, x_scale * sum z * x).
@@ -216,8 +200,8 @@ hipError_t launch_clear_word(uint32_t *w, hipStream_t st) {
     return hipGetLastError();
 }
 
-hipError_t launch_finalize(const double *partials, int n, DevState *s, hipStream_t st) {
-    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(CHAIN_THREADS), 0, st, partials, n, s);
+hipError_t launch_finalize(StepPartials part, int n, DevState *s, hipStream_t st) {
+    hipLaunchKernelGGL(finalize_kernel, dim3(1), dim3(CHAIN_THREADS), 0, st, part, n, s);
     return hipGetLastError();
 }
 

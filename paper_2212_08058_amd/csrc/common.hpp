@@ -66,13 +66,15 @@ struct DevState {
     // steps): 1: the current buffer holds w = f x g (see FwdOpP), 2: uniform
     // start, no step taken yet (the iterate is the constant 1, w = f itself).
     int32_t pform;
-    // Product form: float bits of max |w| over buffer 0 / buffer 1 (the
-    // buffer a step writes collects it; the step's finalisation clears the
-    // entry of the buffer it read, which the next step writes).
+    // Product form: float bits of max |w| over buffer 0 / buffer 1, set for
+    // the buffer a step wrote by that step's finalisation.
     uint32_t wmax[2];
     // Batched chains, plain form: 1 after a rejected warm start until the
     // clip's buffer has been refilled with the uniform start.
     int32_t refill;
+    // Single-clip chains: 1 while the last step's finalisation is still to be
+    // formed from its partial sums (see resolve_state).
+    int32_t pending;
 };
 
 static_assert(sizeof(DevState) <= 256, "the iteration state lives in a 256-byte workspace slot");
@@ -112,7 +114,8 @@ constexpr int FINAL_THREADS = 256;
 // Step finalisation from the reduced sums P1 = sum z * x_stored and
 // P2 = sum z^2: n = ||z||, x_{k+1} = z / n (Eq. 8), cos = <x_{k+1}, x_k> =
 // scale * P1 / n, residual = sqrt(2 - 2 cos), and the stopping rules.
-__device__ __forceinline__ void step_finalize(DevState *s, double p1, double p2) {
+// wm: float bits of max |w| of the buffer the step wrote (product form).
+__device__ __forceinline__ void step_finalize(DevState *s, double p1, double p2, uint32_t wm = 0u) {
     const double scale = s->scale;
     const double nz = sqrt(p2);
     if (!isfinite(nz) || !isfinite(p1)) {
@@ -130,8 +133,8 @@ __device__ __forceinline__ void step_finalize(DevState *s, double p1, double p2)
     s->lambda = nz;
     s->residual = sqrt(fmax(0.0, 2.0 - 2.0 * c));
     s->scale = 1.0 / nz;
-    s->wmax[s->cur] = 0u;  // the buffer just read is the next step's output
     s->cur ^= 1;
+    s->wmax[s->cur] = wm;
     s->iters += 1;
     if (s->pform == 2) s->pform = 1;
     if (s->iters <= 2) s->first_res[s->iters - 1] = s->residual;
@@ -181,6 +184,124 @@ __device__ __forceinline__ float block_max(float v, float *lds) {
         for (int i = 0; i < NW; ++i) m = fmaxf(m, lds[i]);
     }
     return m;
+}
+
+// Partial results of a step's workgroups: [n][2] sums, [n] float bits of max |w|.
+struct StepPartials {
+    double *sums;
+    uint32_t *wmax;
+};
+
+// The sums of n workgroups' partial pairs, and the largest of their maxima, in
+// the order of one FINAL_THREADS workgroup (thread i adds entries i, i +
+// FINAL_THREADS, ..., then the tree of block_sum) whatever NTHR is. Valid in
+// thread 0. sh: 3 * FINAL_THREADS / 64 doubles.
+template <int NTHR>
+__device__ __forceinline__ void sum_partials(const double *sums, const uint32_t *wmax, int n, double *sh, double &p1,
+                                             double &p2, uint32_t &wm) {
+    constexpr int NW = FINAL_THREADS / 64;
+    const int lane = threadIdx.x & 63;
+#pragma unroll
+    for (int v0 = 0; v0 < FINAL_THREADS; v0 += NTHR) {
+        const int v = v0 + (int)threadIdx.x;
+        if (v < FINAL_THREADS) {  // whole wavefronts
+            double a = 0.0, b = 0.0;
+            uint32_t m = 0u;
+            for (int i = v; i < n; i += FINAL_THREADS) {
+                a += sums[2 * i];
+                b += sums[2 * i + 1];
+                const uint32_t w = wmax ? wmax[i] : 0u;
+                m = w > m ? w : m;
+            }
+#pragma unroll
+            for (int off = 32; off >= 1; off >>= 1) {
+                a += __shfl_xor(a, off, 64);
+                b += __shfl_xor(b, off, 64);
+                const uint32_t w = (uint32_t)__shfl_xor((int)m, off, 64);
+                m = w > m ? w : m;
+            }
+            if (lane == 0) {
+                sh[v >> 6] = a;
+                sh[NW + (v >> 6)] = b;
+                sh[2 * NW + (v >> 6)] = (double)m;  // exact
+            }
+        }
+    }
+    __syncthreads();
+    p1 = p2 = 0.0;
+    wm = 0u;
+    if (threadIdx.x == 0) {
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            p1 += sh[i];
+            p2 += sh[NW + i];
+            const uint32_t w = (uint32_t)sh[2 * NW + i];
+            wm = w > wm ? w : wm;
+        }
+    }
+}
+
+// The chain's state as a launch finds it. A step does not finalise itself: its
+// workgroups leave partial sums, and every workgroup of the next launch (the
+// next step, or the final pass) forms the finalisation from them for itself, at
+// its start, all with the same result; workgroup 0 writes it to the other
+// state slot for the launch after. So a step needs no counter that its
+// workgroups raise one after the other (16 ns each: 14 us for 840), no last
+// workgroup that polls for the others' sums, and no launch of its own. `in` and `out` are
+// different slots, as the launch's own partials are another set than the ones
+// read here. After the call *st holds the state (LDS); pend is the value of
+// its `pending` written to `out` (the launch leaves partial sums itself).
+template <int NTHR>
+__device__ __forceinline__ void resolve_state(const DevState *in, StepPartials part, int n, DevState *st, double *sh,
+                                              DevState *out, int pend) {
+    constexpr int NWORD = (int)(sizeof(DevState) / 4);
+    static_assert(NWORD <= 64 && NTHR >= 64, "one wavefront copies the state");
+    if (threadIdx.x < NWORD) reinterpret_cast<uint32_t *>(st)[threadIdx.x] = reinterpret_cast<const uint32_t *>(in)[threadIdx.x];
+    double p1, p2;
+    uint32_t wm;
+    sum_partials<NTHR>(part.sums, part.wmax, n, sh, p1, p2, wm);
+    if (threadIdx.x == 0) {
+        if (st->pending) {
+            st->pending = 0;
+            if (!st->done) step_finalize(st, p1, p2, wm);
+        }
+        if (out && blockIdx.x == 0) {
+            *out = *st;
+            out->pending = pend && !st->done ? 1 : 0;
+        }
+    }
+    __syncthreads();
+}
+
+// Sums of two values and the maximum of a third over a workgroup, valid in
+// thread 0 (the order of block_sum). sh: 3 * NTHR / 64 doubles.
+template <int NTHR>
+__device__ __forceinline__ void block_reduce(double &a, double &b, float &m, double *sh) {
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) {
+        a += __shfl_xor(a, off, 64);
+        b += __shfl_xor(b, off, 64);
+        m = fmaxf(m, __shfl_xor(m, off, 64));
+    }
+    constexpr int NW = NTHR / 64;
+    const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
+    __syncthreads();
+    if (lane == 0) {
+        sh[wid] = a;
+        sh[NW + wid] = b;
+        sh[2 * NW + wid] = (double)m;
+    }
+    __syncthreads();
+    if (threadIdx.x == 0) {
+        a = b = 0.0;
+        m = 0.f;
+#pragma unroll
+        for (int i = 0; i < NW; ++i) {
+            a += sh[i];
+            b += sh[NW + i];
+            m = fmaxf(m, (float)sh[2 * NW + i]);
+        }
+    }
 }
 
 // Reads partial-sum slot i of a step finalised by its last workgroup (see

@@ -3,6 +3,8 @@
 // STPI_VARIANTS(X) (the compiled (RS, RT, TH, TW, NTHR, RY, QX, OCC, PIPE) list) defined.
 #pragma once
 
+#include <cmath>
+
 #include "aux.hpp"
 #include "batch.hpp"
 #include "chain.hpp"
@@ -23,8 +25,25 @@ hipError_t sumsq_impl(const void *x, size_t n, double *partials, hipStream_t s) 
     return hipGetLastError();
 }
 
-hipError_t normalize_impl(void *x, const void *buf1, size_t n, const DevState *st_, hipStream_t s) {
-    hipLaunchKernelGGL(normalize_kernel<ST_>, dim3(1024), dim3(256), 0, s, (ST_ *)x, (const ST_ *)buf1, n, st_);
+// Workgroups of a streaming pass over n elements: up to 1024, each with at
+// least a few 16-byte chunks per thread (a small volume's pass is not spread
+// over workgroups that find nothing to do).
+dim3 stream_grid(size_t n) {
+    const size_t per = 256 * 4 * (16 / sizeof(ST_));
+    const size_t g = (n + per - 1) / per;
+    return dim3((unsigned)(g < 1 ? 1 : (g > 1024 ? 1024 : g)));
+}
+
+hipError_t uniform_start_impl(void *x, size_t n, DevState *st_, double tol, int max_iters, hipStream_t s) {
+    hipLaunchKernelGGL(uniform_start_kernel<ST_>, stream_grid(n), dim3(256), 0, s, (ST_ *)x, n, st_,
+                       1.0 / std::sqrt((double)n), tol, max_iters);
+    return hipGetLastError();
+}
+
+hipError_t normalize_impl(void *x, const void *buf1, size_t n, const DevState *st_, StepPartials part, int nparts,
+                          DevState *out, hipStream_t s) {
+    hipLaunchKernelGGL(normalize_kernel<ST_>, stream_grid(n), dim3(256), 0, s, (ST_ *)x, (const ST_ *)buf1, n, st_,
+                       part, nparts, out);
     return hipGetLastError();
 }
 
@@ -40,9 +59,10 @@ hipError_t to_product_impl(const void *f, const void *x, void *buf1, size_t n, D
     return hipGetLastError();
 }
 
-hipError_t from_product_impl(void *x, const void *buf1, const void *f, size_t n, const DevState *st_, hipStream_t s) {
-    hipLaunchKernelGGL(from_product_kernel<ST_>, dim3(1024), dim3(256), 0, s, (ST_ *)x, (const ST_ *)buf1,
-                       (const ST_ *)f, n, st_);
+hipError_t from_product_impl(void *x, const void *buf1, const void *f, size_t n, const DevState *st_,
+                             StepPartials part, int nparts, DevState *out, hipStream_t s) {
+    hipLaunchKernelGGL(from_product_kernel<ST_>, stream_grid(n), dim3(256), 0, s, (ST_ *)x, (const ST_ *)buf1,
+                       (const ST_ *)f, n, st_, part, nparts, out);
     return hipGetLastError();
 }
 
@@ -157,7 +177,7 @@ hipError_t batch_refill_impl(void *x, void *buf1, const ClipDesc *clips, const D
 }
 
 const DtypeOps kOps = {sizeof(ST_),       kVariants,        (int)(sizeof(kVariants) / sizeof(kVariants[0])),
-                       &fill_ones_impl,   &sumsq_impl,      &normalize_impl,
+                       &fill_ones_impl, &uniform_start_impl,   &sumsq_impl,      &normalize_impl,
                        &bound_impl,        &to_product_impl, &from_product_impl,
                        kAdj,              kNAdj,            &combine_fwd_impl,
                        &combine_bwd_impl, &scale_impl,      &dot_impl,

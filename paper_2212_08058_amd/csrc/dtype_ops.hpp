@@ -12,13 +12,18 @@ struct DtypeOps {
     const Variant *variants;     // compiled step kernels
     int nvariants;
     hipError_t (*fill_ones)(void *x, size_t n, hipStream_t);
+    // x <- 1 and a new chain's state (uniform start, plain form)
+    hipError_t (*uniform_start)(void *x, size_t n, DevState *s, double tol, int max_iters, hipStream_t);
     hipError_t (*sumsq)(const void *x, size_t n, double *partials, hipStream_t);
-    hipError_t (*normalize)(void *x, const void *buf1, size_t n, const DevState *s, hipStream_t);
+    // x <- the unit iterate; nparts > 0: of a chain whose last step is still to be finalised (see normalize_kernel)
+    hipError_t (*normalize)(void *x, const void *buf1, size_t n, const DevState *s, StepPartials part, int nparts,
+                            DevState *s_out, hipStream_t);
     // *out = max(*out, max |f| or max |f x|) as float bits (matrix-core step variants)
     hipError_t (*bound)(size_t n, const void *f, const void *x, uint32_t *out, hipStream_t);
     // product-form chains: start (w = f x g into buf1) and final pass (x = unit iterate)
     hipError_t (*to_product)(const void *f, const void *x, void *buf1, size_t n, DevState *s, hipStream_t);
-    hipError_t (*from_product)(void *x, const void *buf1, const void *f, size_t n, const DevState *s, hipStream_t);
+    hipError_t (*from_product)(void *x, const void *buf1, const void *f, size_t n, const DevState *s,
+                               StepPartials part, int nparts, DevState *s_out, hipStream_t);
     // differentiation path (null where a storage type does not provide it)
     const AdjVariant *adj_variants;
     int nadj;

@@ -246,7 +246,7 @@ int stpi_exp_iterate(const stpi_problem *p, const void *s, const void *f, double
         for (int k = 0; k < n; ++k) {
             if ((e = exp_launch(p, s, f, alpha, x, buf1, state, partials, 1.0, st)) != hipSuccess)
                 return hip_fail(e, "exact-affinity step");
-            if ((e = launch_finalize(partials, exp_units(p), state, st)) != hipSuccess)
+            if ((e = launch_finalize({partials, nullptr}, exp_units(p), state, st)) != hipSuccess)
                 return hip_fail(e, "finalize");
         }
         done += n;
@@ -257,7 +257,7 @@ int stpi_exp_iterate(const stpi_problem *p, const void *s, const void *f, double
             if (hs.done) break;
         }
     }
-    if ((e = ops->normalize(x, buf1, N, state, st)) != hipSuccess) return hip_fail(e, "normalize");
+    if ((e = ops->normalize(x, buf1, N, state, {nullptr, nullptr}, 0, nullptr, st)) != hipSuccess) return hip_fail(e, "normalize");
     if ((e = hipMemcpyAsync(&hs, state, sizeof(hs), hipMemcpyDeviceToHost, st)) != hipSuccess ||
         (e = hipStreamSynchronize(st)) != hipSuccess)
         return hip_fail(e, "state readback");

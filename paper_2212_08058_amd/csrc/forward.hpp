@@ -18,9 +18,14 @@ struct FwdLaunch {
     const double *norm_in;  // single step: if set, x_scale = 1 / *norm_in (read on the device)
     void *vout;             // if set, also store v = G (f x) (x unit) for the adjoint
     double *partials;    // [tiles * nseg][2] doubles
+    uint32_t *wpart;     // iterate mode: [tiles * nseg] maxima (see StepPartials)
+    // iterate mode: the slot this step's state goes to and the previous step's
+    // partials (resolve_state); state_out null: the state is already final
+    // (a separate kernel finalises every step)
+    DevState *state_out;
+    StepPartials prev_part;
     int T, H, W;
     int nseg;            // frame segments per tile (0 is read as 1)
-    int fuse;            // iterate mode: finalise the step in its last workgroup (if the variant can)
     int no_prev;         // iterate mode: the step's inner product with the previous iterate is not formed
     // matrix-core variants: float bits of a bound on |f x_stored scale| (iterate
     // mode: on |f|, the iterate being unit; single step: on |f x_stored|, scaled
@@ -46,9 +51,11 @@ struct FwdArgs {
     const ST *f;
     ST *buf0;
     ST *buf1;
-    DevState *state;
+    const DevState *state;
+    DevState *state_out;       // see FwdLaunch
+    StepPartials prev_part;
     double *partials;
-    int fuse;  // 1: the last workgroup to finish reduces the partials and finalises the step
+    uint32_t *wpart;
     int no_prev;  // 1: the previous iterate is not read at the outputs (p1 = 0; see FwdOp::prev)
     double x_scale;
     const double *norm_in;
@@ -351,7 +358,9 @@ struct FwdOpP {
 // with NTHR = 512, OCC = 4 lets two workgroups share a CU).
 // PIPE: 1 selects the software-pipelined tile loop (stencil_tile_pipe), 2 its
 // straight-line form (stencil_tile_flat), 3 the matrix-core tile loop
-// (stencil_tile_mfma; RS = 16, any space radius up to 16).
+// (stencil_tile_mfma; RS = 16, any space radius up to 16), 4 one output frame
+// per workgroup with all its input frames at once (stencil_tile_gather; the
+// launch's frame segments are the T single frames).
 // PF: product-form chain step (PIPE 3, iterate mode only).
 template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX, int OCC, int PIPE, bool PF>
 __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
@@ -365,8 +374,9 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
     // bfloat16 product-form chains stage their raw bfloat16 values (one U plane)
     constexpr bool EXACT = PF && std::is_same<ST, bf16>::value;
     __shared__ CT lds[PIPE == 3 ? MfmaLds<PIPE, TH, TW, NTHR, PAD, EXACT ? 1 : 2>::value
-                                : (PIPE ? PG::LDS_ELEMS : G::LDS_ELEMS)];
-    __shared__ double red[NTHR / 64];
+                                : (PIPE == 1 || PIPE == 2 ? PG::LDS_ELEMS : G::LDS_ELEMS)];
+    constexpr int RED = 3 * (NTHR > FINAL_THREADS ? NTHR : FINAL_THREADS) / 64;
+    __shared__ double red[RED];
 
     const int nbx = (a.W + TW - 1) / TW, nby = (a.H + TH - 1) / TH;
     // consecutive units share an XCD: neighbouring tiles of one frame segment
@@ -380,12 +390,19 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
     FwdOp<ST> op;
     op.f = a.f;
     double scale;
+    __shared__ DevState st;  // iterate mode: the state this step works on
     if (a.state) {
-        if (a.state->done) return;
-        const int cur = a.state->cur;
+        if (a.state_out)
+            resolve_state<NTHR>(a.state, a.prev_part, ntiles * a.nseg, &st, red, a.state_out, 1);
+        else {
+            if (threadIdx.x == 0) st = *a.state;
+            __syncthreads();
+        }
+        if (__builtin_amdgcn_readfirstlane(st.done)) return;
+        const int cur = __builtin_amdgcn_readfirstlane(st.cur);
         op.src = cur ? a.buf1 : a.buf0;
         op.dst = cur ? a.buf0 : a.buf1;
-        scale = a.state->scale;
+        scale = st.scale;
     } else {
         op.src = a.buf0;
         op.dst = a.buf1;
@@ -396,6 +413,7 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
     op.plane = (size_t)a.H * a.W;
     op.pbytes = (uint32_t)(op.plane * sizeof(ST));
     double d1 = 0.0, d2 = 0.0;
+    float wm = 0.f;  // product form: max |w| stored by this thread
     const int x0 = (tile % nbx) * TW, y0 = (tile / nbx) * TH;
     op.cut = x0 + TW > a.W;  // 4-wide epilogue loads read past the right edge here
     op.prev = !a.no_prev;
@@ -410,11 +428,11 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
         }
         __syncthreads();
         // staging multiplier umul = scale 2^S with |f x scale 2^S| < 2^10, output scale 2^-S
-        float bound = __uint_as_float(*a.ubound);
+        float bound = __uint_as_float(a.state ? st.ubound : *a.ubound);
         if constexpr (PF) {
             const int e = bound_exponent(bound, PRODUCT_ELIM);
-            const bool first = a.state->pform == 2;
-            const int cur = a.state->cur;
+            const bool first = __builtin_amdgcn_readfirstlane(st.pform) == 2;
+            const int cur = __builtin_amdgcn_readfirstlane(st.cur);
             FwdOpP<ST> pp;
             pp.f = a.f;
             pp.src = first ? a.f : op.src;
@@ -427,7 +445,7 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
             pp.cut = x0 + TW > a.W;
             pp.prev = op.prev;
             // staging power of two from the input's own maximum
-            const float win = first ? bound : __uint_as_float(a.state->wmax[cur]);
+            const float win = first ? bound : __uint_as_float(st.wmax[cur]);
             float umul;
             if constexpr (EXACT) {
                 // the y-pass multiplies the staged bfloat16 w by ginv_in
@@ -445,8 +463,7 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
                                                           x0, y0, lds, d1, d2);
             d1 *= pp.ginv_in * pp.ginv_out;
             d2 *= pp.ginv_out * pp.ginv_out;
-            const float m = block_max<NTHR>(pp.wmax, reinterpret_cast<float *>(red));
-            if (threadIdx.x == 0 && m > 0.f) atomicMax(&a.state->wmax[cur ^ 1], __float_as_uint(m));
+            wm = pp.wmax;
         } else {
             if (!a.state) bound *= (float)fabs(scale);
             const int e = bound_exponent(bound, 100);
@@ -455,59 +472,19 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
             stencil_tile_mfma<CT, RT, TH, TW, NTHR, PAD>(op, a.taps, tapl, umul, a.rs, a.T, t0, t1, a.H, a.W, x0, y0,
                                                    lds, d1, d2);
         }
-    } else if constexpr (PIPE == 2)
+    } else if constexpr (PIPE == 4)
+        stencil_tile_gather<CT, RS, RT, TH, TW, NTHR, RY>(op, a.taps, a.T, t0, a.H, a.W, x0, y0, lds, d1, d2);
+    else if constexpr (PIPE == 2)
         stencil_tile_flat<CT, RS, RT, TH, TW, NTHR, RY, QX>(op, a.taps, a.T, t0, t1, a.H, a.W, x0, y0, lds, d1, d2);
     else if constexpr (PIPE == 1)
         stencil_tile_pipe<CT, RS, RT, TH, TW, NTHR, RY, QX>(op, a.taps, a.T, t0, t1, a.H, a.W, x0, y0, lds, d1, d2);
     else
         stencil_tile<CT, RS, RT, TH, TW, NTHR, RY, QX>(op, a.taps, a.T, t0, t1, a.H, a.W, x0, y0, lds, d1, d2);
-    const double s1 = block_sum<NTHR>(d1, red);
-    const double s2 = block_sum<NTHR>(d2, red);
-    __shared__ int s_last;
+    block_reduce<NTHR>(d1, d2, wm, red);
     if (threadIdx.x == 0) {
-        if (a.fuse) {
-            // Publish the two sums device-wide: agent-scope stores write through
-            // the XCD's L2 into slots the last workgroup polls (PARTIAL_EMPTY);
-            // the wait makes sure they are done before this workgroup is counted
-            // in. Only these values cross workgroups, so no full L2 write-back is
-            // needed (the kernel boundary orders the rest).
-            __hip_atomic_store(&a.partials[2 * unit], s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&a.partials[2 * unit + 1], s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __builtin_amdgcn_s_waitcnt(0);
-            s_last = __hip_atomic_fetch_add(&a.state->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                     (unsigned)(nbx * nby * a.nseg - 1);
-        } else {
-            a.partials[2 * unit] = s1;
-            a.partials[2 * unit + 1] = s2;
-        }
-    }
-    if constexpr (NTHR >= FINAL_THREADS) {
-        if (!a.fuse) return;
-        __syncthreads();
-        if (!__builtin_amdgcn_readfirstlane(s_last)) return;
-        // last workgroup: the step finalisation, summed in the order of the
-        // separate finalisation kernel (threads >= FINAL_THREADS add zeros);
-        // agent-scope loads read the published sums past the local L2
-        const int n = nbx * nby * a.nseg;
-        double p1 = 0.0, p2 = 0.0;
-        bool late = false;
-        if (threadIdx.x < FINAL_THREADS)
-            for (int i = threadIdx.x; i < n; i += FINAL_THREADS) {
-                p1 += take_partial(&a.partials[2 * i], &late);
-                p2 += take_partial(&a.partials[2 * i + 1], &late);
-            }
-        p1 = block_sum<NTHR>(p1, red);
-        p2 = block_sum<NTHR>(p2, red);
-        __shared__ int s_late;
-        if (threadIdx.x == 0) s_late = 0;
-        __syncthreads();
-        if (late) s_late = 1;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            if (s_late) a.state->flags |= FLAG_SYNC;
-            step_finalize(a.state, p1, p2);
-            a.state->arrive = 0u;
-        }
+        a.partials[2 * unit] = d1;
+        a.partials[2 * unit + 1] = d2;
+        if (PF) a.wpart[unit] = __float_as_uint(wm);
     }
 }
 
@@ -519,8 +496,11 @@ hipError_t launch_fwd(const FwdLaunch &L, hipStream_t stream) {
     a.buf0 = (ST *)L.buf0;
     a.buf1 = (ST *)L.buf1;
     a.state = L.state;
+    a.state_out = L.state_out;
+    a.prev_part = L.prev_part;
+    if (!PF) a.prev_part.wmax = nullptr;
     a.partials = L.partials;
-    a.fuse = L.state && L.fuse && NTHR >= FINAL_THREADS ? 1 : 0;
+    a.wpart = L.wpart;
     a.no_prev = L.state && L.no_prev ? 1 : 0;
     a.x_scale = L.x_scale;
     a.norm_in = L.norm_in;
@@ -528,13 +508,14 @@ hipError_t launch_fwd(const FwdLaunch &L, hipStream_t stream) {
     a.T = L.T;
     a.H = L.H;
     a.W = L.W;
-    a.nseg = L.nseg > 0 ? L.nseg : 1;
+    a.nseg = PIPE == 4 ? L.T : (L.nseg > 0 ? L.nseg : 1);
     a.ubound = L.ubound;
     a.rs = 0;
     for (int d = 1; d <= 16; ++d)
         if (L.gs[16 + d] != 0.0) a.rs = d;
     if (PIPE == 3 && !L.ubound) return hipErrorInvalidValue;
-    if (PF && (!L.state || L.vout)) return hipErrorInvalidValue;
+    if (PF && (!L.state || L.vout || !L.wpart)) return hipErrorInvalidValue;
+    if (L.state && L.state_out == L.state) return hipErrorInvalidValue;
     // L holds taps centred at index 16 (space) and 8 (time), zero beyond the
     // problem's radii; the kernel wants them centred at its compiled RS, RT.
     for (int i = 0; i < 2 * 16 + 1; ++i) a.taps.gs[i] = CT(0);
@@ -546,11 +527,6 @@ hipError_t launch_fwd(const FwdLaunch &L, hipStream_t stream) {
     hipLaunchKernelGGL((fwd_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, OCC, PIPE, PF>), dim3(per * NUM_XCD),
                        dim3(NTHR), 0, stream, a);
     return hipGetLastError();
-}
-
-template <int NTHR>
-constexpr bool fwd_can_fuse() {
-    return NTHR >= FINAL_THREADS;
 }
 
 // Matrix-core variants report the occupancy of their product-form kernel,

@@ -89,6 +89,26 @@ static double variant_cost(const Variant &v, const stpi_problem *p) {
     return taps * cover;
 }
 
+static int tiles_for(const Variant &v, const stpi_problem *p) {
+    return ((p->W + v.TW - 1) / v.TW) * ((p->H + v.TH - 1) / v.TH);
+}
+
+// Whether a loop with a workgroup per tile and output frame (PIPE 4) beats the
+// streamed loops. It costs about 5.5 us plus 7 us per thousand 16 x 64 tiles
+// and frames (it re-reads 2 r_t + 1 frames for each), a streamed step 8 us plus
+// about a third of a microsecond per frame of its segments. Measured at r =
+// (4, 2), chain step in us, streamed / 8 x 32 / 16 x 64 tile: 8x64x112 10.3 / 5.8 /
+// 6.7 (256 and 64 workgroups), 64x48x64 15.4 / 7.5 / 6.4 (768, 192), 16x120x214
+// 12.3 / 12.6 / 9.0 (1680, 512), 32x120x214 13.1 / 18.7 / 12.1 (3360, 1024),
+// 2x480x854 9.1 / 18.0 / 11.2 (3240, 840). So: the small tile while every
+// workgroup has a CU of its own, the large one up to two per CU on clips longer
+// than the temporal window.
+static bool gather_pays(const Variant &v, const stpi_problem *p) {
+    const int64_t units = (int64_t)tiles_for(v, p) * p->T;
+    if (v.TH * v.TW <= 256) return units <= device_cus();
+    return units <= 2 * device_cus() && p->T > 2 * v.RT;
+}
+
 const Variant *choose_variant(const stpi_problem *p, int forced_index, bool allow_mfma) {
     const DtypeOps *ops = ops_for(p->dtype);
     if (forced_index >= 0 && forced_index < ops->nvariants && !allow_mfma && ops->variants[forced_index].PIPE == 3)
@@ -110,6 +130,10 @@ const Variant *choose_variant(const stpi_problem *p, int forced_index, bool allo
         const Variant &v = ops->variants[i];
         if (v.RS < p->r_s || v.RT < p->r_t) continue;
         if (v.PIPE == 3 && !allow_mfma) continue;
+        if (v.PIPE == 4) {
+            if (gather_pays(v, p)) return &v;
+            continue;
+        }
         const double c = variant_cost(v, p);
         if (c < best_cost) {
             best_cost = c;
@@ -117,10 +141,6 @@ const Variant *choose_variant(const stpi_problem *p, int forced_index, bool allo
         }
     }
     return best;
-}
-
-static int tiles_for(const Variant &v, const stpi_problem *p) {
-    return ((p->W + v.TW - 1) / v.TW) * ((p->H + v.TH - 1) / v.TH);
 }
 
 int device_cus() {
@@ -178,6 +198,7 @@ int split_short_tiles(int tiles, int T, int RT) {
 // its few workgroups, not by work: there segments may be as short as 2 RT
 // frames and up to STPI_NSEG_MAX per tile.
 int segments_for(const Variant &v, const stpi_problem *p) {
+    if (v.PIPE == 4) return p->T;  // a workgroup per frame
     const int tiles = tiles_for(v, p);
     const int resident = device_cus() * v.blocks_per_cu();
     const int rt = v.RT > 0 ? v.RT : 1;
@@ -194,13 +215,15 @@ int segments_for(const Variant &v, const stpi_problem *p) {
 
 int grid_blocks(const Variant &v, const stpi_problem *p) { return tiles_for(v, p) * segments_for(v, p); }
 
-// Workspace: [state 256 B][partials][ping-pong volume]. The partials area
-// holds the largest grid any compiled variant can use for this frame size.
+// Workspace: [3 state slots][2 x partial sums][2 x maxima][ping-pong volume].
+// A partials set holds the largest grid any compiled variant can use for this
+// frame size.
 size_t partials_capacity(const stpi_problem *p) {
     const DtypeOps *ops = ops_for(p->dtype);
     size_t cap = (size_t)NORM_BLOCKS_HOST;
     for (int i = 0; i < ops->nvariants; ++i) {
-        const size_t g = (size_t)tiles_for(ops->variants[i], p) * STPI_NSEG_MAX;
+        const Variant &v = ops->variants[i];
+        const size_t g = (size_t)tiles_for(v, p) * (v.PIPE == 4 ? (size_t)p->T : (size_t)STPI_NSEG_MAX);
         if (g > cap) cap = g;
     }
     for (int i = 0; i < ops->nadj; ++i) {
@@ -216,13 +239,20 @@ WsLayout layout_for(const stpi_problem *p) {
     const DtypeOps *ops = ops_for(p->dtype);
     const size_t N = (size_t)p->T * p->H * p->W;
     L.state_off = 0;
-    L.partials_off = 256;
+    L.partials_off = (FINAL_SLOT + 1) * STATE_SLOT;
     L.partials_cap = partials_capacity(p);
-    size_t off = L.partials_off + L.partials_cap * 2 * sizeof(double);
+    L.wmax_off = L.partials_off + 2 * L.partials_cap * 2 * sizeof(double);
+    size_t off = L.wmax_off + 2 * L.partials_cap * sizeof(uint32_t);
     off = (off + 255) & ~(size_t)255;
     L.buf_off = off;
     L.total = off + ((N * ops->elem + 255) & ~(size_t)255);
     return L;
+}
+
+ChainMem chain_mem(const WsLayout &L, void *ws) {
+    char *w = (char *)ws;
+    return {(DevState *)(w + L.state_off), (double *)(w + L.partials_off), (uint32_t *)(w + L.wmax_off),
+            L.partials_cap, w + L.buf_off};
 }
 
 static int g_forced_variant = -1;
@@ -257,7 +287,7 @@ static std::vector<GraphEntry> g_graphs;
 static unsigned long long g_graph_clock = 0;
 constexpr size_t GRAPH_CACHE_MAX = 16;
 
-// STPI_NO_FUSE=1 keeps the step finalisation in its own kernel (for comparison).
+// STPI_NO_FUSE=1 finalises every step in a kernel of its own (for comparison).
 bool fusion_disabled() {
     const char *e = std::getenv("STPI_NO_FUSE");
     return e && e[0] == '1';
@@ -285,9 +315,8 @@ struct ChainArgs {
     const DtypeOps *ops;
     const Variant *v;
     const void *f;
-    void *x, *buf1;
-    DevState *state;
-    double *partials;
+    void *x;
+    ChainMem m;
     int init, max_iters;
     double tol;
     int pform;
@@ -296,18 +325,15 @@ struct ChainArgs {
 int enqueue_chain_part(const ChainArgs &a, int part, hipStream_t s) {
     switch (part) {
         case CHAIN_ALL:
-            return enqueue_iteration(a.p, a.ops, a.v, a.f, a.x, a.buf1, a.state, a.partials, a.init, a.max_iters,
-                                     a.tol, s, a.pform);
+            return enqueue_iteration(a.p, a.ops, a.v, a.f, a.x, a.m, a.init, a.max_iters, a.tol, s, a.pform);
         case CHAIN_HEAD: {
-            const int rc = enqueue_chain_init(a.p, a.ops, a.x, a.state, a.partials, a.init, a.max_iters, a.tol, s,
-                                              a.v, a.f, a.buf1, a.pform);
-            return rc ? rc
-                      : enqueue_chain_steps(a.p, a.v, a.f, a.x, a.buf1, a.state, a.partials, CHAIN_CHUNK, s, a.pform);
+            const int rc = enqueue_chain_init(a.p, a.ops, a.x, a.m, a.init, a.max_iters, a.tol, s, a.v, a.f, a.pform);
+            return rc ? rc : enqueue_chain_steps(a.p, a.v, a.f, a.x, a.m, CHAIN_CHUNK, s, a.pform);
         }
         case CHAIN_CHUNK_PART:
-            return enqueue_chain_steps(a.p, a.v, a.f, a.x, a.buf1, a.state, a.partials, CHAIN_CHUNK, s, a.pform);
-        default:
-            return enqueue_chain_tail(a.p, a.ops, a.f, a.x, a.buf1, a.state, s, a.pform);
+            return enqueue_chain_steps(a.p, a.v, a.f, a.x, a.m, CHAIN_CHUNK, s, a.pform);
+        default:  // after whole segments
+            return enqueue_chain_tail(a.p, a.ops, a.v, a.f, a.x, a.m, CHAIN_CHUNK, s, a.pform);
     }
 }
 
@@ -567,9 +593,7 @@ int stpi_iterate(const stpi_problem *p, const void *f, void *x, int init, int ma
     hipStream_t s = (hipStream_t)stream;
     const DtypeOps *ops = ops_for(p->dtype);
     const size_t N = (size_t)p->T * p->H * p->W;
-    DevState *state = (DevState *)((char *)ws + L.state_off);
-    double *partials = (double *)((char *)ws + L.partials_off);
-    void *buf1 = (char *)ws + L.buf_off;
+    const ChainMem m = chain_mem(L, ws);
 
     // A run in tolerance mode stops early, but a chain of max_iters steps
     // would still launch every (step, finalise) pair (they exit at once when
@@ -578,7 +602,7 @@ int stpi_iterate(const stpi_problem *p, const void *f, void *x, int init, int ma
     // behind so the device never waits for it.
     const bool chunked = tol > 0.0 && max_iters > 2 * CHAIN_CHUNK;
     const int pform = chain_pform(v, max_iters);
-    ChainArgs ca{p, ops, v, f, x, buf1, state, partials, init, max_iters, tol, pform};
+    ChainArgs ca{p, ops, v, f, x, m, init, max_iters, tol, pform};
     const bool use_graphs = s != nullptr && graphs_enabled();
     auto run = [&](int part) -> int {
         if (!use_graphs) return enqueue_chain_part(ca, part, s);
@@ -606,8 +630,9 @@ int stpi_iterate(const stpi_problem *p, const void *f, void *x, int init, int ma
         if (!poll || !ev) return fail(STPI_EHIP, "pinned poll buffer or event unavailable");
         hipError_t e;
         for (int issued = CHAIN_CHUNK; issued < max_iters; issued += CHAIN_CHUNK) {
-            // state after the chunks issued so far, then one more chunk while it travels
-            if ((e = hipMemcpyAsync(poll, state, sizeof(DevState), hipMemcpyDeviceToHost, s)) != hipSuccess)
+            // state after the chunks issued so far (their last step not yet
+            // finalised), then one more chunk while it travels
+            if ((e = hipMemcpyAsync(poll, m.state, sizeof(DevState), hipMemcpyDeviceToHost, s)) != hipSuccess)
                 return hip_fail(e, "state poll");
             if ((e = hipEventRecord(ev, s)) != hipSuccess) return hip_fail(e, "poll event");
             if ((rc = run(CHAIN_CHUNK_PART))) return rc;
@@ -619,7 +644,7 @@ int stpi_iterate(const stpi_problem *p, const void *f, void *x, int init, int ma
     if (!out) return STPI_OK;
 
     DevState hs;
-    hipError_t e = hipMemcpyAsync(&hs, state, sizeof(hs), hipMemcpyDeviceToHost, s);
+    hipError_t e = hipMemcpyAsync(&hs, m.slot(FINAL_SLOT), sizeof(hs), hipMemcpyDeviceToHost, s);
     if (e != hipSuccess) return hip_fail(e, "state readback");
     e = hipStreamSynchronize(s);
     if (e != hipSuccess) return hip_fail(e, "stream synchronize");
@@ -632,10 +657,6 @@ int stpi_iterate(const stpi_problem *p, const void *f, void *x, int init, int ma
     out->first_residuals[0] = hs.first_res[0];
     out->first_residuals[1] = hs.first_res[1];
     out->status = STPI_OK;
-    if (hs.flags & FLAG_SYNC) {
-        out->status = STPI_EHIP;
-        return fail(STPI_EHIP, "a step's partial sums did not arrive (step %d)", hs.iters + 1);
-    }
     if (hs.flags & FLAG_NONFINITE) out->status = STPI_ENONFINITE;
     else if (hs.flags & FLAG_ZERO) out->status = STPI_EZERO_NORM;
     (void)N;
@@ -703,16 +724,14 @@ int stpi_time_chain_step(const stpi_problem *p, const void *f, void *x, void *ws
     if (!v) return fail(STPI_EUNSUPPORTED, "no eligible kernel variant");
     hipStream_t s = (hipStream_t)stream;
     const DtypeOps *ops = ops_for(p->dtype);
-    DevState *state = (DevState *)((char *)ws + L.state_off);
-    double *partials = (double *)((char *)ws + L.partials_off);
-    void *buf1 = (char *)ws + L.buf_off;
+    const ChainMem m = chain_mem(L, ws);
     // a fixed-count chain long enough that no timed step finds it done
     const int total = reps + 2;
     const int pform = chain_pform(v, total);
     if (product_form) *product_form = pform;
-    rc = enqueue_chain_init(p, ops, x, state, partials, 1, total, 0.0, s, v, f, buf1, pform);
+    rc = enqueue_chain_init(p, ops, x, m, 1, total, 0.0, s, v, f, pform);
     // the steps as a fixed-count chain of `total` steps runs them
-    if (!rc) rc = enqueue_chain_steps(p, v, f, x, buf1, state, partials, 1, s, pform, total, 0);
+    if (!rc) rc = enqueue_chain_steps(p, v, f, x, m, 1, s, pform, total, 0);
     if (rc) return rc;
     hipEvent_t e0, e1;
     hipError_t e;
@@ -722,7 +741,7 @@ int stpi_time_chain_step(const stpi_problem *p, const void *f, void *x, void *ws
         return hip_fail(e, "event create");
     }
     e = hipEventRecord(e0, s);
-    if (e == hipSuccess) rc = enqueue_chain_steps(p, v, f, x, buf1, state, partials, reps, s, pform, total, 1);
+    if (e == hipSuccess) rc = enqueue_chain_steps(p, v, f, x, m, reps, s, pform, total, 1);
     if (e == hipSuccess && !rc) e = hipEventRecord(e1, s);
     if (e == hipSuccess && !rc) e = hipEventSynchronize(e1);
     float ms = 0.0f;
@@ -786,84 +805,93 @@ int stpi_set_variant(int index) {
 
 namespace stpi {
 
-// Enqueues start vector, max_iters (step, finalise) pairs and the final
-// normalisation. No host synchronisation.
-int enqueue_chain_init(const stpi_problem *p, const DtypeOps *ops, void *x, DevState *state, double *partials,
-                       int init, int max_iters, double tol, hipStream_t s, const Variant *v, const void *f,
-                       void *buf1, int pform) {
+// Whether the chain's steps leave their finalisation to the next launch.
+static bool deferred(const Variant *v, const stpi_problem *p) {
+    return grid_blocks(*v, p) <= DEFER_MAX_UNITS && !fusion_disabled();
+}
+
+// Enqueues start vector, max_iters steps and the final pass. No host
+// synchronisation.
+int enqueue_chain_init(const stpi_problem *p, const DtypeOps *ops, void *x, const ChainMem &m, int init,
+                       int max_iters, double tol, hipStream_t s, const Variant *v, const void *f, int pform) {
     const size_t N = (size_t)p->T * p->H * p->W;
+    DevState *state = m.state;
     hipError_t e;
     if (init == 1) {
         // product form: the first step stages f itself, the constant start is never stored
-        if (!pform && (e = ops->fill_ones(x, N, s)) != hipSuccess) return hip_fail(e, "fill");
-        if ((e = launch_state_init(state, 1.0 / std::sqrt((double)N), tol, max_iters, 0, pform ? 2 : 0, s)) !=
-            hipSuccess)
-            return hip_fail(e, "init");
+        e = pform ? launch_state_init(state, 1.0 / std::sqrt((double)N), tol, max_iters, 0, 2, s)
+                  : ops->uniform_start(x, N, state, tol, max_iters, s);
+        if (e != hipSuccess) return hip_fail(e, "init");
     } else {
         if ((e = launch_state_init(state, 1.0, tol, max_iters, init == 2 ? 1 : 0, 0, s)) != hipSuccess)
             return hip_fail(e, "init");
-        if ((e = ops->sumsq(x, N, partials, s)) != hipSuccess) return hip_fail(e, "norm");
-        if ((e = launch_state_from_norm(partials, NORM_BLOCKS_HOST, state, s)) != hipSuccess)
+        if ((e = ops->sumsq(x, N, m.partials, s)) != hipSuccess) return hip_fail(e, "norm");
+        if ((e = launch_state_from_norm(m.partials, NORM_BLOCKS_HOST, state, s)) != hipSuccess)
             return hip_fail(e, "init norm");
     }
     // matrix-core steps scale their operands by max |f| (the iterate is unit)
     if (v && v->PIPE == 3 && (e = ops->bound(N, f, nullptr, &state->ubound, s)) != hipSuccess)
         return hip_fail(e, "operand bound");
-    if (pform && init != 1 && (e = ops->to_product(f, x, buf1, N, state, s)) != hipSuccess)
+    if (pform && init != 1 && (e = ops->to_product(f, x, m.buf1, N, state, s)) != hipSuccess)
         return hip_fail(e, "product-form start");
-    // steps that finalise themselves poll their partial-sum slots
-    if (v && (e = launch_partials_empty(partials, grid_blocks(*v, p), s)) != hipSuccess)
-        return hip_fail(e, "partials");
-    if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "init");
     return STPI_OK;
 }
 
-int enqueue_chain_tail(const stpi_problem *p, const DtypeOps *ops, const void *f, void *x, void *buf1,
-                       DevState *state, hipStream_t s, int pform) {
+int enqueue_chain_tail(const stpi_problem *p, const DtypeOps *ops, const Variant *v, const void *f, void *x,
+                       const ChainMem &m, int steps, hipStream_t s, int pform) {
     const size_t N = (size_t)p->T * p->H * p->W;
-    const hipError_t e =
-        pform ? ops->from_product(x, buf1, f, N, state, s) : ops->normalize(x, buf1, N, state, s);
+    const bool defer = steps > 0 && deferred(v, p);
+    const DevState *last = m.slot(defer ? steps & 1 : 0);
+    StepPartials part = m.set((steps + 1) & 1);
+    if (!pform) part.wmax = nullptr;
+    const int np = defer ? grid_blocks(*v, p) : 0;
+    const hipError_t e = pform ? ops->from_product(x, m.buf1, f, N, last, part, np, m.slot(FINAL_SLOT), s)
+                               : ops->normalize(x, m.buf1, N, last, part, np, m.slot(FINAL_SLOT), s);
     return e == hipSuccess ? STPI_OK : hip_fail(e, "normalize");
 }
 
-int enqueue_chain_steps(const stpi_problem *p, const Variant *v, const void *f, void *x, void *buf1, DevState *state,
-                        double *partials, int steps, hipStream_t s, int pform, int fixed_total, int k0) {
+int enqueue_chain_steps(const stpi_problem *p, const Variant *v, const void *f, void *x, const ChainMem &m, int steps,
+                        hipStream_t s, int pform, int fixed_total, int k0) {
     hipError_t e;
     FwdLaunch FL;
     std::memset(&FL, 0, sizeof(FL));
     FL.f = f;
     FL.buf0 = x;
-    FL.buf1 = buf1;
-    FL.state = state;
-    FL.ubound = &state->ubound;
-    FL.partials = partials;
+    FL.buf1 = m.buf1;
     FL.T = p->T;
     FL.H = p->H;
     FL.W = p->W;
     FL.nseg = segments_for(*v, p);
+    FL.ubound = &m.state->ubound;
     make_taps(p, FL.gs, FL.gt);
     const int nb = grid_blocks(*v, p);
-    // workgroups of FINAL_THREADS or more finalise the step themselves (the
-    // last one to finish), saving a launch per step
-    FL.fuse = v->NTHR >= FINAL_THREADS && !fusion_disabled() ? 1 : 0;
+    const bool defer = deferred(v, p);
     const FwdLaunchFn launch = pform ? v->launch_p : v->launch;
     if (!launch) return fail(STPI_EUNSUPPORTED, "variant has no product-form step");
     for (int k = 0; k < steps; ++k) {
-        const int kk = k0 + k;
+        const int kk = k0 + k, slot = defer ? kk & 1 : 0;
         FL.no_prev = fixed_total > 0 && kk >= 2 && kk < fixed_total - 1 ? 1 : 0;
+        FL.state = m.slot(slot);
+        FL.state_out = defer ? m.slot(slot ^ 1) : nullptr;
+        const StepPartials mine = m.set(slot);
+        FL.partials = mine.sums;
+        FL.wpart = mine.wmax;
+        FL.prev_part = m.set(slot ^ 1);
         if ((e = launch(FL, s)) != hipSuccess) return hip_fail(e, "step kernel launch");
-        if (!FL.fuse && (e = launch_finalize(partials, nb, state, s)) != hipSuccess)
-            return hip_fail(e, "finalize launch");
+        if (!defer) {
+            StepPartials part = mine;
+            if (!pform) part.wmax = nullptr;
+            if ((e = launch_finalize(part, nb, m.state, s)) != hipSuccess) return hip_fail(e, "finalize launch");
+        }
     }
     return STPI_OK;
 }
 
 int enqueue_iteration(const stpi_problem *p, const DtypeOps *ops, const Variant *v, const void *f, void *x,
-                      void *buf1, DevState *state, double *partials, int init, int max_iters, double tol,
-                      hipStream_t s, int pform) {
-    int rc = enqueue_chain_init(p, ops, x, state, partials, init, max_iters, tol, s, v, f, buf1, pform);
-    if (!rc) rc = enqueue_chain_steps(p, v, f, x, buf1, state, partials, max_iters, s, pform, tol > 0.0 ? 0 : max_iters);
-    return rc ? rc : enqueue_chain_tail(p, ops, f, x, buf1, state, s, pform);
+                      const ChainMem &m, int init, int max_iters, double tol, hipStream_t s, int pform) {
+    int rc = enqueue_chain_init(p, ops, x, m, init, max_iters, tol, s, v, f, pform);
+    if (!rc) rc = enqueue_chain_steps(p, v, f, x, m, max_iters, s, pform, tol > 0.0 ? 0 : max_iters);
+    return rc ? rc : enqueue_chain_tail(p, ops, v, f, x, m, max_iters, s, pform);
 }
 
 }  // namespace stpi

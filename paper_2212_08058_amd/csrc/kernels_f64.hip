@@ -10,7 +10,9 @@
     X(4, 2, 16, 64, 256, 8, 4, 1, 1)      \
     X(8, 3, 16, 64, 256, 8, 4, 1, 0)      \
     X(8, 8, 16, 64, 256, 8, 4, 1, 0)      \
-    X(16, 8, 16, 64, 256, 8, 4, 1, 0)
+    X(16, 8, 16, 64, 256, 8, 4, 1, 0)     \
+    X(4, 2, 8, 32, 256, 2, 1, 1, 4)       \
+    X(4, 2, 16, 64, 256, 4, 1, 1, 4)
 #define STPI_ADJ_VARIANTS(X)     \
     X(1, 1, 16, 64, 256, 8, 4)   \
     X(2, 2, 16, 64, 256, 8, 4)   \

@@ -227,7 +227,7 @@ int stpi_sfseg_iterate(const stpi_problem *p, const void *s, const void *f, doub
         const int n = tol > 0.0 ? std::min(CHAIN_CHUNK, max_iters - done) : max_iters;
         for (int k = 0; k < n; ++k) {
             if ((e = v->launch(SL, st)) != hipSuccess) return hip_fail(e, "sfseg step launch");
-            if (!SL.fuse && (e = launch_finalize(partials, nunits, state, st)) != hipSuccess)
+            if (!SL.fuse && (e = launch_finalize({partials, nullptr}, nunits, state, st)) != hipSuccess)
                 return hip_fail(e, "finalize launch");
         }
         done += n;
@@ -238,7 +238,7 @@ int stpi_sfseg_iterate(const stpi_problem *p, const void *s, const void *f, doub
             if (hs.done) break;
         }
     }
-    if ((e = ops->normalize(x, buf1, N, state, st)) != hipSuccess) return hip_fail(e, "normalize");
+    if ((e = ops->normalize(x, buf1, N, state, {nullptr, nullptr}, 0, nullptr, st)) != hipSuccess) return hip_fail(e, "normalize");
     if ((e = hipMemcpyAsync(&hs, state, sizeof(hs), hipMemcpyDeviceToHost, st)) != hipSuccess ||
         (e = hipStreamSynchronize(st)) != hipSuccess)
         return hip_fail(e, "state readback");

@@ -757,4 +757,70 @@ __device__ __forceinline__ void stencil_tile_flat(const Op &op, const Taps<CT> &
     });
 }
 
+// One output frame of a tile with every input frame at once (small volumes).
+// The streamed loops above walk a tile's frames one after the other, about a
+// microsecond each: a volume with few tiles leaves most of the chip idle and
+// its step takes as long as that walk. Here a workgroup owns one frame of one
+// tile and the temporal pass comes first, on the staged elements: each thread
+// loads the 2 RT + 1 input frames of its elements (all in flight together) and
+// stores their tap-weighted sum, so one y-pass, one x-pass and two barriers
+// remain. Each input is read 2 RT + 1 times (and the halo each time) from the
+// caches, and every output frame is its own workgroup, which pays while the
+// whole volume is a few workgroups per CU (gather_pays in host.cpp).
+template <class CT, int RS, int RT, int TH, int TW, int NTHR, int RY, class Op>
+__device__ __forceinline__ void stencil_tile_gather(const Op &op, const Taps<CT> &tp, int T, int t, int H, int W,
+                                                    int x0, int y0, CT *lds, double &d1, double &d2) {
+    using G = Geometry<RS, RT, TH, TW, NTHR, RY, 1>;
+    constexpr int NC = G::NC, NU = G::NU, NPF = G::NPF, LW = G::LW, RSA = G::RSA, NYI = G::NYI, IPT = G::IPT;
+    constexpr uint32_t ESZ = Op::ESZ;
+    static_assert(TH * TW % NTHR == 0, "whole rounds of outputs");
+    const int tid = threadIdx.x;
+    CT *U = lds, *Y = lds + G::NUP;
+    uint32_t poff[NPF], ooff[IPT][1];
+#pragma unroll
+    for (int k = 0; k < NPF; ++k) {
+        const int e = tid + k * NTHR;
+        const int gy = y0 - RS + e / NC, gx = x0 - RS + e % NC;
+        const bool ok = e < NU && (unsigned)gy < (unsigned)H && (unsigned)gx < (unsigned)W;
+        poff[k] = ok ? (uint32_t)(gy * W + gx) * ESZ : OOB;
+    }
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+        const int o = tid + i * NTHR, gy = y0 + o / TW, gx = x0 + o % TW;
+        ooff[i][0] = gy < H && gx < W ? (uint32_t)(gy * W + gx) * ESZ : OOB;
+    }
+    typename Op::template Raw<NPF> raw[2 * RT + 1];
+#pragma unroll
+    for (int dt = -RT; dt <= RT; ++dt)
+        op.template fetch<NPF>(t + dt, poff, raw[dt + RT], t + dt >= 0 && t + dt < T);
+    typename Op::template OutRaw<IPT, 1> oraw;
+    op.template fetch_out<IPT, 1>(t, ooff, oraw, true);
+#pragma unroll
+    for (int k = 0; k < NPF; ++k) {
+        CT s = CT(0);
+#pragma unroll
+        for (int dt = 0; dt <= 2 * RT; ++dt) s = fma(tp.gt[dt], op.template input<NPF>(raw[dt], k), s);
+        const int e = tid + k * NTHR;
+        if (NU % NTHR == 0 || k < NPF - 1 || e < NU) U[e] = s;
+    }
+    __syncthreads();
+#pragma unroll
+    for (int it = tid; it < NYI; it += NTHR) {
+        const int c = it % NC, g = it / NC;
+        ypass_item<CT, RS, RY, NC, LW>(U + (g * RY) * NC + c, Y + (g * RY) * LW + c + (RSA - RS), tp);
+    }
+    __syncthreads();
+    CT v[IPT][1];
+#pragma unroll
+    for (int i = 0; i < IPT; ++i) {
+        const int o = tid + i * NTHR;
+        const CT *row = Y + (o / TW) * LW + o % TW + (RSA - RS);
+        CT s = CT(0);
+#pragma unroll
+        for (int d = 0; d <= 2 * RS; ++d) s = fma(tp.gs[d], row[d], s);
+        v[i][0] = s;
+    }
+    op.template emit_frame<IPT, 1>(t, v, oraw, ooff, d1, d2);
+}
+
 }  // namespace stpi

@@ -471,3 +471,48 @@ def test_fixed_count_skips_no_reported_value(P, dtype, shape, kp):
         assert torch.equal(x_fix, x_all)
         for key in ("residual", "lambda_", "rayleigh", "r1", "r2", "flags"):
             assert r_fix[key] == r_all[key], (key, r_fix[key], r_all[key])
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float64])
+@pytest.mark.parametrize("shape,kp", [
+    ((1, 1, 1), (1.0, 1.0, 2, 1)), ((2, 8, 32), (2.0, 1.0, 4, 2)), ((5, 9, 33), (2.0, 1.0, 4, 2)),
+    ((7, 17, 65), (1.5, 0.8, 3, 1)), ((16, 64, 112), (2.0, 1.0, 4, 2)), ((6, 100, 130), (1.0, 0.75, 2, 2)),
+    ((5, 33, 129), (1.0, 0.5, 0, 0))])
+def test_single_frame_workgroups(P, dtype, shape, kp):
+    """The loop with a workgroup per tile and output frame, forced over tile
+    edges and chosen by itself on small volumes: one step per voxel against the
+    oracle, and a tolerance run and a fixed-count run (steps finalised by the
+    launch after them) against the oracle's iteration. Tolerances as the other
+    step tests; residuals as test_start_vector's."""
+    from paper_2212_08058_amd import _native as N
+    import ctypes
+    code = {torch.float32: N.STPI_F32, torch.bfloat16: N.STPI_BF16, torch.float64: N.STPI_F64}[dtype]
+    rng = np.random.default_rng(sum(shape))
+    f = rng.uniform(0.05, 1.0, shape)
+    fd = to_dev(f, dtype)
+    f64 = fd.double().cpu().numpy()
+    kern, k = P.Kernel(*kp), OKf(*kp)
+    tol = TOL[dtype]
+    xr, info = oracle.iterate(f64, k, iters=5)
+    forced = [-1]
+    for i in range(N.lib.stpi_variant_count(code)):
+        a = (ctypes.c_int * 9)()
+        N.lib.stpi_variant_info(code, i, a)
+        if a[8] == 4 and a[0] >= kern.r_s and a[1] >= kern.r_t:
+            forced.append(i)
+    assert len(forced) > 1
+    try:
+        for i in forced:
+            assert N.lib.stpi_set_variant(i) == 0
+            _step_case(P, shape, kern, dtype, 3)
+            for stream in (None, torch.cuda.Stream()):
+                x, r = P.power_iterate(fd, kern, iters=5, stream=stream)
+                torch.cuda.synchronize()
+                assert r["iters"] == 5
+                assert rel_l2(x.double().cpu().numpy(), xr) <= 4 * tol
+                assert abs(r["lambda_"] - info.lambdas[-1]) <= 4 * tol * info.lambdas[-1]
+            x2, r2 = P.power_iterate(fd, kern, tol=1e-300, max_iters=5)
+            torch.cuda.synchronize()
+            assert torch.equal(x, x2) and r["residual"] == r2["residual"] and r["r1"] == r2["r1"]
+    finally:
+        N.lib.stpi_set_variant(-1)
