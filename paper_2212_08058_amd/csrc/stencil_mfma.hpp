@@ -143,6 +143,23 @@ __device__ __forceinline__ void split4(const float4_t &v, half4_t &h, half4_t &l
     for (int j = 0; j < 4; ++j) l[j] = (_Float16)__builtin_fmaf(-(float)h[j], one, v[j]);
 }
 
+// Band taps in the operand layout, split: lane l, element j of K block kb holds
+// g(32 kb + 8 (l / 16) + j - PAD - l % 16). tapl: 33 space taps centred at 16.
+template <class G, int PAD>
+__device__ __forceinline__ void band_taps(const float *tapl, int lane, half8_t (&thi)[G::KB], half8_t (&tlo)[G::KB]) {
+#pragma unroll
+    for (int kb = 0; kb < G::KB; ++kb)
+#pragma unroll
+        for (int j = 0; j < 8; ++j) {
+            const int d = 32 * kb + 8 * (lane >> 4) + j - PAD - (lane & 15);
+            const float g = (d >= -16 && d <= 16) ? tapl[d + 16] : 0.f;
+            _Float16 h, l;
+            split_half(g, h, l);
+            thi[kb][j] = h;
+            tlo[kb][j] = l;
+        }
+}
+
 // y-pass products of one 16 x 16 block of Y (one dependency chain).
 template <class G>
 __device__ __forceinline__ float4_t mfma_yblock_mma(const _Float16 *U, int b, int lane, const half8_t (&thi)[G::KB],
@@ -235,20 +252,8 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
     _Float16 *const U0 = reinterpret_cast<_Float16 *>(lds);
     _Float16 *const Y0 = U0 + 2 * G::UBUF;
 
-    // band taps in the operand layout: lane l, element j of K block kb holds
-    // g(32 kb + 8 (l / 16) + j - PAD - l % 16)
     half8_t thi[G::KB], tlo[G::KB];
-#pragma unroll
-    for (int kb = 0; kb < G::KB; ++kb)
-#pragma unroll
-        for (int j = 0; j < 8; ++j) {
-            const int d = 32 * kb + 8 * (lane >> 4) + j - PAD - (lane & 15);
-            const float g = (d >= -16 && d <= 16) ? tapl[d + 16] : 0.f;
-            _Float16 h, l;
-            split_half(g, h, l);
-            thi[kb][j] = h;
-            tlo[kb][j] = l;
-        }
+    band_taps<G, PAD>(tapl, lane, thi, tlo);
     // EXACT: the y-pass taps times umul (a power of two, so exact in float) as
     // two bfloat16 parts
     bf16x8_t bhi[G::KB], blo[G::KB];
@@ -353,7 +358,7 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
 #pragma unroll
             for (int m = 0; m < G::YPW; ++m) {
                 const int b = wid + m * G::NWAVE;
-                if (G::NYB % G::NWAVE == 0 || b < G::NYB) {
+                if (G::NYB % G::NWAVE == 0 || m < G::YPW - 1 || b < G::NYB) {
                     if constexpr (EXACT)
                         ya[m] = mfma_yblock_mma_bf16<G>(U, b, lane, bhi, blo);
                     else
@@ -404,7 +409,7 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
 #pragma unroll
             for (int m = 0; m < G::YPW; ++m) {
                 const int b = wid + m * G::NWAVE;
-                if (G::NYB % G::NWAVE == 0 || b < G::NYB) mfma_yblock_store<G>(Y, b, lane, ya[m], one);
+                if (G::NYB % G::NWAVE == 0 || m < G::YPW - 1 || b < G::NYB) mfma_yblock_store<G>(Y, b, lane, ya[m], one);
             }
         }
         __syncthreads();
