@@ -15,13 +15,20 @@ namespace stpi {
 namespace {
 
 #define STPI_SFSEG_ENTRY(ST, RS, RT, TH, TW, NTHR, RY, QX) \
-    {RS, RT, TH, TW, NTHR, &launch_sfseg<ST, RS, RT, TH, TW, NTHR, RY, QX>, &sfseg_blocks_per_cu<ST, RS, RT, TH, TW, NTHR, RY, QX>}
+    {RS, RT, TH, TW, NTHR, 0, &launch_sfseg<ST, RS, RT, TH, TW, NTHR, RY, QX>, &sfseg_blocks_per_cu<ST, RS, RT, TH, TW, NTHR, RY, QX>}
+// matrix-core spatial passes, slab margin RS (8 or 16)
+#define STPI_SFSEG_MFMA(RS, RT, TH, TW, NTHR) \
+    {RS, RT, TH, TW, NTHR, 1, &launch_sfseg_mfma<RT, TH, TW, NTHR, RS>, &sfseg_mfma_blocks_per_cu<RT, TH, TW, NTHR, RS>}
 
-// Compiled (RS, RT) pairs: the smallest one covering the problem's radii is used.
+// Compiled (RS, RT) pairs: the smallest one covering the problem's radii is
+// used (but see sfseg_variant). The matrix-core form took the place of vector
+// loops at (8, 3) and (16, 5): chain step in us, vector / matrix cores, r =
+// (8, 3): 8x64x112 23 / 21, 5x233x347 19.4 / 19.6, 32x240x432 59 / 49, 64x480x854
+// 276 / 196; r = (15, 5): 58 / 35, 43 / 32, 124 / 69, 486 / 286.
 const SfsegVariant kSfsegF32[] = {
     STPI_SFSEG_ENTRY(float, 4, 2, 16, 64, 256, 8, 4),
-    STPI_SFSEG_ENTRY(float, 8, 3, 16, 64, 256, 8, 4),
-    STPI_SFSEG_ENTRY(float, 16, 5, 32, 64, 512, 8, 4),
+    STPI_SFSEG_MFMA(8, 3, 32, 64, 512),
+    STPI_SFSEG_MFMA(16, 5, 32, 64, 512),
 };
 const SfsegVariant kSfsegF64[] = {
     STPI_SFSEG_ENTRY(double, 4, 2, 16, 64, 256, 8, 4),
@@ -31,8 +38,16 @@ const SfsegVariant *sfseg_variant(const stpi_problem *p) {
     const SfsegVariant *list = p->dtype == STPI_F64 ? kSfsegF64 : kSfsegF32;
     const int n = p->dtype == STPI_F64 ? (int)(sizeof(kSfsegF64) / sizeof(kSfsegF64[0]))
                                        : (int)(sizeof(kSfsegF32) / sizeof(kSfsegF32[0]));
-    for (int i = 0; i < n; ++i)
-        if (list[i].RS >= p->r_s && list[i].RT >= p->r_t) return &list[i];
+    // The vector loop is the better one at r <= (4, 2) until its arithmetic and
+    // not its frame-by-frame latency counts. Chain step in us, vector (4, 2) /
+    // matrix-core (8, 3): 16x240x432 24 / 30, 32x240x432 38 / 47, 32x480x854 96 /
+    // 81, 64x480x854 219 / 189 (3.3 and 13 M voxels lie on either side).
+    const bool large = (int64_t)p->T * p->H * p->W >= (int64_t)8 << 20;
+    for (int i = 0; i < n; ++i) {
+        if (list[i].RS < p->r_s || list[i].RT < p->r_t) continue;
+        if (i == 0 && n > 1 && large) continue;
+        return &list[i];
+    }
     return nullptr;
 }
 
@@ -53,19 +68,21 @@ int sfseg_segments(const SfsegVariant &v, const stpi_problem *p) {
     return nseg;
 }
 
-struct SfsegLayout {
-    size_t partials_off, partials_cap, buf_off, total;
-};
-
-SfsegLayout sfseg_layout(const stpi_problem *p, const SfsegVariant &v) {
-    SfsegLayout L;
+// Workspace as the single-field chain's (WsLayout): state slots, two sets of
+// partial sums and maxima (the range check's partials share the first set's
+// room), the ping-pong volume. The first slot also holds a single step's
+// operand bounds.
+WsLayout sfseg_layout(const stpi_problem *p, const SfsegVariant &v) {
+    WsLayout L;
     const size_t elem = p->dtype == STPI_F64 ? 8 : 4;
-    L.partials_off = 256;
-    L.partials_cap = std::max((size_t)sfseg_tiles(v, p) * STPI_NSEG_MAX, (size_t)std::max(NORM_BLOCKS_HOST,
-                                                                                        SFSEG_RANGE_BLOCKS));
-    size_t off = L.partials_off + ((L.partials_cap * 3 * sizeof(double) + 255) & ~(size_t)255);
-    L.buf_off = off;
-    L.total = off + (((size_t)p->T * p->H * p->W * elem + 255) & ~(size_t)255);
+    L.state_off = 0;
+    L.partials_off = (FINAL_SLOT + 1) * STATE_SLOT;
+    L.partials_cap = std::max((size_t)sfseg_tiles(v, p) * STPI_NSEG_MAX,
+                              (size_t)std::max(NORM_BLOCKS_HOST, 2 * SFSEG_RANGE_BLOCKS));
+    L.wmax_off = L.partials_off + 2 * L.partials_cap * 2 * sizeof(double);
+    const size_t off = L.wmax_off + 2 * L.partials_cap * sizeof(uint32_t);
+    L.buf_off = (off + 255) & ~(size_t)255;
+    L.total = L.buf_off + (((size_t)p->T * p->H * p->W * elem + 255) & ~(size_t)255);
     return L;
 }
 
@@ -89,33 +106,39 @@ void sfseg_fill(SfsegLaunch &L, const stpi_problem *p, const void *s, const void
     make_taps(p, L.gs, L.gt);
 }
 
-// states: flags |= FLAG_AFFINITY and done when some affinity of Eq. 2 can be
-// negative (alpha (max f - min f)^2 > 1, a negative s, or a NaN).
-__global__ void sfseg_range_check_kernel(const double *partials, int n, double alpha, DevState *s) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double fmn = INFINITY, fmx = -INFINITY, smn = INFINITY;
-    bool nan = false;
-    for (int b = 0; b < n; ++b) {
-        const double a = partials[3 * b], c = partials[3 * b + 1], e = partials[3 * b + 2];
-        nan |= a != a || c != c || e != e;
-        fmn = fmin(fmn, a);
-        fmx = fmax(fmx, c);
-        smn = fmin(smn, e);
+// The chain's checks and bounds from the range partials: flags |=
+// FLAG_AFFINITY and done when some affinity of Eq. 2 can be negative (alpha
+// (max f - min f)^2 > 1, a negative s, or a NaN); ubound = max |f|, and for the
+// uniform start (the constant 1) wmax[0] = max |s x| = max s.
+__global__ __launch_bounds__(256) void sfseg_range_check_kernel(const double *partials, int n, double alpha, int uniform,
+                                                                DevState *s) {
+    __shared__ SfsegRange rw[256 / 64];
+    SfsegRange r = SFSEG_RANGE_EMPTY;
+    for (int b = threadIdx.x; b < n; b += 256) {
+        r.take(SfsegRange{partials[4 * b], partials[4 * b + 1], partials[4 * b + 2], partials[4 * b + 3]});
     }
-    const double d = fmx - fmn;
-    if (nan || smn < 0.0 || alpha * d * d > 1.0) {
+    r.wave();
+    if ((threadIdx.x & 63) == 0) rw[threadIdx.x >> 6] = r;
+    __syncthreads();
+    if (threadIdx.x != 0) return;
+    for (int w = 1; w < 256 / 64; ++w) r.take(rw[w]);
+    const double d = r.fmx - r.fmn;
+    if (d != d || r.smn != r.smn || r.smn < 0.0 || alpha * d * d > 1.0) {
         s->flags |= FLAG_AFFINITY;
         s->done = 1;
+        return;
     }
+    s->ubound = __float_as_uint((float)fmax(fabs(r.fmn), fabs(r.fmx)));
+    if (uniform) s->wmax[0] = __float_as_uint((float)r.smx);
 }
 
 template <class ST>
-hipError_t sfseg_range(size_t n, const void *s, const void *f, double *partials, double alpha, DevState *state,
-                       hipStream_t st) {
+hipError_t sfseg_range(size_t n, const void *s, const void *f, double *partials, double alpha, int uniform,
+                       DevState *state, hipStream_t st) {
     hipLaunchKernelGGL(sfseg_range_kernel<ST>, dim3(SFSEG_RANGE_BLOCKS), dim3(256), 0, st, n, (const ST *)s,
                        (const ST *)f, partials);
-    hipLaunchKernelGGL(sfseg_range_check_kernel, dim3(1), dim3(64), 0, st, partials, SFSEG_RANGE_BLOCKS, alpha,
-                       state);
+    hipLaunchKernelGGL(sfseg_range_check_kernel, dim3(1), dim3(256), 0, st, partials, SFSEG_RANGE_BLOCKS, alpha,
+                       uniform, state);
     return hipGetLastError();
 }
 
@@ -159,7 +182,7 @@ int stpi_sfseg_step(const stpi_problem *p, const void *s, const void *f, double 
     if (z == s || z == f || z == x) return fail(STPI_EINVAL, "z must not alias s, f or x");
     if (!(alpha > 0.0) || !std::isfinite(alpha)) return fail(STPI_EINVAL, "alpha must be finite and > 0");
     if (!std::isfinite(x_scale)) return fail(STPI_EINVAL, "x_scale must be finite");
-    const SfsegLayout L = sfseg_layout(p, *v);
+    const WsLayout L = sfseg_layout(p, *v);
     if (!ws || ws_bytes < L.total) return fail(STPI_EWORKSPACE, "sfseg workspace needs %zu bytes", L.total);
     hipStream_t st = (hipStream_t)stream;
     SfsegLaunch SL;
@@ -169,7 +192,17 @@ int stpi_sfseg_step(const stpi_problem *p, const void *s, const void *f, double 
     SL.x_scale = x_scale;
     SL.partials = (double *)((char *)ws + L.partials_off);
     SL.nseg = sfseg_segments(*v, p);
-    hipError_t e = v->launch(SL, st);
+    hipError_t e;
+    if (v->mfma) {
+        uint32_t *words = (uint32_t *)ws;
+        SL.bounds = words;
+        for (int i = 0; i < 2; ++i)
+            if ((e = launch_clear_word(words + i, st)) != hipSuccess) return hip_fail(e, "operand bound");
+        hipLaunchKernelGGL(sfseg_bounds_kernel, dim3(1024), dim3(256), 0, st, (size_t)p->T * p->H * p->W,
+                           (const float *)s, (const float *)f, (const float *)x, words);
+        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "operand bound");
+    }
+    e = v->launch(SL, st);
     if (e != hipSuccess) return hip_fail(e, "sfseg step launch");
     e = launch_step_sums(SL.partials, sfseg_tiles(*v, p) * SL.nseg, x_scale, d_sums, st);
     return e == hipSuccess ? STPI_OK : hip_fail(e, "step sums launch");
@@ -187,59 +220,73 @@ int stpi_sfseg_iterate(const stpi_problem *p, const void *s, const void *f, doub
     if (max_iters < 0) return fail(STPI_EINVAL, "max_iters must be >= 0");
     if (init != 0 && init != 1) return fail(STPI_EINVAL, "init must be 0 (use x) or 1 (uniform)");
     if (!std::isfinite(tol)) return fail(STPI_EINVAL, "tol must be finite");
-    const SfsegLayout L = sfseg_layout(p, *v);
+    const WsLayout L = sfseg_layout(p, *v);
     if (!ws || ws_bytes < L.total) return fail(STPI_EWORKSPACE, "sfseg workspace needs %zu bytes", L.total);
     std::memset(out, 0, sizeof(*out));
     hipStream_t st = (hipStream_t)stream;
     const DtypeOps *ops = ops_for(p->dtype);
     const size_t N = (size_t)p->T * p->H * p->W;
-    DevState *state = (DevState *)ws;
-    double *partials = (double *)((char *)ws + L.partials_off);
-    void *buf1 = (char *)ws + L.buf_off;
+    const ChainMem m = chain_mem(L, ws);
+    DevState *state = m.state;
     hipError_t e;
     // start vector and state (as stpi_iterate's plain form)
     if (init == 1) {
-        if ((e = ops->fill_ones(x, N, st)) != hipSuccess) return hip_fail(e, "fill");
-        if ((e = launch_state_init(state, 1.0 / std::sqrt((double)N), tol, max_iters, 0, 0, st)) != hipSuccess)
-            return hip_fail(e, "init");
+        if ((e = ops->uniform_start(x, N, state, tol, max_iters, st)) != hipSuccess) return hip_fail(e, "init");
     } else {
         if ((e = launch_state_init(state, 1.0, tol, max_iters, 0, 0, st)) != hipSuccess) return hip_fail(e, "init");
-        if ((e = ops->sumsq(x, N, partials, st)) != hipSuccess) return hip_fail(e, "norm");
-        if ((e = launch_state_from_norm(partials, NORM_BLOCKS_HOST, state, st)) != hipSuccess)
+        if ((e = ops->sumsq(x, N, m.partials, st)) != hipSuccess) return hip_fail(e, "norm");
+        if ((e = launch_state_from_norm(m.partials, NORM_BLOCKS_HOST, state, st)) != hipSuccess)
             return hip_fail(e, "init norm");
     }
-    e = p->dtype == STPI_F64 ? sfseg_range<double>(N, s, f, partials, alpha, state, st)
-                             : sfseg_range<float>(N, s, f, partials, alpha, state, st);
+    e = p->dtype == STPI_F64 ? sfseg_range<double>(N, s, f, m.partials, alpha, init, state, st)
+                             : sfseg_range<float>(N, s, f, m.partials, alpha, init, state, st);
     if (e != hipSuccess) return hip_fail(e, "affinity range check");
+    // the first step's staging bound from the caller's start
+    if (v->mfma && init != 1 && (e = ops->bound(N, s, x, &state->wmax[0], st)) != hipSuccess)
+        return hip_fail(e, "operand bound");
     SfsegLaunch SL;
     sfseg_fill(SL, p, s, f, alpha);
     SL.buf0 = x;
-    SL.buf1 = buf1;
-    SL.state = state;
-    SL.partials = partials;
+    SL.buf1 = m.buf1;
     SL.nseg = sfseg_segments(*v, p);
-    SL.fuse = v->NTHR >= FINAL_THREADS && !fusion_disabled() ? 1 : 0;
     const int nunits = sfseg_tiles(*v, p) * SL.nseg;
-    if ((e = launch_partials_empty(partials, nunits, st)) != hipSuccess) return hip_fail(e, "partials");
+    const bool defer = nunits <= DEFER_MAX_UNITS && !fusion_disabled();
     // steps in chunks; a tolerance run checks the stop flag after each chunk
+    // (its last step not yet finalised)
     DevState hs;
-    for (int done = 0; done < max_iters;) {
+    int done = 0;
+    while (done < max_iters) {
         const int n = tol > 0.0 ? std::min(CHAIN_CHUNK, max_iters - done) : max_iters;
         for (int k = 0; k < n; ++k) {
+            const int kk = done + k, slot = defer ? kk & 1 : 0;
+            SL.no_prev = tol <= 0.0 && kk >= 2 && kk < max_iters - 1 ? 1 : 0;
+            SL.state = m.slot(slot);
+            SL.state_out = defer ? m.slot(slot ^ 1) : nullptr;
+            StepPartials mine = m.set(slot);
+            SL.partials = mine.sums;
+            SL.wpart = mine.wmax;
+            SL.prev_part = m.set(slot ^ 1);
             if ((e = v->launch(SL, st)) != hipSuccess) return hip_fail(e, "sfseg step launch");
-            if (!SL.fuse && (e = launch_finalize({partials, nullptr}, nunits, state, st)) != hipSuccess)
+            if (!v->mfma) mine.wmax = nullptr;
+            if (!defer && (e = launch_finalize(mine, nunits, state, st)) != hipSuccess)
                 return hip_fail(e, "finalize launch");
         }
         done += n;
         if (done < max_iters) {
-            if ((e = hipMemcpyAsync(&hs, state, sizeof(hs), hipMemcpyDeviceToHost, st)) != hipSuccess ||
+            if ((e = hipMemcpyAsync(&hs, m.slot(defer ? done & 1 : 0), sizeof(hs), hipMemcpyDeviceToHost, st)) !=
+                    hipSuccess ||
                 (e = hipStreamSynchronize(st)) != hipSuccess)
                 return hip_fail(e, "stop check");
             if (hs.done) break;
         }
     }
-    if ((e = ops->normalize(x, buf1, N, state, {nullptr, nullptr}, 0, nullptr, st)) != hipSuccess) return hip_fail(e, "normalize");
-    if ((e = hipMemcpyAsync(&hs, state, sizeof(hs), hipMemcpyDeviceToHost, st)) != hipSuccess ||
+    const bool pend = defer && done > 0;
+    StepPartials last = m.set((done + 1) & 1);
+    if (!v->mfma) last.wmax = nullptr;
+    if ((e = ops->normalize(x, m.buf1, N, m.slot(pend ? done & 1 : 0), last, pend ? nunits : 0, m.slot(FINAL_SLOT),
+                            st)) != hipSuccess)
+        return hip_fail(e, "normalize");
+    if ((e = hipMemcpyAsync(&hs, m.slot(FINAL_SLOT), sizeof(hs), hipMemcpyDeviceToHost, st)) != hipSuccess ||
         (e = hipStreamSynchronize(st)) != hipSuccess)
         return hip_fail(e, "state readback");
     out->iters = hs.iters;
@@ -254,10 +301,6 @@ int stpi_sfseg_iterate(const stpi_problem *p, const void *s, const void *f, doub
         out->status = STPI_EINVAL;
         return fail(STPI_EINVAL, "sfseg: an affinity 1 - alpha (f_i - f_j)^2 can be negative (alpha (max f - min f)^2 "
                                  "> 1), or s has a negative or NaN value");
-    }
-    if (hs.flags & FLAG_SYNC) {
-        out->status = STPI_EHIP;
-        return fail(STPI_EHIP, "a step's partial sums did not arrive (step %d)", hs.iters + 1);
     }
     out->status = (hs.flags & FLAG_NONFINITE) ? STPI_ENONFINITE : (hs.flags & FLAG_ZERO) ? STPI_EZERO_NORM : 0;
     if (out->status) return fail(out->status, "iteration stopped after %d steps: %s", hs.iters,

@@ -13,11 +13,13 @@
 // 2 RT + 1 output frames (the t-pass), and recombines them per output voxel
 // with that voxel's own s and f. Zero padding comes from out-of-range buffer
 // loads, as in the single-field step. The reduction partials (sum z^2 and
-// sum z x_stored) and the last-workgroup finalisation are those of the
-// single-field step kernel.
+// sum z x_stored) and their finalisation by the next launch are those of the
+// single-field step kernel. At larger radii the two spatial passes run on the
+// matrix cores (sfseg_mfma_kernel).
 #pragma once
 
 #include "stencil.hpp"
+#include "stencil_mfma.hpp"
 
 namespace stpi {
 
@@ -28,15 +30,48 @@ struct SfsegArgs {
     const ST *f;  // pairwise feature
     ST *buf0;
     ST *buf1;
-    DevState *state;  // null: single step (src = buf0, dst = buf1, scale x_scale)
+    const DevState *state;  // null: single step (src = buf0, dst = buf1, scale x_scale)
+    DevState *state_out;    // as FwdArgs
+    StepPartials prev_part;
     double *partials;
-    int fuse;
+    uint32_t *wpart;
+    const uint32_t *bounds;  // matrix-core kernel, single step: float bits of max |s x|, max |f|
+    int no_prev;             // the previous iterate is not read at the outputs (sum z x_stored = 0)
     double x_scale;
     CT ainv;  // 1 / alpha
     int T, H, W;
     int nseg;
+    int rs;  // the problem's space radius
     Taps<CT> taps;
 };
+
+// The launch's view of the iteration: buffers and scale. False: nothing to do.
+template <int NTHR, class ST>
+__device__ __forceinline__ bool sfseg_begin(const SfsegArgs<ST> &a, int nunits, DevState &st, double *red,
+                                            const ST *&src, ST *&dst, double &scale) {
+    if (!a.state) {
+        src = a.buf0;
+        dst = a.buf1;
+        scale = a.x_scale;
+        return true;
+    }
+    if (a.state_out) {
+        resolve_state<NTHR>(a.state, a.prev_part, nunits, &st, red, a.state_out, 1);
+    } else {
+        if (threadIdx.x == 0) st = *a.state;
+        __syncthreads();
+    }
+    if (__builtin_amdgcn_readfirstlane(st.done)) return false;
+    const int cur = __builtin_amdgcn_readfirstlane(st.cur);
+    src = cur ? a.buf1 : a.buf0;
+    dst = cur ? a.buf0 : a.buf1;
+    scale = st.scale;
+    return true;
+}
+template <int NTHR>
+constexpr int sfseg_red() {
+    return 3 * (NTHR > FINAL_THREADS ? NTHR : FINAL_THREADS) / 64;
+}
 
 template <int RS, int RT, int TH, int TW, int NTHR, int RY, int QX>
 struct SfsegGeometry {
@@ -55,7 +90,8 @@ __global__ __launch_bounds__(NTHR) void sfseg_step_kernel(SfsegArgs<ST> a) {
     constexpr int NYI = G::NYI, NQ = G::NQ, NXI = G::NXI, IPT = G::IPT, NTS = G::NTS;
     constexpr uint32_t ESZ = IO::SZ;
     __shared__ CT lds[SG::LDS_ELEMS];
-    __shared__ double red[NTHR / 64];
+    __shared__ double red[sfseg_red<NTHR>()];
+    __shared__ DevState st;
 
     const int nbx = (a.W + TW - 1) / TW, nby = (a.H + TH - 1) / TH;
     const int unit = xcd_tile(blockIdx.x, nbx * nby * a.nseg);
@@ -65,17 +101,7 @@ __global__ __launch_bounds__(NTHR) void sfseg_step_kernel(SfsegArgs<ST> a) {
     const ST *src;
     ST *dst;
     double scale;
-    if (a.state) {
-        if (a.state->done) return;
-        const int cur = a.state->cur;
-        src = cur ? a.buf1 : a.buf0;
-        dst = cur ? a.buf0 : a.buf1;
-        scale = a.state->scale;
-    } else {
-        src = a.buf0;
-        dst = a.buf1;
-        scale = a.x_scale;
-    }
+    if (!sfseg_begin<NTHR>(a, nbx * nby * a.nseg, st, red, src, dst, scale)) return;
     const CT sc = (CT)scale;
     const size_t plane = (size_t)a.H * a.W;
     const uint32_t pbytes = (uint32_t)(plane * ESZ);
@@ -153,7 +179,7 @@ __global__ __launch_bounds__(NTHR) void sfseg_step_kernel(SfsegArgs<ST> a) {
             const uint32_t pb = emit ? pbytes : 0u;
             const auto rs = make_rsrc(a.s + to * plane, pb);
             const auto rf = make_rsrc(a.f + to * plane, pb);
-            const auto rx = make_rsrc(src + to * plane, pb);
+            const auto rx = make_rsrc(src + to * plane, a.no_prev ? 0u : pb);
 #pragma unroll
             for (int ii = 0; ii < IPT; ++ii)
 #pragma unroll
@@ -254,88 +280,370 @@ __global__ __launch_bounds__(NTHR) void sfseg_step_kernel(SfsegArgs<ST> a) {
                 for (int q = 0; q < QX; ++q) acc[m][es][ii][q] = CT(0);
     });
 
-    const double s1 = block_sum<NTHR>(d1, red);
-    const double s2 = block_sum<NTHR>(d2, red);
-    __shared__ int s_last;
+    float unused = 0.f;
+    block_reduce<NTHR>(d1, d2, unused, red);
     if (threadIdx.x == 0) {
-        if (a.fuse) {
-            // as the single-field step: write-through publication, polled slots
-            __hip_atomic_store(&a.partials[2 * unit], s1, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __hip_atomic_store(&a.partials[2 * unit + 1], s2, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-            __builtin_amdgcn_s_waitcnt(0);
-            s_last = __hip_atomic_fetch_add(&a.state->arrive, 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) ==
-                     (unsigned)(nbx * nby * a.nseg - 1);
-        } else {
-            a.partials[2 * unit] = s1;
-            a.partials[2 * unit + 1] = s2;
+        a.partials[2 * unit] = d1;
+        a.partials[2 * unit + 1] = d2;
+    }
+}
+
+// The same step with both spatial passes of the three fields on the matrix
+// cores (float; operands split into two half-precision parts, three products
+// each, as stencil_tile_mfma). Per frame a workgroup (TH x TW outputs) stages
+// the three fields of its slab once into half-precision hi and lo planes,
+// y-filters 3 MB NYC blocks into the Y planes, and x-filters one block per field
+// and wavefront. Three fields' planes fill the LDS (148 KB at 32 x 64, margin
+// 16), so they are single-buffered and a frame has two barriers:
+//   region 1: x-pass of frame k, staging of frame k + 1, the loads of frame
+//             k + 2 (as early as their registers are free: issued before the
+//             y-pass instead, the step takes 303 us, after it 320), t-pass,
+//             epilogue and stores of frame k;
+//   region 2: y-pass of frame k + 1.
+// The t-pass is a transposed filter: the sums of the output frames still open
+// move down one slot as a tap is added (acc[i] = acc[i + 1] + g v, one
+// multiply-add with another destination), so the ring needs no index and the
+// frame loop no unrolling (3 x 11 slots would unroll to more than the
+// instruction cache).
+// Range: u1 = s x takes the power of two that puts its largest value (collected
+// as max |s z| by the step that wrote z, or by a bound pass) into [2^9, 2^10);
+// f is scaled by 2^-ef (max |f| < 2^ef), so f u1 and f^2 u1 stay in range; the
+// epilogue undoes the powers of two.
+// Bound by nothing alone: per frame the vector ALU, the LDS, the first-level
+// cache (three arrays on a slab three times the tile) and the matrix cores take
+// 35, 37, 41 and 15% of the time, and two barriers a frame with one workgroup
+// per CU keep them from overlapping. The vector-ALU form of these radii took 486
+// us per step at 64x480x854, r = (15, 5), this takes 286 us. (Staging by 16-byte
+// loads of 4 x 4 blocks: 368 us, their unaligned row pieces cost the cache more.)
+// g v + c with a result register of its own: the compiler forms the two-operand
+// multiply-add, which needs a copy of c first when c stays live or moves.
+__device__ __forceinline__ float fma3(float g, float v, float c) {
+    float d;
+    asm("v_fma_f32 %0, %1, %2, %3" : "=v"(d) : "s"(g), "v"(v), "v"(c));
+    return d;
+}
+
+template <int RT, int TH, int TW, int NTHR, int PAD>
+struct SfsegMfma {
+    using G = MfmaGeometry<TH, TW, NTHR, PAD, 2>;
+    static constexpr int UF = G::UBUF, YF = G::YBUF;  // one field's hi and lo planes
+    static constexpr int LDS_HALVES = 3 * (UF + YF);
+    static constexpr int NG4 = G::SR / 4;             // staging items: 4 rows of a slab column
+    static constexpr int NITEM = G::SC * NG4;
+    static constexpr int IPS = (NITEM + NTHR - 1) / NTHR;
+    static constexpr int NPF = 4 * IPS;
+    static constexpr int NYB = 3 * G::NYB;
+    static constexpr int YPW = (NYB + G::NWAVE - 1) / G::NWAVE;
+    static_assert(LDS_HALVES * 2 + 2048 <= 160 * 1024, "LDS");
+    static_assert(G::SR % 4 == 0 && G::XPW == 1, "one output block per wavefront and field");
+};
+
+template <int RT, int TH, int TW, int NTHR, int PAD>
+__global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
+    using S = SfsegMfma<RT, TH, TW, NTHR, PAD>;
+    using G = typename S::G;
+    using IO = BufIO<float>;
+    constexpr int NTS = 2 * RT + 1, NPF = S::NPF, IPS = S::IPS;
+    __shared__ __align__(16) _Float16 lds[S::LDS_HALVES];
+    __shared__ double red[sfseg_red<NTHR>()];
+    __shared__ DevState st;
+    __shared__ float tapl[2 * 16 + 1];
+    const int nbx = (a.W + TW - 1) / TW, nby = (a.H + TH - 1) / TH, ntiles = nbx * nby;
+    const int unit = xcd_tile(blockIdx.x, ntiles * a.nseg);
+    if (unit < 0) return;
+    const int tile = unit % ntiles, seg = unit / ntiles;
+    const int t0 = (int)((int64_t)seg * a.T / a.nseg), t1 = (int)((int64_t)(seg + 1) * a.T / a.nseg);
+    const float *src;
+    float *dst;
+    double scale;
+    if (!sfseg_begin<NTHR>(a, ntiles * a.nseg, st, red, src, dst, scale)) return;
+    if (threadIdx.x < 2 * 16 + 1) {
+        float g = 0.f;
+#pragma unroll
+        for (int i = 0; i < 2 * 16 + 1; ++i) g = (int)threadIdx.x == i ? a.taps.gs[i] : g;
+        tapl[threadIdx.x] = g;
+    }
+    __syncthreads();
+    // powers of two of the staging (see above)
+    const float b1 = __uint_as_float(a.state ? st.wmax[st.cur] : a.bounds[0]);
+    const float bf = __uint_as_float(a.state ? st.ubound : a.bounds[1]);
+    const int e1 = bound_exponent((float)((double)b1 * fabs(scale)), 100), ef = bound_exponent(bf, PRODUCT_ELIM);
+    const float umul = (float)(scale * ldexp(1.0, 10 - e1)), fmul = ldexpf(1.f, -ef);
+    const float kb = ldexpf(1.f, 2 * ef), kc = ldexpf(2.f, ef), ko = ldexpf(1.f, e1 - 10);
+
+    const size_t plane = (size_t)a.H * a.W;
+    const uint32_t pbytes = (uint32_t)(plane * 4);
+    const int x0 = (tile % nbx) * TW, y0 = (tile / nbx) * TH;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
+    _Float16 *const U = lds, *const Y = lds + 3 * S::UF;
+    half8_t thi[G::KB], tlo[G::KB];
+    band_taps<G, PAD>(tapl, lane, thi, tlo);
+    // zero the U rows and Y columns that only the last K block reads (none when PAD = 8)
+    constexpr int ZR = G::UK > G::SR ? G::UK - G::SR : 1, ZC = G::YW > G::SC ? G::YW - G::SC : 1;
+    for (int i = tid; i < 6 * G::SC * (G::UK - G::SR); i += NTHR) {
+        const int k = i % ZR, rest = i / ZR;
+        U[(rest / G::SC) * G::UPL + (rest % G::SC) * G::UP + G::SR + k] = (_Float16)0.f;
+    }
+    for (int i = tid; i < 6 * TH * (G::YW - G::SC); i += NTHR) {
+        const int k = i % ZC, rest = i / ZC;
+        Y[(rest / TH) * G::YPL + (rest % TH) * G::YP + G::SC + k] = (_Float16)0.f;
+    }
+    uint32_t poff[NPF];
+#pragma unroll
+    for (int m = 0; m < IPS; ++m) {
+        const int it = tid + m * NTHR, c = it % G::SC, g = it / G::SC, gx = x0 - PAD + c;
+        const bool colok = it < S::NITEM && c >= PAD - a.rs && c < TW + PAD + a.rs && (unsigned)gx < (unsigned)a.W;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int r = 4 * g + j, gy = y0 - PAD + r;
+            const bool ok = colok && r >= PAD - a.rs && r < TH + PAD + a.rs && (unsigned)gy < (unsigned)a.H;
+            poff[4 * m + j] = ok ? (uint32_t)(gy * a.W + gx) * 4 : OOB;
         }
     }
-    if constexpr (NTHR >= FINAL_THREADS) {
-        if (!a.fuse) return;
-        __syncthreads();
-        if (!__builtin_amdgcn_readfirstlane(s_last)) return;
-        const int n = nbx * nby * a.nseg;
-        double p1 = 0.0, p2 = 0.0;
-        bool late = false;
-        if (threadIdx.x < FINAL_THREADS)
-            for (int i = threadIdx.x; i < n; i += FINAL_THREADS) {
-                p1 += take_partial(&a.partials[2 * i], &late);
-                p2 += take_partial(&a.partials[2 * i + 1], &late);
-            }
-        p1 = block_sum<NTHR>(p1, red);
-        p2 = block_sum<NTHR>(p2, red);
-        __shared__ int s_late;
-        if (threadIdx.x == 0) s_late = 0;
-        __syncthreads();
-        if (late) s_late = 1;
-        __syncthreads();
-        if (threadIdx.x == 0) {
-            if (s_late) a.state->flags |= FLAG_SYNC;
-            step_finalize(a.state, p1, p2);
-            a.state->arrive = 0u;
+    // this lane's outputs: row li, columns 4 lg .. + 3 of the wavefront's block
+    const int orow = y0 + 16 * (wid / G::NB) + (lane & 15), ocol = x0 + 16 * (wid % G::NB) + 4 * (lane >> 4);
+    const int nout = orow < a.H ? (a.W - ocol < 0 ? 0 : (a.W - ocol < 4 ? a.W - ocol : 4)) : 0;
+    const uint32_t ooff = nout > 0 ? (uint32_t)(orow * a.W + ocol) * 4 : OOB;
+
+    float acc[3][NTS][4];
+#pragma unroll
+    for (int m = 0; m < 3; ++m)
+#pragma unroll
+        for (int i = 0; i < NTS; ++i)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) acc[m][i][q] = 0.f;
+    const FrameWalk<RT> fw(a.T, t0, t1);
+    const int nin = fw.nin;
+    const float one = opaque(1.f);
+    float ps[NPF], pf[NPF], px[NPF];
+    // an empty range when !ok (see FwdOp::fetch)
+    auto fetch = [&](int t, bool ok) __attribute__((always_inline)) {
+        const size_t o = (size_t)(ok ? t : 0) * plane;
+        const uint32_t pb = ok ? pbytes : 0u;
+        const auto rs = make_rsrc(a.s + o, pb), rf = make_rsrc(a.f + o, pb), rx = make_rsrc(src + o, pb);
+#pragma unroll
+        for (int k = 0; k < NPF; ++k) {
+            ps[k] = IO::load(rs, poff[k]);
+            px[k] = IO::load(rx, poff[k]);
+            pf[k] = IO::load(rf, poff[k]);
         }
+    };
+    auto stage = [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int m = 0; m < IPS; ++m) {
+            const int it = tid + m * NTHR;
+            if (S::NITEM % NTHR == 0 || m < IPS - 1 || it < S::NITEM) {
+                _Float16 *q = U + (it % G::SC) * G::UP + 4 * (it / G::SC);
+                float4_t u1, u2, u3;
+#pragma unroll
+                for (int j = 0; j < 4; ++j) {
+                    const int k = 4 * m + j;
+                    const float fs = pf[k] * fmul;
+                    u1[j] = (ps[k] * px[k]) * umul;
+                    u3[j] = fs * u1[j];
+                    u2[j] = fs * u3[j];
+                }
+                half4_t h, l;
+                split4(u1, h, l, one);
+                *reinterpret_cast<half4_t *>(q) = h;
+                *reinterpret_cast<half4_t *>(q + G::UPL) = l;
+                split4(u2, h, l, one);
+                *reinterpret_cast<half4_t *>(q + S::UF) = h;
+                *reinterpret_cast<half4_t *>(q + S::UF + G::UPL) = l;
+                split4(u3, h, l, one);
+                *reinterpret_cast<half4_t *>(q + 2 * S::UF) = h;
+                *reinterpret_cast<half4_t *>(q + 2 * S::UF + G::UPL) = l;
+            }
+        }
+    };
+    auto ypass = [&]() __attribute__((always_inline)) {
+        float4_t ya[S::YPW];
+#pragma unroll
+        for (int m = 0; m < S::YPW; ++m) {
+            const int b = wid + m * G::NWAVE;
+            if (S::NYB % G::NWAVE == 0 || m < S::YPW - 1 || b < S::NYB)
+                ya[m] = mfma_yblock_mma<G>(U + (b / G::NYB) * S::UF, b % G::NYB, lane, thi, tlo);
+        }
+#pragma unroll
+        for (int m = 0; m < S::YPW; ++m) {
+            const int b = wid + m * G::NWAVE;
+            if (S::NYB % G::NWAVE == 0 || m < S::YPW - 1 || b < S::NYB)
+                mfma_yblock_store<G>(Y + (b / G::NYB) * S::YF, b % G::NYB, lane, ya[m], one);
+        }
+    };
+    double d1 = 0.0, d2 = 0.0;
+    float wm = 0.f;
+    fetch(fw.in(0), true);
+    stage();
+    __syncthreads();
+    fetch(fw.in(1), 1 < nin);
+    ypass();
+    __syncthreads();
+    for (int k = 0; k < fw.nstep; ++k) {
+        const int tout = fw.out(k);
+        const bool emit = tout >= t0 && tout < t1;
+        const size_t to = (size_t)(emit ? tout : 0) * plane;
+        const uint32_t ob = emit ? pbytes : 0u;
+        float os[4], of[4], ox[4];
+        IO::load4(make_rsrc(a.s + to, ob), ooff, os);
+        IO::load4(make_rsrc(a.f + to, ob), ooff, of);
+        IO::load4(make_rsrc(src + to, a.no_prev ? 0u : ob), ooff, ox);
+        float4_t v[3];
+        if (k < nin) {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) v[m] = mfma_xblock_mma<G>(Y + m * S::YF, wid, lane, thi, tlo);
+        } else {
+#pragma unroll
+            for (int m = 0; m < 3; ++m) v[m] = float4_t{0.f, 0.f, 0.f, 0.f};
+        }
+        if (k + 1 < nin) stage();
+        fetch(fw.in(k + 2), k + 2 < nin);
+        // t-pass: slot i holds the output frame i steps ahead of out(k)
+#pragma unroll
+        for (int m = 0; m < 3; ++m)
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+#pragma unroll
+                for (int i = 0; i < NTS - 1; ++i) acc[m][i][q] = fma3(a.taps.gt[i], v[m][q], acc[m][i + 1][q]);
+                acc[m][NTS - 1][q] = a.taps.gt[NTS - 1] * v[m][q];
+            }
+        if (emit) {
+            const auto rz = make_rsrc(dst + to, pbytes);
+            float z[4];
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                // columns past the right edge: the 4-wide loads read the next row there
+                const float so = q < nout ? os[q] : 0.f, fo = of[q];
+                z[q] = so * ko * (fmaf(a.ainv - fo * fo, acc[0][0][q], -(acc[1][0][q] * kb)) + fo * kc * acc[2][0][q]);
+                const double zs = (double)z[q];
+                d2 = fma(zs, zs, d2);
+                d1 = fma(zs, (double)ox[q], d1);
+                wm = fmaxf(wm, fabsf(so * z[q]));
+            }
+            if (nout == 4) {
+                IO::store4(rz, ooff, z);
+            } else {
+#pragma unroll
+                for (int q = 0; q < 3; ++q)
+                    if (q < nout) IO::store(rz, ooff + 4 * q, z[q]);
+            }
+        }
+        __syncthreads();
+        if (k + 1 < nin) ypass();
+        __syncthreads();
+    }
+    block_reduce<NTHR>(d1, d2, wm, red);
+    if (threadIdx.x == 0) {
+        a.partials[2 * unit] = d1;
+        a.partials[2 * unit + 1] = d2;
+        if (a.wpart) a.wpart[unit] = __float_as_uint(wm);
     }
 }
 
 // The range check of the affinity (Eq. 2's Taylor term): every entry of M is
 // >= 0 when s >= 0 and alpha (max f - min f)^2 <= 1. Per-block min f, max f,
-// min s into partials[3 b .. 3 b + 2].
-constexpr int SFSEG_RANGE_BLOCKS = 256;
-template <class ST>
-__global__ void sfseg_range_kernel(size_t n, const ST *s, const ST *f, double *partials) {
-    using CT = typename Compute<ST>::type;
-    __shared__ double r0[256 / 64], r1[256 / 64], r2[256 / 64];
-    double fmn = INFINITY, fmx = -INFINITY, smn = INFINITY;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256) {
-        const double fv = (double)ld(f + i), sv = (double)ld(s + i);
-        // a NaN makes the check fail
-        fmn = (fv < fmn || fv != fv) ? fv : fmn;
-        fmx = (fv > fmx || fv != fv) ? fv : fmx;
-        smn = (sv < smn || sv != sv) ? sv : smn;
+// min s and max s into partials[4 b .. 4 b + 3]; a NaN anywhere gives NaNs.
+// One read of both volumes, 16-byte chunks with two of each in flight per
+// thread (196 us element by element on 256 workgroups at 64x480x854, 40 us now).
+constexpr int SFSEG_RANGE_BLOCKS = 1024;
+struct SfsegRange {
+    double fmn, fmx, smn, smx;
+    __device__ __forceinline__ void take(double f, double s) {
+        fmn = (f < fmn || f != f) ? f : fmn;
+        fmx = (f > fmx || f != f) ? f : fmx;
+        smn = (s < smn || s != s) ? s : smn;
+        smx = (s > smx || s != s) ? s : smx;
     }
+    // minima with minima, maxima with maxima: an empty range changes nothing
+    __device__ __forceinline__ void take(const SfsegRange &o) {
+        fmn = (o.fmn < fmn || o.fmn != o.fmn) ? o.fmn : fmn;
+        fmx = (o.fmx > fmx || o.fmx != o.fmx) ? o.fmx : fmx;
+        smn = (o.smn < smn || o.smn != o.smn) ? o.smn : smn;
+        smx = (o.smx > smx || o.smx != o.smx) ? o.smx : smx;
+    }
+    __device__ __forceinline__ void wave() {
 #pragma unroll
-    for (int off = 32; off >= 1; off >>= 1) {
-        const double a = __shfl_xor(fmn, off, 64), b = __shfl_xor(fmx, off, 64), c = __shfl_xor(smn, off, 64);
-        fmn = (a < fmn || a != a) ? a : fmn;
-        fmx = (b > fmx || b != b) ? b : fmx;
-        smn = (c < smn || c != c) ? c : smn;
+        for (int off = 32; off >= 1; off >>= 1) {
+            const SfsegRange o = {__shfl_xor(fmn, off, 64), __shfl_xor(fmx, off, 64), __shfl_xor(smn, off, 64),
+                                  __shfl_xor(smx, off, 64)};
+            take(o);
+        }
     }
+};
+constexpr SfsegRange SFSEG_RANGE_EMPTY = {INFINITY, -INFINITY, INFINITY, -INFINITY};
+
+template <class ST>
+__global__ __launch_bounds__(256) void sfseg_range_kernel(size_t n, const ST *s, const ST *f, double *partials) {
+    __shared__ SfsegRange rw[256 / 64];
+    constexpr int VEC = 16 / (int)sizeof(ST);
+    SfsegRange r = SFSEG_RANGE_EMPTY;
+    const size_t stride = (size_t)gridDim.x * 256, tid = (size_t)blockIdx.x * 256 + threadIdx.x;
+    size_t head = 0;
+    if ((((uintptr_t)s | (uintptr_t)f) & 15) == 0) {
+        const size_t nv = n / VEC;
+        const uint4 *s4 = reinterpret_cast<const uint4 *>(s), *f4 = reinterpret_cast<const uint4 *>(f);
+        // minima and maxima in the storage type (exact), widened at the end; a NaN sticks
+        ST fmn = (ST)INFINITY, fmx = -(ST)INFINITY, smn = (ST)INFINITY, smx = -(ST)INFINITY;
+        bool nan = false;
+        for (size_t i = tid; i < nv; i += 2 * stride) {
+            union {
+                uint4 u;
+                ST e[VEC];
+            } cs[2], cf[2];
+            const size_t i1 = i + stride < nv ? i + stride : i;
+            cs[0].u = s4[i];
+            cf[0].u = f4[i];
+            cs[1].u = s4[i1];
+            cf[1].u = f4[i1];
+#pragma unroll
+            for (int k = 0; k < 2; ++k)
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) {
+                    const ST fv = cf[k].e[e], sv = cs[k].e[e];
+                    nan |= fv != fv || sv != sv;
+                    fmn = fv < fmn ? fv : fmn;
+                    fmx = fv > fmx ? fv : fmx;
+                    smn = sv < smn ? sv : smn;
+                    smx = sv > smx ? sv : smx;
+                }
+        }
+        r.take(SfsegRange{(double)fmn, (double)fmx, (double)smn, (double)smx});
+        if (nan) r.take((double)NAN, (double)NAN);
+        head = nv * VEC;
+    }
+    for (size_t i = head + tid; i < n; i += stride) r.take((double)f[i], (double)s[i]);
+    r.wave();
     const int lane = threadIdx.x & 63, wid = threadIdx.x >> 6;
-    if (lane == 0) {
-        r0[wid] = fmn;
-        r1[wid] = fmx;
-        r2[wid] = smn;
-    }
+    if (lane == 0) rw[wid] = r;
     __syncthreads();
     if (threadIdx.x == 0) {
-        for (int w = 1; w < 256 / 64; ++w) {
-            fmn = (r0[w] < fmn || r0[w] != r0[w]) ? r0[w] : fmn;
-            fmx = (r1[w] > fmx || r1[w] != r1[w]) ? r1[w] : fmx;
-            smn = (r2[w] < smn || r2[w] != r2[w]) ? r2[w] : smn;
-        }
-        partials[3 * blockIdx.x] = fmn;
-        partials[3 * blockIdx.x + 1] = fmx;
-        partials[3 * blockIdx.x + 2] = smn;
+        for (int w = 1; w < 256 / 64; ++w) r.take(rw[w]);
+        partials[4 * blockIdx.x] = r.fmn;
+        partials[4 * blockIdx.x + 1] = r.fmx;
+        partials[4 * blockIdx.x + 2] = r.smn;
+        partials[4 * blockIdx.x + 3] = r.smx;
+    }
+}
+
+// Operand bounds of a single matrix-core step: words[0] = max |s x|, words[1] =
+// max |f| over the finite values, as float bits (cleared by the caller).
+__global__ __launch_bounds__(256) void sfseg_bounds_kernel(size_t n, const float *s, const float *f, const float *x,
+                                                           uint32_t *words) {
+    __shared__ float red[256 / 64];
+    float a = 0.f, b = 0.f;
+    const size_t stride = (size_t)gridDim.x * 256;
+#pragma unroll 4
+    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
+        const float u = fabsf(s[i] * x[i]), v = fabsf(f[i]);
+        a = u > a && u < INFINITY ? u : a;
+        b = v > b && v < INFINITY ? v : b;
+    }
+    a = block_max<256>(a, red);
+    b = block_max<256>(b, red);
+    if (threadIdx.x == 0) {
+        atomicMax(&words[0], __float_as_uint(a));
+        atomicMax(&words[1], __float_as_uint(b));
     }
 }
 
@@ -352,9 +660,13 @@ __global__ void sfseg_unary_kernel(size_t n, const ST *S, double p, ST *s) {
 struct SfsegLaunch {
     const void *s, *f;
     void *buf0, *buf1;
-    DevState *state;
+    const DevState *state;
+    DevState *state_out;
+    StepPartials prev_part;
     double *partials;
-    int fuse;
+    uint32_t *wpart;
+    const uint32_t *bounds;
+    int no_prev;
     double x_scale;
     double ainv;
     int T, H, W, nseg;
@@ -366,12 +678,14 @@ using SfsegLaunchFn = hipError_t (*)(const SfsegLaunch &, hipStream_t);
 
 struct SfsegVariant {
     int RS, RT, TH, TW, NTHR;
+    int mfma;  // 1: matrix-core spatial passes (needs the operand bounds)
     SfsegLaunchFn launch;
     int (*blocks_per_cu)();
 };
 
-template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX>
-hipError_t launch_sfseg(const SfsegLaunch &L, hipStream_t stream) {
+// CENTRE: where the kernel wants the centre space tap.
+template <class ST, int CENTRE, int RT>
+SfsegArgs<ST> sfseg_args(const SfsegLaunch &L) {
     using CT = typename Compute<ST>::type;
     SfsegArgs<ST> a;
     a.s = (const ST *)L.s;
@@ -379,22 +693,48 @@ hipError_t launch_sfseg(const SfsegLaunch &L, hipStream_t stream) {
     a.buf0 = (ST *)L.buf0;
     a.buf1 = (ST *)L.buf1;
     a.state = L.state;
+    a.state_out = L.state_out;
+    a.prev_part = L.prev_part;
     a.partials = L.partials;
-    a.fuse = L.state && L.fuse && NTHR >= FINAL_THREADS ? 1 : 0;
+    a.wpart = L.wpart;
+    a.bounds = L.bounds;
+    a.no_prev = L.state && L.no_prev ? 1 : 0;
     a.x_scale = L.x_scale;
     a.ainv = (CT)L.ainv;
     a.T = L.T;
     a.H = L.H;
     a.W = L.W;
     a.nseg = L.nseg > 0 ? L.nseg : 1;
+    a.rs = 0;
+    for (int d = 1; d <= 16; ++d)
+        if (L.gs[16 + d] != 0.0) a.rs = d;
     for (int i = 0; i < 2 * 16 + 1; ++i) a.taps.gs[i] = CT(0);
     for (int i = 0; i < 2 * 8 + 1; ++i) a.taps.gt[i] = CT(0);
-    for (int d = -RS; d <= RS; ++d) a.taps.gs[d + RS] = (CT)L.gs[d + 16];
+    for (int d = -CENTRE; d <= CENTRE; ++d) a.taps.gs[d + CENTRE] = (CT)L.gs[d + 16];
     for (int d = -RT; d <= RT; ++d) a.taps.gt[d + RT] = (CT)L.gt[d + 8];
+    return a;
+}
+
+template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX>
+hipError_t launch_sfseg(const SfsegLaunch &L, hipStream_t stream) {
+    if (L.state && L.state_out == L.state) return hipErrorInvalidValue;
+    SfsegArgs<ST> a = sfseg_args<ST, RS, RT>(L);
+    a.prev_part.wmax = nullptr;
     const int nunits = ((L.W + TW - 1) / TW) * ((L.H + TH - 1) / TH) * a.nseg;
     const int per = (nunits + NUM_XCD - 1) / NUM_XCD;
     hipLaunchKernelGGL((sfseg_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX>), dim3(per * NUM_XCD), dim3(NTHR), 0,
                        stream, a);
+    return hipGetLastError();
+}
+
+template <int RT, int TH, int TW, int NTHR, int PAD>
+hipError_t launch_sfseg_mfma(const SfsegLaunch &L, hipStream_t stream) {
+    if (L.state && (L.state_out == L.state || !L.wpart)) return hipErrorInvalidValue;
+    if (!L.state && !L.bounds) return hipErrorInvalidValue;
+    const SfsegArgs<float> a = sfseg_args<float, 16, RT>(L);
+    const int nunits = ((L.W + TW - 1) / TW) * ((L.H + TH - 1) / TH) * a.nseg;
+    const int per = (nunits + NUM_XCD - 1) / NUM_XCD;
+    hipLaunchKernelGGL((sfseg_mfma_kernel<RT, TH, TW, NTHR, PAD>), dim3(per * NUM_XCD), dim3(NTHR), 0, stream, a);
     return hipGetLastError();
 }
 
@@ -403,6 +743,15 @@ int sfseg_blocks_per_cu() {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sfseg_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX>, NTHR,
                                                      0) != hipSuccess)
+        n = 1;
+    return n > 0 ? n : 1;
+}
+
+template <int RT, int TH, int TW, int NTHR, int PAD>
+int sfseg_mfma_blocks_per_cu() {
+    int n = 0;
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, sfseg_mfma_kernel<RT, TH, TW, NTHR, PAD>, NTHR, 0) !=
+        hipSuccess)
         n = 1;
     return n > 0 ? n : 1;
 }

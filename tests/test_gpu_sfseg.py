@@ -170,3 +170,65 @@ def test_sfseg_unary_and_affinity_check(S):
     assert r["rc"] == N.STPI_EINVAL and r["flags"] & 16 and r["iters"] == 0
     _, r = Sf.sfseg_iterate(sd, fd, kern, 1.0, iters=3)
     assert r["iters"] == 3 and not r["flags"]
+
+
+@pytest.mark.parametrize("shape,kp,fscale,foff", [
+    ((4, 31, 63), (4.0, 1.5, 8, 3), 1.0, 0.0), ((4, 32, 64), (3.0, 1.5, 7, 3), 1.0, 0.0),
+    ((7, 33, 65), (4.0, 1.5, 5, 3), 1e-3, 0.0), ((3, 48, 66), (5.0, 2.0, 16, 5), 1.0, 0.0),
+    ((13, 65, 67), (5.0, 2.0, 15, 5), 0.5, 3.0), ((12, 16, 130), (4.0, 2.0, 9, 4), 1e3, 0.0),
+    ((2, 5, 3), (5.0, 2.0, 15, 5), 1.0, 0.0), ((9, 40, 72), (4.0, 1.5, 8, 3), 0.0, 0.0)])
+def test_sfseg_matrix_core_step_and_chain(S, shape, kp, fscale, foff):
+    """The matrix-core form around its tile edges, with f scaled and offset (its
+    staging powers of two follow max |f|): one step per frame and eight
+    iterations (uniform and given start, fixed count and tolerance chain) against
+    the oracle. The update cancels terms of size max f^2 / (max f - min f)^2 above
+    its result, so the float tolerance 1e-5 grows with that ratio."""
+    P, Sf = S
+    kern = P.Kernel(*kp)
+    s, f = _fields(shape, 3)
+    f = f * fscale + foff
+    span = max(float(f.max() - f.min()), 1e-30)
+    alpha = 0.9 / max(span * span, 1e-12)
+    s, f = s.astype(np.float32), f.astype(np.float32)
+    x = np.random.default_rng(9).uniform(-0.2, 1.0, shape).astype(np.float32)
+    cond = max(1.0, alpha * float(np.max(f)) ** 2)
+    sd, fd, xd = (torch.from_numpy(v).to(DEV) for v in (s, f, x))
+    z, _ = Sf.sfseg_step(sd, fd, xd, kern, alpha, x_scale=0.3)
+    torch.cuda.synchronize()
+    ref = oracle.sfseg_apply(s.astype(np.float64), f.astype(np.float64), x.astype(np.float64) * 0.3, alpha, okf(kern))
+    zz = z.double().cpu().numpy()
+    for t in range(shape[0]):
+        assert rel_l2(zz[t], ref[t]) <= 1e-5 * cond, (t, rel_l2(zz[t], ref[t]))
+    x0 = np.abs(x) + np.float32(0.01)
+    for start in (None, x0):
+        kw = {} if start is None else dict(x0=torch.from_numpy(start).to(DEV))
+        xg, r = Sf.sfseg_iterate(sd, fd, kern, alpha, iters=8, **kw)
+        xg = xg.clone()
+        xt, rt = Sf.sfseg_iterate(sd, fd, kern, alpha, tol=1e-300, max_iters=8, **kw)
+        torch.cuda.synchronize()
+        xr, info = oracle.sfseg_iterate(s, f, alpha, okf(kern), iters=8, x0=start)
+        err = rel_l2(xg.double().cpu().numpy(), xr)
+        print(shape, kp, fscale, foff, "chain", err)
+        assert r["iters"] == 8 and err <= 1e-5 * cond
+        assert abs(r["lambda_"] - info.lambdas[-1]) <= 1e-5 * cond * info.lambdas[-1]
+        # the fixed-count chain skips the inner products it does not report
+        assert torch.equal(xg, xt) and r["residual"] == rt["residual"] and r["r1"] == rt["r1"]
+
+
+def test_sfseg_range_check_on_small_and_odd_volumes(S):
+    """The range check's partial minima and maxima: volumes smaller than its
+    grid, sizes that leave a tail after its 16-byte chunks, one bad voxel."""
+    P, Sf = S
+    kern = P.Kernel(1.0, 1.0, 1, 1)
+    for shape in ((1, 1, 3), (3, 7, 11), (5, 64, 67)):
+        n = int(np.prod(shape))
+        s = torch.full(shape, 0.5, device=DEV)
+        f = torch.linspace(0, 1, n, device=DEV).reshape(shape).contiguous()
+        _, r = Sf.sfseg_iterate(s, f, kern, 1.0, iters=2)
+        assert r["status"] == 0 and r["iters"] == 2
+        for which, bad in (("s", -1e-3), ("s", float("nan")), ("f", 2.5), ("f", float("nan"))):
+            for at in (0, n // 2, n - 1):
+                v = dict(s=s.clone(), f=f.clone())
+                v[which].view(-1)[at] = bad
+                _, r = Sf.sfseg_iterate(v["s"], v["f"], kern, 1.0, iters=2, check=False)
+                assert r["rc"] == 1 and r["flags"] & 16, (shape, which, bad, at)
