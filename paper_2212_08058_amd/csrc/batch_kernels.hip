@@ -27,7 +27,6 @@ __global__ void batch_init_kernel(DevState *states, const ClipDesc *clips, int n
     s->flags = 0u;
     s->max_iters = max_iters;
     s->converged = 0;
-    s->arrive = 0u;
     s->ubound = 0u;
     s->wmax[0] = s->wmax[1] = 0u;
     s->refill = 0;

@@ -58,7 +58,6 @@ struct DevState {
     uint32_t flags;    // bit 0 zero norm, bit 1 non-finite
     int32_t max_iters;
     int32_t converged;
-    uint32_t arrive;   // workgroups of the running step that stored their partial sums
     uint32_t ubound;   // float bits of max |f| (matrix-core step variants)
     double first_res[2];  // residuals after the chain's first and second steps
     int32_t check_rise;   // 1: stop after the second step if its residual is above the first's
@@ -93,17 +92,6 @@ __device__ __forceinline__ int bound_exponent(float bound, int lim) {
 // Product-form chains keep 2^(+-2e) normal floats.
 constexpr int PRODUCT_ELIM = 60;
 
-// An empty partial-sum slot of a step whose last workgroup finalises it: a
-// signalling-NaN pattern that arithmetic never produces (its NaNs are quiet).
-// Each workgroup overwrites its slot with an agent-scope atomic store; the last
-// workgroup reads every slot until it no longer holds this pattern (so it sees
-// the stored value by the coherence of that one location, without a cache
-// write-back) and puts the pattern back for the next step.
-constexpr uint64_t PARTIAL_EMPTY = 0x7ff4dead5a17ab1eull;
-// Reads of one slot before the wait is abandoned (never reached in practice:
-// the arrival counter is only bumped after the slot's store has completed).
-constexpr int PARTIAL_SPIN_LIMIT = 1 << 20;
-constexpr uint32_t FLAG_SYNC = 8u;  // a partial sum never arrived (see PARTIAL_SPIN_LIMIT)
 constexpr uint32_t FLAG_AFFINITY = 16u;  // full operator: a Taylor affinity could be negative (see sfseg.hip)
 
 // Workgroup size and summation order of the per-step reduction of partial
@@ -302,20 +290,6 @@ __device__ __forceinline__ void block_reduce(double &a, double &b, float &m, dou
             m = fmaxf(m, (float)sh[2 * NW + i]);
         }
     }
-}
-
-// Reads partial-sum slot i of a step finalised by its last workgroup (see
-// PARTIAL_EMPTY) and empties it again; *late is set if it never arrived.
-__device__ __forceinline__ double take_partial(double *slot, bool *late) {
-    uint64_t *w = reinterpret_cast<uint64_t *>(slot);
-    uint64_t v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    for (int k = 0; v == PARTIAL_EMPTY && k < PARTIAL_SPIN_LIMIT; ++k) {
-        __builtin_amdgcn_s_sleep(1);
-        v = __hip_atomic_load(w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    }
-    if (v == PARTIAL_EMPTY) *late = true;
-    __hip_atomic_store(w, PARTIAL_EMPTY, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-    return __longlong_as_double((long long)v);
 }
 
 }  // namespace stpi

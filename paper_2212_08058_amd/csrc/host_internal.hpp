@@ -83,7 +83,6 @@ hipError_t launch_state_init(DevState *s, double scale, double tol, int max_iter
                              hipStream_t st);
 hipError_t launch_state_from_norm(const double *partials, int n, DevState *s, hipStream_t st);
 hipError_t launch_clear_word(uint32_t *w, hipStream_t st);
-hipError_t launch_partials_empty(double *partials, int n, hipStream_t st);
 bool fusion_disabled();
 int device_cus();  // compute units of the current device
 hipError_t launch_finalize(StepPartials part, int n, DevState *s, hipStream_t st);
