@@ -53,15 +53,18 @@ __global__ void step_sums_kernel(const double *partials, int n, double x_scale, 
     }
 }
 
-// g_a_c = sum of partials; dL/dw = a (g_a - <a, g_a>)  (softmax Jacobian)
-__global__ void combine_bwd_finalize(int C, int nblocks, const double *partials, const double *w, double *gw) {
+// g_a_c = sum of partials; dL/dw = a (g_a - <a, g_a>)  (softmax Jacobian). A
+// wavefront per channel.
+__global__ __launch_bounds__(1024) void combine_bwd_finalize(int C, int nblocks, const double *partials, const double *w,
+                                                             double *gw) {
     __shared__ double ga[MAX_CHANNELS];
-    __shared__ double red[AUX_THREADS / 64];
-    for (int c = 0; c < C; ++c) {
+    const int lane = threadIdx.x & 63;
+    for (int c = threadIdx.x >> 6; c < C; c += 1024 / 64) {
         double s = 0.0;
-        for (int b = threadIdx.x; b < nblocks; b += AUX_THREADS) s += partials[(size_t)b * C + c];
-        const double t = block_sum<AUX_THREADS>(s, red);
-        if (threadIdx.x == 0) ga[c] = t;
+        for (int b = lane; b < nblocks; b += 64) s += partials[(size_t)b * C + c];
+#pragma unroll
+        for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+        if (lane == 0) ga[c] = s;
     }
     __syncthreads();
     if (threadIdx.x == 0) {
@@ -73,19 +76,33 @@ __global__ void combine_bwd_finalize(int C, int nblocks, const double *partials,
     }
 }
 
-// scalars[0] = max, scalars[1] = its first index
-__global__ void max_finalize(int nblocks, const double *partials, double *scalars) {
-    if (threadIdx.x != 0) return;
+// scalars[0] = max, scalars[1] = its first index (one thread walking the
+// partials in turn took 64 us for 512 of them, this 4)
+__global__ __launch_bounds__(CHAIN_THREADS) void max_finalize(int nblocks, const double *partials, double *scalars) {
+    __shared__ double sv[CHAIN_THREADS], si[CHAIN_THREADS];
     double bv = -1e300, bi = 1e300;
-    for (int b = 0; b < nblocks; ++b) {
-        const double v = partials[2 * b], i = partials[2 * b + 1];
+    auto take = [&](double v, double i) {
         if (v > bv || (v == bv && i < bi)) {
             bv = v;
             bi = i;
         }
+    };
+    for (int b = threadIdx.x; b < nblocks; b += CHAIN_THREADS) take(partials[2 * b], partials[2 * b + 1]);
+    sv[threadIdx.x] = bv;
+    si[threadIdx.x] = bi;
+    __syncthreads();
+    for (int s = CHAIN_THREADS / 2; s > 0; s >>= 1) {
+        if ((int)threadIdx.x < s) {
+            take(sv[threadIdx.x + s], si[threadIdx.x + s]);
+            sv[threadIdx.x] = bv;
+            si[threadIdx.x] = bi;
+        }
+        __syncthreads();
     }
-    scalars[0] = bv;
-    scalars[1] = bi;
+    if (threadIdx.x == 0) {
+        scalars[0] = bv;
+        scalars[1] = bi;
+    }
 }
 
 // out = (sum_b partials[2b]) / (a_norm ? *a_norm : 1)
@@ -111,12 +128,12 @@ __global__ void sum0_finalize(const double *partials, int n, double *out) {
 
 hipError_t launch_combine_bwd_finalize(int C, int nblocks, const double *partials, const double *w, double *gw,
                                        hipStream_t st) {
-    hipLaunchKernelGGL(combine_bwd_finalize, dim3(1), dim3(AUX_THREADS), 0, st, C, nblocks, partials, w, gw);
+    hipLaunchKernelGGL(combine_bwd_finalize, dim3(1), dim3(1024), 0, st, C, nblocks, partials, w, gw);
     return hipGetLastError();
 }
 
 hipError_t launch_max_finalize(int nblocks, const double *partials, double *scalars, hipStream_t st) {
-    hipLaunchKernelGGL(max_finalize, dim3(1), dim3(64), 0, st, nblocks, partials, scalars);
+    hipLaunchKernelGGL(max_finalize, dim3(1), dim3(CHAIN_THREADS), 0, st, nblocks, partials, scalars);
     return hipGetLastError();
 }
 

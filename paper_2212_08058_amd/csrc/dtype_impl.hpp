@@ -89,7 +89,7 @@ hipError_t combine_fwd_impl(int C, size_t n, const void *fc, const double *w, vo
     return hipGetLastError();
 }
 hipError_t combine_bwd_impl(int C, size_t n, const void *fc, const void *gf, double *partials, hipStream_t s) {
-    hipLaunchKernelGGL(combine_bwd_kernel<ST_>, dim3(AUX_BLOCKS), dim3(AUX_THREADS), 0, s, C, n, (const ST_ *)fc,
+    hipLaunchKernelGGL(combine_bwd_kernel<ST_>, dim3(AUX_BLOCKS, (C + CB_CH - 1) / CB_CH), dim3(AUX_THREADS), 0, s, C, n, (const ST_ *)fc,
                        (const ST_ *)gf, partials);
     return hipGetLastError();
 }

@@ -12,6 +12,7 @@
 #include <cmath>
 
 #include "../../include/stpi.h"
+#include "aux.hpp"
 #include "common.hpp"
 #include "host_internal.hpp"
 
@@ -19,79 +20,138 @@ namespace stpi {
 namespace {
 
 constexpr int PP_THREADS = 256;
-constexpr int PP_BLOCKS = 256;      // grid of the whole-volume reductions
+constexpr int PP_BLOCKS = 256;      // grid of the whole-volume reductions (their partials' room)
+constexpr int PP_WIDE = 1024;       // and their workgroup: one of them fills a CU's latency
 constexpr int FD_BLOCKS = 16;       // blocks per frame in the Focal-Dice sums
 
-__device__ __forceinline__ double sigmoid_d(double a) { return 0.5 * (1.0 + tanh(0.5 * a)); }
+__device__ __forceinline__ double sigmoid_d(double a) { return 1.0 / (1.0 + exp(-a)); }
 
-template <class ST>
-__global__ void combine_sigmoid_fwd_kernel(int C, size_t n, const ST *fc, const double *w, const double *b, ST *f) {
+// f = sigmoid(sum_c w_c fc_c + b), PP_CH channels' loads in flight together.
+constexpr int PP_CH = 8;
+template <class ST, int VEC>
+__device__ __forceinline__ void combine_sigmoid_range(int C, size_t n, size_t m, const ST *fc, const double *w, double b,
+                                                      ST *f) {
     using CT = typename Compute<ST>::type;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        double a = *b;
-        for (int c = 0; c < C; ++c) a = fma(w[c], (double)ld(fc + (size_t)c * n + i), a);
-        st(f + i, (CT)sigmoid_d(a));
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < m; i += (size_t)gridDim.x * blockDim.x) {
+        double a[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) a[e] = b;
+        for (int c0 = 0; c0 < C; c0 += PP_CH) {
+            Elems<ST, VEC> x[PP_CH];
+#pragma unroll
+            for (int c = 0; c < PP_CH; ++c)
+                if (c0 + c < C) x[c] = load_elems<ST, VEC>(fc + (size_t)(c0 + c) * n, i);
+#pragma unroll
+            for (int c = 0; c < PP_CH; ++c)
+                if (c0 + c < C) {
+#pragma unroll
+                    for (int e = 0; e < VEC; ++e) a[e] = fma(w[c0 + c], (double)x[c].v[e], a[e]);
+                }
+        }
+        if constexpr (VEC == 1) {
+            st(f + i, (CT)sigmoid_d(a[0]));
+        } else {
+            Chunk16<ST> o;
+#pragma unroll
+            for (int e = 0; e < VEC; ++e) st(&o.e[e], (CT)sigmoid_d(a[e]));
+            reinterpret_cast<uint4 *>(f)[i] = o.u;
+        }
     }
+}
+template <class ST>
+__global__ __launch_bounds__(PP_THREADS) void combine_sigmoid_fwd_kernel(int C, size_t n, const ST *fc, const double *w,
+                                                                         const double *b, ST *f) {
+    constexpr int VEC = 16 / (int)sizeof(ST);
+    if ((((uintptr_t)fc | (uintptr_t)f) & 15) == 0 && n % VEC == 0)
+        combine_sigmoid_range<ST, VEC>(C, n, n / VEC, fc, w, *b, f);
+    else
+        combine_sigmoid_range<ST, 1>(C, n, n, fc, w, *b, f);
 }
 
 // partials[block][c] = sum over the block's elements of g_f f (1 - f) fc_c, c < C;
-// partials[block][C] = sum of g_f f (1 - f).
-template <class ST>
-__global__ void combine_sigmoid_bwd_kernel(int C, size_t n, const ST *fc, const ST *f, const ST *g_f,
-                                           double *partials) {
-    __shared__ double red[PP_THREADS / 64];
-    double acc[STPI_MAX_CHANNELS + 1];
-    for (int c = 0; c <= C; ++c) acc[c] = 0.0;
-    for (size_t i = (size_t)blockIdx.x * PP_THREADS + threadIdx.x; i < n; i += (size_t)gridDim.x * PP_THREADS) {
-        const double fv = (double)ld(f + i);
-        const double ga = (double)ld(g_f + i) * fv * (1.0 - fv);
-        for (int c = 0; c < C; ++c) acc[c] = fma(ga, (double)ld(fc + (size_t)c * n + i), acc[c]);
-        acc[C] += ga;
+// partials[block][C] = sum of g_f f (1 - f). The PP_CH channels of blockIdx.y,
+// their sums in registers (indexed by a run-time channel they lay in memory:
+// 195 us for 8 channels of 32x240x432, this 32); its first slice adds the bias.
+template <class ST, int VEC>
+__device__ __forceinline__ void combine_sigmoid_bwd_range(int nc, size_t n, size_t m, const ST *fc, const ST *f,
+                                                          const ST *g_f, double (&acc)[PP_CH + 1]) {
+    for (size_t i = (size_t)blockIdx.x * PP_WIDE + threadIdx.x; i < m; i += (size_t)gridDim.x * PP_WIDE) {
+        const Elems<ST, VEC> fv = load_elems<ST, VEC>(f, i), gv = load_elems<ST, VEC>(g_f, i);
+        Elems<ST, VEC> x[PP_CH];
+#pragma unroll
+        for (int c = 0; c < PP_CH; ++c)
+            if (c < nc) x[c] = load_elems<ST, VEC>(fc + (size_t)c * n, i);
+        double ga[VEC];
+#pragma unroll
+        for (int e = 0; e < VEC; ++e) {
+            ga[e] = (double)gv.v[e] * (double)fv.v[e] * (1.0 - (double)fv.v[e]);
+            acc[PP_CH] += ga[e];
+        }
+#pragma unroll
+        for (int c = 0; c < PP_CH; ++c)
+            if (c < nc) {
+#pragma unroll
+                for (int e = 0; e < VEC; ++e) acc[c] = fma(ga[e], (double)x[c].v[e], acc[c]);
+            }
     }
-    for (int c = 0; c <= C; ++c) {
-        const double s = block_sum<PP_THREADS>(acc[c], red);
-        if (threadIdx.x == 0) partials[(size_t)blockIdx.x * (C + 1) + c] = s;
+}
+template <class ST>
+__global__ __launch_bounds__(PP_WIDE) void combine_sigmoid_bwd_kernel(int C, size_t n, const ST *fc, const ST *f,
+                                                                      const ST *g_f, double *partials) {
+    __shared__ double red[PP_WIDE / 64];
+    constexpr int VEC = 16 / (int)sizeof(ST);
+    const int c0 = blockIdx.y * PP_CH, nc = C - c0 < PP_CH ? C - c0 : PP_CH;
+    fc += (size_t)c0 * n;
+    double acc[PP_CH + 1] = {};
+    if ((((uintptr_t)fc | (uintptr_t)f | (uintptr_t)g_f) & 15) == 0 && n % VEC == 0)
+        combine_sigmoid_bwd_range<ST, VEC>(nc, n, n / VEC, fc, f, g_f, acc);
+    else
+        combine_sigmoid_bwd_range<ST, 1>(nc, n, n, fc, f, g_f, acc);
+#pragma unroll
+    for (int c = 0; c <= PP_CH; ++c) {
+        if (c < PP_CH ? c >= nc : c0 > 0) continue;
+        const double s = block_sum<PP_WIDE>(acc[c], red);
+        if (threadIdx.x == 0) partials[(size_t)blockIdx.x * (C + 1) + (c < PP_CH ? c0 + c : C)] = s;
     }
 }
 
-__global__ void combine_sigmoid_bwd_finalize(int C, int nb, const double *partials, double *g_wb) {
-    const int c = threadIdx.x;
-    if (c > C) return;
+// A wavefront per entry.
+__global__ __launch_bounds__(64) void combine_sigmoid_bwd_finalize(int C, int nb, const double *partials, double *g_wb) {
+    const int c = blockIdx.x;
     double s = 0.0;
-    for (int blk = 0; blk < nb; ++blk) s += partials[(size_t)blk * (C + 1) + c];
-    g_wb[c] = s;
+    for (int blk = threadIdx.x; blk < nb; blk += 64) s += partials[(size_t)blk * (C + 1) + c];
+#pragma unroll
+    for (int off = 32; off >= 1; off >>= 1) s += __shfl_xor(s, off, 64);
+    if (threadIdx.x == 0) g_wb[c] = s;
 }
 
-// b = sigmoid(kappa (sqrt(n) z / ||z|| - theta)); partials of sum b^2.
+// b = sigmoid(kappa (sqrt(n) z / ||z|| - theta)); partials of sum b^2. Bound by
+// the double exponential; workgroups of 256 left the CUs a quarter full (34 us at
+// 32x240x432, this 13; the backward 32 and 14.5).
 template <class ST>
-__global__ void softbin_fwd_kernel(size_t n, const ST *z, const double *znorm, double kappa, double theta, ST *b,
-                                   double *partials) {
+__global__ __launch_bounds__(PP_WIDE) void softbin_fwd_kernel(size_t n, const ST *z, const double *znorm, double kappa,
+                                                              double theta, ST *b, double *partials) {
     using CT = typename Compute<ST>::type;
-    __shared__ double red[PP_THREADS / 64];
+    __shared__ double red[PP_WIDE / 64];
     const double sc = sqrt((double)n) / *znorm;
     double acc = 0.0;
-    for (size_t i = (size_t)blockIdx.x * PP_THREADS + threadIdx.x; i < n; i += (size_t)gridDim.x * PP_THREADS) {
+    for (size_t i = (size_t)blockIdx.x * PP_WIDE + threadIdx.x; i < n; i += (size_t)gridDim.x * PP_WIDE) {
         const CT v = (CT)sigmoid_d(kappa * ((double)ld(z + i) * sc - theta));
         st(b + i, v);
         const double vs = (double)stored_value(b + i, v);
         acc = fma(vs, vs, acc);
     }
-    const double s = block_sum<PP_THREADS>(acc, red);
+    const double s = block_sum<PP_WIDE>(acc, red);
     if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
-__global__ void sqrt_sum_kernel(int nb, const double *partials, double *out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
+// *out = the sum of nb partials, or its square root.
+__global__ __launch_bounds__(PP_THREADS) void sum_kernel(int nb, const double *partials, int root, double *out) {
+    __shared__ double red[PP_THREADS / 64];
     double s = 0.0;
-    for (int i = 0; i < nb; ++i) s += partials[i];
-    *out = sqrt(s);
-}
-
-__global__ void sum_kernel(int nb, const double *partials, double *out) {
-    if (threadIdx.x != 0 || blockIdx.x != 0) return;
-    double s = 0.0;
-    for (int i = 0; i < nb; ++i) s += partials[i];
-    *out = s;
+    for (int i = threadIdx.x; i < nb; i += PP_THREADS) s += partials[i];
+    s = block_sum<PP_THREADS>(s, red);
+    if (threadIdx.x == 0) *out = root ? sqrt(s) : s;
 }
 
 // Backward of b = softbin(y), y = z_prev / ||z_prev||, with g given w.r.t.
@@ -99,24 +159,25 @@ __global__ void sum_kernel(int nb, const double *partials, double *out) {
 // w.r.t. b itself (unit = 0): g_y = g_b b (1 - b) kappa sqrt(n); partials of
 // <y, g_y>.
 template <class ST>
-__global__ void softbin_bwd_kernel(size_t n, int unit, const ST *g, const double *d, const ST *b,
-                                   const double *bnorm, const ST *z_prev, const double *znorm_prev, double kappa,
-                                   ST *g_y, double *partials) {
+__global__ __launch_bounds__(PP_WIDE) void softbin_bwd_kernel(size_t n, int unit, const ST *g, const double *d,
+                                                              const ST *b, const double *bnorm, const ST *z_prev,
+                                                              const double *znorm_prev, double kappa, ST *g_y,
+                                                              double *partials) {
     using CT = typename Compute<ST>::type;
-    __shared__ double red[PP_THREADS / 64];
+    __shared__ double red[PP_WIDE / 64];
     const double ib = unit ? 1.0 / *bnorm : 1.0;
     const double dd = unit ? *d : 0.0;
     const double ks = kappa * sqrt((double)n);
     const double iz = 1.0 / *znorm_prev;
     double acc = 0.0;
-    for (size_t i = (size_t)blockIdx.x * PP_THREADS + threadIdx.x; i < n; i += (size_t)gridDim.x * PP_THREADS) {
+    for (size_t i = (size_t)blockIdx.x * PP_WIDE + threadIdx.x; i < n; i += (size_t)gridDim.x * PP_WIDE) {
         const double bv = (double)ld(b + i);
         const double gb = ((double)ld(g + i) - bv * ib * dd) * ib;
         const CT gy = (CT)(gb * bv * (1.0 - bv) * ks);
         st(g_y + i, gy);
         acc = fma((double)ld(z_prev + i) * iz, (double)stored_value(g_y + i, gy), acc);
     }
-    const double s = block_sum<PP_THREADS>(acc, red);
+    const double s = block_sum<PP_WIDE>(acc, red);
     if (threadIdx.x == 0) partials[blockIdx.x] = s;
 }
 
@@ -220,12 +281,12 @@ int stpi_combine_sigmoid_bwd(int C, int64_t n, int dtype, const void *fc, const 
     hipStream_t st = (hipStream_t)stream;
     double *partials = (double *)ws;
     if (dtype == STPI_F64)
-        hipLaunchKernelGGL(combine_sigmoid_bwd_kernel<double>, dim3(PP_BLOCKS), dim3(PP_THREADS), 0, st, C,
+        hipLaunchKernelGGL(combine_sigmoid_bwd_kernel<double>, dim3(PP_BLOCKS, (C + PP_CH - 1) / PP_CH), dim3(PP_WIDE), 0, st, C,
                            (size_t)n, (const double *)fc, (const double *)f, (const double *)g_f, partials);
     else
-        hipLaunchKernelGGL(combine_sigmoid_bwd_kernel<float>, dim3(PP_BLOCKS), dim3(PP_THREADS), 0, st, C,
+        hipLaunchKernelGGL(combine_sigmoid_bwd_kernel<float>, dim3(PP_BLOCKS, (C + PP_CH - 1) / PP_CH), dim3(PP_WIDE), 0, st, C,
                            (size_t)n, (const float *)fc, (const float *)f, (const float *)g_f, partials);
-    hipLaunchKernelGGL(combine_sigmoid_bwd_finalize, dim3(1), dim3(128), 0, st, C, PP_BLOCKS, partials, g_wb);
+    hipLaunchKernelGGL(combine_sigmoid_bwd_finalize, dim3(C + 1), dim3(64), 0, st, C, PP_BLOCKS, partials, g_wb);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? STPI_OK : hip_fail(e, "combine sigmoid backward");
 }
@@ -243,12 +304,12 @@ int stpi_softbin_fwd(int64_t n, int dtype, const void *z, const double *znorm, d
     hipStream_t st = (hipStream_t)stream;
     double *partials = (double *)ws;
     if (dtype == STPI_F64)
-        hipLaunchKernelGGL(softbin_fwd_kernel<double>, dim3(PP_BLOCKS), dim3(PP_THREADS), 0, st, (size_t)n,
+        hipLaunchKernelGGL(softbin_fwd_kernel<double>, dim3(PP_BLOCKS), dim3(PP_WIDE), 0, st, (size_t)n,
                            (const double *)z, znorm, kappa, theta, (double *)b, partials);
     else
-        hipLaunchKernelGGL(softbin_fwd_kernel<float>, dim3(PP_BLOCKS), dim3(PP_THREADS), 0, st, (size_t)n,
+        hipLaunchKernelGGL(softbin_fwd_kernel<float>, dim3(PP_BLOCKS), dim3(PP_WIDE), 0, st, (size_t)n,
                            (const float *)z, znorm, kappa, theta, (float *)b, partials);
-    hipLaunchKernelGGL(sqrt_sum_kernel, dim3(1), dim3(64), 0, st, PP_BLOCKS, partials, bnorm);
+    hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(PP_THREADS), 0, st, PP_BLOCKS, partials, 1, bnorm);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? STPI_OK : hip_fail(e, "softbin forward");
 }
@@ -268,14 +329,14 @@ int stpi_softbin_bwd(int64_t n, int dtype, int unit, const void *g, const double
     hipStream_t st = (hipStream_t)stream;
     double *partials = (double *)ws;
     if (dtype == STPI_F64)
-        hipLaunchKernelGGL(softbin_bwd_kernel<double>, dim3(PP_BLOCKS), dim3(PP_THREADS), 0, st, (size_t)n, unit,
+        hipLaunchKernelGGL(softbin_bwd_kernel<double>, dim3(PP_BLOCKS), dim3(PP_WIDE), 0, st, (size_t)n, unit,
                            (const double *)g, d, (const double *)b, bnorm, (const double *)z_prev, znorm_prev, kappa,
                            (double *)g_y, partials);
     else
-        hipLaunchKernelGGL(softbin_bwd_kernel<float>, dim3(PP_BLOCKS), dim3(PP_THREADS), 0, st, (size_t)n, unit,
+        hipLaunchKernelGGL(softbin_bwd_kernel<float>, dim3(PP_BLOCKS), dim3(PP_WIDE), 0, st, (size_t)n, unit,
                            (const float *)g, d, (const float *)b, bnorm, (const float *)z_prev, znorm_prev, kappa,
                            (float *)g_y, partials);
-    hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(64), 0, st, PP_BLOCKS, partials, d_prev);
+    hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(PP_THREADS), 0, st, PP_BLOCKS, partials, 0, d_prev);
     const hipError_t e = hipGetLastError();
     return e == hipSuccess ? STPI_OK : hip_fail(e, "softbin backward");
 }
@@ -308,7 +369,7 @@ int stpi_focal_dice(int T, int64_t plane, int dtype, const void *x, const uint8_
                            (size_t)plane, (const float *)x, gt, partials);
     hipLaunchKernelGGL(focal_dice_frames_kernel, dim3((T + 63) / 64), dim3(64), 0, st, T, partials, gamma, eps, coef,
                        terms);
-    hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(64), 0, st, T, terms, loss);
+    hipLaunchKernelGGL(sum_kernel, dim3(1), dim3(PP_THREADS), 0, st, T, terms, 0, loss);
     if (dtype == STPI_F64)
         hipLaunchKernelGGL(focal_dice_grad_kernel<double>, dim3(64, T), dim3(PP_THREADS), 0, st, (size_t)plane, gt,
                            coef, (double *)g_x);

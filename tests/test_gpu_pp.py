@@ -172,3 +172,41 @@ def test_learned_weights_favour_the_clean_channels(L):
           f"salt-and-pepper mean {sp:.3f}")
     assert losses[-1] < losses[0]
     assert clean > 1.2 * sp > 0
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.float64])
+@pytest.mark.parametrize("C,n,off", [(1, 1, 0), (7, 4096, 0), (8, 4099, 0), (9, 4096, 1), (64, 1028, 0), (17, 1028, 2)])
+def test_combination_reductions_over_channel_chunks(L, dtype, C, n, off):
+    """The combinations and their backward sums where channels or elements do
+    not fill a chunk and where the arrays are not 16-byte aligned. The sums run
+    in FP64 over fewer than 2^13 terms: 1e-12 of the sum of magnitudes."""
+    P, Lm = L
+    from paper_2212_08058_amd import _native as N
+    code = N.STPI_F64 if dtype == torch.float64 else N.STPI_F32
+    rng = np.random.default_rng(1000 * C + n + off)
+
+    def put(a):
+        t = torch.empty(a.size + off, dtype=dtype, device=DEV)
+        t[off:].copy_(torch.from_numpy(a.ravel()))
+        return t[off:]
+
+    fc, gf, w = put(rng.uniform(0, 1, (C, n))), put(rng.standard_normal(n)), rng.standard_normal(C)
+    f, b = put(np.zeros(n)), 0.3
+    wd, bd = torch.from_numpy(w).to(DEV), torch.tensor([b], dtype=torch.float64, device=DEV)
+    aux = torch.empty(N.AUX_WS_BYTES, dtype=torch.uint8, device=DEV)
+    gw, gwb = torch.empty(C, dtype=torch.float64, device=DEV), torch.empty(C + 1, dtype=torch.float64, device=DEV)
+    N.check(N.lib.stpi_combine_sigmoid_fwd(C, n, code, fc.data_ptr(), wd.data_ptr(), bd.data_ptr(), f.data_ptr(), None))
+    N.check(N.lib.stpi_combine_sigmoid_bwd(C, n, code, fc.data_ptr(), f.data_ptr(), gf.data_ptr(), gwb.data_ptr(),
+                                           aux.data_ptr(), aux.numel(), None))
+    N.check(N.lib.stpi_combine_bwd(C, n, code, fc.data_ptr(), wd.data_ptr(), gf.data_ptr(), gw.data_ptr(),
+                                   aux.data_ptr(), aux.numel(), None))
+    X, G, F = (t.double().cpu().numpy() for t in (fc, gf, f))
+    X = X.reshape(C, n)
+    eps = 1.2e-7 if dtype == torch.float32 else 1e-14
+    assert np.max(np.abs(F - 1.0 / (1.0 + np.exp(-(w @ X + b))))) <= eps
+    ga = G * F * (1.0 - F)
+    ref = np.append(X @ ga, ga.sum())
+    mag = np.append(np.abs(X) @ np.abs(ga), np.abs(ga).sum())
+    assert np.all(np.abs(gwb.cpu().numpy() - ref) <= 1e-12 * mag)
+    ref = oracle.combine_bwd(X, w, G)
+    assert np.max(np.abs(gw.cpu().numpy() - ref)) <= 1e-12 * np.max(np.abs(X) @ np.abs(G))
