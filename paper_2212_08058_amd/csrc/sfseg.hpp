@@ -499,6 +499,9 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
         }
         if (k + 1 < nin) stage();
         fetch(fw.in(k + 2), k + 2 < nin);
+        // fma3 is inline assembly, for which the compiler inserts no wait states
+        // after the products that made v
+        asm volatile("s_nop 15\n\ts_nop 7" : "+v"(v[0]), "+v"(v[1]), "+v"(v[2]));
         // t-pass: slot i holds the output frame i steps ahead of out(k)
 #pragma unroll
         for (int m = 0; m < 3; ++m)
