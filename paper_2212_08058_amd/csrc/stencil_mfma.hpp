@@ -26,6 +26,15 @@
 // loads, then the matrix-core products of both passes (they read buffers
 // written before the phase's barrier), then does the vector work (staging,
 // t-ring, epilogue) while those run, and stores the y-pass result last.
+// Loads, products, staging and the y-pass store run in every phase, also in the
+// first and last ones where a frame does not exist: what they then write is
+// rewritten before it is read, and without branches around them a phase is one
+// stretch of code that the compiler schedules as a whole (with the two-step
+// split below, a step of 64x480x854 at r = (15, 5) 111 -> 105 us in float and 91
+// -> 86 in bfloat16). Nothing binds a phase alone at this size: without the
+// products and their LDS reads it takes 9% less, without the staging loads 17%,
+// with all loads hitting the L2 14%; two wavefronts per SIMD, the most the ring
+// leaves registers for, overlap the rest only in part.
 // Per frame:
 //   stage:  u' on the (TH + 2 PAD) x (TW + 2 PAD) slab around the tile (PAD =
 //           8 or 16, at least the space radius), split into
@@ -125,6 +134,17 @@ __device__ __forceinline__ int stage_item(int tid, int m) {
 __device__ __forceinline__ void split_half(float v, _Float16 &hi, _Float16 &lo) {
     hi = (_Float16)v;
     lo = (_Float16)(v - (float)hi);
+}
+
+// Two products a m and b m as packed half-precision hi and lo parts: hi =
+// fp16(a m), lo = fp16(a m - hi), each rounded once from the exact product by a
+// mixed-precision fma that writes its half of the word (two instructions per
+// value; the plain form took 3.5 and could round hi in two steps).
+__device__ __forceinline__ void split_scaled2(float a, float b, float m, uint32_t &hi, uint32_t &lo) {
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(a), "v"(m));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(b), "v"(m));
+    asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(a), "v"(m), "v"(hi));
+    asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(b), "v"(m), "v"(hi));
 }
 
 // Launders a constant so the compiler keeps it as an operand (fma(x, 1, y)
@@ -331,13 +351,40 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
 
     const int nphase = fw.nstep + 2;
     const float one = opaque(1.f);
+    auto stage = [&](int p) __attribute__((always_inline)) {
+        _Float16 *U = U0 + (p & 1) * G::UBUF;
+#pragma unroll
+        for (int m = 0; m < IPS; ++m) {
+            const int it = stage_item<G, NTHR>(tid, m);
+            if (G::NITEM % NTHR == 0 || m < IPS - 1 || it < G::NITEM) {
+                const int c = it % G::SC, g = it / G::SC;
+                _Float16 *q = U + c * G::UP + 8 * g;
+                if constexpr (EXACT) {
+                    u16x8_t h;  // the inputs' own bfloat16 bits
+#pragma unroll
+                    for (int j = 0; j < 8; ++j)
+                        h[j] = (unsigned short)(__float_as_uint(op.template input<NPF>(pf, 8 * m + j)) >> 16);
+                    *reinterpret_cast<u16x8_t *>(q) = h;
+                } else {
+                    uint4 h, l;
+                    uint32_t *hp = &h.x, *lp = &l.x;
+#pragma unroll
+                    for (int j = 0; j < 4; ++j)
+                        split_scaled2(op.template input<NPF>(pf, 8 * m + 2 * j),
+                                      op.template input<NPF>(pf, 8 * m + 2 * j + 1), umul, hp[j], lp[j]);
+                    *reinterpret_cast<uint4 *>(q) = h;
+                    *reinterpret_cast<uint4 *>(q + G::UPL) = l;
+                }
+            }
+        }
+        op.template fetch<NPF>(fw.in(p + 1), poff, pf, p + 1 < nin);
+    };
     ring_loop<NTS, -2>(nphase, [&](auto ring_pos, int p) __attribute__((always_inline)) {
         constexpr int J = decltype(ring_pos)::value;
         const int tx = p - 2;
         const int tout = fw.out(tx);
         const bool emit = tx >= 0 && tout >= t0 && tout < t1;
         const bool xlive = tx >= 0 && tx < nin;
-        const bool ylive = p >= 1 && p - 1 < nin;
         // the epilogue's loads go first: they have the whole phase to arrive.
         // Both load groups are issued in every phase (on an empty range when
         // not needed) so that the memory-counter waits before each use allow
@@ -347,13 +394,13 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
         // buffers they read were written before the last barrier), issued
         // before the vector work of the phase so that they run beside it
         float4_t xa[XPW];
-        if (xlive) {
+        {
             const _Float16 *Y = Y0 + (tx & 1) * G::YBUF;
 #pragma unroll
             for (int i = 0; i < XPW; ++i) xa[i] = mfma_xblock_mma<G>(Y, wid * XPW + i, lane, thi, tlo);
         }
         float4_t ya[G::YPW];
-        if (ylive) {
+        {
             const _Float16 *U = U0 + ((p - 1) & 1) * G::UBUF;
 #pragma unroll
             for (int m = 0; m < G::YPW; ++m) {
@@ -366,45 +413,16 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
                 }
             }
         }
-        if (p < nin) {
-            _Float16 *U = U0 + (p & 1) * G::UBUF;
-#pragma unroll
-            for (int m = 0; m < IPS; ++m) {
-                const int it = stage_item<G, NTHR>(tid, m);
-                if (G::NITEM % NTHR == 0 || m < IPS - 1 || it < G::NITEM) {
-                    const int c = it % G::SC, g = it / G::SC;
-                    _Float16 *q = U + c * G::UP + 8 * g;
-                    if constexpr (EXACT) {
-                        u16x8_t h;  // the inputs' own bfloat16 bits
-#pragma unroll
-                        for (int j = 0; j < 8; ++j)
-                            h[j] = (unsigned short)(__float_as_uint(op.template input<NPF>(pf, 8 * m + j)) >> 16);
-                        *reinterpret_cast<u16x8_t *>(q) = h;
-                    } else {
-                        half8_t h, l;
-#pragma unroll
-                        for (int j = 0; j < 8; ++j) {
-                            _Float16 a, b;
-                            split_half(op.template input<NPF>(pf, 8 * m + j) * umul, a, b);
-                            h[j] = a;
-                            l[j] = b;
-                        }
-                        *reinterpret_cast<half8_t *>(q) = h;
-                        *reinterpret_cast<half8_t *>(q + G::UPL) = l;
-                    }
-                }
-            }
-        }
-        op.template fetch<NPF>(fw.in(p + 1), poff, pf, p + 1 < nin);
-        if (tx >= 0) {
+        stage(p);
+        {
             CT v[XPW][4];
 #pragma unroll
             for (int i = 0; i < XPW; ++i)
 #pragma unroll
-                for (int q = 0; q < 4; ++q) v[i][q] = xlive ? xa[i][q] : CT(0);
+                for (int q = 0; q < 4; ++q) v[i][q] = xa[i][q];
             ring_step<J, CT, RT, XPW, 4>(acc, v, tp, xlive, emit, tout, op, ooff, oraw, d1, d2);
         }
-        if (ylive) {
+        {
             _Float16 *Y = Y0 + ((p - 1) & 1) * G::YBUF;
 #pragma unroll
             for (int m = 0; m < G::YPW; ++m) {
