@@ -109,6 +109,31 @@ static bool gather_pays(const Variant &v, const stpi_problem *p) {
     return units <= 2 * device_cus() && p->T > 2 * v.RT;
 }
 
+// Relative duration of a step on one of the matrix-core tiles of a margin: the
+// phases of its slowest frame segment times the cost of a phase. A wide tile
+// (32 x 128 or 64 x 64, one workgroup per CU) counts 1 per phase. A 32 x 64 tile
+// (two per CU) has half the work in a phase and more halo: it wins while its
+// workgroups have a CU each, and is about even with the wide tile where two
+// share one, better while the chain's three volumes stay in the 256 MB
+// last-level cache and worse when the larger halo comes from HBM. Measured, us
+// per chain step, wide / 32 x 64: float, r = (8, 3): 21x233x347 27.8 / 19.8,
+// 32x240x432 27.8 / 26.7, 64x360x640 46.6 / 43.9, 64x480x854 90.6 / 96.4,
+// 96x480x854 130 / 146; bfloat16, r = (15, 5): 21x233x347 41.8 / 34.6,
+// 32x240x432 48.3 / 40.6, 16x480x854 36.3 / 42.1, 64x480x854 82.2 / 85.5.
+static double mfma_tile_cost(const Variant &v, const stpi_problem *p) {
+    const int nseg = segments_for(v, p);
+    const long units = (long)tiles_for(v, p) * nseg, cus = device_cus();
+    const int per_cu = v.blocks_per_cu();
+    const double rounds = std::ceil((double)units / (double)(cus * per_cu));
+    double phase = v.TH >= 64 ? 1.02 : 1.0;  // 64 x 64 behind 32 x 128 by 1 to 3% at every size measured
+    if (per_cu >= 2) {
+        const double bytes = 3.0 * p->T * p->H * p->W * (double)ops_for(p->dtype)->elem;
+        if (v.RS > 8) phase = units <= cus ? 0.84 : 1.04;
+        else phase = units <= cus ? 0.71 : bytes > 256.0 * 1024 * 1024 ? 1.06 : 0.95;
+    }
+    return segment_phases(p->T, v.RT, nseg) * rounds * phase;
+}
+
 const Variant *choose_variant(const stpi_problem *p, int forced_index, bool allow_mfma) {
     const DtypeOps *ops = ops_for(p->dtype);
     if (forced_index >= 0 && forced_index < ops->nvariants && !allow_mfma && ops->variants[forced_index].PIPE == 3)
@@ -140,7 +165,20 @@ const Variant *choose_variant(const stpi_problem *p, int forced_index, bool allo
             best = &v;
         }
     }
-    return best;
+    if (!best || best->PIPE != 3) return best;
+    // the tile among the matrix-core variants of the same radii
+    const Variant *tile = best;
+    double tile_cost = mfma_tile_cost(*best, p);
+    for (int i = 0; i < ops->nvariants; ++i) {
+        const Variant &v = ops->variants[i];
+        if (v.PIPE != 3 || v.RS != best->RS || v.RT != best->RT) continue;
+        const double c = mfma_tile_cost(v, p);
+        if (c < tile_cost) {
+            tile_cost = c;
+            tile = &v;
+        }
+    }
+    return tile;
 }
 
 int device_cus() {

@@ -602,3 +602,40 @@ def test_frame_segments_walk_both_ways(P, shape, kp):
                 assert err <= 2.0 ** -8 and worst <= 2.0 ** -7, (i, err, worst)
                 assert abs(r["lambda_"] - infob.lambdas[-1]) <= 2.0 ** -8 * infob.lambdas[-1]
     assert split, "no matrix-core variant split the frames of this shape"
+
+
+@pytest.mark.parametrize("dtype,kp,shape,tile", [
+    (torch.float32, (4.0, 1.5, 8, 3), (21, 233, 347), (32, 64)),    # every 32 x 64 workgroup has a CU
+    (torch.float32, (4.0, 1.5, 8, 3), (32, 480, 854), (32, 64)),    # two per CU, volumes in the last-level cache
+    (torch.float32, (4.0, 1.5, 8, 3), (64, 480, 854), (32, 128)),   # volumes beyond it
+    (torch.float32, (5.0, 2.0, 15, 5), (16, 480, 854), (32, 128)),
+    (torch.bfloat16, (5.0, 2.0, 15, 5), (21, 233, 347), (32, 64)),
+    (torch.bfloat16, (5.0, 2.0, 15, 5), (16, 480, 854), (32, 128)),  # two segments against one
+])
+def test_default_tile_among_the_matrix_core_variants(P, dtype, kp, shape, tile):
+    """The tile a chain takes by default, and that its result is the one of
+    every other tile of the same radii. The tiles differ in the order of the
+    global sums only (FP64), so in the scale of the iterate: two chains agree to
+    float rounding, and in bfloat16 storage to one unit of the last place."""
+    from paper_2212_08058_amd import _native as N
+    k = P.Kernel(*kp)
+    code = N.STPI_F32 if dtype == torch.float32 else N.STPI_BF16
+    info = (ctypes.c_int32 * 9)()
+    chosen = P.launch_shape(shape, k, dtype=dtype)["variant"]
+    assert N.lib.stpi_variant_info(code, chosen, info) == 0
+    assert info[8] == 3 and (info[2], info[3]) == tile
+    if shape[0] > 21:
+        return
+    g = torch.Generator(device=DEV).manual_seed(sum(shape))
+    f = torch.rand(shape, generator=g, device=DEV).to(dtype)
+    x, _ = P.power_iterate(f, k, iters=3)
+    for i, vi in mfma_variants(code):
+        if (vi[0], vi[1]) != (info[0], info[1]) or i == chosen:
+            continue
+        assert N.lib.stpi_set_variant(i) == 0
+        try:
+            y, _ = P.power_iterate(f, k, iters=3)
+        finally:
+            N.lib.stpi_set_variant(-1)
+        d = float((x.double() - y.double()).abs().max() / x.double().abs().max())
+        assert d <= (1e-6 if dtype == torch.float32 else 2.0 ** -7)
