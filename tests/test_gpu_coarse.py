@@ -133,3 +133,14 @@ def test_scale_kernel(P, dtype):
     assert np.array_equal(z.double().cpu().numpy(), ref)
     e = torch.empty(0, dtype=dtype, device=DEV)
     api.scale(e, 2.0)
+
+
+@pytest.mark.parametrize("dtype,tol", DTYPES)
+@pytest.mark.parametrize("shape,sy,st", [((2, 3, 256), 1, 1), ((3, 5, 257), 1, 2), ((2, 7, 515), 2, 1),
+                                         ((3, 4, 1030), 7, 3), ((1, 1, 1), 3, 2), ((5, 2, 300), 400, 9)])
+def test_upsample_rows_around_a_span(P, dtype, tol, shape, sy, st):
+    """Rows of one, two and more spans of 256 outputs, whole and not, and coarse
+    rows from one value per output to one for all. Two blends more or less in
+    another order: each rounds by half a unit of values below 1."""
+    test_upsample_matches_oracle(P, dtype, tol, 0, shape, sy, st)
+    test_upsample_matches_oracle(P, dtype, tol, 1, shape, sy, st)
