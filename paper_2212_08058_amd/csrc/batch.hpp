@@ -309,6 +309,24 @@ int batch_blocks_per_cu() {
 
 constexpr int BATCH_NORM_BLOCKS = 64;  // workgroups per clip in the per-clip reductions
 
+// Workgroups per clip in the streaming passes without partial results. The
+// longest clip ends last, so its elements need many workgroups, and each access
+// 16 bytes where the clip's arrays allow it: with 64 workgroups and single
+// elements the final pass over 48 clips took 2647 us (now 1420) and the bound
+// 1068 (442).
+constexpr int BATCH_STREAM_BLOCKS = 512;
+
+// whole(i) for every 16-byte chunk i of a clip's n elements, one(i) for every
+// element beyond them (all elements when ptrs, the or of the arrays' addresses,
+// is not a multiple of 16).
+template <class ST, class W, class O>
+__device__ __forceinline__ void stream_clip(size_t n, uintptr_t ptrs, W &&whole, O &&one) {
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+    const size_t nv = (ptrs & 15) == 0 ? n / (16 / sizeof(ST)) : 0;
+    for (size_t i = i0; i < nv; i += stride) whole(i);
+    for (size_t i = nv * (16 / sizeof(ST)) + i0; i < n; i += stride) one(i);
+}
+
 // Plain-form batch after a rejected warm start: the current buffer of every
 // clip marked for it <- 1 (the finalisation already set the uniform scale).
 template <class ST>
@@ -359,8 +377,16 @@ __global__ void batch_bound_kernel(const ST *f, const ClipDesc *clips, DevState 
     const ClipDesc cd = clips[blockIdx.y];
     const size_t n = (size_t)cd.T * cd.H * cd.W;
     float m = 0.f;
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += (size_t)gridDim.x * 256)
-        m = fmaxf(m, fabsf((float)ld(f + cd.offset + i)));
+    f += cd.offset;
+    stream_clip<ST>(
+        n, (uintptr_t)f,
+        [&](size_t i) {
+            Chunk16<ST> c;
+            c.u = reinterpret_cast<const uint4 *>(f)[i];
+#pragma unroll
+            for (int e = 0; e < 16 / (int)sizeof(ST); ++e) m = fmaxf(m, fabsf((float)ld(&c.e[e])));
+        },
+        [&](size_t i) { m = fmaxf(m, fabsf((float)ld(f + i))); });
 #pragma unroll
     for (int off = 32; off >= 1; off >>= 1) m = fmaxf(m, __shfl_xor(m, off, 64));
     if ((threadIdx.x & 63) == 0) red[threadIdx.x >> 6] = m;
@@ -381,11 +407,28 @@ __global__ void batch_to_product_kernel(const ST *f, const ST *x, ST *w, const C
     const CT g = (CT)ldexp(1.0, -2 * bound_exponent(__uint_as_float(s->ubound), PRODUCT_ELIM));
     const size_t n = (size_t)cd.T * cd.H * cd.W;
     float m = 0.f;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
-        const CT v = (ld(f + cd.offset + i) * ld(x + cd.offset + i)) * g;
-        st(w + cd.offset + i, v);
-        m = fmaxf(m, fabsf((float)stored_value(w + cd.offset + i, v)));
-    }
+    f += cd.offset;
+    x += cd.offset;
+    w += cd.offset;
+    stream_clip<ST>(
+        n, (uintptr_t)f | (uintptr_t)x | (uintptr_t)w,
+        [&](size_t i) {
+            Chunk16<ST> c, cx;
+            c.u = reinterpret_cast<const uint4 *>(f)[i];
+            cx.u = reinterpret_cast<const uint4 *>(x)[i];
+#pragma unroll
+            for (int e = 0; e < 16 / (int)sizeof(ST); ++e) {
+                const CT v = (ld(&c.e[e]) * ld(&cx.e[e])) * g;
+                m = fmaxf(m, fabsf((float)stored_value(&c.e[e], v)));
+                st(&c.e[e], v);
+            }
+            reinterpret_cast<uint4 *>(w)[i] = c.u;
+        },
+        [&](size_t i) {
+            const CT v = (ld(f + i) * ld(x + i)) * g;
+            st(w + i, v);
+            m = fmaxf(m, fabsf((float)stored_value(w + i, v)));
+        });
     m = block_max<256>(m, red);
     if (threadIdx.x == 0 && m > 0.f) atomicMax(&s->wmax[1], __float_as_uint(m));
     if (blockIdx.x == 0 && threadIdx.x == 0) {
@@ -402,18 +445,29 @@ __global__ void batch_from_product_kernel(ST *x, const ST *buf1, const ST *f, co
     const ClipDesc cd = clips[blockIdx.y];
     const DevState *s = states + blockIdx.y;
     const size_t n = (size_t)cd.T * cd.H * cd.W;
-    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+    f += cd.offset;
+    const ST *src = s->cur ? buf1 + cd.offset : x + cd.offset;
+    x += cd.offset;
     if (s->pform == 2) {
         const CT c = (CT)s->scale;
-        for (size_t i = i0; i < n; i += stride) st(x + cd.offset + i, c);
+        const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+        for (size_t i = i0; i < n; i += stride) st(x + i, c);
         return;
     }
-    const ST *src = (s->cur ? buf1 : x) + cd.offset;
     const double m = s->scale * ldexp(1.0, 2 * bound_exponent(__uint_as_float(s->ubound), PRODUCT_ELIM));
-    for (size_t i = i0; i < n; i += stride) {
-        const CT fv = ld(f + cd.offset + i);
-        st(x + cd.offset + i, fv != CT(0) ? (CT)((double)ld(src + i) / (double)fv * m) : CT(0));
-    }
+    auto value = [&](CT wv, CT fv) -> CT { return fv != CT(0) ? (CT)((double)wv / (double)fv * m) : CT(0); };
+    // each thread reads and writes the same chunk, so x may be src
+    stream_clip<ST>(
+        n, (uintptr_t)x | (uintptr_t)src | (uintptr_t)f,
+        [&](size_t i) {
+            Chunk16<ST> c, cf;
+            c.u = reinterpret_cast<const uint4 *>(src)[i];
+            cf.u = reinterpret_cast<const uint4 *>(f)[i];
+#pragma unroll
+            for (int e = 0; e < 16 / (int)sizeof(ST); ++e) st(&c.e[e], value(ld(&c.e[e]), ld(&cf.e[e])));
+            reinterpret_cast<uint4 *>(x)[i] = c.u;
+        },
+        [&](size_t i) { st(x + i, value(ld(src + i), ld(f + i))); });
 }
 
 // x[clip] <- scale_clip * (current iterate of the clip)
@@ -425,8 +479,17 @@ __global__ void batch_normalize_kernel(ST *x, const ST *buf1, const ClipDesc *cl
     const ST *src = (s->cur ? buf1 : x) + cd.offset;
     const CT scale = (CT)s->scale;
     const size_t n = (size_t)cd.T * cd.H * cd.W;
-    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-        st(x + cd.offset + i, scale * ld(src + i));
+    x += cd.offset;
+    stream_clip<ST>(
+        n, (uintptr_t)x | (uintptr_t)src,
+        [&](size_t i) {
+            Chunk16<ST> c;
+            c.u = reinterpret_cast<const uint4 *>(src)[i];
+#pragma unroll
+            for (int e = 0; e < 16 / (int)sizeof(ST); ++e) st(&c.e[e], scale * ld(&c.e[e]));
+            reinterpret_cast<uint4 *>(x)[i] = c.u;
+        },
+        [&](size_t i) { st(x + i, scale * ld(src + i)); });
 }
 
 }  // namespace stpi

@@ -146,25 +146,25 @@ hipError_t batch_sumsq_impl(const void *x, const ClipDesc *clips, int nclips, do
 }
 hipError_t batch_normalize_impl(void *x, const void *buf1, const ClipDesc *clips, const DevState *states, int nclips,
                                 hipStream_t s) {
-    hipLaunchKernelGGL(batch_normalize_kernel<ST_>, dim3(BATCH_NORM_BLOCKS, nclips), dim3(256), 0, s, (ST_ *)x,
+    hipLaunchKernelGGL(batch_normalize_kernel<ST_>, dim3(BATCH_STREAM_BLOCKS, nclips), dim3(256), 0, s, (ST_ *)x,
                        (const ST_ *)buf1, clips, states);
     return hipGetLastError();
 }
 
 hipError_t batch_bound_impl(const void *f, const ClipDesc *clips, DevState *states, int nclips, hipStream_t s) {
-    hipLaunchKernelGGL(batch_bound_kernel<ST_>, dim3(BATCH_NORM_BLOCKS, nclips), dim3(256), 0, s, (const ST_ *)f,
+    hipLaunchKernelGGL(batch_bound_kernel<ST_>, dim3(BATCH_STREAM_BLOCKS, nclips), dim3(256), 0, s, (const ST_ *)f,
                        clips, states);
     return hipGetLastError();
 }
 hipError_t batch_to_product_impl(const void *f, const void *x, void *buf1, const ClipDesc *clips, DevState *states,
                                  int nclips, hipStream_t s) {
-    hipLaunchKernelGGL(batch_to_product_kernel<ST_>, dim3(BATCH_NORM_BLOCKS, nclips), dim3(256), 0, s,
+    hipLaunchKernelGGL(batch_to_product_kernel<ST_>, dim3(BATCH_STREAM_BLOCKS, nclips), dim3(256), 0, s,
                        (const ST_ *)f, (const ST_ *)x, (ST_ *)buf1, clips, states);
     return hipGetLastError();
 }
 hipError_t batch_from_product_impl(void *x, const void *buf1, const void *f, const ClipDesc *clips,
                                    const DevState *states, int nclips, hipStream_t s) {
-    hipLaunchKernelGGL(batch_from_product_kernel<ST_>, dim3(BATCH_NORM_BLOCKS, nclips), dim3(256), 0, s, (ST_ *)x,
+    hipLaunchKernelGGL(batch_from_product_kernel<ST_>, dim3(BATCH_STREAM_BLOCKS, nclips), dim3(256), 0, s, (ST_ *)x,
                        (const ST_ *)buf1, (const ST_ *)f, clips, states);
     return hipGetLastError();
 }

@@ -981,10 +981,21 @@ __global__ __launch_bounds__(1024) void wgrad_reduce(int nblocks, const float *p
     }
 }
 
-// Start vector from the net output: x0 = max(y, 0) + eps (normalised by the iteration).
+// Start vector from the net output: x0 = max(y, 0) + eps (normalised by the
+// iteration), 16 bytes at a time where the arrays allow it (32x480x854 19 us,
+// 33 by single elements on a fixed 1024 workgroups).
 __global__ void warm_x0_kernel(size_t V, const float *y, float eps, float *x0) {
-    for (size_t v = (size_t)blockIdx.x * blockDim.x + threadIdx.x; v < V; v += (size_t)gridDim.x * blockDim.x)
-        x0[v] = fmaxf(y[v], 0.0f) + eps;
+    const size_t i0 = (size_t)blockIdx.x * blockDim.x + threadIdx.x, stride = (size_t)gridDim.x * blockDim.x;
+    const size_t nv = (((uintptr_t)y | (uintptr_t)x0) & 15) == 0 ? V / 4 : 0;
+    for (size_t i = i0; i < nv; i += stride) {
+        float4 v = reinterpret_cast<const float4 *>(y)[i];
+        v.x = fmaxf(v.x, 0.0f) + eps;
+        v.y = fmaxf(v.y, 0.0f) + eps;
+        v.z = fmaxf(v.z, 0.0f) + eps;
+        v.w = fmaxf(v.w, 0.0f) + eps;
+        reinterpret_cast<float4 *>(x0)[i] = v;
+    }
+    for (size_t v = 4 * nv + i0; v < V; v += stride) x0[v] = fmaxf(y[v], 0.0f) + eps;
 }
 
 constexpr int WG1_BLOCKS = 1024;  // x 4 wavefronts: wgrad1_kernel's partial sums (448 floats each)
@@ -1153,7 +1164,7 @@ int stpi_net_backward(const stpi_problem *p, const float *f, const void *prep, c
 int stpi_net_warm_start(int64_t n, const float *y, float eps, float *x0, void *stream) {
     clear_error();
     if (n < 1 || !y || !x0) return fail(STPI_EINVAL, "bad arguments");
-    hipLaunchKernelGGL(warm_x0_kernel, dim3(1024), dim3(256), 0, (hipStream_t)stream, (size_t)n, y, eps, x0);
+    hipLaunchKernelGGL(warm_x0_kernel, dim3(2048), dim3(256), 0, (hipStream_t)stream, (size_t)n, y, eps, x0);
     hipError_t e = hipGetLastError();
     return e == hipSuccess ? STPI_OK : hip_fail(e, "warm start");
 }

@@ -309,3 +309,26 @@ def test_batch_converged_clips_leave_the_tile_list(P):
         xo, ro = one.iterate(one.pack([torch.from_numpy(f).to(DEV)]), max_iters=300, tol=1e-4)
         assert ro[0]["iters"] == res[i]["iters"] and ro[0]["converged"] == res[i]["converged"]
         assert torch.equal(list(one.views(xo))[0], list(plan.views(x_flat))[i])
+
+
+@pytest.mark.parametrize("off", [0, 1])
+def test_streaming_passes_of_unaligned_volumes(P, off):
+    """The passes over whole clips (bound, start, final pass) take 16 bytes at a
+    time where they may: the same chain on volumes one element past a 16-byte
+    boundary, with clips whose sizes are no multiple of a chunk. The
+    passes work element by element either way, so the iterates are equal."""
+    Pm, B = P
+    kern = Pm.Kernel(4.0, 1.5, 8, 3)
+    plan = B.BatchPlan(SHAPES, kern)
+    fs = [torch.from_numpy(f).to(DEV) for f in _clips(SHAPES, 3)]
+    ref, _ = plan.iterate(plan.pack(fs), max_iters=4, tol=0.0)
+    start = plan.pack([f + 0.25 for f in fs])
+    ref0, _ = plan.iterate(plan.pack(fs), x_flat=start.clone(), init=0, max_iters=4, tol=0.0)
+    buf = [torch.zeros(plan.extent + off, device=DEV)[off:] for _ in range(3)]
+    plan.pack(fs, out=buf[0])
+    got, _ = plan.iterate(buf[0], x_flat=buf[1], max_iters=4, tol=0.0)
+    buf[2].copy_(start)
+    got0, _ = plan.iterate(buf[0], x_flat=buf[2], init=0, max_iters=4, tol=0.0)
+    for a, b in ((ref, got), (ref0, got0)):
+        for u, v in zip(plan.views(a), plan.views(b)):
+            assert torch.equal(u, v)
