@@ -435,25 +435,22 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
             const int it = tid + m * NTHR;
             if (S::NITEM % NTHR == 0 || m < IPS - 1 || it < S::NITEM) {
                 _Float16 *q = U + (it % G::SC) * G::UP + 4 * (it / G::SC);
-                float4_t u1, u2, u3;
+                uint2 h[3], l[3];  // the three fields: w, w f^2, w f
 #pragma unroll
-                for (int j = 0; j < 4; ++j) {
-                    const int k = 4 * m + j;
-                    const float fs = pf[k] * fmul;
-                    u1[j] = (ps[k] * px[k]) * umul;
-                    u3[j] = fs * u1[j];
-                    u2[j] = fs * u3[j];
+                for (int j = 0; j < 2; ++j) {
+                    const int k = 4 * m + 2 * j;
+                    const float w0 = ps[k] * px[k], w1 = ps[k + 1] * px[k + 1];
+                    const float u0 = w0 * umul, u1 = w1 * umul;
+                    const float f0 = pf[k] * fmul, f1 = pf[k + 1] * fmul;
+                    split_scaled2(w0, umul, w1, umul, (&h[0].x)[j], (&l[0].x)[j]);
+                    split_scaled2(u0, f0, u1, f1, (&h[2].x)[j], (&l[2].x)[j]);
+                    split_scaled2(f0 * u0, f0, f1 * u1, f1, (&h[1].x)[j], (&l[1].x)[j]);
                 }
-                half4_t h, l;
-                split4(u1, h, l, one);
-                *reinterpret_cast<half4_t *>(q) = h;
-                *reinterpret_cast<half4_t *>(q + G::UPL) = l;
-                split4(u2, h, l, one);
-                *reinterpret_cast<half4_t *>(q + S::UF) = h;
-                *reinterpret_cast<half4_t *>(q + S::UF + G::UPL) = l;
-                split4(u3, h, l, one);
-                *reinterpret_cast<half4_t *>(q + 2 * S::UF) = h;
-                *reinterpret_cast<half4_t *>(q + 2 * S::UF + G::UPL) = l;
+#pragma unroll
+                for (int c = 0; c < 3; ++c) {
+                    *reinterpret_cast<uint2 *>(q + c * S::UF) = h[c];
+                    *reinterpret_cast<uint2 *>(q + c * S::UF + G::UPL) = l[c];
+                }
             }
         }
     };
@@ -490,14 +487,11 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
         IO::load4(make_rsrc(a.f + to, ob), ooff, of);
         IO::load4(make_rsrc(src + to, a.no_prev ? 0u : ob), ooff, ox);
         float4_t v[3];
-        if (k < nin) {
+        // without branches, as the single-field loop: past the last input frame
+        // the loads return 0, and with them the staged fields and the products
 #pragma unroll
-            for (int m = 0; m < 3; ++m) v[m] = mfma_xblock_mma<G>(Y + m * S::YF, wid, lane, thi, tlo);
-        } else {
-#pragma unroll
-            for (int m = 0; m < 3; ++m) v[m] = float4_t{0.f, 0.f, 0.f, 0.f};
-        }
-        if (k + 1 < nin) stage();
+        for (int m = 0; m < 3; ++m) v[m] = mfma_xblock_mma<G>(Y + m * S::YF, wid, lane, thi, tlo);
+        stage();
         fetch(fw.in(k + 2), k + 2 < nin);
         // fma3 is inline assembly, for which the compiler inserts no wait states
         // after the products that made v
@@ -533,7 +527,7 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
             }
         }
         __syncthreads();
-        if (k + 1 < nin) ypass();
+        ypass();
         __syncthreads();
     }
     block_reduce<NTHR>(d1, d2, wm, red);

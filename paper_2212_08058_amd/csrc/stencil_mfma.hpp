@@ -136,15 +136,15 @@ __device__ __forceinline__ void split_half(float v, _Float16 &hi, _Float16 &lo) 
     lo = (_Float16)(v - (float)hi);
 }
 
-// Two products a m and b m as packed half-precision hi and lo parts: hi =
-// fp16(a m), lo = fp16(a m - hi), each rounded once from the exact product by a
+// Two products a ma and b mb as packed half-precision hi and lo parts: hi =
+// fp16(a ma), lo = fp16(a ma - hi), each rounded once from the exact product by a
 // mixed-precision fma that writes its half of the word (two instructions per
 // value; the plain form took 3.5 and could round hi in two steps).
-__device__ __forceinline__ void split_scaled2(float a, float b, float m, uint32_t &hi, uint32_t &lo) {
-    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(a), "v"(m));
-    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(b), "v"(m));
-    asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(a), "v"(m), "v"(hi));
-    asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(b), "v"(m), "v"(hi));
+__device__ __forceinline__ void split_scaled2(float a, float ma, float b, float mb, uint32_t &hi, uint32_t &lo) {
+    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(a), "v"(ma));
+    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(b), "v"(mb));
+    asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(a), "v"(ma), "v"(hi));
+    asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(b), "v"(mb), "v"(hi));
 }
 
 // Launders a constant so the compiler keeps it as an operand (fma(x, 1, y)
@@ -370,7 +370,7 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
                     uint32_t *hp = &h.x, *lp = &l.x;
 #pragma unroll
                     for (int j = 0; j < 4; ++j)
-                        split_scaled2(op.template input<NPF>(pf, 8 * m + 2 * j),
+                        split_scaled2(op.template input<NPF>(pf, 8 * m + 2 * j), umul,
                                       op.template input<NPF>(pf, 8 * m + 2 * j + 1), umul, hp[j], lp[j]);
                     *reinterpret_cast<uint4 *>(q) = h;
                     *reinterpret_cast<uint4 *>(q + G::UPL) = l;
