@@ -209,19 +209,23 @@ int segment_phases(int T, int RT, int k) {
     return worst;
 }
 
-// A tile that the rules below leave whole: when every segment can have a CU
-// of its own, the step takes as long as its slowest segment, so split the
-// frames where that lowers the phase count (a whole tile ends with RT
-// epilogue-only phases that a split with a backward last segment avoids;
-// short clips, e.g. the windows of an online run, gain most).
-int split_short_tiles(int tiles, int T, int RT) {
+// Segments per tile beyond the `from` that the rules below give: while every
+// segment can have a CU of its own, the step takes as long as its slowest
+// segment, so the frames are split further where that lowers the phase count (a
+// whole tile also ends with RT epilogue-only phases that a split with a backward
+// last segment avoids; short clips, e.g. the windows of an online run, gain
+// most). What the added segments re-stage runs on CUs that were idle. Measured,
+// us per chain step before / after: float r = (15, 5) 24x90x108 45.3 / 34.7 (1
+// segment / 4), 32x240x432 52.0 / 38.5 (3 / 8), 96x270x480 81.3 / 60.4 (4 / 7),
+// 64x360x640 75.2 / 65.0 (3 / 4); r = (8, 3) 21x233x347 19.8 / 18.5 (3 / 4),
+// 96x270x480 54.0 / 42.5 (4 / 7); bfloat16 r = (15, 5) 32x240x432 40.5 / 36.0.
+int split_short_tiles(int tiles, int T, int RT, int from) {
     const int cus = device_cus();
-    if (2L * tiles > cus) return 1;
     const int kmax = std::min(std::min(cus / tiles, STPI_NSEG_MAX), T);
     // more segments only for at least two phases fewer (each adds a
     // workgroup that re-stages RT frames)
-    int best = 1;
-    for (int k = 2; k <= kmax; ++k)
+    int best = from;
+    for (int k = from + 1; k <= kmax; ++k)
         if (segment_phases(T, RT, k) + 1 < segment_phases(T, RT, best)) best = k;
     return best;
 }
@@ -247,8 +251,7 @@ int segments_for(const Variant &v, const stpi_problem *p) {
         const int small = std::min(std::min(fit, p->T / (2 * rt)), STPI_NSEG_MAX);
         if (small > nseg) nseg = small;
     }
-    if (nseg == 1) nseg = split_short_tiles(tiles, p->T, v.RT);
-    return nseg;
+    return split_short_tiles(tiles, p->T, v.RT, nseg);
 }
 
 int grid_blocks(const Variant &v, const stpi_problem *p) { return tiles_for(v, p) * segments_for(v, p); }

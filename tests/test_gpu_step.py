@@ -516,3 +516,21 @@ def test_single_frame_workgroups(P, dtype, shape, kp):
             assert torch.equal(x, x2) and r["residual"] == r2["residual"] and r["r1"] == r2["r1"]
     finally:
         N.lib.stpi_set_variant(-1)
+
+
+@pytest.mark.parametrize("kp", [(5.0, 2.0, 15, 5), (4.0, 1.5, 8, 3)])
+@pytest.mark.parametrize("shape", [(11, 20, 30), (24, 30, 140), (5, 33, 70), (2, 17, 9)])
+def test_segments_on_idle_compute_units(P, kp, shape):
+    """Clips of few tiles are cut into segments shorter than the temporal
+    radius: three iterations against the FP64 oracle, at the suite's float bar
+    of 1e-5 per step."""
+    k = P.Kernel(*kp)
+    d = P.launch_shape(shape, k)
+    assert shape[0] < 10 or d["segments"] > max(1, shape[0] // (4 * kp[3]))
+    rng = np.random.default_rng(sum(shape))
+    f = rng.uniform(0.0, 1.0, shape).astype(np.float32)
+    x, r = P.power_iterate(torch.from_numpy(f).to("cuda:0"), k, iters=3)
+    ref, info = oracle.iterate(f, oracle.Kernel(float(np.float32(kp[0])), float(np.float32(kp[1])), kp[2], kp[3]),
+                               iters=3)
+    err = np.linalg.norm(x.double().cpu().numpy() - ref) / np.linalg.norm(ref)
+    assert err <= 1e-5 and abs(r["lambda_"] - info.lambdas[-1]) <= 1e-5 * info.lambdas[-1]
