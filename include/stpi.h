@@ -284,7 +284,7 @@ int stpi_time_step(const stpi_problem *p, const void *f, const void *x, void *z,
                    int variant, int reps, void *stream, double *avg_ms);
 
 /* Average duration in milliseconds of one step of an iteration chain, as
- * stpi_iterate runs it (the step kernel with its fused finalisation; on a
+ * stpi_iterate runs it (the step kernel, which also finalises the step before; on a
  * matrix-core variant the product form, see stpi_iterate), measured with HIP
  * events on `stream` around `reps` back-to-back steps of a fixed-count chain
  * from the uniform start (steps 2 .. reps + 1 of a chain of reps + 2, so all

@@ -100,13 +100,16 @@ static int tiles_for(const Variant &v, const stpi_problem *p) {
 // (4, 2), chain step in us, streamed / 8 x 32 / 16 x 64 tile: 8x64x112 10.3 / 5.8 /
 // 6.7 (256 and 64 workgroups), 64x48x64 15.4 / 7.5 / 6.4 (768, 192), 16x120x214
 // 12.3 / 12.6 / 9.0 (1680, 512), 32x120x214 13.1 / 18.7 / 12.1 (3360, 1024),
-// 2x480x854 9.1 / 18.0 / 11.2 (3240, 840). So: the small tile while every
-// workgroup has a CU of its own, the large one up to two per CU on clips longer
-// than the temporal window.
+// 2x480x854 9.1 / 18.0 / 11.2 (3240, 840); streamed / 16 x 64: 8x240x432 11.3 /
+// 12.3 (840), 12x200x300 12.2 / 11.9 (780), 24x120x216 12.4 / 10.5 (768),
+// 128x64x112 23.2 / 11.1 (1024), 10x230x432 12.0 / 14.8 (1050). So: the small
+// tile while every workgroup has a CU of its own, the large one up to two per CU
+// on clips longer than the temporal window and up to four per CU on clips of
+// more than twice that.
 static bool gather_pays(const Variant &v, const stpi_problem *p) {
     const int64_t units = (int64_t)tiles_for(v, p) * p->T;
     if (v.TH * v.TW <= 256) return units <= device_cus();
-    return units <= 2 * device_cus() && p->T > 2 * v.RT;
+    return (units <= 2 * device_cus() && p->T > 2 * v.RT) || (units <= 4 * device_cus() && p->T > 4 * v.RT);
 }
 
 // Relative duration of a step on one of the matrix-core tiles of a margin: the

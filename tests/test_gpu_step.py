@@ -534,3 +534,31 @@ def test_segments_on_idle_compute_units(P, kp, shape):
                                iters=3)
     err = np.linalg.norm(x.double().cpu().numpy() - ref) / np.linalg.norm(ref)
     assert err <= 1e-5 and abs(r["lambda_"] - info.lambdas[-1]) <= 1e-5 * info.lambdas[-1]
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float64])
+@pytest.mark.parametrize("shape,gather", [((128, 64, 112), True), ((12, 16, 64 * 64), True), ((9, 16, 7230), True),
+                                          ((8, 16, 64 * 80), False), ((9, 16, 64 * 115), False)])
+def test_gather_on_up_to_four_workgroups_per_cu(P, dtype, shape, gather):
+    """The loop that a small volume takes by itself on either side of 4 x 256
+    tiles and frames and of twice the temporal window: four iterations agree
+    with the streamed loop of the same tile (another order of the temporal and
+    global sums: four steps of the suite's step tolerance)."""
+    import ctypes
+    from paper_2212_08058_amd import _native as N
+    code = {torch.float32: N.STPI_F32, torch.bfloat16: N.STPI_BF16, torch.float64: N.STPI_F64}[dtype]
+    kern = P.Kernel(2.0, 1.0, 4, 2)
+    info = (ctypes.c_int * 9)()
+    assert N.lib.stpi_variant_info(code, P.launch_shape(shape, kern, dtype=dtype)["variant"], info) == 0
+    assert (info[8] == 4) == gather
+    streamed = next(i for i in range(N.lib.stpi_variant_count(code))
+                    if N.lib.stpi_variant_info(code, i, info) == 0 and info[8] == 0 and (info[0], info[1]) == (4, 2))
+    fd = to_dev(np.random.default_rng(sum(shape)).uniform(0.05, 1.0, shape), dtype)
+    x, r = P.power_iterate(fd, kern, iters=4)
+    try:
+        assert N.lib.stpi_set_variant(streamed) == 0
+        y, q = P.power_iterate(fd, kern, iters=4)
+    finally:
+        N.lib.stpi_set_variant(-1)
+    assert rel_l2(x.double().cpu().numpy(), y.double().cpu().numpy()) <= 4 * TOL[dtype]
+    assert abs(r["lambda_"] - q["lambda_"]) <= 4 * TOL[dtype] * q["lambda_"]
