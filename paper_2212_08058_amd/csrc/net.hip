@@ -221,45 +221,44 @@ __global__ __launch_bounds__(256) void one_channel_kernel(Dims d, const float *f
         s0[m] = ok && (unsigned)gx < (unsigned)d.W ? (uint32_t)(gy * d.W + gx) * 4 : OOB_OFF;
         s1[m] = ok && (unsigned)(gx + 1) < (unsigned)d.W ? (uint32_t)(gy * d.W + gx + 1) * 4 : OOB_OFF;
     }
-    float e0[NST], e1[NST];
-    auto fetch = [&](int t) __attribute__((always_inline)) {
+    float e0[3][NST], e1[3][NST];  // up to three frames' loads in flight
+    auto fetch = [&](int t, int slot) __attribute__((always_inline)) {
         const bool ok = t >= 0 && t < d.T;
         const size_t plane = (size_t)d.H * d.W;
         const auto r = __builtin_amdgcn_make_buffer_rsrc(const_cast<float *>(f + (ok ? t : 0) * plane), (short)0,
                                                          ok ? (int)(plane * sizeof(float)) : 0, 0x00020000);
 #pragma unroll
         for (int m = 0; m < NST; ++m) {
-            e0[m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, s0[m], 0, 0));
-            e1[m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, s1[m], 0, 0));
+            e0[slot][m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, s0[m], 0, 0));
+            e1[slot][m] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(r, s1[m], 0, 0));
         }
     };
-    auto stage = [&](int t) __attribute__((always_inline)) {
+    auto stage = [&](int t, int slot) __attribute__((always_inline)) {
         uint32_t *q = lds + (t & 3) * PARTS * CT_V;
 #pragma unroll
         for (int m = 0; m < NST; ++m) {
             const int v = tid + 256 * m;
             if (CT_V % 256 == 0 || m < NST - 1 || v < CT_V) {
-                float a = e0[m], b = e1[m];
+                float a = e0[slot][m], b = e1[slot][m];
 #pragma unroll
                 for (int k = 0; k < PARTS; ++k) {
-                    const uint32_t w = f32x2_to_bf16x2_bits(a, b);
-                    q[k * CT_V + v] = w;
-                    a -= __uint_as_float(w << 16);  // exact remainder
-                    b -= __uint_as_float(w & 0xffff0000u);
+                    const uint32_t h = f32x2_to_bf16x2_bits(a, b);
+                    q[k * CT_V + v] = h;
+                    a -= __uint_as_float(h << 16);  // exact remainder
+                    b -= __uint_as_float(h & 0xffff0000u);
                 }
             }
         }
     };
     const int x = u.x0 + c0 + n;
 #pragma unroll
-    for (int k = -1; k <= 1; ++k) {
-        fetch(u.t0 + k);
-        stage(u.t0 + k);
-    }
+    for (int k = 0; k < 3; ++k) fetch(u.t0 - 1 + k, k);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) stage(u.t0 - 1 + k, k);
     __syncthreads();
     for (int t = u.t0; t < u.t1; ++t) {
         const bool more = t + 1 < u.t1;
-        if (more) fetch(t + 2);
+        if (more) fetch(t + 2, 0);
         bf16x4 mk[MODE == 0 ? 1 : 8];  // the mask of the step's outputs, in flight beside the products
         if constexpr (MODE == 1) {
 #pragma unroll
@@ -308,7 +307,7 @@ __global__ __launch_bounds__(256) void one_channel_kernel(Dims d, const float *f
             }
             *reinterpret_cast<bf16x4 *>(out + v * C + 4 * kq) = o;
         }
-        if (more) stage(t + 2);
+        if (more) stage(t + 2, 0);
         __syncthreads();
     }
 }
@@ -338,7 +337,7 @@ constexpr int CV_FRAME = 2 * CV_PLANE;
 constexpr int CV_ROWS = 8;             // output rows per wavefront
 
 template <int MODE>
-__global__ __launch_bounds__(256, 2) void conv16_kernel(Dims d, const short *in, const bf16x4 (*A)[64],
+__global__ __launch_bounds__(256, MODE == 0 ? 4 : 2) void conv16_kernel(Dims d, const short *in, const bf16x4 (*A)[64],
                                                         const float *bias, const short *mask, short *out, int nseg) {
     __shared__ __align__(16) short lds[4 * CV_FRAME];
     TileUnit u;
@@ -386,19 +385,19 @@ __global__ __launch_bounds__(256, 2) void conv16_kernel(Dims d, const short *in,
         const bool ok = it < NIT && (unsigned)gy < (unsigned)d.H && (unsigned)gx < (unsigned)d.W;
         soff[m] = ok ? (uint32_t)(gy * d.W + gx) * (C * 2) + 16 * (it & 1) : OOB_OFF;
     }
-    uint4 st[NST];
-    auto fetch = [&](int t) __attribute__((always_inline)) {
+    uint4 st[3][NST];  // up to three frames' loads in flight
+    auto fetch = [&](int t, int slot) __attribute__((always_inline)) {
         const auto r = frame_rsrc(in, d, t);
 #pragma unroll
-        for (int m = 0; m < NST; ++m) st[m] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, soff[m], 0, 0));
+        for (int m = 0; m < NST; ++m) st[slot][m] = __builtin_bit_cast(uint4, __builtin_amdgcn_raw_buffer_load_b128(r, soff[m], 0, 0));
     };
-    auto stage = [&](int t) __attribute__((always_inline)) {
+    auto stage = [&](int t, int slot) __attribute__((always_inline)) {
         short *f = lds + (t & 3) * CV_FRAME;
 #pragma unroll
         for (int m = 0; m < NST; ++m) {
             const int it = tid + 256 * m;
             if (NIT % 256 == 0 || m < NST - 1 || it < NIT)
-                *reinterpret_cast<uint4 *>(f + (it & 1) * CV_PLANE + (it >> 1) * 8) = st[m];
+                *reinterpret_cast<uint4 *>(f + (it & 1) * CV_PLANE + (it >> 1) * 8) = st[slot][m];
         }
     };
     const int r0 = CV_ROWS * (wid >> 1), c0 = 16 * (wid & 1);  // the wavefront's rows and columns of the tile
@@ -413,14 +412,13 @@ __global__ __launch_bounds__(256, 2) void conv16_kernel(Dims d, const short *in,
     const int off1 = (kq / 2) * CV_PLANE + (r0 * CT_C + c0 + n) * 8 + 4 * (kq % 2);
     const int x = u.x0 + c0 + n;
 #pragma unroll
-    for (int k = -1; k <= 1; ++k) {
-        fetch(u.t0 + k);
-        stage(u.t0 + k);
-    }
+    for (int k = 0; k < 3; ++k) fetch(u.t0 - 1 + k, k);
+#pragma unroll
+    for (int k = 0; k < 3; ++k) stage(u.t0 - 1 + k, k);
     __syncthreads();
     for (int t = u.t0; t < u.t1; ++t) {
         const bool more = t + 1 < u.t1;
-        if (more) fetch(t + 2);
+        if (more) fetch(t + 2, 0);
         bf16x4 mk[MODE == 0 ? 1 : CV_ROWS];  // the mask of the step's outputs, in flight beside the products
         if constexpr (MODE == 1) {
 #pragma unroll
@@ -498,7 +496,7 @@ __global__ __launch_bounds__(256, 2) void conv16_kernel(Dims d, const short *in,
             }
             *reinterpret_cast<bf16x4 *>(out + v * C + 4 * kq) = o;
         }
-        if (more) stage(t + 2);
+        if (more) stage(t + 2, 0);
         __syncthreads();
     }
 }
@@ -719,39 +717,38 @@ __global__ __launch_bounds__(256, 2) void wgrad16_kernel(Dims d, const short *a,
         const int strip = r / d.H, ys = r - strip * d.H;
         const int t = strip / nxc, X0 = (strip - t * nxc) * WG_XC;
         const int ye = ys + (rend - r) < d.H ? ys + (rend - r) : d.H;
-        Block4x8 blk;
-        short edge = 0;
+        Block4x8 blk[3];  // up to three rows' loads in flight
+        short edge[3] = {0, 0, 0};
         // loads of row ya of a (three frames) and row yg of g
-        auto load_rows = [&](int ya, int yg) __attribute__((always_inline)) {
+        auto load_rows = [&](int ya, int yg, int slot) __attribute__((always_inline)) {
             const int tt = wid < 3 ? t + wid - 1 : t, yy = wid < 3 ? ya : yg;
             const bool ok = tt >= 0 && tt < d.T && yy >= 0 && yy < d.H;
             const uint32_t row = (uint32_t)(((size_t)(ok ? tt : 0) * d.H + (ok ? yy : 0)) * d.W) * (C * 2);
-            load_block(blk, wid < 3 ? ra : rg, ok, row, X0 + bx, d.W, half);
+            load_block(blk[slot], wid < 3 ? ra : rg, ok, row, X0 + bx, d.W, half);
             if (wid == 3) {  // the strip's neighbours of g: lanes 0 .. 15 x - 1, 16 .. 31 x + WG_XC
                 const int xe = lane < 16 ? X0 - 1 : X0 + WG_XC;
-                edge = load_b16(rg, ok && lane < 32 && xe >= 0 && xe < d.W ? row + (uint32_t)xe * (C * 2) + 2 * ch
-                                                                          : OOB_OFF);
+                edge[slot] = load_b16(rg, ok && lane < 32 && xe >= 0 && xe < d.W ? row + (uint32_t)xe * (C * 2) + 2 * ch
+                                                                            : OOB_OFF);
             }
         };
-        auto store_rows = [&](int ya, int yg) __attribute__((always_inline)) {
+        auto store_rows = [&](int ya, int yg, int slot) __attribute__((always_inline)) {
             if (wid < 3) {
-                store_block(blk, La + (wid * 4 + (ya & 3)) * WG_ROW_A + bx, WG_AP, half);
+                store_block(blk[slot], La + (wid * 4 + (ya & 3)) * WG_ROW_A + bx, WG_AP, half);
             } else {
                 short *dst = Lg + (yg & 1) * WG_ROW_G;
-                store_block(blk, dst + WG_GO + bx, WG_GP, half);
-                if (lane < 32) dst[ch * WG_GP + (lane < 16 ? WG_GO - 1 : WG_GO + WG_XC)] = edge;
+                store_block(blk[slot], dst + WG_GO + bx, WG_GP, half);
+                if (lane < 32) dst[ch * WG_GP + (lane < 16 ? WG_GO - 1 : WG_GO + WG_XC)] = edge[slot];
             }
         };
         // rows ys - 1, ys, ys + 1 of a and row ys of g (rows of g outside the range are never read)
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            load_rows(ys - 1 + k, ys);
-            store_rows(ys - 1 + k, ys);
-        }
+        for (int k = 0; k < 3; ++k) load_rows(ys - 1 + k, ys, k);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) store_rows(ys - 1 + k, ys, k);
         __syncthreads();
         for (int y = ys; y < ye; ++y) {
             const bool more = y + 1 < ye;
-            if (more) load_rows(y + 2, y + 1);
+            if (more) load_rows(y + 2, y + 1, 0);
             if (X0 + 32 * wid < d.W) {
                 const short *gp = Lg + (y & 1) * WG_ROW_G + ch * WG_GP + WG_GO + 32 * wid + 8 * kv;
                 const uint4 m = *reinterpret_cast<const uint4 *>(gp);
@@ -771,7 +768,7 @@ __global__ __launch_bounds__(256, 2) void wgrad16_kernel(Dims d, const short *a,
                             __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf[dx], af, acc[3 * k + dx], 0, 0, 0);
                 }
             }
-            if (more) store_rows(y + 2, y + 1);
+            if (more) store_rows(y + 2, y + 1, 0);
             __syncthreads();
         }
         r += ye - ys;
@@ -852,34 +849,34 @@ __global__ __launch_bounds__(256) void wgrad1_kernel(Dims d, const short *x16, c
         const int strip = r / d.H, ys = r - strip * d.H;
         const int t = strip / nxc, X0 = (strip - t * nxc) * WG_XC;
         const int ye = ys + (rend - r) < d.H ? ys + (rend - r) : d.H;
-        Block4x8 blk;
-        float z[3];
+        Block4x8 blk[3];  // up to three rows' loads in flight
+        float z[3][3];
         // wavefront 0 stages a row of X, wavefronts 1 .. 3 a row of Z of the
         // frames t - 1 .. t + 1 (columns X0 - 1 .. X0 + WG_XC)
-        auto load_rows = [&](int yx, int yz) __attribute__((always_inline)) {
+        auto load_rows = [&](int yx, int yz, int slot) __attribute__((always_inline)) {
             const int tt = wid == 0 ? t : t + wid - 2, yy = wid == 0 ? yx : yz;
             const bool ok = tt >= 0 && tt < d.T && yy >= 0 && yy < d.H;
             const size_t row = ((size_t)(ok ? tt : 0) * d.H + (ok ? yy : 0)) * d.W;
             if (wid == 0) {
-                load_block(blk, rx, ok, (uint32_t)row * (C * 2), X0 + 4 * (lane >> 1), d.W, lane & 1);
+                load_block(blk[slot], rx, ok, (uint32_t)row * (C * 2), X0 + 4 * (lane >> 1), d.W, lane & 1);
             } else {
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
                     const int e = lane + 64 * k, xe = X0 - 1 + e;
-                    z[k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                    z[slot][k] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
                         rz, ok && e < WG_XC + 2 && xe >= 0 && xe < d.W ? (uint32_t)(row + xe) * 4 : OOB_OFF, 0, 0));
                 }
             }
         };
-        auto store_rows = [&](int yx, int yz) __attribute__((always_inline)) {
+        auto store_rows = [&](int yx, int yz, int slot) __attribute__((always_inline)) {
             if (wid == 0) {
-                store_block(blk, Lx + (yx & 1) * WG_ROW_A + 4 * (lane >> 1), WG_AP, lane & 1);
+                store_block(blk[slot], Lx + (yx & 1) * WG_ROW_A + 4 * (lane >> 1), WG_AP, lane & 1);
             } else {
                 short *dst = Lz + ((wid - 1) * 4 + (yz & 3)) * WG_AP;
 #pragma unroll
                 for (int k = 0; k < 3; ++k) {
                     const int e = lane + 64 * k;  // column X0 - 1 + e: index e - s of the plane shifted by s - 1
-                    float rest = z[k];
+                    float rest = z[slot][k];
 #pragma unroll
                     for (int q = 0; q < PARTS; ++q) {
                         const short b = bfbits(rest);
@@ -892,14 +889,13 @@ __global__ __launch_bounds__(256) void wgrad1_kernel(Dims d, const short *x16, c
             }
         };
 #pragma unroll
-        for (int k = 0; k < 3; ++k) {
-            load_rows(ys, ys - 1 + k);
-            store_rows(ys, ys - 1 + k);
-        }
+        for (int k = 0; k < 3; ++k) load_rows(ys, ys - 1 + k, k);
+#pragma unroll
+        for (int k = 0; k < 3; ++k) store_rows(ys, ys - 1 + k, k);
         __syncthreads();
         for (int y = ys; y < ye; ++y) {
             const bool more = y + 1 < ye;
-            if (more) load_rows(y + 1, y + 2);
+            if (more) load_rows(y + 1, y + 2, 0);
             if (X0 + 32 * wid < d.W) {
                 const bf16v8 xf =
                     *reinterpret_cast<const bf16v8 *>(Lx + (y & 1) * WG_ROW_A + c * WG_AP + 32 * wid + 8 * kv);
@@ -918,7 +914,7 @@ __global__ __launch_bounds__(256) void wgrad1_kernel(Dims d, const short *x16, c
                         bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_frag(), zf[0], bacc, 0, 0, 0);
                 }
             }
-            if (more) store_rows(y + 1, y + 2);
+            if (more) store_rows(y + 1, y + 2, 0);
             __syncthreads();
         }
         r += ye - ys;
@@ -1092,10 +1088,12 @@ static int tile_segments(const stpi_problem *p) {
 
 // Workgroups of a weight-gradient launch: as many as fit at once (two per CU
 // of wgrad16_kernel, four of wgrad1_kernel), and at least six row steps each (a
-// share starts by staging three rows).
+// share starts by staging three rows), or two where not every CU would have one
+// (4x64x80: wgrad16 22.7 -> 18.7 us, wgrad1 12.3 -> 6.5 and 8.6 -> 4.7, with
+// the first three rows' loads in flight together).
 static int wgrad_units(const stpi_problem *p, int most) {
     const int64_t rows = (int64_t)p->T * ((p->W + WG_XC - 1) / WG_XC) * p->H;
-    return (int)std::min<int64_t>(most, std::max<int64_t>(1, rows / 6));
+    return (int)std::min<int64_t>(most, std::max<int64_t>(1, std::max(rows / 6, std::min<int64_t>(rows / 2, device_cus()))));
 }
 
 int stpi_net_forward(const stpi_problem *p, const float *f, const void *prep, float *y, void *ws, size_t ws_bytes,
