@@ -137,7 +137,13 @@ static double mfma_tile_cost(const Variant &v, const stpi_problem *p) {
     return segment_phases(p->T, v.RT, nseg) * rounds * phase;
 }
 
-const Variant *choose_variant(const stpi_problem *p, int forced_index, bool allow_mfma) {
+// tape: a step of a differentiated pass. It runs on the vector units and keeps
+// one order of its float sums at every size (streamed frames, base_segments):
+// small gradients that are differences of large sums, such as the bias's, move by
+// their own rounding with that order, more than float gradients of the same
+// problem should between two sizes' paths.
+const Variant *choose_variant(const stpi_problem *p, int forced_index, bool tape) {
+    const bool allow_mfma = !tape;
     const DtypeOps *ops = ops_for(p->dtype);
     if (forced_index >= 0 && forced_index < ops->nvariants && !allow_mfma && ops->variants[forced_index].PIPE == 3)
         forced_index = -1;
@@ -150,7 +156,7 @@ const Variant *choose_variant(const stpi_problem *p, int forced_index, bool allo
     int tuned = tuned_variant(p);
     if (tuned >= 0 && tuned < ops->nvariants) {
         const Variant &v = ops->variants[tuned];
-        if (v.RS >= p->r_s && v.RT >= p->r_t && (allow_mfma || v.PIPE != 3)) return &v;
+        if (v.RS >= p->r_s && v.RT >= p->r_t && (!tape || v.PIPE < 3)) return &v;
     }
     const Variant *best = nullptr;
     double best_cost = 1e300;
@@ -159,7 +165,7 @@ const Variant *choose_variant(const stpi_problem *p, int forced_index, bool allo
         if (v.RS < p->r_s || v.RT < p->r_t) continue;
         if (v.PIPE == 3 && !allow_mfma) continue;
         if (v.PIPE == 4) {
-            if (gather_pays(v, p)) return &v;
+            if (!tape && gather_pays(v, p)) return &v;
             continue;
         }
         const double c = variant_cost(v, p);
@@ -242,8 +248,7 @@ int split_short_tiles(int tiles, int T, int RT, int from) {
 // level of a two-level start) is bound by the frame-after-frame latency of
 // its few workgroups, not by work: there segments may be as short as 2 RT
 // frames and up to STPI_NSEG_MAX per tile.
-int segments_for(const Variant &v, const stpi_problem *p) {
-    if (v.PIPE == 4) return p->T;  // a workgroup per frame
+static int base_segments(const Variant &v, const stpi_problem *p) {
     const int tiles = tiles_for(v, p);
     const int resident = device_cus() * v.blocks_per_cu();
     const int rt = v.RT > 0 ? v.RT : 1;
@@ -254,10 +259,22 @@ int segments_for(const Variant &v, const stpi_problem *p) {
         const int small = std::min(std::min(fit, p->T / (2 * rt)), STPI_NSEG_MAX);
         if (small > nseg) nseg = small;
     }
-    return split_short_tiles(tiles, p->T, v.RT, nseg);
+    return nseg;
+}
+
+int segments_for(const Variant &v, const stpi_problem *p) {
+    if (v.PIPE == 4) return p->T;  // a workgroup per frame
+    return split_short_tiles(tiles_for(v, p), p->T, v.RT, base_segments(v, p));
+}
+
+int tape_segments(const Variant &v, const stpi_problem *p) {
+    if (v.PIPE == 4) return p->T;
+    const int nseg = base_segments(v, p);
+    return nseg == 1 ? split_short_tiles(tiles_for(v, p), p->T, v.RT) : nseg;
 }
 
 int grid_blocks(const Variant &v, const stpi_problem *p) { return tiles_for(v, p) * segments_for(v, p); }
+int tape_blocks(const Variant &v, const stpi_problem *p) { return tiles_for(v, p) * tape_segments(v, p); }
 
 // Workspace: [3 state slots][2 x partial sums][2 x maxima][ping-pong volume].
 // A partials set holds the largest grid any compiled variant can use for this

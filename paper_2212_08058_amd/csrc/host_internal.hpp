@@ -46,11 +46,12 @@ void clear_error();
 const DtypeOps *ops_for(int dtype);
 int validate_problem(const stpi_problem *p);
 void make_taps(const stpi_problem *p, double *gs, double *gt);
-// allow_mfma false skips the matrix-core variants (callers that cannot supply
-// their operand bound).
-const Variant *choose_variant(const stpi_problem *p, int forced_index, bool allow_mfma = true);
+// tape: for a step of a differentiated pass (a streamed vector loop; see host.cpp).
+const Variant *choose_variant(const stpi_problem *p, int forced_index, bool tape = false);
 int grid_blocks(const Variant &v, const stpi_problem *p);
 int segments_for(const Variant &v, const stpi_problem *p);
+int tape_segments(const Variant &v, const stpi_problem *p);  // of a step of a differentiated pass
+int tape_blocks(const Variant &v, const stpi_problem *p);
 // Phases of the slowest of k frame segments of a T-frame tile, and the split
 // of a tile the occupancy rules leave whole (see host.cpp).
 int segment_phases(int T, int RT, int k);

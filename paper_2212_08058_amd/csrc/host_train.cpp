@@ -37,15 +37,15 @@ const AdjVariant *choose_adj_variant(const stpi_problem *p) {
 }
 
 // Frame segments of an adjoint launch (one workgroup per CU): as the forward
-// step's, at least 4 r_t frames long while the tiles leave CUs idle, and further
-// ones where they shorten the slowest (16x120x216, r = (4, 2): 18.0 us with 2,
-// 13.2 with 5).
+// tape step's, at least 4 r_t frames long while the tiles leave CUs idle, and a
+// tile left whole split where that shortens its slowest segment.
 int adj_segments(const AdjVariant &v, const stpi_problem *p) {
     const int tiles = ((p->W + v.TW - 1) / v.TW) * ((p->H + v.TH - 1) / v.TH);
     const int rt = v.RT > 0 ? v.RT : 1;
     int nseg = std::min(std::min(device_cus() / tiles, p->T / (4 * rt)), 4);
     if (nseg < 1) nseg = 1;
-    return split_short_tiles(tiles, p->T, v.RT, nseg);
+    if (nseg == 1) nseg = split_short_tiles(tiles, p->T, v.RT);
+    return nseg;
 }
 
 int adj_grid_blocks(const AdjVariant &v, const stpi_problem *p) {
@@ -78,7 +78,7 @@ int stpi_train_step(const stpi_problem *p, const void *f, const void *z_in, cons
         return fail(STPI_EINVAL, "outputs must not alias inputs");
     const WsLayout L = layout_for(p);
     if (!ws || ws_bytes < L.total) return fail(STPI_EWORKSPACE, "workspace needs %zu bytes", L.total);
-    const Variant *v = choose_variant(p, forced_variant(), false);
+    const Variant *v = choose_variant(p, forced_variant(), true);
     if (!v) return fail(STPI_EUNSUPPORTED, "no compiled kernel for radii (%d, %d)", p->r_s, p->r_t);
     hipStream_t s = (hipStream_t)stream;
     FwdLaunch FL;
@@ -93,11 +93,11 @@ int stpi_train_step(const stpi_problem *p, const void *f, const void *z_in, cons
     FL.T = p->T;
     FL.H = p->H;
     FL.W = p->W;
-    FL.nseg = segments_for(*v, p);
+    FL.nseg = tape_segments(*v, p);
     make_taps(p, FL.gs, FL.gt);
     hipError_t e = v->launch(FL, s);
     if (e != hipSuccess) return hip_fail(e, "train step launch");
-    e = launch_norm_finalize(FL.partials, grid_blocks(*v, p), norm_out, s);
+    e = launch_norm_finalize(FL.partials, tape_blocks(*v, p), norm_out, s);
     return e == hipSuccess ? STPI_OK : hip_fail(e, "norm finalize");
 }
 
