@@ -89,6 +89,20 @@ static const BatchVariant *choose_batch_variant(const stpi_problem *proto, const
             best = &b;
         }
     }
+    if (!best || best->PIPE != 3 || best->blocks_per_cu() < 2) return best;
+    // Where the volumes of a step do not stay in the 256 MB last-level cache, the
+    // wide matrix-core tile, which re-reads less halo, beats the one that shares
+    // a CU with another (as mfma_tile_cost in host.cpp). Measured, ms for 20
+    // iterations, 32 x 64 / 32 x 128, float, r = (8, 3): 24 clips of 92 M voxels
+    // 10.5 / 7.2, 24 of 113 M 10.7 / 9.6, 12 of 104 M 8.75 / 8.11, 16 of 147 M
+    // 10.87 / 10.83, 24 of 291 M 23.6 / 22.1.
+    double bytes = 0.0;
+    for (const auto &c : clips) bytes += 3.0 * c.T * c.H * c.W * (double)ops->elem;
+    if (bytes > 256.0 * 1024 * 1024)
+        for (int i = 0; i < ops->nbatch; ++i) {
+            const BatchVariant &b = ops->batch_variants[i];
+            if (b.PIPE == 3 && b.RS == best->RS && b.RT == best->RT && b.TH * b.TW > best->TH * best->TW) return &b;
+        }
     return best;
 }
 

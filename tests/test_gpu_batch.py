@@ -332,3 +332,24 @@ def test_streaming_passes_of_unaligned_volumes(P, off):
     for a, b in ((ref, got), (ref0, got0)):
         for u, v in zip(plan.views(a), plan.views(b)):
             assert torch.equal(u, v)
+
+
+@pytest.mark.parametrize("shapes,tile", [([(16, 480, 854), (16, 480, 854), (12, 479, 853), (9, 480, 640)], (32, 64)),
+                                         ([(16, 480, 854), (16, 480, 854), (12, 479, 853), (9, 480, 640)] * 2,
+                                          (32, 128))])
+def test_batch_tile_by_total_volume(P, shapes, tile):
+    """Below and above 256 MB of step volumes: the tile the batch takes, and each
+    clip against its own single-clip chain (other tiles or segments: the
+    global and temporal sums in another order, float rounding)."""
+    Pm, B = P
+    kern = Pm.Kernel(4.0, 1.5, 8, 3)
+    plan = B.BatchPlan(shapes, kern)
+    info = plan.info()
+    assert info["PIPE"] == 3 and (info["TH"], info["TW"]) == tile
+    g = torch.Generator(device=DEV).manual_seed(5)
+    fs = [torch.rand(s, generator=g, device=DEV) for s in shapes]
+    x_flat, res = plan.iterate(plan.pack(fs), max_iters=3, tol=0.0)
+    for f, xv, r in zip(fs, plan.views(x_flat), res):
+        y, q = Pm.power_iterate(f, kern, iters=3)
+        assert float((xv.double() - y.double()).norm() / y.double().norm()) <= 1e-6
+        assert abs(r["lambda_"] - q["lambda_"]) <= 1e-6 * q["lambda_"]
