@@ -136,15 +136,20 @@ __device__ __forceinline__ void split_half(float v, _Float16 &hi, _Float16 &lo) 
     lo = (_Float16)(v - (float)hi);
 }
 
+typedef _Float16 half2_t __attribute__((ext_vector_type(2)));
+
 // Two products a ma and b mb as packed half-precision hi and lo parts: hi =
-// fp16(a ma), lo = fp16(a ma - hi), each rounded once from the exact product by a
-// mixed-precision fma that writes its half of the word (two instructions per
-// value; the plain form took 3.5 and could round hi in two steps).
+// fp16(a ma), lo = fp16(a ma - hi), from the unrounded product. The compiler
+// makes each a mixed-precision fma that writes its half of the word (two
+// instructions per value; the plain form took 3.5). It has to be the compiler
+// that makes them: these instructions run between matrix-core products, and for
+// inline assembly it keeps none of the wait states that a write to a register
+// of a product in flight needs.
 __device__ __forceinline__ void split_scaled2(float a, float ma, float b, float mb, uint32_t &hi, uint32_t &lo) {
-    asm("v_fma_mixlo_f16 %0, %1, %2, 0" : "=v"(hi) : "v"(a), "v"(ma));
-    asm("v_fma_mixhi_f16 %0, %1, %2, 0" : "+v"(hi) : "v"(b), "v"(mb));
-    asm("v_fma_mixlo_f16 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(lo) : "v"(a), "v"(ma), "v"(hi));
-    asm("v_fma_mixhi_f16 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "+v"(lo) : "v"(b), "v"(mb), "v"(hi));
+    const half2_t h = {(_Float16)__builtin_fmaf(a, ma, 0.f), (_Float16)__builtin_fmaf(b, mb, 0.f)};
+    const half2_t l = {(_Float16)__builtin_fmaf(a, ma, -(float)h.x), (_Float16)__builtin_fmaf(b, mb, -(float)h.y)};
+    hi = __builtin_bit_cast(uint32_t, h);
+    lo = __builtin_bit_cast(uint32_t, l);
 }
 
 // Launders a constant so the compiler keeps it as an operand (fma(x, 1, y)

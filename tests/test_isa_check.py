@@ -47,3 +47,51 @@ def test_accepts_uniform_loop_exit(checker):
 
 def test_accepts_lane_divergent_loop_without_barrier(checker):
     assert checker._loops_with_barrier_and_lane_exit(LANE_EXIT.replace("\ts_barrier\n", "")) == []
+
+
+PRODUCT = """_Z6kernelv:
+.LBB0_1:
+	v_mfma_f32_16x16x32_f16 v[0:3], v[4:7], v[8:11], v[12:15]
+{between}	;;#ASMSTART
+	v_fma_mixlo_f16 {dst}, {src}, v41, 0
+	;;#ASMEND
+{back}	s_cbranch_scc1 .LBB0_1
+	s_endpgm
+.Lfunc_end0:
+"""
+
+
+@pytest.mark.parametrize("dst,src,states,ok", [
+    ("v2", "v40", 7, False), ("v2", "v40", 8, True),      # writes the result
+    ("v42", "v1", 7, False), ("v42", "v1", 8, True),      # reads it
+    ("v13", "v40", 2, False), ("v13", "v40", 3, True),    # writes the C operand
+    ("v42", "v13", 0, True), ("v42", "v40", 0, True),     # reads the C operand; no overlap
+])
+def test_inline_assembly_behind_a_product(checker, dst, src, states, ok):
+    between = "" if states == 0 else "\ts_nop %d\n" % (states - 1)
+    text = PRODUCT.format(between=between, dst=dst, src=src, back="\ts_nop 0\n")
+    found = checker._inline_asm_waits(text)
+    assert (found == []) == ok, found
+    # the compiler's own instructions are its business
+    assert checker._inline_asm_waits(text.replace("\t;;#ASMSTART\n", "").replace("\t;;#ASMEND\n", "")) == []
+
+
+@pytest.mark.parametrize("back,ok", [("", False), ("\ts_nop 0\n", True)])
+def test_inline_assembly_in_front_of_a_product(checker, back, ok):
+    # around the loop: a write of an operand, a branch, the product
+    found = checker._inline_asm_waits(PRODUCT.format(between="", dst="v9", src="v40", back=back))
+    assert [(n, need) for _, _, _, n, need in found] == ([] if ok else [(1, 2)])
+
+
+def test_built_device_code_keeps_the_waits(checker):
+    """The assembly the last build left: matrix-core products are there, and no
+    inline assembly lies too close to one."""
+    path = os.path.join(HERE, "..", "_build")
+    files = [f for f in ("kernels_f32.hip.s", "kernels_bf16.hip.s", "sfseg.hip.s") if os.path.exists(os.path.join(path, f))]
+    if not files:
+        pytest.skip("no device assembly here")
+    for f in files:
+        with open(os.path.join(path, f)) as fh:
+            text = fh.read()
+        assert "v_mfma_f32_16x16x32_f16" in text
+        assert checker._inline_asm_waits(text) == []
