@@ -14,9 +14,14 @@ import os
 import re
 import subprocess
 
-# Scalar-memory writes (stores, atomics, write-back of the scalar cache) are
-# not used anywhere in this library; the device code is checked for them.
-FORBIDDEN_PREFIXES = ("s_store", "s_atomic", "s_dcache_wb", "s_buffer_store", "s_scratch_store", "s_buffer_atomic")
+# Of the scalar-memory instructions only loads are allowed: none whose name
+# holds one of these words.
+_SCALAR_MEMORY_WORDS = {"store", "atomic", "dcache"}
+
+
+def _scalar_memory_write(op: str) -> bool:
+    words = op.split("_")
+    return words[0] == "s" and not _SCALAR_MEMORY_WORDS.isdisjoint(words)
 
 
 def _device_asm(src: str, hipcc: str, flags, build_dir: str) -> str:
@@ -38,8 +43,7 @@ def check_device_code(srcs, jobs, hipcc, flags, build_dir) -> None:
     for a in asms:
         with open(a) as fh:
             for ln, line in enumerate(fh, 1):
-                op = line.strip().split(" ", 1)[0]
-                if op.startswith(FORBIDDEN_PREFIXES):
+                if _scalar_memory_write(re.split(r"\s", line.strip(), maxsplit=1)[0]):
                     bad.append(f"{os.path.basename(a)}:{ln}: {line.strip()}")
     if bad:
         raise RuntimeError("scalar-memory writes in device code:\n" + "\n".join(bad[:20]))

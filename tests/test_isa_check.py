@@ -37,6 +37,14 @@ def checker():
     return mod
 
 
+@pytest.mark.parametrize("words,bad", [
+    (("s", "load", "dwordx4"), False), (("s", "buffer", "load", "dword"), False), (("s", "mov", "b32"), False),
+    (("global", "store", "dword"), False), (("ds", "add", "u32"), False), (("s", "store", "dword"), True),
+    (("s", "buffer", "store", "dword"), True), (("s", "atomic", "add"), True), (("s", "dcache", "wb"), True)])
+def test_scalar_memory_is_for_loads(checker, words, bad):
+    assert checker._scalar_memory_write("_".join(words)) == bad
+
+
 def test_flags_barrier_in_lane_divergent_loop(checker):
     assert checker._loops_with_barrier_and_lane_exit(LANE_EXIT) == [("_Z6kernelv", "BB0_2")]
 
