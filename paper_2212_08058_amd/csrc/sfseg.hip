@@ -21,12 +21,12 @@ namespace {
     {RS, RT, TH, TW, NTHR, 1, &launch_sfseg_mfma<RT, TH, TW, NTHR, RS>, &sfseg_mfma_blocks_per_cu<RT, TH, TW, NTHR, RS>}
 
 // Compiled (RS, RT) pairs: the smallest one covering the problem's radii is
-// used (but see sfseg_variant). The matrix-core form took the place of vector
-// loops at (8, 3) and (16, 5): chain step in us, vector / matrix cores, r =
-// (8, 3): 8x64x112 23 / 21, 5x233x347 19.4 / 19.6, 32x240x432 59 / 49, 64x480x854
-// 276 / 196; r = (15, 5): 58 / 35, 43 / 32, 124 / 69, 486 / 286.
+// used, in its matrix-core form for the steps of an iteration where that pays
+// (see sfseg_variant).
 const SfsegVariant kSfsegF32[] = {
     STPI_SFSEG_ENTRY(float, 4, 2, 16, 64, 256, 8, 4),
+    STPI_SFSEG_ENTRY(float, 8, 3, 16, 64, 256, 8, 4),
+    STPI_SFSEG_ENTRY(float, 16, 5, 32, 64, 512, 8, 4),
     STPI_SFSEG_MFMA(8, 3, 32, 64, 512),
     STPI_SFSEG_MFMA(16, 5, 32, 64, 512),
 };
@@ -34,21 +34,28 @@ const SfsegVariant kSfsegF64[] = {
     STPI_SFSEG_ENTRY(double, 4, 2, 16, 64, 256, 8, 4),
 };
 
-const SfsegVariant *sfseg_variant(const stpi_problem *p) {
+// chain: for the steps of an iteration. There the matrix-core form is taken
+// beyond r = (8, 3), and at (8, 3) on volumes whose arithmetic and not their
+// frame-by-frame latency counts. Chain step in us, vector / matrix cores, r =
+// (15, 5): 8x64x112 58 / 45, 5x233x347 43 / 43, 32x240x432 126 / 84, 64x480x854 485
+// / 347; r = (8, 3): 5x233x347 20 / 26, 16x240x432 36 / 41, 32x240x432 59 / 50,
+// 64x480x854 280 / 247 (1.7 and 3.3 M voxels lie on either side); r = (4, 2), no
+// matrix-core form: 64x480x854 220 against 237 with the one of (8, 3). A single
+// step runs the vector form: there a value that is not finite reaches the
+// outputs whose window holds it and no others, as its products with the zeros
+// of a band would.
+const SfsegVariant *sfseg_variant(const stpi_problem *p, bool chain) {
     const SfsegVariant *list = p->dtype == STPI_F64 ? kSfsegF64 : kSfsegF32;
     const int n = p->dtype == STPI_F64 ? (int)(sizeof(kSfsegF64) / sizeof(kSfsegF64[0]))
                                        : (int)(sizeof(kSfsegF32) / sizeof(kSfsegF32[0]));
-    // The vector loop is the better one at r <= (4, 2) until its arithmetic and
-    // not its frame-by-frame latency counts. Chain step in us, vector (4, 2) /
-    // matrix-core (8, 3): 16x240x432 24 / 30, 32x240x432 38 / 47, 32x480x854 96 /
-    // 81, 64x480x854 219 / 189 (3.3 and 13 M voxels lie on either side).
-    const bool large = (int64_t)p->T * p->H * p->W >= (int64_t)8 << 20;
-    for (int i = 0; i < n; ++i) {
-        if (list[i].RS < p->r_s || list[i].RT < p->r_t) continue;
-        if (i == 0 && n > 1 && large) continue;
-        return &list[i];
-    }
-    return nullptr;
+    const SfsegVariant *v = nullptr;
+    for (int i = 0; i < n && !v; ++i)
+        if (list[i].RS >= p->r_s && list[i].RT >= p->r_t && !list[i].mfma) v = &list[i];
+    if (!v || !chain) return v;
+    const bool pays = v->RS > 8 || (int64_t)p->T * p->H * p->W >= (int64_t)5 << 19;
+    for (int i = 0; i < n; ++i)
+        if (list[i].mfma && list[i].RS == v->RS && list[i].RT == v->RT && pays) return &list[i];
+    return v;
 }
 
 int sfseg_tiles(const SfsegVariant &v, const stpi_problem *p) {
@@ -67,29 +74,28 @@ int sfseg_segments(const SfsegVariant &v, const stpi_problem *p) {
     return split_short_tiles(std::max(tiles, 1), p->T, v.RT, nseg);
 }
 
-// Workspace as the single-field chain's (WsLayout): state slots, two sets of
-// partial sums and maxima (the range check's partials share the first set's
-// room), the ping-pong volume. The first slot also holds a single step's
-// operand bounds.
-WsLayout sfseg_layout(const stpi_problem *p, const SfsegVariant &v) {
+// Workspace as the single-field chain's (WsLayout), without maxima: state
+// slots, two sets of partial sums (the range check's partials share the first
+// set's room), the ping-pong volume. One size for steps and iterations.
+WsLayout sfseg_layout(const stpi_problem *p) {
     WsLayout L;
     const size_t elem = p->dtype == STPI_F64 ? 8 : 4;
     L.state_off = 0;
     L.partials_off = (FINAL_SLOT + 1) * STATE_SLOT;
-    L.partials_cap = std::max((size_t)sfseg_tiles(v, p) * STPI_NSEG_MAX,
-                              (size_t)std::max(NORM_BLOCKS_HOST, 2 * SFSEG_RANGE_BLOCKS));
-    L.wmax_off = L.partials_off + 2 * L.partials_cap * 2 * sizeof(double);
-    const size_t off = L.wmax_off + 2 * L.partials_cap * sizeof(uint32_t);
+    const int tiles = std::max(sfseg_tiles(*sfseg_variant(p, false), p), sfseg_tiles(*sfseg_variant(p, true), p));
+    L.partials_cap = std::max((size_t)tiles * STPI_NSEG_MAX, (size_t)std::max(NORM_BLOCKS_HOST, 2 * SFSEG_RANGE_BLOCKS));
+    L.wmax_off = L.partials_off;
+    const size_t off = L.partials_off + 2 * L.partials_cap * 2 * sizeof(double);
     L.buf_off = (off + 255) & ~(size_t)255;
     L.total = L.buf_off + (((size_t)p->T * p->H * p->W * elem + 255) & ~(size_t)255);
     return L;
 }
 
-int sfseg_check(const stpi_problem *p, const SfsegVariant **v) {
+int sfseg_check(const stpi_problem *p, bool chain, const SfsegVariant **v) {
     int rc = validate_problem(p);
     if (rc) return rc;
     if (p->dtype != STPI_F32 && p->dtype != STPI_F64) return fail(STPI_EUNSUPPORTED, "sfseg: float or double only");
-    *v = sfseg_variant(p);
+    *v = sfseg_variant(p, chain);
     if (!*v) return fail(STPI_EUNSUPPORTED, "sfseg: no compiled kernel for radii (%d, %d)", p->r_s, p->r_t);
     return STPI_OK;
 }
@@ -105,39 +111,34 @@ void sfseg_fill(SfsegLaunch &L, const stpi_problem *p, const void *s, const void
     make_taps(p, L.gs, L.gt);
 }
 
-// The chain's checks and bounds from the range partials: flags |=
-// FLAG_AFFINITY and done when some affinity of Eq. 2 can be negative (alpha
-// (max f - min f)^2 > 1, a negative s, or a NaN); ubound = max |f|, and for the
-// uniform start (the constant 1) wmax[0] = max |s x| = max s.
-__global__ __launch_bounds__(256) void sfseg_range_check_kernel(const double *partials, int n, double alpha, int uniform,
-                                                                DevState *s) {
+// The chain's check from the range partials: flags |= FLAG_AFFINITY and done
+// when some affinity of Eq. 2 can be negative (alpha (max f - min f)^2 > 1, a
+// negative s, or a NaN).
+__global__ __launch_bounds__(256) void sfseg_range_check_kernel(const double *partials, int n, double alpha, DevState *s) {
     __shared__ SfsegRange rw[256 / 64];
     SfsegRange r = SFSEG_RANGE_EMPTY;
-    for (int b = threadIdx.x; b < n; b += 256) {
-        r.take(SfsegRange{partials[4 * b], partials[4 * b + 1], partials[4 * b + 2], partials[4 * b + 3]});
-    }
+    for (int b = threadIdx.x; b < n; b += 256)
+        r.take(SfsegRange{partials[3 * b], partials[3 * b + 1], partials[3 * b + 2]});
     r.wave();
     if ((threadIdx.x & 63) == 0) rw[threadIdx.x >> 6] = r;
     __syncthreads();
     if (threadIdx.x != 0) return;
     for (int w = 1; w < 256 / 64; ++w) r.take(rw[w]);
     const double d = r.fmx - r.fmn;
-    if (d != d || r.smn != r.smn || r.smn < 0.0 || alpha * d * d > 1.0) {
+    const bool nan = r.fmn != r.fmn || r.fmx != r.fmx || r.smn != r.smn;
+    if (nan || r.smn < 0.0 || alpha * d * d > 1.0) {
         s->flags |= FLAG_AFFINITY;
         s->done = 1;
-        return;
     }
-    s->ubound = __float_as_uint((float)fmax(fabs(r.fmn), fabs(r.fmx)));
-    if (uniform) s->wmax[0] = __float_as_uint((float)r.smx);
 }
 
 template <class ST>
-hipError_t sfseg_range(size_t n, const void *s, const void *f, double *partials, double alpha, int uniform,
-                       DevState *state, hipStream_t st) {
+hipError_t sfseg_range(size_t n, const void *s, const void *f, double *partials, double alpha, DevState *state,
+                       hipStream_t st) {
     hipLaunchKernelGGL(sfseg_range_kernel<ST>, dim3(SFSEG_RANGE_BLOCKS), dim3(256), 0, st, n, (const ST *)s,
                        (const ST *)f, partials);
     hipLaunchKernelGGL(sfseg_range_check_kernel, dim3(1), dim3(256), 0, st, partials, SFSEG_RANGE_BLOCKS, alpha,
-                       uniform, state);
+                       state);
     return hipGetLastError();
 }
 
@@ -167,21 +168,21 @@ int stpi_sfseg_unary(int64_t n, int dtype, const void *S, double p, void *s, voi
 
 size_t stpi_sfseg_workspace_bytes(const stpi_problem *p) {
     const SfsegVariant *v = nullptr;
-    if (sfseg_check(p, &v) != STPI_OK) return 0;
-    return sfseg_layout(p, *v).total;
+    if (sfseg_check(p, false, &v) != STPI_OK) return 0;
+    return sfseg_layout(p).total;
 }
 
 int stpi_sfseg_step(const stpi_problem *p, const void *s, const void *f, double alpha, const void *x,
                     double x_scale, void *z, double *d_sums, void *ws, size_t ws_bytes, void *stream) {
     clear_error();
     const SfsegVariant *v = nullptr;
-    int rc = sfseg_check(p, &v);
+    int rc = sfseg_check(p, false, &v);
     if (rc) return rc;
     if (!s || !f || !x || !z || !d_sums) return fail(STPI_EINVAL, "NULL buffer");
     if (z == s || z == f || z == x) return fail(STPI_EINVAL, "z must not alias s, f or x");
     if (!(alpha > 0.0) || !std::isfinite(alpha)) return fail(STPI_EINVAL, "alpha must be finite and > 0");
     if (!std::isfinite(x_scale)) return fail(STPI_EINVAL, "x_scale must be finite");
-    const WsLayout L = sfseg_layout(p, *v);
+    const WsLayout L = sfseg_layout(p);
     if (!ws || ws_bytes < L.total) return fail(STPI_EWORKSPACE, "sfseg workspace needs %zu bytes", L.total);
     hipStream_t st = (hipStream_t)stream;
     SfsegLaunch SL;
@@ -191,17 +192,7 @@ int stpi_sfseg_step(const stpi_problem *p, const void *s, const void *f, double 
     SL.x_scale = x_scale;
     SL.partials = (double *)((char *)ws + L.partials_off);
     SL.nseg = sfseg_segments(*v, p);
-    hipError_t e;
-    if (v->mfma) {
-        uint32_t *words = (uint32_t *)ws;
-        SL.bounds = words;
-        for (int i = 0; i < 2; ++i)
-            if ((e = launch_clear_word(words + i, st)) != hipSuccess) return hip_fail(e, "operand bound");
-        hipLaunchKernelGGL(sfseg_bounds_kernel, dim3(1024), dim3(256), 0, st, (size_t)p->T * p->H * p->W,
-                           (const float *)s, (const float *)f, (const float *)x, words);
-        if ((e = hipGetLastError()) != hipSuccess) return hip_fail(e, "operand bound");
-    }
-    e = v->launch(SL, st);
+    hipError_t e = v->launch(SL, st);
     if (e != hipSuccess) return hip_fail(e, "sfseg step launch");
     e = launch_step_sums(SL.partials, sfseg_tiles(*v, p) * SL.nseg, x_scale, d_sums, st);
     return e == hipSuccess ? STPI_OK : hip_fail(e, "step sums launch");
@@ -211,7 +202,7 @@ int stpi_sfseg_iterate(const stpi_problem *p, const void *s, const void *f, doub
                        int max_iters, double tol, void *ws, size_t ws_bytes, stpi_result *out, void *stream) {
     clear_error();
     const SfsegVariant *v = nullptr;
-    int rc = sfseg_check(p, &v);
+    int rc = sfseg_check(p, true, &v);
     if (rc) return rc;
     if (!s || !f || !x || !out) return fail(STPI_EINVAL, "NULL buffer or result");
     if (x == s || x == f) return fail(STPI_EINVAL, "x must not alias s or f");
@@ -219,7 +210,7 @@ int stpi_sfseg_iterate(const stpi_problem *p, const void *s, const void *f, doub
     if (max_iters < 0) return fail(STPI_EINVAL, "max_iters must be >= 0");
     if (init != 0 && init != 1) return fail(STPI_EINVAL, "init must be 0 (use x) or 1 (uniform)");
     if (!std::isfinite(tol)) return fail(STPI_EINVAL, "tol must be finite");
-    const WsLayout L = sfseg_layout(p, *v);
+    const WsLayout L = sfseg_layout(p);
     if (!ws || ws_bytes < L.total) return fail(STPI_EWORKSPACE, "sfseg workspace needs %zu bytes", L.total);
     std::memset(out, 0, sizeof(*out));
     hipStream_t st = (hipStream_t)stream;
@@ -237,12 +228,9 @@ int stpi_sfseg_iterate(const stpi_problem *p, const void *s, const void *f, doub
         if ((e = launch_state_from_norm(m.partials, NORM_BLOCKS_HOST, state, st)) != hipSuccess)
             return hip_fail(e, "init norm");
     }
-    e = p->dtype == STPI_F64 ? sfseg_range<double>(N, s, f, m.partials, alpha, init, state, st)
-                             : sfseg_range<float>(N, s, f, m.partials, alpha, init, state, st);
+    e = p->dtype == STPI_F64 ? sfseg_range<double>(N, s, f, m.partials, alpha, state, st)
+                             : sfseg_range<float>(N, s, f, m.partials, alpha, state, st);
     if (e != hipSuccess) return hip_fail(e, "affinity range check");
-    // the first step's staging bound from the caller's start
-    if (v->mfma && init != 1 && (e = ops->bound(N, s, x, &state->wmax[0], st)) != hipSuccess)
-        return hip_fail(e, "operand bound");
     SfsegLaunch SL;
     sfseg_fill(SL, p, s, f, alpha);
     SL.buf0 = x;
@@ -261,13 +249,10 @@ int stpi_sfseg_iterate(const stpi_problem *p, const void *s, const void *f, doub
             SL.no_prev = tol <= 0.0 && kk >= 2 && kk < max_iters - 1 ? 1 : 0;
             SL.state = m.slot(slot);
             SL.state_out = defer ? m.slot(slot ^ 1) : nullptr;
-            StepPartials mine = m.set(slot);
-            SL.partials = mine.sums;
-            SL.wpart = mine.wmax;
-            SL.prev_part = m.set(slot ^ 1);
+            SL.partials = m.set(slot).sums;
+            SL.prev_part = {m.set(slot ^ 1).sums, nullptr};
             if ((e = v->launch(SL, st)) != hipSuccess) return hip_fail(e, "sfseg step launch");
-            if (!v->mfma) mine.wmax = nullptr;
-            if (!defer && (e = launch_finalize(mine, nunits, state, st)) != hipSuccess)
+            if (!defer && (e = launch_finalize({SL.partials, nullptr}, nunits, state, st)) != hipSuccess)
                 return hip_fail(e, "finalize launch");
         }
         done += n;
@@ -280,8 +265,7 @@ int stpi_sfseg_iterate(const stpi_problem *p, const void *s, const void *f, doub
         }
     }
     const bool pend = defer && done > 0;
-    StepPartials last = m.set((done + 1) & 1);
-    if (!v->mfma) last.wmax = nullptr;
+    const StepPartials last = {m.set((done + 1) & 1).sums, nullptr};
     if ((e = ops->normalize(x, m.buf1, N, m.slot(pend ? done & 1 : 0), last, pend ? nunits : 0, m.slot(FINAL_SLOT),
                             st)) != hipSuccess)
         return hip_fail(e, "normalize");

@@ -34,9 +34,7 @@ struct SfsegArgs {
     DevState *state_out;    // as FwdArgs
     StepPartials prev_part;
     double *partials;
-    uint32_t *wpart;
-    const uint32_t *bounds;  // matrix-core kernel, single step: float bits of max |s x|, max |f|
-    int no_prev;             // the previous iterate is not read at the outputs (sum z x_stored = 0)
+    int no_prev;  // the previous iterate is not read at the outputs (sum z x_stored = 0)
     double x_scale;
     CT ainv;  // 1 / alpha
     int T, H, W;
@@ -288,33 +286,6 @@ __global__ __launch_bounds__(NTHR) void sfseg_step_kernel(SfsegArgs<ST> a) {
     }
 }
 
-// The same step with both spatial passes of the three fields on the matrix
-// cores (float; operands split into two half-precision parts, three products
-// each, as stencil_tile_mfma). Per frame a workgroup (TH x TW outputs) stages
-// the three fields of its slab once into half-precision hi and lo planes,
-// y-filters 3 MB NYC blocks into the Y planes, and x-filters one block per field
-// and wavefront. Three fields' planes fill the LDS (148 KB at 32 x 64, margin
-// 16), so they are single-buffered and a frame has two barriers:
-//   region 1: x-pass of frame k, staging of frame k + 1, the loads of frame
-//             k + 2 (as early as their registers are free: issued before the
-//             y-pass instead, the step takes 303 us, after it 320), t-pass,
-//             epilogue and stores of frame k;
-//   region 2: y-pass of frame k + 1.
-// The t-pass is a transposed filter: the sums of the output frames still open
-// move down one slot as a tap is added (acc[i] = acc[i + 1] + g v, one
-// multiply-add with another destination), so the ring needs no index and the
-// frame loop no unrolling (3 x 11 slots would unroll to more than the
-// instruction cache).
-// Range: u1 = s x takes the power of two that puts its largest value (collected
-// as max |s z| by the step that wrote z, or by a bound pass) into [2^9, 2^10);
-// f is scaled by 2^-ef (max |f| < 2^ef), so f u1 and f^2 u1 stay in range; the
-// epilogue undoes the powers of two.
-// Bound by nothing alone: per frame the vector ALU, the LDS, the first-level
-// cache (three arrays on a slab three times the tile) and the matrix cores take
-// 35, 37, 41 and 15% of the time, and two barriers a frame with one workgroup
-// per CU keep them from overlapping. The vector-ALU form of these radii took 486
-// us per step at 64x480x854, r = (15, 5), this takes 286 us. (Staging by 16-byte
-// loads of 4 x 4 blocks: 368 us, their unaligned row pieces cost the cache more.)
 // g v + c with a result register of its own: the compiler forms the two-operand
 // multiply-add, which needs a copy of c first when c stays live or moves.
 __device__ __forceinline__ float fma3(float g, float v, float c) {
@@ -323,28 +294,55 @@ __device__ __forceinline__ float fma3(float g, float v, float c) {
     return d;
 }
 
+// The same step with both spatial passes of the three fields on the matrix
+// cores, in float (v_mfma_f32_16x16x4_f32, whose products and sums round as the
+// vector form's multiply-adds do): a 1D pass over 16 outputs is a product with a
+// banded matrix of 16 + 2 PAD columns, as in stencil_tile_mfma. The order of a
+// product's K index is free, so the four lane groups each take a quarter of the
+// band's columns in a row: a lane reads its operands of all products of a block
+// as 16-byte pieces. (Half-precision parts run at four times the rate: 286 us a
+// step at 64x480x854, r = (15, 5), against 347 here and 485 in the vector form.
+// But they keep a value to 2^-34 of the volume's largest only, so a region far
+// below it came out with few bits, or as 0.)
+// Per frame a workgroup (TH x TW outputs) stages the three fields of its slab
+// once, y-filters 3 MB NYC blocks into the Y planes, and x-filters one block
+// per field and wavefront. The planes are single-buffered and a frame has two
+// barriers:
+//   region 1: x-pass of frame k, staging of frame k + 1, the loads of frame
+//             k + 2 (as early as their registers are free), t-pass, epilogue
+//             and stores of frame k;
+//   region 2: y-pass of frame k + 1.
+// The t-pass is a transposed filter: the sums of the output frames still open
+// move down one slot as a tap is added (acc[i] = acc[i + 1] + g v, one
+// multiply-add with another destination), so the ring needs no index and the
+// frame loop no unrolling (3 x 11 slots would unroll to more than the
+// instruction cache).
 template <int RT, int TH, int TW, int NTHR, int PAD>
 struct SfsegMfma {
-    using G = MfmaGeometry<TH, TW, NTHR, PAD, 2>;
-    static constexpr int UF = G::UBUF, YF = G::YBUF;  // one field's hi and lo planes
-    static constexpr int LDS_HALVES = 3 * (UF + YF);
-    static constexpr int NG4 = G::SR / 4;             // staging items: 4 rows of a slab column
-    static constexpr int NITEM = G::SC * NG4;
+    static constexpr int MB = TH / 16, NB = TW / 16;            // output blocks down / across
+    static constexpr int SR = TH + 2 * PAD, SC = TW + 2 * PAD;  // staged slab rows / columns
+    static constexpr int NK = (16 + 2 * PAD) / 4;               // products per block = operands per lane
+    // floats per line: an odd number of 16-byte pieces, so that the pieces of 16 lanes lie in different banks
+    static constexpr int pitch(int n) { return ((n + 3) / 4 | 1) * 4; }
+    static constexpr int UP = pitch(SR), YP = pitch(SC);
+    static constexpr int UF = SC * UP, YF = TH * YP;  // a field's planes: staged [column][row], y-filtered [row][column]
+    static constexpr int NG4 = SR / 4;                // staging items: 4 rows of a slab column
+    static constexpr int NITEM = SC * NG4;
     static constexpr int IPS = (NITEM + NTHR - 1) / NTHR;
     static constexpr int NPF = 4 * IPS;
-    static constexpr int NYB = 3 * G::NYB;
-    static constexpr int YPW = (NYB + G::NWAVE - 1) / G::NWAVE;
-    static_assert(LDS_HALVES * 2 + 2048 <= 160 * 1024, "LDS");
-    static_assert(G::SR % 4 == 0 && G::XPW == 1, "one output block per wavefront and field");
+    static constexpr int NWAVE = NTHR / 64;
+    static constexpr int NYC = SC / 16, NYB1 = MB * NYC, NYB = 3 * NYB1;  // y-pass blocks
+    static constexpr int YPW = (NYB + NWAVE - 1) / NWAVE;
+    static_assert(3 * (UF + YF) * 4 + 2048 <= 160 * 1024, "LDS");
+    static_assert(SR % 4 == 0 && NK % 4 == 0 && MB * NB == NWAVE, "one output block per wavefront and field");
 };
 
 template <int RT, int TH, int TW, int NTHR, int PAD>
 __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
     using S = SfsegMfma<RT, TH, TW, NTHR, PAD>;
-    using G = typename S::G;
     using IO = BufIO<float>;
-    constexpr int NTS = 2 * RT + 1, NPF = S::NPF, IPS = S::IPS;
-    __shared__ __align__(16) _Float16 lds[S::LDS_HALVES];
+    constexpr int NTS = 2 * RT + 1, NPF = S::NPF, IPS = S::IPS, NK = S::NK;
+    __shared__ __align__(16) float lds[3 * (S::UF + S::YF)];
     __shared__ double red[sfseg_red<NTHR>()];
     __shared__ DevState st;
     __shared__ float tapl[2 * 16 + 1];
@@ -357,6 +355,7 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
     float *dst;
     double scale;
     if (!sfseg_begin<NTHR>(a, ntiles * a.nseg, st, red, src, dst, scale)) return;
+    const float sc = (float)scale;
     if (threadIdx.x < 2 * 16 + 1) {
         float g = 0.f;
 #pragma unroll
@@ -364,35 +363,24 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
         tapl[threadIdx.x] = g;
     }
     __syncthreads();
-    // powers of two of the staging (see above)
-    const float b1 = __uint_as_float(a.state ? st.wmax[st.cur] : a.bounds[0]);
-    const float bf = __uint_as_float(a.state ? st.ubound : a.bounds[1]);
-    const int e1 = bound_exponent((float)((double)b1 * fabs(scale)), 100), ef = bound_exponent(bf, PRODUCT_ELIM);
-    const float umul = (float)(scale * ldexp(1.0, 10 - e1)), fmul = ldexpf(1.f, -ef);
-    const float kb = ldexpf(1.f, 2 * ef), kc = ldexpf(2.f, ef), ko = ldexpf(1.f, e1 - 10);
 
     const size_t plane = (size_t)a.H * a.W;
     const uint32_t pbytes = (uint32_t)(plane * 4);
     const int x0 = (tile % nbx) * TW, y0 = (tile / nbx) * TH;
-    const int tid = threadIdx.x, lane = tid & 63;
+    const int tid = threadIdx.x, lane = tid & 63, li = lane & 15, lg = lane >> 4;
     const int wid = __builtin_amdgcn_readfirstlane(tid >> 6);
-    _Float16 *const U = lds, *const Y = lds + 3 * S::UF;
-    half8_t thi[G::KB], tlo[G::KB];
-    band_taps<G, PAD>(tapl, lane, thi, tlo);
-    // zero the U rows and Y columns that only the last K block reads (none when PAD = 8)
-    constexpr int ZR = G::UK > G::SR ? G::UK - G::SR : 1, ZC = G::YW > G::SC ? G::YW - G::SC : 1;
-    for (int i = tid; i < 6 * G::SC * (G::UK - G::SR); i += NTHR) {
-        const int k = i % ZR, rest = i / ZR;
-        U[(rest / G::SC) * G::UPL + (rest % G::SC) * G::UP + G::SR + k] = (_Float16)0.f;
-    }
-    for (int i = tid; i < 6 * TH * (G::YW - G::SC); i += NTHR) {
-        const int k = i % ZC, rest = i / ZC;
-        Y[(rest / TH) * G::YPL + (rest % TH) * G::YP + G::SC + k] = (_Float16)0.f;
+    float *const U = lds, *const Y = lds + 3 * S::UF;
+    // band taps: product k of a block takes band column NK lg + k
+    float tap[NK];
+#pragma unroll
+    for (int k = 0; k < NK; ++k) {
+        const int d = NK * lg + k - PAD - li;
+        tap[k] = (d >= -16 && d <= 16) ? tapl[d + 16] : 0.f;
     }
     uint32_t poff[NPF];
 #pragma unroll
     for (int m = 0; m < IPS; ++m) {
-        const int it = tid + m * NTHR, c = it % G::SC, g = it / G::SC, gx = x0 - PAD + c;
+        const int it = tid + m * NTHR, c = it % S::SC, g = it / S::SC, gx = x0 - PAD + c;
         const bool colok = it < S::NITEM && c >= PAD - a.rs && c < TW + PAD + a.rs && (unsigned)gx < (unsigned)a.W;
 #pragma unroll
         for (int j = 0; j < 4; ++j) {
@@ -402,7 +390,7 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
         }
     }
     // this lane's outputs: row li, columns 4 lg .. + 3 of the wavefront's block
-    const int orow = y0 + 16 * (wid / G::NB) + (lane & 15), ocol = x0 + 16 * (wid % G::NB) + 4 * (lane >> 4);
+    const int orow = y0 + 16 * (wid / S::NB) + li, ocol = x0 + 16 * (wid % S::NB) + 4 * lg;
     const int nout = orow < a.H ? (a.W - ocol < 0 ? 0 : (a.W - ocol < 4 ? a.W - ocol : 4)) : 0;
     const uint32_t ooff = nout > 0 ? (uint32_t)(orow * a.W + ocol) * 4 : OOB;
 
@@ -415,7 +403,6 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
             for (int q = 0; q < 4; ++q) acc[m][i][q] = 0.f;
     const FrameWalk<RT> fw(a.T, t0, t1);
     const int nin = fw.nin;
-    const float one = opaque(1.f);
     float ps[NPF], pf[NPF], px[NPF];
     // an empty range when !ok (see FwdOp::fetch)
     auto fetch = [&](int t, bool ok) __attribute__((always_inline)) {
@@ -434,43 +421,49 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
         for (int m = 0; m < IPS; ++m) {
             const int it = tid + m * NTHR;
             if (S::NITEM % NTHR == 0 || m < IPS - 1 || it < S::NITEM) {
-                _Float16 *q = U + (it % G::SC) * G::UP + 4 * (it / G::SC);
-                uint2 h[3], l[3];  // the three fields: w, w f^2, w f
+                float *q = U + (it % S::SC) * S::UP + 4 * (it / S::SC);
+                float4_t u[3];  // the three fields: u, u f^2, u f
 #pragma unroll
-                for (int j = 0; j < 2; ++j) {
-                    const int k = 4 * m + 2 * j;
-                    const float w0 = ps[k] * px[k], w1 = ps[k + 1] * px[k + 1];
-                    const float u0 = w0 * umul, u1 = w1 * umul;
-                    const float f0 = pf[k] * fmul, f1 = pf[k + 1] * fmul;
-                    split_scaled2(w0, umul, w1, umul, (&h[0].x)[j], (&l[0].x)[j]);
-                    split_scaled2(u0, f0, u1, f1, (&h[2].x)[j], (&l[2].x)[j]);
-                    split_scaled2(f0 * u0, f0, f1 * u1, f1, (&h[1].x)[j], (&l[1].x)[j]);
+                for (int j = 0; j < 4; ++j) {
+                    const int k = 4 * m + j;
+                    u[0][j] = (ps[k] * px[k]) * sc;
+                    u[2][j] = pf[k] * u[0][j];
+                    u[1][j] = pf[k] * u[2][j];
                 }
 #pragma unroll
-                for (int c = 0; c < 3; ++c) {
-                    *reinterpret_cast<uint2 *>(q + c * S::UF) = h[c];
-                    *reinterpret_cast<uint2 *>(q + c * S::UF + G::UPL) = l[c];
-                }
+                for (int c = 0; c < 3; ++c) *reinterpret_cast<float4_t *>(q + c * S::UF) = u[c];
             }
+        }
+    };
+    auto operands = [&](const float *p, float (&w)[NK]) __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < NK / 4; ++j) {
+            const float4_t t = reinterpret_cast<const float4_t *>(p + NK * lg)[j];
+#pragma unroll
+            for (int e = 0; e < 4; ++e) w[4 * j + e] = t[e];
         }
     };
     auto ypass = [&]() __attribute__((always_inline)) {
         float4_t ya[S::YPW];
 #pragma unroll
         for (int m = 0; m < S::YPW; ++m) {
-            const int b = wid + m * G::NWAVE;
-            if (S::NYB % G::NWAVE == 0 || m < S::YPW - 1 || b < S::NYB)
-                ya[m] = mfma_yblock_mma<G>(U + (b / G::NYB) * S::UF, b % G::NYB, lane, thi, tlo);
+            const int b = wid + m * S::NWAVE, f = b / S::NYB1, rb = b % S::NYB1 / S::NYC, cb = b % S::NYC;
+            if (S::NYB % S::NWAVE == 0 || m < S::YPW - 1 || b < S::NYB) {
+                float w[NK];
+                operands(U + f * S::UF + (16 * cb + li) * S::UP + 16 * rb, w);
+                ya[m] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int k = 0; k < NK; ++k) ya[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[k], tap[k], ya[m], 0, 0, 0);
+            }
         }
 #pragma unroll
         for (int m = 0; m < S::YPW; ++m) {
-            const int b = wid + m * G::NWAVE;
-            if (S::NYB % G::NWAVE == 0 || m < S::YPW - 1 || b < S::NYB)
-                mfma_yblock_store<G>(Y + (b / G::NYB) * S::YF, b % G::NYB, lane, ya[m], one);
+            const int b = wid + m * S::NWAVE, f = b / S::NYB1, rb = b % S::NYB1 / S::NYC, cb = b % S::NYC;
+            if (S::NYB % S::NWAVE == 0 || m < S::YPW - 1 || b < S::NYB)
+                *reinterpret_cast<float4_t *>(Y + f * S::YF + (16 * rb + li) * S::YP + 16 * cb + 4 * lg) = ya[m];
         }
     };
     double d1 = 0.0, d2 = 0.0;
-    float wm = 0.f;
     fetch(fw.in(0), true);
     stage();
     __syncthreads();
@@ -490,7 +483,13 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
         // without branches, as the single-field loop: past the last input frame
         // the loads return 0, and with them the staged fields and the products
 #pragma unroll
-        for (int m = 0; m < 3; ++m) v[m] = mfma_xblock_mma<G>(Y + m * S::YF, wid, lane, thi, tlo);
+        for (int m = 0; m < 3; ++m) {
+            float w[NK];
+            operands(Y + m * S::YF + (16 * (wid / S::NB) + li) * S::YP + 16 * (wid % S::NB), w);
+            v[m] = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+            for (int i = 0; i < NK; ++i) v[m] = __builtin_amdgcn_mfma_f32_16x16x4f32(tap[i], w[i], v[m], 0, 0, 0);
+        }
         stage();
         fetch(fw.in(k + 2), k + 2 < nin);
         // fma3 is inline assembly, for which the compiler inserts no wait states
@@ -511,12 +510,12 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
                 // columns past the right edge: the 4-wide loads read the next row there
-                const float so = q < nout ? os[q] : 0.f, fo = of[q];
-                z[q] = so * ko * (fmaf(a.ainv - fo * fo, acc[0][0][q], -(acc[1][0][q] * kb)) + fo * kc * acc[2][0][q]);
+                const float fo = of[q];
+                const float A = acc[0][0][q], B = acc[1][0][q], C = acc[2][0][q];
+                z[q] = q < nout ? os[q] * (fmaf(a.ainv - fo * fo, A, -B) + 2.f * fo * C) : 0.f;
                 const double zs = (double)z[q];
                 d2 = fma(zs, zs, d2);
                 d1 = fma(zs, (double)ox[q], d1);
-                wm = fmaxf(wm, fabsf(so * z[q]));
             }
             if (nout == 4) {
                 IO::store4(rz, ooff, z);
@@ -530,45 +529,42 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
         ypass();
         __syncthreads();
     }
-    block_reduce<NTHR>(d1, d2, wm, red);
+    float unused = 0.f;
+    block_reduce<NTHR>(d1, d2, unused, red);
     if (threadIdx.x == 0) {
         a.partials[2 * unit] = d1;
         a.partials[2 * unit + 1] = d2;
-        if (a.wpart) a.wpart[unit] = __float_as_uint(wm);
     }
 }
 
 // The range check of the affinity (Eq. 2's Taylor term): every entry of M is
 // >= 0 when s >= 0 and alpha (max f - min f)^2 <= 1. Per-block min f, max f,
-// min s and max s into partials[4 b .. 4 b + 3]; a NaN anywhere gives NaNs.
+// min s into partials[3 b .. 3 b + 2]; a NaN anywhere gives NaNs.
 // One read of both volumes, 16-byte chunks with two of each in flight per
 // thread (196 us element by element on 256 workgroups at 64x480x854, 40 us now).
 constexpr int SFSEG_RANGE_BLOCKS = 1024;
 struct SfsegRange {
-    double fmn, fmx, smn, smx;
+    double fmn, fmx, smn;
     __device__ __forceinline__ void take(double f, double s) {
         fmn = (f < fmn || f != f) ? f : fmn;
         fmx = (f > fmx || f != f) ? f : fmx;
         smn = (s < smn || s != s) ? s : smn;
-        smx = (s > smx || s != s) ? s : smx;
     }
     // minima with minima, maxima with maxima: an empty range changes nothing
     __device__ __forceinline__ void take(const SfsegRange &o) {
         fmn = (o.fmn < fmn || o.fmn != o.fmn) ? o.fmn : fmn;
         fmx = (o.fmx > fmx || o.fmx != o.fmx) ? o.fmx : fmx;
         smn = (o.smn < smn || o.smn != o.smn) ? o.smn : smn;
-        smx = (o.smx > smx || o.smx != o.smx) ? o.smx : smx;
     }
     __device__ __forceinline__ void wave() {
 #pragma unroll
         for (int off = 32; off >= 1; off >>= 1) {
-            const SfsegRange o = {__shfl_xor(fmn, off, 64), __shfl_xor(fmx, off, 64), __shfl_xor(smn, off, 64),
-                                  __shfl_xor(smx, off, 64)};
+            const SfsegRange o = {__shfl_xor(fmn, off, 64), __shfl_xor(fmx, off, 64), __shfl_xor(smn, off, 64)};
             take(o);
         }
     }
 };
-constexpr SfsegRange SFSEG_RANGE_EMPTY = {INFINITY, -INFINITY, INFINITY, -INFINITY};
+constexpr SfsegRange SFSEG_RANGE_EMPTY = {INFINITY, -INFINITY, INFINITY};
 
 template <class ST>
 __global__ __launch_bounds__(256) void sfseg_range_kernel(size_t n, const ST *s, const ST *f, double *partials) {
@@ -581,7 +577,7 @@ __global__ __launch_bounds__(256) void sfseg_range_kernel(size_t n, const ST *s,
         const size_t nv = n / VEC;
         const uint4 *s4 = reinterpret_cast<const uint4 *>(s), *f4 = reinterpret_cast<const uint4 *>(f);
         // minima and maxima in the storage type (exact), widened at the end; a NaN sticks
-        ST fmn = (ST)INFINITY, fmx = -(ST)INFINITY, smn = (ST)INFINITY, smx = -(ST)INFINITY;
+        ST fmn = (ST)INFINITY, fmx = -(ST)INFINITY, smn = (ST)INFINITY;
         bool nan = false;
         for (size_t i = tid; i < nv; i += 2 * stride) {
             union {
@@ -602,10 +598,9 @@ __global__ __launch_bounds__(256) void sfseg_range_kernel(size_t n, const ST *s,
                     fmn = fv < fmn ? fv : fmn;
                     fmx = fv > fmx ? fv : fmx;
                     smn = sv < smn ? sv : smn;
-                    smx = sv > smx ? sv : smx;
                 }
         }
-        r.take(SfsegRange{(double)fmn, (double)fmx, (double)smn, (double)smx});
+        r.take(SfsegRange{(double)fmn, (double)fmx, (double)smn});
         if (nan) r.take((double)NAN, (double)NAN);
         head = nv * VEC;
     }
@@ -616,31 +611,9 @@ __global__ __launch_bounds__(256) void sfseg_range_kernel(size_t n, const ST *s,
     __syncthreads();
     if (threadIdx.x == 0) {
         for (int w = 1; w < 256 / 64; ++w) r.take(rw[w]);
-        partials[4 * blockIdx.x] = r.fmn;
-        partials[4 * blockIdx.x + 1] = r.fmx;
-        partials[4 * blockIdx.x + 2] = r.smn;
-        partials[4 * blockIdx.x + 3] = r.smx;
-    }
-}
-
-// Operand bounds of a single matrix-core step: words[0] = max |s x|, words[1] =
-// max |f| over the finite values, as float bits (cleared by the caller).
-__global__ __launch_bounds__(256) void sfseg_bounds_kernel(size_t n, const float *s, const float *f, const float *x,
-                                                           uint32_t *words) {
-    __shared__ float red[256 / 64];
-    float a = 0.f, b = 0.f;
-    const size_t stride = (size_t)gridDim.x * 256;
-#pragma unroll 4
-    for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n; i += stride) {
-        const float u = fabsf(s[i] * x[i]), v = fabsf(f[i]);
-        a = u > a && u < INFINITY ? u : a;
-        b = v > b && v < INFINITY ? v : b;
-    }
-    a = block_max<256>(a, red);
-    b = block_max<256>(b, red);
-    if (threadIdx.x == 0) {
-        atomicMax(&words[0], __float_as_uint(a));
-        atomicMax(&words[1], __float_as_uint(b));
+        partials[3 * blockIdx.x] = r.fmn;
+        partials[3 * blockIdx.x + 1] = r.fmx;
+        partials[3 * blockIdx.x + 2] = r.smn;
     }
 }
 
@@ -661,8 +634,6 @@ struct SfsegLaunch {
     DevState *state_out;
     StepPartials prev_part;
     double *partials;
-    uint32_t *wpart;
-    const uint32_t *bounds;
     int no_prev;
     double x_scale;
     double ainv;
@@ -675,7 +646,7 @@ using SfsegLaunchFn = hipError_t (*)(const SfsegLaunch &, hipStream_t);
 
 struct SfsegVariant {
     int RS, RT, TH, TW, NTHR;
-    int mfma;  // 1: matrix-core spatial passes (needs the operand bounds)
+    int mfma;  // 1: matrix-core spatial passes
     SfsegLaunchFn launch;
     int (*blocks_per_cu)();
 };
@@ -693,8 +664,6 @@ SfsegArgs<ST> sfseg_args(const SfsegLaunch &L) {
     a.state_out = L.state_out;
     a.prev_part = L.prev_part;
     a.partials = L.partials;
-    a.wpart = L.wpart;
-    a.bounds = L.bounds;
     a.no_prev = L.state && L.no_prev ? 1 : 0;
     a.x_scale = L.x_scale;
     a.ainv = (CT)L.ainv;
@@ -715,8 +684,7 @@ SfsegArgs<ST> sfseg_args(const SfsegLaunch &L) {
 template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX>
 hipError_t launch_sfseg(const SfsegLaunch &L, hipStream_t stream) {
     if (L.state && L.state_out == L.state) return hipErrorInvalidValue;
-    SfsegArgs<ST> a = sfseg_args<ST, RS, RT>(L);
-    a.prev_part.wmax = nullptr;
+    const SfsegArgs<ST> a = sfseg_args<ST, RS, RT>(L);
     const int nunits = ((L.W + TW - 1) / TW) * ((L.H + TH - 1) / TH) * a.nseg;
     const int per = (nunits + NUM_XCD - 1) / NUM_XCD;
     hipLaunchKernelGGL((sfseg_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX>), dim3(per * NUM_XCD), dim3(NTHR), 0,
@@ -726,8 +694,7 @@ hipError_t launch_sfseg(const SfsegLaunch &L, hipStream_t stream) {
 
 template <int RT, int TH, int TW, int NTHR, int PAD>
 hipError_t launch_sfseg_mfma(const SfsegLaunch &L, hipStream_t stream) {
-    if (L.state && (L.state_out == L.state || !L.wpart)) return hipErrorInvalidValue;
-    if (!L.state && !L.bounds) return hipErrorInvalidValue;
+    if (L.state && L.state_out == L.state) return hipErrorInvalidValue;
     const SfsegArgs<float> a = sfseg_args<float, 16, RT>(L);
     const int nunits = ((L.W + TW - 1) / TW) * ((L.H + TH - 1) / TH) * a.nseg;
     const int per = (nunits + NUM_XCD - 1) / NUM_XCD;

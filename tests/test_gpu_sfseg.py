@@ -232,3 +232,95 @@ def test_sfseg_range_check_on_small_and_odd_volumes(S):
                 v[which].view(-1)[at] = bad
                 _, r = Sf.sfseg_iterate(v["s"], v["f"], kern, 1.0, iters=2, check=False)
                 assert r["rc"] == 1 and r["flags"] & 16, (shape, which, bad, at)
+
+
+def _one_iteration_at(P, Sf, s, f, x0, kern, alpha, idx):
+    """(lambda x_1)_i of one iteration from x0 and its FP64 value, at the flat indices idx."""
+    sd, fd, xd = (torch.from_numpy(v).to(DEV) for v in (s, f, x0))
+    x, r = Sf.sfseg_iterate(sd, fd, kern, alpha, iters=1, x0=xd)
+    torch.cuda.synchronize()
+    got = x.double().cpu().numpy().reshape(-1)[idx] * r["lambda_"]
+    x64 = x0.astype(np.float64)
+    ref = oracle.sfseg_apply_at(s, f, x64 / np.linalg.norm(x64), alpha, okf(kern), idx)
+    return got, ref
+
+
+@pytest.mark.parametrize("shape,kp", [
+    ((6, 64, 200), (5.0, 2.0, 15, 5)), ((5, 33, 140), (4.0, 2.0, 9, 4)), ((5, 60, 200), (4.0, 1.5, 8, 3)),
+    ((5, 60, 200), (2.0, 1.0, 4, 2)),
+    # either side of the volume from which r = (8, 3) takes its other form, and a smaller radius beyond it
+    ((11, 464, 470), (4.0, 1.5, 8, 3)), ((12, 470, 470), (4.0, 1.5, 8, 3)), ((12, 470, 470), (4.0, 1.5, 6, 3)),
+    # more workgroups than finalise their steps in the next launch
+    ((2, 650, 1720), (2.0, 1.0, 4, 2)), ((2, 1040, 2060), (5.0, 2.0, 15, 5))])
+def test_sfseg_keeps_float_precision_far_below_the_maximum(S, shape, kp):
+    """s is 1 in the left columns and 1e-7, then 1e-14 further right: every voxel
+    of an iteration keeps float's relative precision, also where a whole
+    neighbourhood lies far below the volume's largest value. All terms of a
+    voxel's sums are positive and the update cancels them by less than 5; the
+    three passes round fewer than 80 times: 80 x 2^-24 x 5 per voxel."""
+    P, Sf = S
+    kern = P.Kernel(*kp)
+    T, H, W = shape
+    rng = np.random.default_rng(W)
+    s = rng.uniform(0.5, 1.0, shape)
+    s[:, :, 60:] *= 1e-7
+    s[:, :, 110:] *= 1e-7
+    s, f = s.astype(np.float32), rng.uniform(0.0, 0.9, shape).astype(np.float32)
+    x0 = rng.uniform(0.5, 1.0, shape).astype(np.float32)
+    cols = np.array([0, 20, 59, 60, 62, 76, 90, 109, 112, 126, W - 1])
+    rows = rng.integers(0, H, 4)
+    idx = np.array([(t * H + y) * W + c for t in (0, T - 1) for y in rows for c in cols])
+    got, ref = _one_iteration_at(P, Sf, s, f, x0, kern, 1.0, idx)
+    err = np.abs(got - ref) / np.abs(ref)
+    print(shape, kp, "largest relative error", err.max(), "of values from", np.abs(ref).min(), "to", np.abs(ref).max())
+    assert err.max() <= 80 * 2.0 ** -24 * 5
+
+
+@pytest.mark.parametrize("kp", [(2.0, 1.0, 4, 2), (4.0, 1.5, 8, 3), (5.0, 2.0, 16, 5)])
+@pytest.mark.parametrize("which,bad", [("x", float("nan")), ("x", float("inf")), ("s", float("nan")), ("f", float("inf"))])
+def test_sfseg_step_keeps_non_finite_values_in_their_window(S, kp, which, bad):
+    """A value that is not finite reaches the outputs whose window holds it and no others."""
+    P, Sf = S
+    kern = P.Kernel(*kp)
+    shape, at = (13, 70, 150), (6, 33, 70)
+    rng = np.random.default_rng(2)
+    v = {k: torch.from_numpy(rng.uniform(0.1, 1.0, shape).astype(np.float32)).to(DEV) for k in "sfx"}
+    clean, _ = Sf.sfseg_step(v["s"], v["f"], v["x"], kern, 1.0)
+    clean = clean.clone()
+    v[which][at] = bad
+    z, _ = Sf.sfseg_step(v["s"], v["f"], v["x"], kern, 1.0)
+    torch.cuda.synchronize()
+    box = torch.zeros(shape, dtype=torch.bool, device=DEV)
+    r_s, r_t = kp[2], kp[3]
+    box[at[0] - r_t:at[0] + r_t + 1, at[1] - r_s:at[1] + r_s + 1, at[2] - r_s:at[2] + r_s + 1] = True
+    assert torch.equal(z[~box], clean[~box])
+    assert not torch.isfinite(z[box]).any()
+
+
+def test_sfseg_infinite_feature_is_a_non_finite_iteration(S):
+    """f infinite everywhere has no range to check: the iteration itself stops on its norm."""
+    from paper_2212_08058_amd import _native as N
+    P, Sf = S
+    s = torch.full((4, 20, 30), 0.5, device=DEV)
+    _, r = Sf.sfseg_iterate(s, torch.full_like(s, float("inf")), P.Kernel(5.0, 2.0, 15, 5), 1.0, iters=2, check=False)
+    assert r["rc"] == 4 and r["flags"] & 2 and not r["flags"] & 16
+
+
+@pytest.mark.parametrize("shape,kp", [((9, 40, 131), (4.0, 1.5, 8, 3)), ((9, 40, 131), (5.0, 2.0, 15, 5)),
+                                      ((12, 470, 470), (4.0, 1.5, 8, 3)), ((7, 40, 131), (2.0, 1.0, 4, 2))])
+def test_sfseg_finalisation_by_the_next_launch_is_bitwise_equal(S, monkeypatch, shape, kp):
+    """The state formed by the next launch and the one formed by a launch of its
+    own are the same, in the vector and the matrix-core form."""
+    P, Sf = S
+    kern = P.Kernel(*kp)
+    rng = np.random.default_rng(5)
+    s, f = (torch.from_numpy(rng.uniform(0.1, 1.0, shape).astype(np.float32)).to(DEV) for _ in range(2))
+    out = []
+    for flag in ("0", "1"):
+        monkeypatch.setenv("STPI_NO_FUSE", flag)
+        for kw in (dict(iters=5), dict(tol=1e-300, max_iters=19)):
+            x, r = Sf.sfseg_iterate(s, f, kern, 1.0, **kw)
+            torch.cuda.synchronize()
+            out.append((x.clone(), {k: r[k] for k in ("iters", "residual", "lambda_", "rayleigh", "r1", "r2", "flags")}))
+    for a, b in zip(out[:2], out[2:]):
+        assert torch.equal(a[0], b[0]) and a[1] == b[1]

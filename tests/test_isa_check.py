@@ -101,5 +101,5 @@ def test_built_device_code_keeps_the_waits(checker):
     for f in files:
         with open(os.path.join(path, f)) as fh:
             text = fh.read()
-        assert "v_mfma_f32_16x16x32_f16" in text
+        assert "v_mfma_f32_16x16x" in text
         assert checker._inline_asm_waits(text) == []
