@@ -121,6 +121,18 @@ __device__ __forceinline__ short load_b16(__amdgpu_buffer_rsrc_t r, uint32_t bof
 typedef short bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
 
+// The exact split of a float into three bfloat16 parts: each part is the rest
+// rounded to bfloat16. A finite value that rounds past the largest bfloat16
+// takes that as its first part; an infinite one is its own first part, with
+// nothing left.
+constexpr float SPLIT_CARE = 0x1.ffp127f;
+__device__ __forceinline__ short first_part(float v) {
+    const short b = bfbits(v);
+    const bool over = fabsf(v) >= SPLIT_CARE && fabsf(v) < INFINITY;
+    return over ? (short)(b - 1) : b;
+}
+__device__ __forceinline__ float split_rest(float v, float part) { return fabsf(v) == INFINITY ? 0.f : v - part; }
+
 // Tile of the layer kernels that stream a tile's frames: CT_H x CT_W voxels,
 // staged with the one-voxel rim their taps reach. A unit is a range of frames
 // of one tile ("segment"); neighbouring tiles of a segment share an XCD.
@@ -242,10 +254,12 @@ __global__ __launch_bounds__(256) void one_channel_kernel(Dims d, const float *f
                 float a = e0[slot][m], b = e1[slot][m];
 #pragma unroll
                 for (int k = 0; k < PARTS; ++k) {
-                    const uint32_t h = f32x2_to_bf16x2_bits(a, b);
+                    uint32_t h = f32x2_to_bf16x2_bits(a, b);
+                    if (PARTS > 1 && k == 0 && fmaxf(fabsf(a), fabsf(b)) >= SPLIT_CARE)
+                        h = (uint32_t)(uint16_t)first_part(a) | (uint32_t)(uint16_t)first_part(b) << 16;
                     q[k * CT_V + v] = h;
-                    a -= __uint_as_float(h << 16);  // exact remainder
-                    b -= __uint_as_float(h & 0xffff0000u);
+                    a = split_rest(a, __uint_as_float(h << 16));
+                    b = split_rest(b, __uint_as_float(h & 0xffff0000u));
                 }
             }
         }
@@ -879,8 +893,8 @@ __global__ __launch_bounds__(256) void wgrad1_kernel(Dims d, const short *x16, c
                     float rest = z[slot][k];
 #pragma unroll
                     for (int q = 0; q < PARTS; ++q) {
-                        const short b = bfbits(rest);
-                        rest -= bf2f(b);
+                        const short b = PARTS > 1 && q == 0 ? first_part(rest) : bfbits(rest);
+                        rest = split_rest(rest, bf2f(b));
 #pragma unroll
                         for (int s = 0; s < 3; ++s)
                             if (e >= s && e - s < WG_XC) dst[(q * 9 + s * 3) * 4 * WG_AP + e - s] = b;

@@ -320,3 +320,46 @@ def test_trained_net_versus_uniform_start(W):
     ratio = sum(r[2] for r in rows) / sum(r[3] for r in rows)
     print(f"wall-time ratio plain / net start: {ratio:.2f}; iterations plain {sum(r[0] for r in rows)}, "
           f"net {sum(r[1] for r in rows)}; fallbacks {sum(r[4] for r in rows)}")
+
+
+def _positive_net(W):
+    """Positive weights and biases: every activation of a positive input is positive."""
+    rng = np.random.default_rng(4)
+    p = rng.uniform(0.02, 0.05, W.init_params(seed=0).numel()).astype(np.float32)
+    return W.WarmStartNet(torch.from_numpy(p).to(DEV))
+
+
+@pytest.mark.parametrize("bad", [float("inf"), float("-inf")])
+def test_backward_of_an_infinite_output(W, bad):
+    """One infinite output well inside the volume: with positive weights and
+    activations every gradient is that infinity (no Inf - Inf, no 0 Inf)."""
+    shape = (10, 26, 40)
+    net = _positive_net(W)
+    f = torch.rand(shape, generator=torch.Generator(device=DEV).manual_seed(1), device=DEV) + 0.1
+    y = net.forward(f)
+    y[5, 13, 20] = bad
+    loss = net.backward(f, y, torch.zeros(shape, device=DEV))
+    torch.cuda.synchronize()
+    assert float(loss) == float("inf")
+    assert bool((net.grad == bad).all())
+
+
+@pytest.mark.parametrize("scale", [float.fromhex(h) for h in ("0x1.fep126", "0x1.ffp126", "0x1.fffffep126")])
+def test_backward_near_the_largest_float(W, scale):
+    """Output gradients between the largest bfloat16 and the largest float: the
+    last layer's gradients are products with them in float (one rounding of the
+    gradient and one of the product, and one of the sum of the parts)."""
+    net = _positive_net(W)
+    f = torch.full((1, 1, 1), 0.5, device=DEV)
+    y = torch.full((1, 1, 1), scale, device=DEV)
+    act = net.forward(f)
+    assert bool((act > 0).all())
+    net.backward(f, y, torch.zeros((1, 1, 1), device=DEV))
+    torch.cuda.synchronize()
+    g_y = 2.0 * scale  # the mean over one voxel
+    assert abs(float(net.grad[-1]) - g_y) <= 2.0 ** -23 * g_y
+    _, cache = oracle.net_forward(f.cpu().numpy(), W.unflatten(net.params), bf16=True)
+    grads = oracle.net_backward(cache, np.full((1, 1, 1), g_y))
+    w4 = net.grad[-1 - 16 * 27:-1].double().cpu().numpy()
+    ref = np.asarray(grads[3][0], np.float64).reshape(-1)
+    assert np.isfinite(w4).all() and rel(w4, ref) <= 1e-2
