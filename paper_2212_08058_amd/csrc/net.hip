@@ -121,6 +121,26 @@ __device__ __forceinline__ short load_b16(__amdgpu_buffer_rsrc_t r, uint32_t bof
 typedef short bf16x8 __attribute__((ext_vector_type(8)));
 typedef __bf16 bf16v8 __attribute__((ext_vector_type(8)));
 
+// A 16 x 16 accumulator and its products, of one K for its whole life. A product
+// that follows one of another K on the same accumulator has to come 4 wait
+// states later: with 0 to 3 between them, half of the sums lacked the earlier
+// product (v_mfma_f32_16x16x16_bf16 and v_mfma_f32_16x16x32_bf16, in either
+// order, small integers; with 4 or more all were right), and the compiler (clang
+// 22 of ROCm 7.2.0) puts none. The build's device-code check looks for such pairs.
+template <int K>
+struct Acc {
+    static_assert(K == 16 || K == 32, "bfloat16 products of 16 x 16 outputs");
+    f32x4 v = {0.f, 0.f, 0.f, 0.f};
+    __device__ __forceinline__ void add(const bf16x4 &a, const bf16x4 &b) {
+        static_assert(K == 16, "operands of a K = 16 product");
+        v = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a, b, v, 0, 0, 0);
+    }
+    __device__ __forceinline__ void add(const bf16v8 &a, const bf16v8 &b) {
+        static_assert(K == 32, "operands of a K = 32 product");
+        v = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, v, 0, 0, 0);
+    }
+};
+
 // The exact split of a float into three bfloat16 parts: each part is the rest
 // rounded to bfloat16. A finite value that rounds past the largest bfloat16
 // takes that as its first part; an infinite one is its own first part, with
@@ -289,10 +309,9 @@ __global__ __launch_bounds__(256) void one_channel_kernel(Dims d, const float *f
             qa[i] = lds + ((t - 1 + fa[i]) & 3) * PARTS * CT_V + oa[i];
             qb[i] = lds + ((t - 1 + fb[i]) & 3) * PARTS * CT_V + ob[i];
         }
-        f32x4 acc[8];
+        Acc<32> acc[8];
 #pragma unroll
         for (int r = 0; r < 8; ++r) {
-            acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
 #pragma unroll
             for (int k = PARTS - 1; k >= 0; --k) {  // smallest part first
                 uint4 b;
@@ -301,8 +320,7 @@ __global__ __launch_bounds__(256) void one_channel_kernel(Dims d, const float *f
                 b.y = __builtin_amdgcn_perm(qb[1][at], qa[1][at], sel[1]);
                 b.z = __builtin_amdgcn_perm(qb[2][at], qa[2][at], sel[2]);
                 b.w = __builtin_amdgcn_perm(qb[3][at], qa[3][at], sel[3]);
-                acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(bf16v8, aw),
-                                                                 __builtin_bit_cast(bf16v8, b), acc[r], 0, 0, 0);
+                acc[r].add(__builtin_bit_cast(bf16v8, aw), __builtin_bit_cast(bf16v8, b));
             }
         }
         // lane holds out[channel 4 kq + j][column n] of each row
@@ -314,10 +332,10 @@ __global__ __launch_bounds__(256) void one_channel_kernel(Dims d, const float *f
             bf16x4 o;
             if (MODE == 0) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) o[j] = bfbits(fmaxf(acc[r][j] + bv[j], 0.0f));
+                for (int j = 0; j < 4; ++j) o[j] = bfbits(fmaxf(acc[r].v[j] + bv[j], 0.0f));
             } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) o[j] = bf2f(mk[r][j]) > 0.0f ? bfbits(acc[r][j]) : (short)0;
+                for (int j = 0; j < 4; ++j) o[j] = bf2f(mk[r][j]) > 0.0f ? bfbits(acc[r].v[j]) : (short)0;
             }
             *reinterpret_cast<bf16x4 *>(out + v * C + 4 * kq) = o;
         }
@@ -339,8 +357,7 @@ __global__ __launch_bounds__(256) void one_channel_kernel(Dims d, const float *f
 // the order of its float sums is part of the network's arithmetic. MODE 1
 // takes two taps an instruction (K = 32): the nine (frame, x) taps of an input
 // row make four pairs and one single, whose upper half is zero in both
-// operands (no product of another K is mixed in: back-to-back K = 16 and
-// K = 32 products on one accumulator came out wrong).
+// operands (no product of another K is mixed in: see Acc).
 // Bound by memory (32 bytes a voxel read, 1.2 times with the rims, and 32
 // written) beside the matrix cores. The form it replaces (a wavefront per 16 x
 // 4 voxels, every row loaded from memory three times and shifted by lane
@@ -443,9 +460,7 @@ __global__ __launch_bounds__(256, MODE == 0 ? 4 : 2) void conv16_kernel(Dims d, 
                     mk[r] = *reinterpret_cast<const bf16x4 *>(mask + (((size_t)t * d.H + y) * d.W + x) * C + 4 * kq);
             }
         }
-        f32x4 acc[CV_ROWS];
-#pragma unroll
-        for (int r = 0; r < CV_ROWS; ++r) acc[r] = f32x4{0.f, 0.f, 0.f, 0.f};
+        Acc<PAIR ? 32 : 16> acc[CV_ROWS];
         if constexpr (PAIR) {
             const short *pp[5];
 #pragma unroll
@@ -470,7 +485,7 @@ __global__ __launch_bounds__(256, MODE == 0 ? 4 : 2) void conv16_kernel(Dims d, 
                     if (r < 0 || r >= CV_ROWS) continue;
 #pragma unroll
                     for (int p = 0; p < 5; ++p)
-                        acc[r] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ap[dy][p], b[p], acc[r], 0, 0, 0);
+                        acc[r].add(ap[dy][p], b[p]);
                 }
             }
         } else {
@@ -488,8 +503,7 @@ __global__ __launch_bounds__(256, MODE == 0 ? 4 : 2) void conv16_kernel(Dims d, 
                         if (r < 0 || r >= CV_ROWS) continue;
 #pragma unroll
                         for (int dx = 0; dx < 3; ++dx)
-                            acc[r] = __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(a1[dt * 9 + dy * 3 + dx], b[dx], acc[r], 0,
-                                                                               0, 0);
+                            acc[r].add(a1[dt * 9 + dy * 3 + dx], b[dx]);
                     }
                 }
             }
@@ -503,10 +517,10 @@ __global__ __launch_bounds__(256, MODE == 0 ? 4 : 2) void conv16_kernel(Dims d, 
             bf16x4 o;
             if (MODE == 0) {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) o[j] = bfbits(fmaxf(acc[r][j] + bv[j], 0.0f));
+                for (int j = 0; j < 4; ++j) o[j] = bfbits(fmaxf(acc[r].v[j] + bv[j], 0.0f));
             } else {
 #pragma unroll
-                for (int j = 0; j < 4; ++j) o[j] = bf2f(mk[r][j]) > 0.0f ? bfbits(acc[r][j]) : (short)0;
+                for (int j = 0; j < 4; ++j) o[j] = bf2f(mk[r][j]) > 0.0f ? bfbits(acc[r].v[j]) : (short)0;
             }
             *reinterpret_cast<bf16x4 *>(out + v * C + 4 * kq) = o;
         }
@@ -721,9 +735,7 @@ __global__ __launch_bounds__(256, 2) void wgrad16_kernel(Dims d, const short *a,
     const auto ra = act_rsrc(a, d), rg = act_rsrc(g, d);
     // staging: wavefront 0 .. 2 the row of frame t - 1 .. t + 1 of a, wavefront 3 the row of g
     const int half = lane & 1, bx = 4 * (lane >> 1);
-    f32x4 acc[NT], bacc = {0.f, 0.f, 0.f, 0.f};
-#pragma unroll
-    for (int tap = 0; tap < NT; ++tap) acc[tap] = f32x4{0.f, 0.f, 0.f, 0.f};
+    Acc<32> acc[NT], bacc;
     const int nxc = strip_count(d);
     const int rend = share_begin(d, unit + 1, nunits);
     int r = share_begin(d, unit, nunits);
@@ -770,7 +782,7 @@ __global__ __launch_bounds__(256, 2) void wgrad16_kernel(Dims d, const short *a,
                 const uint32_t next = *reinterpret_cast<const uint32_t *>(gp + 8);
                 // a at u = v + off: for x shift dx the voxel of g is u - dx
                 const bf16v8 gf[3] = {shift_down(m, next), __builtin_bit_cast(bf16v8, m), shift_up(m, prev)};
-                bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf[1], ones_frag(), bacc, 0, 0, 0);
+                bacc.add(gf[1], ones_frag());
 #pragma unroll
                 for (int k = 0; k < 9; ++k) {
                     const int slot = (k / 3) * 4 + ((y + k % 3 - 1) & 3);
@@ -778,8 +790,7 @@ __global__ __launch_bounds__(256, 2) void wgrad16_kernel(Dims d, const short *a,
                                                                         32 * wid + 8 * kv);
 #pragma unroll
                     for (int dx = 0; dx < 3; ++dx)
-                        acc[3 * k + dx] =
-                            __builtin_amdgcn_mfma_f32_16x16x32_bf16(gf[dx], af, acc[3 * k + dx], 0, 0, 0);
+                        acc[3 * k + dx].add(gf[dx], af);
                 }
             }
             if (more) store_rows(y + 2, y + 1, 0);
@@ -797,13 +808,13 @@ __global__ __launch_bounds__(256, 2) void wgrad16_kernel(Dims d, const short *a,
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int k = (4 * kv + j) * (C * NT + 1) + ch * NT + tap;
-                    red[k] = (w == 0 ? 0.0f : red[k]) + acc[tap][j];
+                    red[k] = (w == 0 ? 0.0f : red[k]) + acc[tap].v[j];
                 }
             if (ch == 0) {
 #pragma unroll
                 for (int j = 0; j < 4; ++j) {
                     const int k = (4 * kv + j) * (C * NT + 1) + C * NT;
-                    red[k] = (w == 0 ? 0.0f : red[k]) + bacc[j];
+                    red[k] = (w == 0 ? 0.0f : red[k]) + bacc.v[j];
                 }
             }
         }
@@ -855,7 +866,7 @@ __global__ __launch_bounds__(256) void wgrad1_kernel(Dims d, const short *x16, c
         zoff[blk] = ((s % 3) * 3 + s / 9) * 4 * WG_AP + 32 * wid + 8 * kv;
         zdy[blk] = (s / 3) % 3 - 1;
     }
-    f32x4 acc[2] = {f32x4{0.f, 0.f, 0.f, 0.f}, f32x4{0.f, 0.f, 0.f, 0.f}}, bacc = {0.f, 0.f, 0.f, 0.f};
+    Acc<32> acc[2], bacc;
     const int nxc = strip_count(d);
     const int rend = share_begin(d, unit + 1, nunits);
     int r = share_begin(d, unit, nunits);
@@ -913,7 +924,7 @@ __global__ __launch_bounds__(256) void wgrad1_kernel(Dims d, const short *x16, c
             if (X0 + 32 * wid < d.W) {
                 const bf16v8 xf =
                     *reinterpret_cast<const bf16v8 *>(Lx + (y & 1) * WG_ROW_A + c * WG_AP + 32 * wid + 8 * kv);
-                if constexpr (MODE == 1) bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, ones_frag(), bacc, 0, 0, 0);
+                if constexpr (MODE == 1) bacc.add(xf, ones_frag());
 #pragma unroll
                 for (int q = PARTS - 1; q >= 0; --q) {  // smallest part first
                     bf16v8 zf[2];
@@ -921,11 +932,11 @@ __global__ __launch_bounds__(256) void wgrad1_kernel(Dims d, const short *x16, c
                     for (int b = 0; b < 2; ++b)
                         zf[b] = *reinterpret_cast<const bf16v8 *>(Lz + q * ZROWS * WG_AP + zoff[b] +
                                                                   ((y + zdy[b]) & 3) * WG_AP);
-                    acc[0] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, zf[0], acc[0], 0, 0, 0);
-                    acc[1] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(xf, zf[1], acc[1], 0, 0, 0);
+                    acc[0].add(xf, zf[0]);
+                    acc[1].add(xf, zf[1]);
                     // column 13 of block 0 is the centre tap
                     if constexpr (MODE == 4)
-                        bacc = __builtin_amdgcn_mfma_f32_16x16x32_bf16(ones_frag(), zf[0], bacc, 0, 0, 0);
+                        bacc.add(ones_frag(), zf[0]);
                 }
             }
             if (more) store_rows(y + 1, y + 2, 0);
@@ -943,13 +954,13 @@ __global__ __launch_bounds__(256) void wgrad1_kernel(Dims d, const short *x16, c
                     if (!tapok[blk]) continue;
                     const int ch = 4 * kv + j, tap = 16 * blk + c;
                     const int k = MODE == 1 ? ch * (NT + 1) + tap : ch * NT + tap;
-                    red[k] = (w == 0 ? 0.0f : red[k]) + acc[blk][j];
+                    red[k] = (w == 0 ? 0.0f : red[k]) + acc[blk].v[j];
                 }
             if (MODE == 1 ? c == 0 : lane == 13) {
 #pragma unroll
                 for (int j = 0; j < (MODE == 1 ? 4 : 1); ++j) {
                     const int k = MODE == 1 ? (4 * kv + j) * (NT + 1) + NT : C * NT;
-                    red[k] = (w == 0 ? 0.0f : red[k]) + bacc[j];
+                    red[k] = (w == 0 ? 0.0f : red[k]) + bacc.v[j];
                 }
             }
         }

@@ -78,28 +78,42 @@ PRODUCT = """_Z6kernelv:
 def test_inline_assembly_behind_a_product(checker, dst, src, states, ok):
     between = "" if states == 0 else "\ts_nop %d\n" % (states - 1)
     text = PRODUCT.format(between=between, dst=dst, src=src, back="\ts_nop 0\n")
-    found = checker._inline_asm_waits(text)
+    found = checker._matrix_core_waits(text)
     assert (found == []) == ok, found
     # the compiler's own instructions are its business
-    assert checker._inline_asm_waits(text.replace("\t;;#ASMSTART\n", "").replace("\t;;#ASMEND\n", "")) == []
+    assert checker._matrix_core_waits(text.replace("\t;;#ASMSTART\n", "").replace("\t;;#ASMEND\n", "")) == []
 
 
 @pytest.mark.parametrize("back,ok", [("", False), ("\ts_nop 0\n", True)])
 def test_inline_assembly_in_front_of_a_product(checker, back, ok):
     # around the loop: a write of an operand, a branch, the product
-    found = checker._inline_asm_waits(PRODUCT.format(between="", dst="v9", src="v40", back=back))
+    found = checker._matrix_core_waits(PRODUCT.format(between="", dst="v9", src="v40", back=back))
     assert [(n, need) for _, _, _, n, need in found] == ([] if ok else [(1, 2)])
 
 
+@pytest.mark.parametrize("second,states,ok", [
+    ("v_mfma_f32_16x16x16_bf16 v[0:3], v[16:17], v[18:19], v[0:3]", 0, False),
+    ("v_mfma_f32_16x16x16_bf16 v[0:3], v[16:17], v[18:19], v[0:3]", 3, False),
+    ("v_mfma_f32_16x16x16_bf16 v[0:3], v[16:17], v[18:19], v[0:3]", 4, True),
+    ("v_mfma_f32_16x16x32_bf16 v[0:3], v[16:19], v[20:23], v[0:3]", 0, True),       # the same shape
+    ("v_mfma_f32_16x16x16_bf16 v[24:27], v[16:17], v[18:19], v[24:27]", 0, True)])  # another accumulator
+def test_products_of_two_shapes_on_one_accumulator(checker, second, states, ok):
+    nop = "\ts_nop %d\n" % (states - 1) if states else ""
+    text = ("_Z6kernelv:\n\tv_mfma_f32_16x16x32_bf16 v[0:3], v[4:7], v[8:11], v[12:15]\n" + nop + "\t" + second +
+            "\n\ts_endpgm\n.Lfunc_end0:\n")
+    found = checker._matrix_core_waits(text)
+    assert [(n, need) for _, _, _, n, need in found] == ([] if ok else [(states, 4)])
+
+
 def test_built_device_code_keeps_the_waits(checker):
-    """The assembly the last build left: matrix-core products are there, and no
-    inline assembly lies too close to one."""
+    """The assembly the last build left: matrix-core products are there, and
+    nothing lies too close to one."""
     path = os.path.join(HERE, "..", "_build")
-    files = [f for f in ("kernels_f32.hip.s", "kernels_bf16.hip.s", "sfseg.hip.s") if os.path.exists(os.path.join(path, f))]
+    files = [f for f in ("kernels_f32.hip.s", "kernels_bf16.hip.s", "sfseg.hip.s", "net.hip.s") if os.path.exists(os.path.join(path, f))]
     if not files:
         pytest.skip("no device assembly here")
     for f in files:
         with open(os.path.join(path, f)) as fh:
             text = fh.read()
-        assert "v_mfma_f32_16x16x" in text
-        assert checker._inline_asm_waits(text) == []
+        assert "v_mfma_f32_" in text
+        assert checker._matrix_core_waits(text) == []
