@@ -4,7 +4,9 @@
 #include <algorithm>
 #include <cmath>
 #include <cstring>
+#include <functional>
 #include <numeric>
+#include <queue>
 #include <vector>
 
 #include "../../include/stpi.h"
@@ -37,6 +39,60 @@ struct stpi_plan {
 };
 
 namespace stpi {
+
+// How long a step over volumes beyond the last-level cache takes on a
+// matrix-core tile, in frame phases of the wide tile (one workgroup per CU): the
+// tiles, longest first, go to the CU with the least to do; where two share a CU
+// a phase takes 1.14, alone 0.85. Measured, ms for 20 iterations, float, r =
+// (8, 3), 32 x 64 / 32 x 128 (and the ratio here): 1 clip of 96x480x854 4.80 / 5.87
+// (0.85), 3 of them 10.7 / 12.1 (0.99), 5 of 96x360x640 9.97 / 11.5 (0.99), 8 uneven
+// ones up to 77x300x484 3.53 / 4.38 (0.85); 2 of 64x480x854 5.12 / 4.69 (1.14), 4 of
+// them 10.3 / 9.02 (1.14), 6 of 48x480x854 10.1 / 10.2 (1.04), one of 96x480x854
+// beside 12 of 8 frames 8.22 / 7.04 (1.12), uneven ones: 23 up to 55x400x527 6.69 /
+// 6.37 (1.01), 24 up to 55x286x446 5.60 / 5.07 (1.04), 21 up to 96x439x765 17.1 /
+// 15.6 (1.11).
+static double batch_span(const BatchVariant &v, const std::vector<ClipDesc> &clips) {
+    const double shared = 1.14, alone = 0.85;
+    std::vector<int> tiles;
+    for (const auto &c : clips)
+        tiles.insert(tiles.end(), (size_t)((c.W + v.TW - 1) / v.TW) * ((c.H + v.TH - 1) / v.TH),
+                     segment_phases(c.T, v.RT, 1));
+    std::sort(tiles.begin(), tiles.end(), std::greater<int>());
+    struct Cu {
+        int64_t given = 0;       // phases dealt to it
+        double time = 0.0;       // when the two running tiles had rest[] left
+        int rest[2] = {0, 0};
+    };
+    std::vector<Cu> cu(device_cus());
+    auto later = [&](int a, int b) { return cu[a].given > cu[b].given; };
+    std::priority_queue<int, std::vector<int>, decltype(later)> least(later);
+    for (int i = 0; i < (int)cu.size(); ++i) least.push(i);
+    const bool two = v.blocks_per_cu() >= 2;
+    for (const int t : tiles) {
+        const int i = least.top();
+        least.pop();
+        Cu &c = cu[i];
+        c.given += t;
+        if (!two) {
+            c.time += t;
+        } else {
+            if (c.rest[0] && c.rest[1]) {  // until the shorter one ends
+                const int m = std::min(c.rest[0], c.rest[1]);
+                c.time += m * shared;
+                c.rest[0] -= m;
+                c.rest[1] -= m;
+            }
+            c.rest[c.rest[0] ? 1 : 0] = t;
+        }
+        least.push(i);
+    }
+    double span = 0.0;
+    for (const Cu &c : cu) {
+        const int both = std::min(c.rest[0], c.rest[1]), last = std::max(c.rest[0], c.rest[1]) - both;
+        span = std::max(span, c.time + both * shared + last * alone);
+    }
+    return span;
+}
 
 static const BatchVariant *choose_batch_variant(const stpi_problem *proto, const std::vector<ClipDesc> &clips) {
     const DtypeOps *ops = ops_for(proto->dtype);
@@ -91,17 +147,17 @@ static const BatchVariant *choose_batch_variant(const stpi_problem *proto, const
     }
     if (!best || best->PIPE != 3 || best->blocks_per_cu() < 2) return best;
     // Where the volumes of a step do not stay in the 256 MB last-level cache, the
-    // wide matrix-core tile, which re-reads less halo, beats the one that shares
-    // a CU with another (as mfma_tile_cost in host.cpp). Measured, ms for 20
-    // iterations, 32 x 64 / 32 x 128, float, r = (8, 3): 24 clips of 92 M voxels
-    // 10.5 / 7.2, 24 of 113 M 10.7 / 9.6, 12 of 104 M 8.75 / 8.11, 16 of 147 M
-    // 10.87 / 10.83, 24 of 291 M 23.6 / 22.1.
+    // wide matrix-core tile, which re-reads less halo, is the better one, unless
+    // its fewer tiles leave compute units idle: clips are not cut into frame
+    // segments here, and a narrow tile runs faster while it has a CU to itself.
     double bytes = 0.0;
     for (const auto &c : clips) bytes += 3.0 * c.T * c.H * c.W * (double)ops->elem;
     if (bytes > 256.0 * 1024 * 1024)
         for (int i = 0; i < ops->nbatch; ++i) {
             const BatchVariant &b = ops->batch_variants[i];
-            if (b.PIPE == 3 && b.RS == best->RS && b.RT == best->RT && b.TH * b.TW > best->TH * best->TW) return &b;
+            if (b.PIPE == 3 && b.RS == best->RS && b.RT == best->RT && b.TH * b.TW > best->TH * best->TW &&
+                batch_span(b, clips) < batch_span(*best, clips))
+                return &b;
         }
     return best;
 }

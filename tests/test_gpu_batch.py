@@ -353,3 +353,16 @@ def test_batch_tile_by_total_volume(P, shapes, tile):
         y, q = Pm.power_iterate(f, kern, iters=3)
         assert float((xv.double() - y.double()).norm() / y.double().norm()) <= 1e-6
         assert abs(r["lambda_"] - q["lambda_"]) <= 1e-6 * q["lambda_"]
+
+
+@pytest.mark.parametrize("shapes,tile", [
+    ([(96, 480, 854)], (32, 64)), ([(96, 360, 640)] * 2, (32, 64)), ([(96, 480, 854)] * 3, (32, 64)),
+    ([(96, 360, 640)] * 5, (32, 64)), ([(64, 480, 854)] * 2, (32, 128)), ([(64, 480, 854)] * 4, (32, 128)),
+    ([(50, 480, 854)] * 3, (32, 64)), ([(96, 480, 854)] + [(8, 480, 854)] * 12, (32, 128)),
+    ([(40, 480, 854)] * 20, (32, 128))])
+def test_batch_tile_of_few_long_clips(P, shapes, tile):
+    """Beyond 256 MB of step volumes the wide tile is taken only where its fewer
+    tiles fill the chip as well: the faster of the two in every measured case."""
+    Pm, B = P
+    info = B.BatchPlan(shapes, Pm.Kernel(4.0, 1.5, 8, 3)).info()
+    assert info["PIPE"] == 3 and (info["TH"], info["TW"]) == tile
