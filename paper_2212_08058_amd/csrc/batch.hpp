@@ -73,7 +73,7 @@ constexpr int batch_min_waves() {
 // PIPE: 1 runs each tile through the software-pipelined tile loop, 3 through
 // the matrix-core tile loop in product form (see FwdOpP: every clip's
 // buffers hold f x g, with g from the clip's own bound on |f|).
-template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX, int PIPE>
+template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX, int PIPE, bool ODD>
 __global__ __launch_bounds__(NTHR, (batch_min_waves<TH, TW, NTHR, PIPE, RS <= 8 ? 8 : 16,
                                                      std::is_same<ST, bf16>::value ? 1 : 2>()))
 void batch_step_kernel(BatchArgs<ST> a) {
@@ -137,7 +137,7 @@ void batch_step_kernel(BatchArgs<ST> a) {
         double d1 = 0.0, d2 = 0.0;
         if (!__builtin_amdgcn_readfirstlane(st_->done)) {
             const int cur = __builtin_amdgcn_readfirstlane(st_->cur);
-            FwdOp<ST> op;
+            FwdOp<ST, ODD> op;
             op.f = a.f + cd.offset;
             op.src = (cur ? a.buf1 : a.buf0) + cd.offset;
             op.dst = (cur ? a.buf0 : a.buf1) + cd.offset;
@@ -148,12 +148,13 @@ void batch_step_kernel(BatchArgs<ST> a) {
             const int T = __builtin_amdgcn_readfirstlane(cd.T);
             const int H = __builtin_amdgcn_readfirstlane(cd.H), W = __builtin_amdgcn_readfirstlane(cd.W);
             op.cut = tx0 + TW > W;  // 4-wide epilogue loads read past the right edge here
+            if (ODD) op.last = last_of_odd_frame(H, W, tx0, ty0, TH, TW);
             if constexpr (PIPE == 3) {
                 // the single-clip product-form step's arithmetic, on this clip's state
                 const float fb = __uint_as_float(st_->ubound);
                 const int e = bound_exponent(fb, PRODUCT_ELIM);
                 const bool first = __builtin_amdgcn_readfirstlane(st_->pform) == 2;
-                FwdOpP<ST> pp;
+                FwdOpP<ST, ODD> pp;
                 pp.f = op.f;
                 pp.src = first ? op.f : op.src;
                 pp.dst = op.dst;
@@ -163,6 +164,7 @@ void batch_step_kernel(BatchArgs<ST> a) {
                 pp.plane = op.plane;
                 pp.pbytes = op.pbytes;
                 pp.cut = tx0 + TW > W;
+                pp.last = op.last;
                 // staging power of two from the input's own maximum (as the single-clip step)
                 const float win = first ? fb : __uint_as_float(st_->wmax[cur]);
                 float umul;
@@ -260,6 +262,7 @@ struct BatchLaunch {
     double *partials;
     const int32_t *active_clip, *active_cum;
     int ntiles, nclips, grid;
+    int odd;  // 1: some clip has frames of an odd number of voxels (see odd_frames_apart)
     double gs[2 * 16 + 1];
     double gt[2 * 8 + 1];
 };
@@ -293,7 +296,14 @@ hipError_t launch_batch(const BatchLaunch &L, hipStream_t stream) {
     for (int i = 0; i < 2 * 8 + 1; ++i) a.taps.gt[i] = CT(0);
     for (int d = -RS; d <= RS; ++d) a.taps.gs[d + RS] = (CT)L.gs[d + 16];
     for (int d = -RT; d <= RT; ++d) a.taps.gt[d + RT] = (CT)L.gt[d + 8];
-    hipLaunchKernelGGL((batch_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, PIPE>), dim3(L.grid), dim3(NTHR), 0,
+    if constexpr (odd_frames_apart<ST, QX, PIPE>()) {
+        if (L.odd) {
+            hipLaunchKernelGGL((batch_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, PIPE, true>), dim3(L.grid),
+                               dim3(NTHR), 0, stream, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((batch_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, PIPE, false>), dim3(L.grid), dim3(NTHR), 0,
                        stream, a);
     return hipGetLastError();
 }
@@ -301,7 +311,7 @@ hipError_t launch_batch(const BatchLaunch &L, hipStream_t stream) {
 template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX, int PIPE>
 int batch_blocks_per_cu() {
     int n = 0;
-    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, PIPE>,
+    if (hipOccupancyMaxActiveBlocksPerMultiprocessor(&n, batch_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, PIPE, false>,
                                                      NTHR, 0) != hipSuccess)
         n = 1;
     return n > 0 ? n : 1;

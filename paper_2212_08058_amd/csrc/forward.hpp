@@ -67,11 +67,47 @@ struct FwdArgs {
     Taps<CT> taps;
 };
 
+// A 4-wide load of bfloat16 values reads words of two. Where a frame's last
+// voxel has no partner (a frame of an odd number of voxels), its word reaches
+// past the frame's range and reads as 0 whole: the workgroup that owns the voxel
+// loads it by itself as well and puts it in place. Kernels of their own (ODD)
+// do so, as the two loads and registers cost the others 3% (20 iterations of
+// 64x480x854 1765 -> 1818 us).
+template <class ST, int QX, int PIPE>
+constexpr bool odd_frames_apart() {
+    return std::is_same<ST, bf16>::value && QX == 4 && PIPE != 2 && PIPE != 4;
+}
+constexpr uint32_t NO_LAST = 1u;  // no element's offset: the voxel is in another tile
+inline __device__ uint32_t last_of_odd_frame(int H, int W, int x0, int y0, int TH, int TW) {
+    if ((H & W & 1) == 0 || x0 + TW < W || y0 + TH < H) return NO_LAST;
+    return (uint32_t)((size_t)H * W - 1) * (uint32_t)sizeof(bf16);
+}
+// Two operand arrays of the epilogue, and with ODD the last voxel's two values.
+template <class CT, int IPT, int QX, bool ODD>
+struct LastVoxel {
+    __device__ __forceinline__ void place(uint32_t, const uint32_t (&)[IPT][QX], CT (&)[IPT][QX], CT (&)[IPT][QX]) const {}
+};
+template <class CT, int IPT, int QX>
+struct LastVoxel<CT, IPT, QX, true> {
+    CT a, b;
+    __device__ __forceinline__ void place(uint32_t last, const uint32_t (&off)[IPT][QX], CT (&va)[IPT][QX],
+                                          CT (&vb)[IPT][QX]) const {
+        if (last == NO_LAST) return;
+#pragma unroll
+        for (int i = 0; i < IPT; ++i)
+#pragma unroll
+            for (int q = 0; q < QX; q += 2) {  // a group starts on a multiple of 4, the voxel's index is even
+                va[i][q] = off[i][q] == last ? a : va[i][q];
+                vb[i][q] = off[i][q] == last ? b : vb[i][q];
+            }
+    }
+};
+
 // u = f * x_stored; z = s f acc with s the scale that makes x unit;
 // p1 += z * x_stored, p2 += z^2 on the values as stored. The products are
 // formed in double, where they are exact for float and bfloat16 operands, so
 // the residual sqrt(2 - 2 cos) keeps its accuracy near convergence.
-template <class ST>
+template <class ST, bool ODD = false>
 struct FwdOp {
     using CT = typename Compute<ST>::type;
     using IO = BufIO<ST>;
@@ -84,6 +120,7 @@ struct FwdOp {
     size_t plane;     // elements per frame
     uint32_t pbytes;  // bytes per frame
     bool cut = false;  // epilogue operands came from 4-wide loads that groups cut by the right edge extend past it
+    uint32_t last = NO_LAST;  // ODD: see last_of_odd_frame
     // false: the epilogue reads the previous iterate on an empty range (as 0),
     // so p1 is 0. A chain of a fixed count of steps uses p1 (the cosine with
     // the previous iterate: the residual and the Rayleigh quotient) only on
@@ -114,6 +151,7 @@ struct FwdOp {
     template <int IPT, int QX>
     struct OutRaw {
         CT f[IPT][QX], x[IPT][QX];
+        LastVoxel<CT, IPT, QX, ODD> last;
     };
     // Epilogue operands, in a fixed count of memory instructions whatever the
     // lanes: with QX = 4 each group moves with one 4-wide access at its first
@@ -125,6 +163,12 @@ struct FwdOp {
                                               bool live = true) const {
         const auto rf = make_rsrc(f + (size_t)(live ? t : 0) * plane, live ? pbytes : 0u);
         const auto rx = make_rsrc(src + (size_t)(live ? t : 0) * plane, live && prev ? pbytes : 0u);
+        if constexpr (ODD) {
+            if (last != NO_LAST) {
+                raw.last.a = IO::load(rf, last);
+                raw.last.b = IO::load(rx, last);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < IPT; ++i) {
             if constexpr (QX == 4) {
@@ -185,8 +229,10 @@ struct FwdOp {
         d2 += emit ? p2 : 0.0;
     }
     template <int IPT, int QX>
-    __device__ __forceinline__ void emit_frame(int t, const CT (&acc)[IPT][QX], const OutRaw<IPT, QX> &raw,
+    __device__ __forceinline__ void emit_frame(int t, const CT (&acc)[IPT][QX], const OutRaw<IPT, QX> &loaded,
                                                const uint32_t (&off)[IPT][QX], double &d1, double &d2) const {
+        OutRaw<IPT, QX> raw = loaded;
+        raw.last.place(last, off, raw.f, raw.x);
         const auto rz = make_rsrc(dst + (size_t)t * plane, pbytes);
         if (vout) {
             const auto rv = make_rsrc(vout + (size_t)t * plane, pbytes);
@@ -247,7 +293,7 @@ __device__ __forceinline__ float recip_or_zero(float fv) {
 // iterate, and the split's half-precision parts keep their full precision
 // for every value within 2^14 of it.
 
-template <class ST>
+template <class ST, bool ODD = false>
 struct FwdOpP {
     using CT = float;
     using IO = BufIO<ST>;
@@ -263,6 +309,7 @@ struct FwdOpP {
     mutable float wmax = 0.f;  // max |w_new| stored by this thread (the next step's staging bound)
     bool cut = false;          // as FwdOp::cut
     bool prev = true;          // as FwdOp::prev
+    uint32_t last = NO_LAST;   // as FwdOp::last
 
     template <int NPF>
     struct Raw {
@@ -281,12 +328,19 @@ struct FwdOpP {
     template <int IPT, int QX>
     struct OutRaw {
         CT f[IPT][QX], u[IPT][QX];
+        LastVoxel<CT, IPT, QX, ODD> last;
     };
     template <int IPT, int QX>  // as FwdOp::fetch_out
     __device__ __forceinline__ void fetch_out(int t, const uint32_t (&off)[IPT][QX], OutRaw<IPT, QX> &raw,
                                               bool live = true) const {
         const auto rf = make_rsrc(f + (size_t)(live ? t : 0) * plane, live ? pbytes : 0u);
         const auto ru = make_rsrc(src + (size_t)(live ? t : 0) * plane, live && prev ? pbytes : 0u);
+        if constexpr (ODD) {
+            if (last != NO_LAST) {
+                raw.last.a = IO::load(rf, last);
+                raw.last.b = IO::load(ru, last);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < IPT; ++i) {
             if constexpr (QX == 4) {
@@ -302,8 +356,10 @@ struct FwdOpP {
         }
     }
     template <int IPT, int QX>
-    __device__ __forceinline__ void emit_frame(int t, const CT (&acc)[IPT][QX], const OutRaw<IPT, QX> &raw,
+    __device__ __forceinline__ void emit_frame(int t, const CT (&acc)[IPT][QX], const OutRaw<IPT, QX> &loaded,
                                                const uint32_t (&off)[IPT][QX], double &d1, double &d2) const {
+        OutRaw<IPT, QX> raw = loaded;
+        raw.last.place(last, off, raw.f, raw.u);
         const auto rw = make_rsrc(dst + (size_t)t * plane, pbytes);
         CT wr[IPT][QX], r[IPT][QX];  // what the stores leave in memory, 1/f
 #pragma unroll
@@ -362,7 +418,7 @@ struct FwdOpP {
 // per workgroup with all its input frames at once (stencil_tile_gather; the
 // launch's frame segments are the T single frames).
 // PF: product-form chain step (PIPE 3, iterate mode only).
-template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX, int OCC, int PIPE, bool PF>
+template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX, int OCC, int PIPE, bool PF, bool ODD>
 __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
     using CT = typename Compute<ST>::type;
     using G = Geometry<RS, RT, TH, TW, NTHR, RY, QX>;
@@ -387,7 +443,7 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
     if (unit < 0) return;
     const int tile = unit % ntiles, seg = unit / ntiles;
     const int t0 = (int)((int64_t)seg * a.T / a.nseg), t1 = (int)((int64_t)(seg + 1) * a.T / a.nseg);
-    FwdOp<ST> op;
+    FwdOp<ST, ODD> op;
     op.f = a.f;
     double scale;
     __shared__ DevState st;  // iterate mode: the state this step works on
@@ -416,6 +472,7 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
     float wm = 0.f;  // product form: max |w| stored by this thread
     const int x0 = (tile % nbx) * TW, y0 = (tile / nbx) * TH;
     op.cut = x0 + TW > a.W;  // 4-wide epilogue loads read past the right edge here
+    if (ODD) op.last = last_of_odd_frame(a.H, a.W, x0, y0, TH, TW);
     op.prev = !a.no_prev;
     if constexpr (PIPE == 3) {
         // space taps centred at 16 (the kernel's are centred at RS)
@@ -433,7 +490,7 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
             const int e = bound_exponent(bound, PRODUCT_ELIM);
             const bool first = __builtin_amdgcn_readfirstlane(st.pform) == 2;
             const int cur = __builtin_amdgcn_readfirstlane(st.cur);
-            FwdOpP<ST> pp;
+            FwdOpP<ST, ODD> pp;
             pp.f = a.f;
             pp.src = first ? a.f : op.src;
             pp.dst = op.dst;
@@ -444,6 +501,7 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
             pp.pbytes = op.pbytes;
             pp.cut = x0 + TW > a.W;
             pp.prev = op.prev;
+            pp.last = op.last;
             // staging power of two from the input's own maximum
             const float win = first ? bound : __uint_as_float(st.wmax[cur]);
             float umul;
@@ -524,7 +582,14 @@ hipError_t launch_fwd(const FwdLaunch &L, hipStream_t stream) {
     for (int d = -RT; d <= RT; ++d) a.taps.gt[d + RT] = (CT)L.gt[d + 8];
     const int nunits = ((L.W + TW - 1) / TW) * ((L.H + TH - 1) / TH) * a.nseg;
     const int per = (nunits + NUM_XCD - 1) / NUM_XCD;
-    hipLaunchKernelGGL((fwd_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, OCC, PIPE, PF>), dim3(per * NUM_XCD),
+    if constexpr (odd_frames_apart<ST, QX, PIPE>()) {
+        if (L.H & L.W & 1) {
+            hipLaunchKernelGGL((fwd_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, OCC, PIPE, PF, true>),
+                               dim3(per * NUM_XCD), dim3(NTHR), 0, stream, a);
+            return hipGetLastError();
+        }
+    }
+    hipLaunchKernelGGL((fwd_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, OCC, PIPE, PF, false>), dim3(per * NUM_XCD),
                        dim3(NTHR), 0, stream, a);
     return hipGetLastError();
 }
@@ -536,7 +601,7 @@ template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX, in
 int fwd_blocks_per_cu() {
     int n = 0;
     if (hipOccupancyMaxActiveBlocksPerMultiprocessor(
-            &n, fwd_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, OCC, PIPE, PIPE == 3>, NTHR, 0) != hipSuccess)
+            &n, fwd_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, OCC, PIPE, PIPE == 3, false>, NTHR, 0) != hipSuccess)
         n = 1;
     return n > 0 ? n : 1;
 }

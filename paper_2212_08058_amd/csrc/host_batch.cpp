@@ -223,6 +223,7 @@ static int enqueue_batch(stpi_plan *P, const void *f, void *x, void *ws, int ini
     BL.ntiles = P->ntiles;
     BL.nclips = P->nclips;
     BL.grid = P->grid;
+    for (const auto &c : P->clips) BL.odd |= c.H & c.W & 1;
     make_taps(&P->proto, BL.gs, BL.gt);
     const int steps = part == 0 ? max_iters : CHAIN_CHUNK;
     for (int k = 0; k < steps; ++k) {

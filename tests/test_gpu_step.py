@@ -562,3 +562,50 @@ def test_gather_on_up_to_four_workgroups_per_cu(P, dtype, shape, gather):
         N.lib.stpi_set_variant(-1)
     assert rel_l2(x.double().cpu().numpy(), y.double().cpu().numpy()) <= 4 * TOL[dtype]
     assert abs(r["lambda_"] - q["lambda_"]) <= 4 * TOL[dtype] * q["lambda_"]
+
+
+@pytest.mark.parametrize("kp", [(2.0, 1.0, 4, 2), (4.0, 1.5, 8, 3), (5.0, 2.0, 15, 5), (3.0, 1.0, 12, 3)])
+@pytest.mark.parametrize("shape", [(3, 1, 1), (3, 1, 3), (3, 5, 7), (4, 33, 65), (2, 17, 131), (2, 31, 217)])
+def test_bfloat16_frames_of_an_odd_number_of_voxels(P, shape, kp):
+    """The last voxel of such a frame shares no word with another of its frame:
+    every voxel of a step and of two iterations, with every variant, against the
+    oracle. A value is rounded to 8 significant bits once per step, and its
+    neighbours' roundings before that average: 2^-7 per voxel and step."""
+    import ctypes
+    from paper_2212_08058_amd import _native as N
+    kern, k = P.Kernel(*kp), OKf(*kp)
+    fd = to_dev(np.random.default_rng(sum(shape)).uniform(0.2, 1.0, shape), torch.bfloat16)
+    f64 = fd.double().cpu().numpy()
+    zr = oracle.apply(f64, f64, k)
+    xr, _ = oracle.iterate(f64, k, iters=2)
+    info, bad = (ctypes.c_int * 9)(), []
+    try:
+        for i in range(-1, N.lib.stpi_variant_count(N.STPI_BF16)):
+            if i >= 0:
+                assert N.lib.stpi_variant_info(N.STPI_BF16, i, info) == 0
+                if info[0] < kern.r_s or info[1] < kern.r_t:
+                    continue
+            assert N.lib.stpi_set_variant(i) == 0
+            z, _ = P.step(fd, fd, kern)
+            x, _ = P.power_iterate(fd, kern, iters=2, check=False)
+            torch.cuda.synchronize()
+            ez = np.max(np.abs(z.double().cpu().numpy() - zr) / zr)
+            ex = np.max(np.abs(x.double().cpu().numpy() - xr) / xr)
+            if not (ez <= 2.0 ** -7 and ex <= 2.0 ** -6):
+                bad.append((i, info[8], ez, ex))
+    finally:
+        N.lib.stpi_set_variant(-1)
+    assert not bad, bad
+
+
+def test_bfloat16_batch_of_odd_frames(P):
+    """As above for clips in one flat buffer."""
+    from paper_2212_08058_amd import batch
+    shapes = [(3, 1, 1), (1, 1, 3), (3, 5, 7), (2, 33, 65), (2, 17, 131)]
+    for kp in ((2.0, 1.0, 4, 2), (4.0, 1.5, 8, 3), (5.0, 2.0, 15, 5)):
+        plan = batch.BatchPlan(shapes, P.Kernel(*kp), torch.bfloat16)
+        fs = [to_dev(np.random.default_rng(i).uniform(0.2, 1.0, s), torch.bfloat16) for i, s in enumerate(shapes)]
+        x, _ = plan.iterate(plan.pack(fs), max_iters=2, tol=0.0)
+        for f, v in zip(fs, plan.views(x)):
+            xr, _ = oracle.iterate(f.double().cpu().numpy(), OKf(*kp), iters=2)
+            assert np.max(np.abs(v.double().cpu().numpy() - xr) / xr) <= 2.0 ** -6, (kp, tuple(f.shape))
