@@ -145,26 +145,27 @@ hipError_t batch_sumsq_impl(const void *x, const ClipDesc *clips, int nclips, do
     return hipGetLastError();
 }
 hipError_t batch_normalize_impl(void *x, const void *buf1, const ClipDesc *clips, const DevState *states, int nclips,
-                                hipStream_t s) {
-    hipLaunchKernelGGL(batch_normalize_kernel<ST_>, dim3(BATCH_STREAM_BLOCKS, nclips), dim3(256), 0, s, (ST_ *)x,
+                                int blocks, hipStream_t s) {
+    hipLaunchKernelGGL(batch_normalize_kernel<ST_>, dim3(blocks, nclips), dim3(256), 0, s, (ST_ *)x,
                        (const ST_ *)buf1, clips, states);
     return hipGetLastError();
 }
 
-hipError_t batch_bound_impl(const void *f, const ClipDesc *clips, DevState *states, int nclips, hipStream_t s) {
-    hipLaunchKernelGGL(batch_bound_kernel<ST_>, dim3(BATCH_STREAM_BLOCKS, nclips), dim3(256), 0, s, (const ST_ *)f,
+hipError_t batch_bound_impl(const void *f, const ClipDesc *clips, DevState *states, int nclips, int blocks,
+                            hipStream_t s) {
+    hipLaunchKernelGGL(batch_bound_kernel<ST_>, dim3(blocks, nclips), dim3(256), 0, s, (const ST_ *)f,
                        clips, states);
     return hipGetLastError();
 }
 hipError_t batch_to_product_impl(const void *f, const void *x, void *buf1, const ClipDesc *clips, DevState *states,
-                                 int nclips, hipStream_t s) {
-    hipLaunchKernelGGL(batch_to_product_kernel<ST_>, dim3(BATCH_STREAM_BLOCKS, nclips), dim3(256), 0, s,
+                                 int nclips, int blocks, hipStream_t s) {
+    hipLaunchKernelGGL(batch_to_product_kernel<ST_>, dim3(blocks, nclips), dim3(256), 0, s,
                        (const ST_ *)f, (const ST_ *)x, (ST_ *)buf1, clips, states);
     return hipGetLastError();
 }
 hipError_t batch_from_product_impl(void *x, const void *buf1, const void *f, const ClipDesc *clips,
-                                   const DevState *states, int nclips, hipStream_t s) {
-    hipLaunchKernelGGL(batch_from_product_kernel<ST_>, dim3(BATCH_STREAM_BLOCKS, nclips), dim3(256), 0, s, (ST_ *)x,
+                                   const DevState *states, int nclips, int blocks, hipStream_t s) {
+    hipLaunchKernelGGL(batch_from_product_kernel<ST_>, dim3(blocks, nclips), dim3(256), 0, s, (ST_ *)x,
                        (const ST_ *)buf1, (const ST_ *)f, clips, states);
     return hipGetLastError();
 }

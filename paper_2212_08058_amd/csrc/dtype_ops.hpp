@@ -42,14 +42,16 @@ struct DtypeOps {
     int nbatch;
     hipError_t (*batch_fill)(void *x, const ClipDesc *clips, int nclips, hipStream_t);
     hipError_t (*batch_sumsq)(const void *x, const ClipDesc *clips, int nclips, double *partials, hipStream_t);
+    // the passes below take `blocks` workgroups per clip (batch_stream_blocks)
     hipError_t (*batch_normalize)(void *x, const void *buf1, const ClipDesc *clips, const DevState *states,
-                                  int nclips, hipStream_t);
+                                  int nclips, int blocks, hipStream_t);
     // matrix-core batch variants (product form): per-clip bound, start and final pass
-    hipError_t (*batch_bound)(const void *f, const ClipDesc *clips, DevState *states, int nclips, hipStream_t);
+    hipError_t (*batch_bound)(const void *f, const ClipDesc *clips, DevState *states, int nclips, int blocks,
+                              hipStream_t);
     hipError_t (*batch_to_product)(const void *f, const void *x, void *buf1, const ClipDesc *clips, DevState *states,
-                                   int nclips, hipStream_t);
+                                   int nclips, int blocks, hipStream_t);
     hipError_t (*batch_from_product)(void *x, const void *buf1, const void *f, const ClipDesc *clips,
-                                     const DevState *states, int nclips, hipStream_t);
+                                     const DevState *states, int nclips, int blocks, hipStream_t);
     // plain-form batch: uniform restart of the clips whose warm start was rejected
     hipError_t (*batch_refill)(void *x, void *buf1, const ClipDesc *clips, const DevState *states, int nclips,
                                hipStream_t);

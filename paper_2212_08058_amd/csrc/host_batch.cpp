@@ -15,6 +15,7 @@
 struct stpi_plan {
     stpi_problem proto;  // sigmas, radii, dtype (T, H, W unused)
     int nclips = 0, ntiles = 0, grid = 0;
+    int stream_blocks = 1;  // workgroups per clip of the streaming passes
     const stpi::BatchVariant *v = nullptr;
     stpi::ClipDesc *d_clips = nullptr;
     stpi::TileDesc *d_tiles = nullptr;
@@ -180,8 +181,8 @@ static int enqueue_batch(stpi_plan *P, const void *f, void *x, void *ws, int ini
     // matrix-core variants run every step in product form (a chain of no steps never launches one)
     const int pform = P->v->PIPE == 3 && max_iters > 0 ? 1 : 0;
     auto tail = [&]() -> hipError_t {
-        return pform ? ops->batch_from_product(x, buf1, f, P->d_clips, states, P->nclips, s)
-                     : ops->batch_normalize(x, buf1, P->d_clips, states, P->nclips, s);
+        return pform ? ops->batch_from_product(x, buf1, f, P->d_clips, states, P->nclips, P->stream_blocks, s)
+                     : ops->batch_normalize(x, buf1, P->d_clips, states, P->nclips, P->stream_blocks, s);
     };
     if (part == 3) {
         if ((e = tail()) != hipSuccess) return hip_fail(e, "batch normalize");
@@ -201,10 +202,11 @@ static int enqueue_batch(stpi_plan *P, const void *f, void *x, void *ws, int ini
             if ((e = launch_batch_state_from_norm(partials, states, P->nclips, ctl, s)) != hipSuccess)
                 return hip_fail(e, "batch norm finalize");
         }
-        if (P->v->PIPE == 3 && (e = ops->batch_bound(f, P->d_clips, states, P->nclips, s)) != hipSuccess)
+        if (P->v->PIPE == 3 &&
+            (e = ops->batch_bound(f, P->d_clips, states, P->nclips, P->stream_blocks, s)) != hipSuccess)
             return hip_fail(e, "batch operand bound");
         if (pform && init != 1 &&
-            (e = ops->batch_to_product(f, x, buf1, P->d_clips, states, P->nclips, s)) != hipSuccess)
+            (e = ops->batch_to_product(f, x, buf1, P->d_clips, states, P->nclips, P->stream_blocks, s)) != hipSuccess)
             return hip_fail(e, "batch product-form start");
         if ((e = compact()) != hipSuccess) return hip_fail(e, "batch active list");
     }
@@ -310,6 +312,9 @@ int stpi_batch_plan(const stpi_clip *clips, int nclips, float sigma_s, float sig
     P->v = v;
     P->clips = cds;
     P->extent = extent;
+    size_t largest = 0;
+    for (const auto &c : cds) largest = std::max(largest, (size_t)c.T * c.H * c.W);
+    P->stream_blocks = batch_stream_blocks(largest, ops_for(dtype)->elem);
     int dev = 0, cus = 256;
     hipDeviceProp_t prop;
     if (hipGetDevice(&dev) == hipSuccess && hipGetDeviceProperties(&prop, dev) == hipSuccess)

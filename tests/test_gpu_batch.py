@@ -366,3 +366,24 @@ def test_batch_tile_of_few_long_clips(P, shapes, tile):
     Pm, B = P
     info = B.BatchPlan(shapes, Pm.Kernel(4.0, 1.5, 8, 3)).info()
     assert info["PIPE"] == 3 and (info["TH"], info["TW"]) == tile
+
+
+@pytest.mark.parametrize("dtype,tol", [(torch.float32, 1e-5), (torch.bfloat16, 3 * 2.0 ** -8), (torch.float64, 1e-12)])
+@pytest.mark.parametrize("shapes", [[(1, 1, 1)], [(1, 1, 3), (2, 3, 5)] * 40, [(4, 32, 32), (4, 32, 33), (1, 2, 2)]])
+def test_streaming_passes_over_small_clips(P, dtype, tol, shapes):
+    """One workgroup and a few more per clip: below, at and above the elements of
+    one, from the uniform and from given starts, against the oracle (bfloat16:
+    a rounding of the iterate per iteration)."""
+    Pm, B = P
+    kern = Pm.Kernel(4.0, 1.5, 8, 3)
+    plan = B.BatchPlan(shapes, kern, dtype)
+    rng = np.random.default_rng(len(shapes))
+    fs, xs = ([torch.from_numpy(rng.uniform(0.1, 1.0, s)).to(dtype).to(DEV) for s in shapes] for _ in range(2))
+    got, _ = plan.iterate(plan.pack(fs), max_iters=3, tol=0.0)
+    got0, _ = plan.iterate(plan.pack(fs), x_flat=plan.pack(xs), init=0, max_iters=3, tol=0.0)
+    for i in range(len(shapes)):
+        f, x0 = fs[i].double().cpu().numpy(), xs[i].double().cpu().numpy()
+        for flat, start in ((got, None), (got0, x0)):
+            ref, _ = oracle.iterate(f, okf(kern), iters=3, x0=start)
+            x = list(plan.views(flat))[i].double().cpu().numpy()
+            assert np.linalg.norm(x - ref) / np.linalg.norm(ref) <= tol, (shapes[i], start is None)
