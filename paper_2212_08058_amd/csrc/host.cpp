@@ -319,8 +319,9 @@ ChainMem chain_mem(const WsLayout &L, void *ws) {
 static int g_forced_variant = -1;
 
 // Captured iteration chains, keyed by every argument that shapes the launch
-// sequence. Replaying a graph removes the per-launch host overhead of the
-// 2 * max_iters + 3 kernels.
+// sequence. Replaying a graph removes the per-launch host overhead of the chain's
+// kernels (one per step, two where the steps are finalised by a launch of their
+// own, and up to five around them).
 struct GraphKey {
     stpi_problem p;
     const void *f;
@@ -331,10 +332,11 @@ struct GraphKey {
     hipStream_t s;
     int part;   // ChainPart
     int pform;  // product-form chain
+    int defer;  // steps finalised by the next launch: the parts of a chain have to agree on it
     bool operator==(const GraphKey &o) const {
         return std::memcmp(&p, &o.p, sizeof(p)) == 0 && f == o.f && x == o.x && ws == o.ws && init == o.init &&
                max_iters == o.max_iters && tol == o.tol && v == o.v && s == o.s && part == o.part &&
-               pform == o.pform;
+               pform == o.pform && defer == o.defer;
     }
 };
 struct GraphEntry {
@@ -380,21 +382,21 @@ struct ChainArgs {
     ChainMem m;
     int init, max_iters;
     double tol;
-    int pform;
+    int pform, defer;
 };
 
 int enqueue_chain_part(const ChainArgs &a, int part, hipStream_t s) {
     switch (part) {
         case CHAIN_ALL:
-            return enqueue_iteration(a.p, a.ops, a.v, a.f, a.x, a.m, a.init, a.max_iters, a.tol, s, a.pform);
+            return enqueue_iteration(a.p, a.ops, a.v, a.f, a.x, a.m, a.init, a.max_iters, a.tol, s, a.pform, a.defer);
         case CHAIN_HEAD: {
             const int rc = enqueue_chain_init(a.p, a.ops, a.x, a.m, a.init, a.max_iters, a.tol, s, a.v, a.f, a.pform);
-            return rc ? rc : enqueue_chain_steps(a.p, a.v, a.f, a.x, a.m, CHAIN_CHUNK, s, a.pform);
+            return rc ? rc : enqueue_chain_steps(a.p, a.v, a.f, a.x, a.m, CHAIN_CHUNK, s, a.pform, a.defer);
         }
         case CHAIN_CHUNK_PART:
-            return enqueue_chain_steps(a.p, a.v, a.f, a.x, a.m, CHAIN_CHUNK, s, a.pform);
+            return enqueue_chain_steps(a.p, a.v, a.f, a.x, a.m, CHAIN_CHUNK, s, a.pform, a.defer);
         default:  // after whole segments
-            return enqueue_chain_tail(a.p, a.ops, a.v, a.f, a.x, a.m, CHAIN_CHUNK, s, a.pform);
+            return enqueue_chain_tail(a.p, a.ops, a.v, a.f, a.x, a.m, CHAIN_CHUNK, s, a.pform, a.defer);
     }
 }
 
@@ -663,7 +665,8 @@ int stpi_iterate(const stpi_problem *p, const void *f, void *x, int init, int ma
     // behind so the device never waits for it.
     const bool chunked = tol > 0.0 && max_iters > 2 * CHAIN_CHUNK;
     const int pform = chain_pform(v, max_iters);
-    ChainArgs ca{p, ops, v, f, x, m, init, max_iters, tol, pform};
+    const int defer = chain_defer(v, p);
+    ChainArgs ca{p, ops, v, f, x, m, init, max_iters, tol, pform, defer};
     const bool use_graphs = s != nullptr && graphs_enabled();
     auto run = [&](int part) -> int {
         if (!use_graphs) return enqueue_chain_part(ca, part, s);
@@ -680,6 +683,7 @@ int stpi_iterate(const stpi_problem *p, const void *f, void *x, int init, int ma
         key.s = s;
         key.part = part;
         key.pform = pform;
+        key.defer = defer;
         return launch_cached_graph(key, [&] { return enqueue_chain_part(ca, part, s); }, s);
     };
     if (!chunked) {
@@ -789,10 +793,11 @@ int stpi_time_chain_step(const stpi_problem *p, const void *f, void *x, void *ws
     // a fixed-count chain long enough that no timed step finds it done
     const int total = reps + 2;
     const int pform = chain_pform(v, total);
+    const int defer = chain_defer(v, p);
     if (product_form) *product_form = pform;
     rc = enqueue_chain_init(p, ops, x, m, 1, total, 0.0, s, v, f, pform);
     // the steps as a fixed-count chain of `total` steps runs them
-    if (!rc) rc = enqueue_chain_steps(p, v, f, x, m, 1, s, pform, total, 0);
+    if (!rc) rc = enqueue_chain_steps(p, v, f, x, m, 1, s, pform, defer, total, 0);
     if (rc) return rc;
     hipEvent_t e0, e1;
     hipError_t e;
@@ -802,7 +807,7 @@ int stpi_time_chain_step(const stpi_problem *p, const void *f, void *x, void *ws
         return hip_fail(e, "event create");
     }
     e = hipEventRecord(e0, s);
-    if (e == hipSuccess) rc = enqueue_chain_steps(p, v, f, x, m, reps, s, pform, total, 1);
+    if (e == hipSuccess) rc = enqueue_chain_steps(p, v, f, x, m, reps, s, pform, defer, total, 1);
     if (e == hipSuccess && !rc) e = hipEventRecord(e1, s);
     if (e == hipSuccess && !rc) e = hipEventSynchronize(e1);
     float ms = 0.0f;
@@ -866,9 +871,8 @@ int stpi_set_variant(int index) {
 
 namespace stpi {
 
-// Whether the chain's steps leave their finalisation to the next launch.
-static bool deferred(const Variant *v, const stpi_problem *p) {
-    return grid_blocks(*v, p) <= DEFER_MAX_UNITS && !fusion_disabled();
+int chain_defer(const Variant *v, const stpi_problem *p) {
+    return grid_blocks(*v, p) <= DEFER_MAX_UNITS && !fusion_disabled() ? 1 : 0;
 }
 
 // Enqueues start vector, max_iters steps and the final pass. No host
@@ -899,9 +903,9 @@ int enqueue_chain_init(const stpi_problem *p, const DtypeOps *ops, void *x, cons
 }
 
 int enqueue_chain_tail(const stpi_problem *p, const DtypeOps *ops, const Variant *v, const void *f, void *x,
-                       const ChainMem &m, int steps, hipStream_t s, int pform) {
+                       const ChainMem &m, int steps, hipStream_t s, int pform, int defer) {
     const size_t N = (size_t)p->T * p->H * p->W;
-    const bool defer = steps > 0 && deferred(v, p);
+    if (steps <= 0) defer = 0;
     const DevState *last = m.slot(defer ? steps & 1 : 0);
     StepPartials part = m.set((steps + 1) & 1);
     if (!pform) part.wmax = nullptr;
@@ -912,7 +916,7 @@ int enqueue_chain_tail(const stpi_problem *p, const DtypeOps *ops, const Variant
 }
 
 int enqueue_chain_steps(const stpi_problem *p, const Variant *v, const void *f, void *x, const ChainMem &m, int steps,
-                        hipStream_t s, int pform, int fixed_total, int k0) {
+                        hipStream_t s, int pform, int defer, int fixed_total, int k0) {
     hipError_t e;
     FwdLaunch FL;
     std::memset(&FL, 0, sizeof(FL));
@@ -926,7 +930,6 @@ int enqueue_chain_steps(const stpi_problem *p, const Variant *v, const void *f, 
     FL.ubound = &m.state->ubound;
     make_taps(p, FL.gs, FL.gt);
     const int nb = grid_blocks(*v, p);
-    const bool defer = deferred(v, p);
     const FwdLaunchFn launch = pform ? v->launch_p : v->launch;
     if (!launch) return fail(STPI_EUNSUPPORTED, "variant has no product-form step");
     for (int k = 0; k < steps; ++k) {
@@ -949,10 +952,10 @@ int enqueue_chain_steps(const stpi_problem *p, const Variant *v, const void *f, 
 }
 
 int enqueue_iteration(const stpi_problem *p, const DtypeOps *ops, const Variant *v, const void *f, void *x,
-                      const ChainMem &m, int init, int max_iters, double tol, hipStream_t s, int pform) {
+                      const ChainMem &m, int init, int max_iters, double tol, hipStream_t s, int pform, int defer) {
     int rc = enqueue_chain_init(p, ops, x, m, init, max_iters, tol, s, v, f, pform);
-    if (!rc) rc = enqueue_chain_steps(p, v, f, x, m, max_iters, s, pform, tol > 0.0 ? 0 : max_iters);
-    return rc ? rc : enqueue_chain_tail(p, ops, v, f, x, m, max_iters, s, pform);
+    if (!rc) rc = enqueue_chain_steps(p, v, f, x, m, max_iters, s, pform, defer, tol > 0.0 ? 0 : max_iters);
+    return rc ? rc : enqueue_chain_tail(p, ops, v, f, x, m, max_iters, s, pform, defer);
 }
 
 }  // namespace stpi

@@ -62,6 +62,9 @@ constexpr int CHAIN_CHUNK = 16;  // steps per replayed chain segment in long tol
 static_assert(CHAIN_CHUNK % 2 == 0, "a segment starts on state slot 0");
 // pform: run the chain in product form (chain_pform decides).
 int chain_pform(const Variant *v, int max_iters);
+// defer: the steps leave their finalisation to the next launch (chain_defer
+// decides, once for all parts of a chain).
+int chain_defer(const Variant *v, const stpi_problem *p);
 int enqueue_chain_init(const stpi_problem *p, const DtypeOps *ops, void *x, const ChainMem &m, int init,
                        int max_iters, double tol, hipStream_t s, const Variant *v, const void *f, int pform);
 // fixed_total > 0: the steps are steps k0 .. k0 + steps - 1 of a chain of
@@ -69,12 +72,12 @@ int enqueue_chain_init(const stpi_problem *p, const DtypeOps *ops, void *x, cons
 // previous iterate (residual, Rayleigh quotient) are used only on the first
 // two steps and the last: the others do not read the previous iterate.
 int enqueue_chain_steps(const stpi_problem *p, const Variant *v, const void *f, void *x, const ChainMem &m, int steps,
-                        hipStream_t s, int pform, int fixed_total = 0, int k0 = 0);
+                        hipStream_t s, int pform, int defer, int fixed_total = 0, int k0 = 0);
 // The final pass after `steps` steps; the chain's result is then in slot FINAL_SLOT.
 int enqueue_chain_tail(const stpi_problem *p, const DtypeOps *ops, const Variant *v, const void *f, void *x,
-                       const ChainMem &m, int steps, hipStream_t s, int pform);
+                       const ChainMem &m, int steps, hipStream_t s, int pform, int defer);
 int enqueue_iteration(const stpi_problem *p, const DtypeOps *ops, const Variant *v, const void *f, void *x,
-                      const ChainMem &m, int init, int max_iters, double tol, hipStream_t s, int pform);
+                      const ChainMem &m, int init, int max_iters, double tol, hipStream_t s, int pform, int defer);
 
 // Variant selection overrides (autotuner and tests).
 int forced_variant();

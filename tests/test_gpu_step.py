@@ -609,3 +609,20 @@ def test_bfloat16_batch_of_odd_frames(P):
         for f, v in zip(fs, plan.views(x)):
             xr, _ = oracle.iterate(f.double().cpu().numpy(), OKf(*kp), iters=2)
             assert np.max(np.abs(v.double().cpu().numpy() - xr) / xr) <= 2.0 ** -6, (kp, tuple(f.shape))
+
+
+def test_finalisation_switch_between_cached_chains(P, monkeypatch):
+    """How a chain's steps are finalised is part of what its captured graphs are
+    cached by: chains of one and of several graphs, switched between runs."""
+    shape, kern = (8, 64, 112), P.Kernel(2.0, 1.0, 4, 2)
+    f = to_dev(np.random.default_rng(3).uniform(0.05, 1.0, shape), torch.float32)
+    x, ws = torch.empty_like(f), torch.empty(P.workspace_bytes(shape, kern), dtype=torch.uint8, device=DEV)
+    stream = torch.cuda.Stream()
+    for kw in (dict(iters=5), dict(tol=1e-300, max_iters=48)):
+        out = []
+        for flag in "0110":
+            monkeypatch.setenv("STPI_NO_FUSE", flag)
+            y, r = P.power_iterate(f, kern, x=x, ws=ws, stream=stream, **kw)
+            torch.cuda.synchronize()
+            out.append((y.clone(), r["iters"], r["residual"], r["lambda_"]))
+        assert all(torch.equal(o[0], out[0][0]) and o[1:] == out[0][1:] for o in out)
