@@ -254,9 +254,9 @@ int stpi_sfseg_iterate(const stpi_problem *p, const void *s, const void *f, doub
 int stpi_variant_count(int dtype);
 /* info[0..8] = RS, RT, TH, TW, NTHR, RY, QX, OCC (min waves per SIMD), PIPE of
  * variant `index` (tile loop: 0 plain, 1 software-pipelined, 2 straight-line,
- * 3 matrix-core spatial passes, 4 one output frame per workgroup with all its
- * input frames at once: launch "segments" are then the clip's frames);
- * STPI_EINVAL if out of range. */
+ * 3 matrix-core spatial passes, 4 output frames one by one with all their input
+ * frames at once: launch "segments" are then the clip's frames, or as many as
+ * four workgroups per CU); STPI_EINVAL if out of range. */
 int stpi_variant_info(int dtype, int index, int32_t info[9]);
 /* Launch shape the step of problem p uses with variant `variant` (-1: the
  * variant stpi_step would choose): info[0] = variant index, info[1] = tiles

@@ -414,13 +414,17 @@ struct FwdOpP {
 // with NTHR = 512, OCC = 4 lets two workgroups share a CU).
 // PIPE: 1 selects the software-pipelined tile loop (stencil_tile_pipe), 2 its
 // straight-line form (stencil_tile_flat), 3 the matrix-core tile loop
-// (stencil_tile_mfma; RS = 16, any space radius up to 16), 4 one output frame
-// per workgroup with all its input frames at once (stencil_tile_gather; the
-// launch's frame segments are the T single frames).
+// (stencil_tile_mfma; RS = 16, any space radius up to 16), 4 the output frames of
+// a segment one by one with all their input frames at once (stencil_tile_gather;
+// segments of one frame while that is at most four workgroups per CU).
+// ALT: the kernel for frames of an odd number of voxels (odd_frames_apart); with
+// PIPE 4 the one for segments of several frames (the loop over them costs the
+// others 0.3 us of 6).
 // PF: product-form chain step (PIPE 3, iterate mode only).
-template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX, int OCC, int PIPE, bool PF, bool ODD>
+template <class ST, int RS, int RT, int TH, int TW, int NTHR, int RY, int QX, int OCC, int PIPE, bool PF, bool ALT>
 __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
     using CT = typename Compute<ST>::type;
+    constexpr bool ODD = ALT && PIPE != 4;
     using G = Geometry<RS, RT, TH, TW, NTHR, RY, QX>;
     using PG = PipeGeometry<RS, RT, TH, TW, NTHR, RY, QX>;
     static_assert(PIPE != 3 || ((RS == 16 || RS == 8) && sizeof(CT) == 4),
@@ -530,9 +534,12 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
             stencil_tile_mfma<CT, RT, TH, TW, NTHR, PAD>(op, a.taps, tapl, umul, a.rs, a.T, t0, t1, a.H, a.W, x0, y0,
                                                    lds, d1, d2);
         }
-    } else if constexpr (PIPE == 4)
-        stencil_tile_gather<CT, RS, RT, TH, TW, NTHR, RY>(op, a.taps, a.T, t0, a.H, a.W, x0, y0, lds, d1, d2);
-    else if constexpr (PIPE == 2)
+    } else if constexpr (PIPE == 4) {
+        int t = t0;
+        do
+            stencil_tile_gather<CT, RS, RT, TH, TW, NTHR, RY>(op, a.taps, a.T, t, a.H, a.W, x0, y0, lds, d1, d2);
+        while (ALT && ++t < t1);
+    } else if constexpr (PIPE == 2)
         stencil_tile_flat<CT, RS, RT, TH, TW, NTHR, RY, QX>(op, a.taps, a.T, t0, t1, a.H, a.W, x0, y0, lds, d1, d2);
     else if constexpr (PIPE == 1)
         stencil_tile_pipe<CT, RS, RT, TH, TW, NTHR, RY, QX>(op, a.taps, a.T, t0, t1, a.H, a.W, x0, y0, lds, d1, d2);
@@ -566,7 +573,7 @@ hipError_t launch_fwd(const FwdLaunch &L, hipStream_t stream) {
     a.T = L.T;
     a.H = L.H;
     a.W = L.W;
-    a.nseg = PIPE == 4 ? L.T : (L.nseg > 0 ? L.nseg : 1);
+    a.nseg = L.nseg > 0 ? L.nseg : 1;
     a.ubound = L.ubound;
     a.rs = 0;
     for (int d = 1; d <= 16; ++d)
@@ -582,8 +589,8 @@ hipError_t launch_fwd(const FwdLaunch &L, hipStream_t stream) {
     for (int d = -RT; d <= RT; ++d) a.taps.gt[d + RT] = (CT)L.gt[d + 8];
     const int nunits = ((L.W + TW - 1) / TW) * ((L.H + TH - 1) / TH) * a.nseg;
     const int per = (nunits + NUM_XCD - 1) / NUM_XCD;
-    if constexpr (odd_frames_apart<ST, QX, PIPE>()) {
-        if (L.H & L.W & 1) {
+    if constexpr (odd_frames_apart<ST, QX, PIPE>() || PIPE == 4) {
+        if (PIPE == 4 ? a.nseg < L.T : (L.H & L.W & 1) != 0) {
             hipLaunchKernelGGL((fwd_step_kernel<ST, RS, RT, TH, TW, NTHR, RY, QX, OCC, PIPE, PF, true>),
                                dim3(per * NUM_XCD), dim3(NTHR), 0, stream, a);
             return hipGetLastError();

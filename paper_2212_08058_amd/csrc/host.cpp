@@ -105,8 +105,12 @@ static int tiles_for(const Variant &v, const stpi_problem *p) {
 // 128x64x112 23.2 / 11.1 (1024), 10x230x432 12.0 / 14.8 (1050). So: the small
 // tile while every workgroup has a CU of its own, the large one up to two per CU
 // on clips longer than the temporal window and up to four per CU on clips of
-// more than twice that.
-static bool gather_pays(const Variant &v, const stpi_problem *p) {
+// more than twice that. The other types lie alike (streamed / 8 x 32 / 16 x 64),
+// bfloat16: 8x64x112 10.7 / 5.6 / 6.6, 16x120x214 10.9 / 12.1 / 8.4, 128x64x112 24.0 /
+// 19.9 / 10.2, 8x240x432 10.9 / 18.4 / 11.1, 10x230x432 11.9 / 20.7 / 13.3; double:
+// 13.2 / 6.1 / 8.1, 14.8 / 16.6 / 12.4, 31.4 / 27.1 / 16.2, 15.2 / 25.5 / 18.2, 16.3 /
+// 28.6 / 22.1, and 12x200x300 16.6 / 22.2 / 16.6.
+bool gather_pays(const Variant &v, const stpi_problem *p) {
     const int64_t units = (int64_t)tiles_for(v, p) * p->T;
     if (v.TH * v.TW <= 256) return units <= device_cus();
     return (units <= 2 * device_cus() && p->T > 2 * v.RT) || (units <= 4 * device_cus() && p->T > 4 * v.RT);
@@ -262,13 +266,19 @@ static int base_segments(const Variant &v, const stpi_problem *p) {
     return nseg;
 }
 
+// Segments of a PIPE 4 launch: single frames, or as many as give the chip four
+// workgroups per CU (such launches are only asked for by index).
+static int gather_segments(const Variant &v, const stpi_problem *p) {
+    return std::min(p->T, std::max(1, 4 * device_cus() / tiles_for(v, p)));
+}
+
 int segments_for(const Variant &v, const stpi_problem *p) {
-    if (v.PIPE == 4) return p->T;  // a workgroup per frame
+    if (v.PIPE == 4) return gather_segments(v, p);
     return split_short_tiles(tiles_for(v, p), p->T, v.RT, base_segments(v, p));
 }
 
 int tape_segments(const Variant &v, const stpi_problem *p) {
-    if (v.PIPE == 4) return p->T;
+    if (v.PIPE == 4) return gather_segments(v, p);
     const int nseg = base_segments(v, p);
     return nseg == 1 ? split_short_tiles(tiles_for(v, p), p->T, v.RT) : nseg;
 }
@@ -278,13 +288,13 @@ int tape_blocks(const Variant &v, const stpi_problem *p) { return tiles_for(v, p
 
 // Workspace: [3 state slots][2 x partial sums][2 x maxima][ping-pong volume].
 // A partials set holds the largest grid any compiled variant can use for this
-// frame size.
+// frame size, whatever the radii.
 size_t partials_capacity(const stpi_problem *p) {
     const DtypeOps *ops = ops_for(p->dtype);
     size_t cap = (size_t)NORM_BLOCKS_HOST;
     for (int i = 0; i < ops->nvariants; ++i) {
         const Variant &v = ops->variants[i];
-        const size_t g = (size_t)tiles_for(v, p) * (v.PIPE == 4 ? (size_t)p->T : (size_t)STPI_NSEG_MAX);
+        const size_t g = (size_t)tiles_for(v, p) * (size_t)(v.PIPE == 4 ? gather_segments(v, p) : STPI_NSEG_MAX);
         if (g > cap) cap = g;
     }
     for (int i = 0; i < ops->nadj; ++i) {

@@ -48,6 +48,7 @@ int validate_problem(const stpi_problem *p);
 void make_taps(const stpi_problem *p, double *gs, double *gt);
 // tape: for a step of a differentiated pass (a streamed vector loop; see host.cpp).
 const Variant *choose_variant(const stpi_problem *p, int forced_index, bool tape = false);
+bool gather_pays(const Variant &v, const stpi_problem *p);  // PIPE 4: see host.cpp
 int grid_blocks(const Variant &v, const stpi_problem *p);
 int segments_for(const Variant &v, const stpi_problem *p);
 int tape_segments(const Variant &v, const stpi_problem *p);  // of a step of a differentiated pass

@@ -151,3 +151,17 @@ def test_short_clips_split_their_frames(native):
             # split only by the phase rule: it saves at least two phases
             assert _walk_phases(T, RT, nseg) + 1 < _walk_phases(T, RT, 1)
     assert _walk_phases(16, 5, 2) == 15 and _walk_phases(16, 5, 1) == 23
+
+
+@pytest.mark.parametrize("H,W", [(480, 854), (64, 112), (233, 347), (1, 1)])
+@pytest.mark.parametrize("dtype,elem", [(0, 4), (1, 2), (2, 8)])
+def test_workspace_beyond_the_volume_is_bounded(native, H, W, dtype, elem):
+    """What a workspace holds beside its volume depends on neither the radii (one
+    may serve several filters of a clip size) nor, on long clips, the length."""
+    def beside(T, r_s, r_t):
+        p = _prob(native, T=T, H=H, W=W, r_s=r_s, r_t=r_t, dtype=dtype)
+        return native.lib.stpi_workspace_bytes(ctypes.byref(p)) - (T * H * W * elem + 255) // 256 * 256
+    tiles = ((H + 7) // 8) * ((W + 31) // 32)  # of the smallest tile
+    for T in (1, 8, 2000, 5000):
+        assert beside(T, 4, 2) == beside(T, 15, 5) == beside(T, 0, 0) > 0
+    assert beside(2000, 4, 2) == beside(5000, 4, 2) <= 40 * max(8 * tiles, 1024) + 1536

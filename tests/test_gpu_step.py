@@ -626,3 +626,35 @@ def test_finalisation_switch_between_cached_chains(P, monkeypatch):
             torch.cuda.synchronize()
             out.append((y.clone(), r["iters"], r["residual"], r["lambda_"]))
         assert all(torch.equal(o[0], out[0][0]) and o[1:] == out[0][1:] for o in out)
+
+
+@pytest.mark.parametrize("dtype", [torch.float32, torch.bfloat16, torch.float64])
+@pytest.mark.parametrize("shape", [(20, 100, 640), (7, 130, 4200), (40, 64, 520)])
+def test_single_frame_loop_over_segments(P, dtype, shape):
+    """Asked for by index, the single-frame loop also takes volumes of more than
+    four workgroups per CU, several frames a workgroup: as the streamed loop of
+    the same radii (other orders of the temporal and global sums)."""
+    import ctypes
+    from paper_2212_08058_amd import _native as N
+    code = {torch.float32: N.STPI_F32, torch.bfloat16: N.STPI_BF16, torch.float64: N.STPI_F64}[dtype]
+    kern, info = P.Kernel(2.0, 1.0, 4, 2), (ctypes.c_int * 9)()
+    fd = to_dev(np.random.default_rng(sum(shape)).uniform(0.05, 1.0, shape), dtype)
+    out = {}
+    try:
+        for i in range(N.lib.stpi_variant_count(code)):
+            assert N.lib.stpi_variant_info(code, i, info) == 0
+            if (info[0], info[1]) != (4, 2) or info[8] not in (0, 4):
+                continue
+            assert N.lib.stpi_set_variant(i) == 0
+            d = P.launch_shape(shape, kern, dtype=dtype)
+            if info[8] == 4:
+                assert d["segments"] == min(shape[0], max(1, 1024 // d["tiles"]))
+            x, r = P.power_iterate(fd, kern, iters=4)
+            torch.cuda.synchronize()
+            out[i] = (info[8], x.double().cpu().numpy(), r["lambda_"])
+    finally:
+        N.lib.stpi_set_variant(-1)
+    ref = next(o for o in out.values() if o[0] == 0)
+    assert sum(o[0] == 4 for o in out.values()) == 2
+    for o in out.values():
+        assert rel_l2(o[1], ref[1]) <= 4 * TOL[dtype] and abs(o[2] - ref[2]) <= 4 * TOL[dtype] * ref[2]
