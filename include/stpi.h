@@ -348,7 +348,9 @@ void stpi_plan_destroy(stpi_plan *plan);
  * buffers it allocates and frees),
  * records the fastest for (device arch, dtype, r_s, r_t, H, W), and writes the
  * whole table to cache_path (if not NULL). Later calls for that key use the
- * recorded variant. Synchronises the device. */
+ * recorded variant; one of PIPE 4, whose time grows with the number of frames,
+ * for clips of up to p->T frames and for longer ones where it pays without a
+ * table. Synchronises the device. */
 int stpi_autotune(const stpi_problem *p, const char *cache_path, int reps, int32_t *best_variant, double *best_ms);
 /* Merges a table written by stpi_autotune into the process's table. */
 int stpi_autotune_load(const char *path);

@@ -1,6 +1,10 @@
 // Tile autotuner: times every compiled step variant that fits a problem with
 // HIP events, keeps the fastest per (device arch, dtype, radii, frame size),
-// and persists the table as text so later processes start tuned.
+// and persists the table as text so later processes start tuned. The time of
+// the single-frame loop (PIPE 4) grows with the number of frames, the streamed
+// loops' hardly while the chip is not full: an entry also holds the clip length
+// it was timed at, and a single-frame loop is taken for clips of up to that
+// length, or where it pays by its own rule.
 #include <hip/hip_runtime.h>
 
 #include <cstdio>
@@ -19,6 +23,7 @@ struct TuneEntry {
     int dtype, rs, rt, H, W;
     int sig[9];  // RS, RT, TH, TW, NTHR, RY, QX, OCC, PIPE of the winner
     double ms;
+    int T;  // frames of the timed clip (0: not known, a table written before it was kept)
 };
 
 static std::mutex g_tune_mu;
@@ -49,8 +54,11 @@ int tuned_variant(const stpi_problem *p) {
     if (g_tune.empty()) return -1;
     const std::string arch = device_arch();
     for (const auto &e : g_tune)
-        if (e.arch == arch && e.dtype == p->dtype && e.rs == p->r_s && e.rt == p->r_t && e.H == p->H && e.W == p->W)
-            return variant_by_sig(p->dtype, e.sig);
+        if (e.arch == arch && e.dtype == p->dtype && e.rs == p->r_s && e.rt == p->r_t && e.H == p->H && e.W == p->W) {
+            const int i = variant_by_sig(p->dtype, e.sig);
+            if (i < 0 || e.sig[8] != 4) return i;
+            return p->T <= e.T || gather_pays(ops_for(p->dtype)->variants[i], p) ? i : -1;
+        }
     return -1;
 }
 
@@ -67,11 +75,11 @@ static int save_table(const char *path) {
     const std::string tmp = std::string(path) + ".tmp";
     FILE *fp = std::fopen(tmp.c_str(), "w");
     if (!fp) return fail(STPI_EINVAL, "cannot write %s", tmp.c_str());
-    std::fprintf(fp, "# stpi autotune v2: arch dtype r_s r_t H W RS RT TH TW NTHR RY QX OCC PIPE ms\n");
+    std::fprintf(fp, "# stpi autotune v2: arch dtype r_s r_t H W RS RT TH TW NTHR RY QX OCC PIPE ms T\n");
     for (const auto &e : g_tune)
-        std::fprintf(fp, "%s %d %d %d %d %d %d %d %d %d %d %d %d %d %d %.6f\n", e.arch.c_str(), e.dtype, e.rs, e.rt,
+        std::fprintf(fp, "%s %d %d %d %d %d %d %d %d %d %d %d %d %d %d %.6f %d\n", e.arch.c_str(), e.dtype, e.rs, e.rt,
                      e.H, e.W, e.sig[0], e.sig[1], e.sig[2], e.sig[3], e.sig[4], e.sig[5], e.sig[6], e.sig[7], e.sig[8],
-                     e.ms);
+                     e.ms, e.T);
     std::fclose(fp);
     if (std::rename(tmp.c_str(), path) != 0) return fail(STPI_EINVAL, "cannot rename %s", tmp.c_str());
     return STPI_OK;
@@ -95,9 +103,10 @@ int stpi_autotune_load(const char *path) {
         if (line[0] == '#') continue;
         char arch[64];
         TuneEntry e;
-        if (std::sscanf(line, "%63s %d %d %d %d %d %d %d %d %d %d %d %d %d %d %lf", arch, &e.dtype, &e.rs, &e.rt,
+        e.T = 0;  // optional last column
+        if (std::sscanf(line, "%63s %d %d %d %d %d %d %d %d %d %d %d %d %d %d %lf %d", arch, &e.dtype, &e.rs, &e.rt,
                         &e.H, &e.W, &e.sig[0], &e.sig[1], &e.sig[2], &e.sig[3], &e.sig[4], &e.sig[5], &e.sig[6],
-                        &e.sig[7], &e.sig[8], &e.ms) != 16)
+                        &e.sig[7], &e.sig[8], &e.ms, &e.T) < 16)
             continue;
         e.arch = arch;
         put_entry(e);
@@ -160,6 +169,7 @@ int stpi_autotune(const stpi_problem *p, const char *cache_path, int reps, int32
     const int sig[9] = {v.RS, v.RT, v.TH, v.TW, v.NTHR, v.RY, v.QX, v.OCC, v.PIPE};
     std::memcpy(te.sig, sig, sizeof(sig));
     te.ms = best_t;
+    te.T = p->T;
     {
         std::lock_guard<std::mutex> lk(g_tune_mu);
         put_entry(te);

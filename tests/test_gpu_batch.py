@@ -387,3 +387,32 @@ def test_streaming_passes_over_small_clips(P, dtype, tol, shapes):
             ref, _ = oracle.iterate(f, okf(kern), iters=3, x0=start)
             x = list(plan.views(flat))[i].double().cpu().numpy()
             assert np.linalg.norm(x - ref) / np.linalg.norm(ref) <= tol, (shapes[i], start is None)
+
+
+def test_autotuned_single_frame_loop_and_the_clip_length(P, tmp_path):
+    """The single-frame loop wins on a short small clip by far; recorded there, it
+    is used for clips of up to that length and where it pays by its own rule, and
+    a clip of the same frame size that is too long for it takes the loop it would
+    take without a table. A table without lengths (16 columns) is read too."""
+    Pm, B = P
+    from paper_2212_08058_amd import _native as N
+    kern, info = Pm.Kernel(2.0, 1.0, 4, 2), (ctypes.c_int32 * 9)()
+
+    def pipe(T):
+        assert N.lib.stpi_variant_info(0, Pm.launch_shape((T, 64, 112), kern)["variant"], info) == 0
+        return info[8]
+
+    path = tmp_path / "tune.txt"
+    B.autotune_clear()
+    try:
+        untuned = {T: pipe(T) for T in (4, 8, 2000)}
+        assert untuned[2000] != 4
+        v, _ = B.autotune((8, 64, 112), kern, cache_path=str(path), reps=20)
+        assert N.lib.stpi_variant_info(0, v, info) == 0 and info[8] == 4
+        for text in (path.read_text(), "\n".join(" ".join(l.split()[:16]) for l in path.read_text().splitlines())):
+            B.autotune_clear()
+            path.write_text(text)
+            B.autotune_load(str(path))
+            assert pipe(4) == pipe(8) == 4 and pipe(2000) == untuned[2000]
+    finally:
+        B.autotune_clear()
