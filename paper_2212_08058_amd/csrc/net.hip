@@ -1096,19 +1096,25 @@ static int net_tiles(const stpi_problem *p) { return ((p->W + CT_W - 1) / CT_W) 
 // Frame segments of the streamed layer kernels (two workgroups per CU): a
 // segment costs its frames plus three (two rim frames and the start), and the
 // chip takes the units in rounds of its resident workgroups, so the split with
-// the fewest frame steps over all rounds.
+// the fewest frame steps over all rounds (4000x8x8, one tile: 512 segments, forward
+// 498 us with at most 64 of them, 110 now; 1000x16x32 145 and 56).
 static int tile_segments(const stpi_problem *p) {
     const int64_t tiles = net_tiles(p), slots = 2 * (int64_t)device_cus();
-    int best = 1;
-    int64_t cost = INT64_MAX;
-    for (int k = 1; k <= p->T && k <= 64; ++k) {
+    int64_t best = 1, cost = INT64_MAX;
+    auto take = [&](int64_t k) {
         const int64_t c = (tiles * k + slots - 1) / slots * ((p->T + k - 1) / k + 3);
         if (c < cost) {
             cost = c;
             best = k;
         }
+    };
+    const int few = std::min(p->T, 64);
+    for (int k = 1; k <= few; ++k) take(k);
+    for (int rounds = 1; rounds <= 8; ++rounds) {  // long clips of few tiles: whole rounds
+        const int64_t k = std::min<int64_t>(p->T, rounds * slots / tiles);
+        if (k > few) take(k);
     }
-    return best;
+    return (int)best;
 }
 
 // Workgroups of a weight-gradient launch: as many as fit at once (two per CU

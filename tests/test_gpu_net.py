@@ -363,3 +363,11 @@ def test_backward_near_the_largest_float(W, scale):
     w4 = net.grad[-1 - 16 * 27:-1].double().cpu().numpy()
     ref = np.asarray(grads[3][0], np.float64).reshape(-1)
     assert np.isfinite(w4).all() and rel(w4, ref) <= 1e-2
+
+
+@pytest.mark.parametrize("shape", [(600, 5, 7), (131, 17, 33)])
+def test_long_clips_of_few_tiles(W, shape):
+    """More than 64 frame segments, of one and two frames: forward and backward as
+    the tests above have them, with their bounds."""
+    test_forward_matches_bf16_oracle(W, shape)
+    test_backward_at_tile_edges(W, shape)
