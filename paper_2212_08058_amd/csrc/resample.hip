@@ -138,6 +138,40 @@ __global__ __launch_bounds__(64 * UP_WAVES) void upsample_kernel(CoarseDims d, i
     }
 }
 
+// One output per thread, for narrow volumes, whose rows would fill a fraction of
+// a span: the same blends in the same order. us, spans / this, linear: 32x4096x8
+// 41 / 9.2, 4000x16x16 23 / 9.1, 64x512x16 14 / 8.8, but 1000x64x64 23.9 / 26.6.
+constexpr int UP_NARROW = 48;
+template <class ST>
+__global__ void upsample_narrow_kernel(CoarseDims d, int mode, const ST *in, const ST *mul, ST *out) {
+    using CT = typename Compute<ST>::type;
+    const size_t n = (size_t)d.T * d.H * d.W;
+    for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) {
+        const int x = (int)(i % d.W);
+        const int y = (int)((i / d.W) % d.H);
+        const int t = (int)(i / ((size_t)d.W * d.H));
+        CT v;
+        if (mode == 0) {
+            v = ld(in + ((size_t)(t / d.st) * d.Hc + y / d.sy) * d.Wc + x / d.sy);
+        } else {
+            int t0, t1, y0, y1, x0, x1;
+            CT wt, wy, wx;
+            lin_axis<CT>(t, d.st, d.Tc, t0, t1, wt);
+            lin_axis<CT>(y, d.sy, d.Hc, y0, y1, wy);
+            lin_axis<CT>(x, d.sy, d.Wc, x0, x1, wx);
+            auto column = [&](int c) {
+                auto at = [&](int tt, int yy) { return (CT)ld(in + ((size_t)tt * d.Hc + yy) * d.Wc + c); };
+                const CT a = at(t0, y0) + wy * (at(t0, y1) - at(t0, y0));
+                const CT b = at(t1, y0) + wy * (at(t1, y1) - at(t1, y0));
+                return a + wt * (b - a);
+            };
+            const CT r0 = column(x0), r1 = column(x1);
+            v = r0 + wx * (r1 - r0);
+        }
+        st(out + i, v * (mul ? (CT)ld(mul + i) : CT(1)));
+    }
+}
+
 template <class ST>
 static hipError_t launch_down(const CoarseDims &d, const void *in, void *out, hipStream_t s) {
     const size_t nc = (size_t)d.Tc * d.Hc * d.Wc;
@@ -149,6 +183,13 @@ static hipError_t launch_down(const CoarseDims &d, const void *in, void *out, hi
 template <class ST>
 static hipError_t launch_up(const CoarseDims &d, int mode, const void *in, const void *mul, void *out,
                             hipStream_t s) {
+    if (d.W <= UP_NARROW) {
+        const size_t n = (size_t)d.T * d.H * d.W;
+        const int blocks = (int)std::min<size_t>((n + 255) / 256, 8192);
+        hipLaunchKernelGGL(upsample_narrow_kernel<ST>, dim3(blocks), dim3(256), 0, s, d, mode, (const ST *)in,
+                           (const ST *)mul, (ST *)out);
+        return hipGetLastError();
+    }
     const int nspan = (d.W + UP_SPAN - 1) / UP_SPAN;
     const int64_t groups = ((int64_t)d.T * d.H + UP_WAVES - 1) / UP_WAVES;
     const dim3 grid((unsigned)nspan, (unsigned)std::min<int64_t>(groups, std::max(1, UP_GROUPS / nspan)));

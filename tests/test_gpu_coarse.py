@@ -144,3 +144,12 @@ def test_upsample_rows_around_a_span(P, dtype, tol, shape, sy, st):
     another order: each rounds by half a unit of values below 1."""
     test_upsample_matches_oracle(P, dtype, tol, 0, shape, sy, st)
     test_upsample_matches_oracle(P, dtype, tol, 1, shape, sy, st)
+
+
+@pytest.mark.parametrize("dtype,tol", DTYPES)
+@pytest.mark.parametrize("W", [1, 3, 47, 48, 49, 128])
+def test_upsample_around_the_narrow_rows(P, dtype, tol, W):
+    """Rows of up to 48 outputs have a kernel of their own."""
+    for sy, st in ((1, 1), (2, 1), (3, 2), (100, 9)):
+        for mode in (0, 1):
+            test_upsample_matches_oracle(P, dtype, tol, mode, (3, 5, W), sy, st)
