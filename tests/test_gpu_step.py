@@ -658,3 +658,28 @@ def test_single_frame_loop_over_segments(P, dtype, shape):
     assert sum(o[0] == 4 for o in out.values()) == 2
     for o in out.values():
         assert rel_l2(o[1], ref[1]) <= 4 * TOL[dtype] and abs(o[2] - ref[2]) <= 4 * TOL[dtype] * ref[2]
+
+
+def test_single_frame_loop_is_as_close_as_the_streamed_one(P):
+    """Small clips take the single-frame loop by themselves: over a few of them
+    their float iterates are no further from FP64 than the streamed loop's."""
+    import ctypes
+    from paper_2212_08058_amd import _native as N
+    kern, info, err = P.Kernel(2.0, 1.0, 4, 2), (ctypes.c_int * 9)(), {0: [], 4: []}
+    streamed = next(i for i in range(N.lib.stpi_variant_count(0))
+                    if N.lib.stpi_variant_info(0, i, info) == 0 and info[8] == 0 and (info[0], info[1]) == (4, 2))
+    try:
+        for shape in ((8, 64, 112), (30, 60, 70), (24, 64, 64), (12, 100, 90)):
+            assert N.lib.stpi_variant_info(0, P.launch_shape(shape, kern)["variant"], info) == 0 and info[8] == 4
+            for seed in range(3):
+                f = np.random.default_rng(seed).uniform(0.05, 1.0, shape).astype(np.float32)
+                ref, _ = oracle.iterate(f, OKf(2.0, 1.0, 4, 2), iters=6)
+                for v, pipe in ((-1, 4), (streamed, 0)):
+                    assert N.lib.stpi_set_variant(v) == 0
+                    x, _ = P.power_iterate(torch.from_numpy(f).to(DEV), kern, iters=6)
+                    err[pipe].append(rel_l2(x.double().cpu().numpy(), ref))
+                N.lib.stpi_set_variant(-1)
+    finally:
+        N.lib.stpi_set_variant(-1)
+    print("from FP64: single-frame", np.mean(err[4]), "streamed", np.mean(err[0]))
+    assert np.mean(err[4]) <= np.mean(err[0])
