@@ -30,6 +30,7 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 VALU_FP32_PEAK_TFLOPS = 256 * 4 * 16 * 2 * 2.4e9 / 1e12   # 78.6: FMA lanes x 2 flop x clock
+MFMA_FP32_PEAK_TFLOPS = 256 * 4 * 64 * 2.4e9 / 1e12       # 157.3: 16x16x4 float products, 2048 flop in 32 cycles
 
 
 def log(msg):
@@ -113,8 +114,9 @@ def sfseg_leg(f_np, kern, iters, steps, warmup, reps, stream, dev):
     """The full operator of Eq. 7 (three filtered fields) on the same clip: s =
     the soft mask to the power p = 0.2, f = a second soft mask in [0, 1]
     (standing in for the optical-flow magnitude), alpha = 1. Whole 20-iteration
-    jobs from the uniform start, and the step kernel timed with HIP events on
-    its stream (each timed call also launches the two-sum reduction kernel)."""
+    jobs from the uniform start, and one step of an iteration: the difference of
+    two runs of different length between HIP events on their stream (at these
+    radii a launch of sfseg_mfma_kernel, which also finalises the step before)."""
     import numpy as np
     import torch
 
@@ -138,22 +140,23 @@ def sfseg_leg(f_np, kern, iters, steps, warmup, reps, stream, dev):
     torch.cuda.synchronize()
     dt = (time.perf_counter() - t0) / steps
     N = s.numel()
-    z = torch.empty_like(s)
-    SF.sfseg_step(s, fd, x, kern, 1.0, z=z, ws=ws, stream=stream)
-    e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
-    e0.record(stream)
-    for _ in range(reps):
-        SF.sfseg_step(s, fd, x, kern, 1.0, z=z, ws=ws, stream=stream)
-    e1.record(stream)
-    e1.synchronize()
-    kms = e0.elapsed_time(e1) / reps
+
+    def run_ms(n):
+        e0, e1 = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+        e0.record(stream)
+        SF.sfseg_iterate(s, fd, kern, 1.0, iters=n, x=x, ws=ws, stream=stream)
+        e1.record(stream)
+        e1.synchronize()
+        return e0.elapsed_time(e1)
+
+    kms = (min(run_ms(reps + 2) for _ in range(3)) - min(run_ms(2) for _ in range(3))) / reps
     # per voxel: 3 fields x (y, x and t taps) multiply-adds + staging and recombination
     flop = 2 * 3 * (2 * (2 * kern.r_s + 1) + (2 * kern.r_t + 1)) + 12
     return {"value": N * iters / dt, "unit": "voxel-iters/s", "ms_per_step": dt * 1e3, "iters": iters,
             "alpha": 1.0, "p": 0.2, "lambda": r["lambda_"], "residual": r["residual"],
-            "roofline": {"bound": "alu", "achieved": flop * N / (kms * 1e-3) / 1e12, "peak": VALU_FP32_PEAK_TFLOPS,
-                         "unit": "TFLOP/s", "frac": flop * N / (kms * 1e-3) / 1e12 / VALU_FP32_PEAK_TFLOPS,
-                         "flop_per_voxel": flop, "kernel": "sfseg_step_kernel", "kernel_ms": kms,
+            "roofline": {"bound": "mfma", "achieved": flop * N / (kms * 1e-3) / 1e12, "peak": MFMA_FP32_PEAK_TFLOPS,
+                         "unit": "TFLOP/s", "frac": flop * N / (kms * 1e-3) / 1e12 / MFMA_FP32_PEAK_TFLOPS,
+                         "flop_per_voxel": flop, "kernel": "sfseg_mfma_kernel", "kernel_ms": kms,
                          "hbm_gbs": 16 * N / (kms * 1e-3) / 1e9, "bytes_per_voxel": 16}}
 
 
@@ -289,9 +292,9 @@ def main():
                            "hbm": hbm}
     prof = profiled_traffic(f"fwd_step_{T}x{H}x{W}_{args.dtype}")
     ctype = "float" if args.dtype == "f32" else "stpi::bf16"
-    sig = f"fwd_step_kernel<{ctype}, " + ", ".join(str(v) for v in vinfo) + (", true>" if product else ", false>")
+    sig = f"fwd_step_kernel<{ctype}, " + ", ".join(str(v) for v in vinfo) + (", true, false>" if product else ", false, false>")
     if prof is not None and sig not in prof["kernel"]:
-        prof = None  # the counters were taken on another tile variant
+        prof = None  # the counters were taken on another kernel
     if prof is not None:
         out["roofline"]["traffic"] = prof["traffic_bytes"]
         out["roofline"]["traffic_note"] = (f"HBM bytes per launch from rocprofv3 FETCH_SIZE x {prof['fetch_scale']:.3f} + "
