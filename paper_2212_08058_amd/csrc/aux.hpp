@@ -42,8 +42,8 @@ __global__ void combine_fwd_kernel(int C, size_t n, const ST *fc, const double *
     }
 }
 
-// One element chunk of NV 16-byte vectors' worth of loads: VEC elements of an
-// array at chunk i when the arrays allow it (16-byte aligned), else one element.
+// VEC elements of an array in one 16-byte load at chunk i where the arrays allow
+// it (16-byte aligned), else one element.
 template <class ST, int VEC>
 struct Elems {
     typename Compute<ST>::type v[VEC];

@@ -4,13 +4,14 @@
 //
 // Weights and activations are bfloat16, accumulation is FP32. Hidden
 // activations are stored channels-last ([voxel][16], 32 bytes per voxel).
-// The two 16 -> 16 layers, and their input gradients, run as implicit GEMMs on
-// the matrix cores (v_mfma_f32_16x16x32_bf16): per wavefront a 16-channel x
-// 16-voxel output block accumulates 27 taps of (16 out x 16 in) weights times
-// (16 in x 16 voxels) inputs, two taps an instruction; so do their weight gradients (wgrad16_kernel,
-// a sum over voxels of 16 x 16 outer products per tap, 32 voxels an instruction). The 1 -> 16 and
-// 16 -> 1 layers and their weight gradients are VALU kernels (their shapes fit
-// the matrix cores badly).
+// All layers and their gradients run on the matrix cores: the two 16 -> 16
+// layers as implicit GEMMs (conv16_kernel: per wavefront a 16-channel x 16-voxel
+// output block accumulates 27 taps of (16 out x 16 in) weights times (16 in x 16
+// voxels) inputs, one tap an instruction in the forward pass, two in the input
+// gradient); their weight gradients as sums over voxels of 16 x 16 outer products
+// per tap, 32 voxels an instruction (wgrad16_kernel); the one-channel layers with
+// their 27 taps as the K dimension or as output rows (one_channel_kernel,
+// conv_out_kernel, wgrad1_kernel).
 //
 // Parameter layout (FP32 masters, PyTorch conv3d order [Cout][Cin][3][3][3]):
 //   w1[16][1][27] b1[16] w2[16][16][27] b2[16] w3[16][16][27] b3[16] w4[1][16][27] b4[1]
@@ -38,9 +39,9 @@ static_assert(NPARAM == 14737, "parameter count");
 typedef short bf16x4 __attribute__((ext_vector_type(4)));
 typedef float f32x4 __attribute__((ext_vector_type(4)));
 
-// Prepared weights (device): rounded FP32 copies for the VALU layers and the
-// per-lane MFMA operand blocks of the 16 -> 16 layers, forward and transposed/
-// flipped (input gradient).
+// Prepared weights (device): float copies, rounded to bfloat16 values, for the
+// one-channel layers and the per-lane MFMA operand blocks of the 16 -> 16 layers,
+// forward and transposed/flipped (input gradient).
 struct Prep {
     float w1[C][NT];       // [co][tap]
     float b1[C];

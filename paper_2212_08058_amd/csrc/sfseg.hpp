@@ -317,6 +317,10 @@ __device__ __forceinline__ float fma3(float g, float v, float c) {
 // multiply-add with another destination), so the ring needs no index and the
 // frame loop no unrolling (3 x 11 slots would unroll to more than the
 // instruction cache).
+// Bound by the matrix cores and by what does not run beside them: on the 210
+// occupied CUs (r = (15, 5), 117 KB of LDS each) they are busy 50% of the time,
+// the vector ALU 22% and the LDS 20%, and two barriers a frame with one workgroup
+// per CU leave the loads, staging and t-pass little of the y-pass to hide behind.
 template <int RT, int TH, int TW, int NTHR, int PAD>
 struct SfsegMfma {
     static constexpr int MB = TH / 16, NB = TW / 16;            // output blocks down / across
@@ -541,7 +545,7 @@ __global__ __launch_bounds__(NTHR) void sfseg_mfma_kernel(SfsegArgs<float> a) {
 // >= 0 when s >= 0 and alpha (max f - min f)^2 <= 1. Per-block min f, max f,
 // min s into partials[3 b .. 3 b + 2]; a NaN anywhere gives NaNs.
 // One read of both volumes, 16-byte chunks with two of each in flight per
-// thread (196 us element by element on 256 workgroups at 64x480x854, 40 us now).
+// thread (196 us element by element on 256 workgroups at 64x480x854, 42 us now).
 constexpr int SFSEG_RANGE_BLOCKS = 1024;
 struct SfsegRange {
     double fmn, fmx, smn;
