@@ -26,15 +26,22 @@
 // loads, then the matrix-core products of both passes (they read buffers
 // written before the phase's barrier), then does the vector work (staging,
 // t-ring, epilogue) while those run, and stores the y-pass result last.
-// Loads, products, staging and the y-pass store run in every phase, also in the
-// first and last ones where a frame does not exist: what they then write is
-// rewritten before it is read, and without branches around them a phase is one
+// Loads, products, staging and the y-pass store run in every phase of the loop,
+// also in the last ones where a frame does not exist: what they then write is
+// not read, and without branches around them a phase is one
 // stretch of code that the compiler schedules as a whole (with the two-step
 // split below, a step of 64x480x854 at r = (15, 5) 111 -> 105 us in float and 91
 // -> 86 in bfloat16). Nothing binds a phase alone at this size: without the
 // products and their LDS reads it takes 9% less, without the staging loads 17%,
 // with all loads hitting the L2 14%; two wavefronts per SIMD, the most the ring
 // leaves registers for, overlap the rest only in part.
+// A clip of few frames is mostly first and last phases. The first two, with no
+// frame to x-filter, run before the loop with what they have. Past the clip's
+// last frame only the epilogue is left: TAIL_APART branches around the rest (one
+// step, r = (15, 5), whole call: 5x49x100 36.6 -> 29.8 us, 7x411x326 56.6 -> 49.0;
+// 12 iterations of 5x112x783 382 -> 335). In bfloat16 that branch makes every
+// phase wait for loads it need not wait for (20 iterations at 64x480x854 1720 ->
+// 2190 us), and the phases stay whole.
 // Per frame:
 //   stage:  u' on the (TH + 2 PAD) x (TW + 2 PAD) slab around the tile (PAD =
 //           8 or 16, at least the space radius), split into
@@ -264,7 +271,15 @@ __device__ __forceinline__ float4_t mfma_xblock_mma(const _Float16 *Y, int b, in
 // plane of raw bfloat16 with no conversion at staging, and the y-pass takes
 // umul into its taps (bfloat16 products, mfma_yblock_mma_bf16). The result
 // is stored in bfloat16, so taps with about 16 significant bits suffice.
-template <class CT, int RT, int TH, int TW, int NTHR, int PAD, bool EXACT = false, class Op>
+// YACC_OUT: the y-pass results are one set of variables for all phases instead
+// of a phase's own. The values are the same and the registers are allocated
+// otherwise; whichever measured faster: one set in the float steps (40
+// iterations at 21x233x347, r = (8, 3): 874 against 891 us) and the bfloat16
+// 32x64 tile (28 at 16x205x231, r = (15, 5): 0.90 against 0.98 ms), a phase's own
+// in the bfloat16 32x128 tile (20 at 64x480x854: 1720 against 1790 us) and the
+// batch (48 clips, 582 M voxels, 50 iterations: 99.6 against 105 ms).
+template <class CT, int RT, int TH, int TW, int NTHR, int PAD, bool TAIL_APART, bool YACC_OUT, bool EXACT = false,
+          class Op>
 __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &tp, const float *tapl, float umul,
                                                   int rs, int T, int t0, int t1, int H, int W, int x0, int y0,
                                                   float *lds, double &d1, double &d2) {
@@ -354,7 +369,6 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
     op.template fetch<NPF>(fw.in(0), poff, pf);
     typename Op::template OutRaw<XPW, 4> oraw;
 
-    const int nphase = fw.nstep + 2;
     const float one = opaque(1.f);
     auto stage = [&](int p) __attribute__((always_inline)) {
         _Float16 *U = U0 + (p & 1) * G::UBUF;
@@ -384,59 +398,73 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
         }
         op.template fetch<NPF>(fw.in(p + 1), poff, pf, p + 1 < nin);
     };
-    ring_loop<NTS, -2>(nphase, [&](auto ring_pos, int p) __attribute__((always_inline)) {
+    // y-pass products of frame k (its U buffer was written before the last
+    // barrier), and their store
+    auto each_yblock = [&](auto &&f) __attribute__((always_inline)) {
+#pragma unroll
+        for (int m = 0; m < G::YPW; ++m) {
+            const int b = wid + m * G::NWAVE;
+            if (G::NYB % G::NWAVE == 0 || m < G::YPW - 1 || b < G::NYB) f(m, b);
+        }
+    };
+    auto ypass = [&](int k, float4_t (&ya)[G::YPW]) __attribute__((always_inline)) {
+        const _Float16 *U = U0 + (k & 1) * G::UBUF;
+        each_yblock([&](int m, int b) __attribute__((always_inline)) {
+            if constexpr (EXACT)
+                ya[m] = mfma_yblock_mma_bf16<G>(U, b, lane, bhi, blo);
+            else
+                ya[m] = mfma_yblock_mma<G>(U, b, lane, thi, tlo);
+        });
+    };
+    auto ystore = [&](int k, const float4_t (&ya)[G::YPW]) __attribute__((always_inline)) {
+        _Float16 *Y = Y0 + (k & 1) * G::YBUF;
+        each_yblock([&](int m, int b) __attribute__((always_inline)) { mfma_yblock_store<G>(Y, b, lane, ya[m], one); });
+    };
+    float4_t yo[G::YPW];
+    // ring step k: the phase that stages frame k + 2, y-filters frame k + 1 and
+    // x-filters frame k
+    auto phase = [&](auto ring_pos, int k) __attribute__((always_inline)) {
         constexpr int J = decltype(ring_pos)::value;
-        const int tx = p - 2;
-        const int tout = fw.out(tx);
-        const bool emit = tx >= 0 && tout >= t0 && tout < t1;
-        const bool xlive = tx >= 0 && tx < nin;
+        const int tout = fw.out(k);
+        const bool emit = tout >= t0 && tout < t1;
         // the epilogue's loads go first: they have the whole phase to arrive.
         // Both load groups are issued in every phase (on an empty range when
         // not needed) so that the memory-counter waits before each use allow
         // for the younger group instead of draining it.
         op.template fetch_out<XPW, 4>(tout, ooff, oraw, emit);
-        // matrix-core products of both passes (frames p - 2 and p - 1; the
-        // buffers they read were written before the last barrier), issued
-        // before the vector work of the phase so that they run beside it
+        CT v[XPW][4];
+        if (TAIL_APART && k >= nin) {  // v is not read
+            ring_step<J, CT, RT, XPW, 4>(acc, v, tp, false, emit, tout, op, ooff, oraw, d1, d2);
+            return;
+        }
+        // matrix-core products of both passes (the buffers they read were
+        // written before the last barrier), issued before the vector work of
+        // the phase so that they run beside it
         float4_t xa[XPW];
         {
-            const _Float16 *Y = Y0 + (tx & 1) * G::YBUF;
+            const _Float16 *Y = Y0 + (k & 1) * G::YBUF;
 #pragma unroll
             for (int i = 0; i < XPW; ++i) xa[i] = mfma_xblock_mma<G>(Y, wid * XPW + i, lane, thi, tlo);
         }
-        float4_t ya[G::YPW];
-        {
-            const _Float16 *U = U0 + ((p - 1) & 1) * G::UBUF;
+        float4_t yl[G::YPW];
+        float4_t(&ya)[G::YPW] = YACC_OUT ? yo : yl;
+        ypass(k + 1, ya);
+        stage(k + 2);
 #pragma unroll
-            for (int m = 0; m < G::YPW; ++m) {
-                const int b = wid + m * G::NWAVE;
-                if (G::NYB % G::NWAVE == 0 || m < G::YPW - 1 || b < G::NYB) {
-                    if constexpr (EXACT)
-                        ya[m] = mfma_yblock_mma_bf16<G>(U, b, lane, bhi, blo);
-                    else
-                        ya[m] = mfma_yblock_mma<G>(U, b, lane, thi, tlo);
-                }
-            }
-        }
-        stage(p);
-        {
-            CT v[XPW][4];
+        for (int i = 0; i < XPW; ++i)
 #pragma unroll
-            for (int i = 0; i < XPW; ++i)
-#pragma unroll
-                for (int q = 0; q < 4; ++q) v[i][q] = xa[i][q];
-            ring_step<J, CT, RT, XPW, 4>(acc, v, tp, xlive, emit, tout, op, ooff, oraw, d1, d2);
-        }
-        {
-            _Float16 *Y = Y0 + ((p - 1) & 1) * G::YBUF;
-#pragma unroll
-            for (int m = 0; m < G::YPW; ++m) {
-                const int b = wid + m * G::NWAVE;
-                if (G::NYB % G::NWAVE == 0 || m < G::YPW - 1 || b < G::NYB) mfma_yblock_store<G>(Y, b, lane, ya[m], one);
-            }
-        }
+            for (int q = 0; q < 4; ++q) v[i][q] = xa[i][q];
+        ring_step<J, CT, RT, XPW, 4>(acc, v, tp, TAIL_APART || k < nin, emit, tout, op, ooff, oraw, d1, d2);
+        ystore(k + 1, ya);
         __syncthreads();
-    });
+    };
+    stage(0);
+    __syncthreads();
+    ypass(0, yo);
+    stage(1);
+    ystore(0, yo);
+    __syncthreads();
+    ring_loop<NTS, 0>(fw.nstep, phase);
 }
 
 }  // namespace stpi

@@ -639,3 +639,31 @@ def test_default_tile_among_the_matrix_core_variants(P, dtype, kp, shape, tile):
             N.lib.stpi_set_variant(-1)
         d = float((x.double() - y.double()).abs().max() / x.double().abs().max())
         assert d <= (1e-6 if dtype == torch.float32 else 2.0 ** -7)
+
+
+@pytest.mark.parametrize("T", [1, 2, 4, 6, 7, 11, 12, 23])
+@pytest.mark.parametrize("kp", [(5.0, 2.0, 15, 5), (4.0, 1.5, 8, 3)])
+def test_clips_of_few_frames(P, kp, T):
+    """First and last phases of a tile: clips below the time radius, at the
+    length of the ring of open output frames and one past it, and twice that,
+    whole and in segments; a step and a two-step chain, frame by frame."""
+    from paper_2212_08058_amd import _native as N
+    k = P.Kernel(*kp)
+    g = torch.Generator().manual_seed(100 + T)
+    for dtype, code, tol in ((torch.float32, N.STPI_F32, 1e-5), (torch.bfloat16, N.STPI_BF16, 2.0 ** -7)):
+        f = torch.rand((T, 37, 141), generator=g).to(dtype)
+        x = torch.rand((T, 37, 141), generator=g).to(dtype)
+        fn, xn = f.double().numpy(), x.double().numpy()
+        zr = oracle.apply(fn, xn, OKf(k))
+        yr, _ = oracle.iterate(fn, OKf(k), iters=2, x0=xn)
+        for i, vi in mfma_variants(code):
+            if vi[0] < k.r_s or vi[1] < k.r_t:
+                continue
+            with forced(i):
+                z, _ = P.step(f.to(DEV), x.to(DEV), k)
+                y, _ = P.power_iterate(f.to(DEV), k, iters=2, x0=x.to(DEV))
+                torch.cuda.synchronize()
+            z, y = z.double().cpu().numpy(), y.double().cpu().numpy()
+            print(T, kp, dtype, vi[:5], [f"{rel_l2(z[t], zr[t]):.1e}/{rel_l2(y[t], yr[t]):.1e}" for t in range(T)])
+            for t in range(T):
+                assert rel_l2(z[t], zr[t]) <= tol and rel_l2(y[t], yr[t]) <= tol, (i, t)
