@@ -177,8 +177,8 @@ void batch_step_kernel(BatchArgs<ST> a) {
                     pp.sg = ldexpf(1.f, ein - 10 - 2 * e);
                     umul = (float)(st_->scale * ldexp(1.0, 10 - ein) * pp.ginv_in);
                 }
-                stencil_tile_mfma<CT, RT, TH, TW, NTHR, PAD, false, false, EXACT>(pp, a.taps, tapl, umul, a.rs, T, 0, T,
-                                                                                  H, W, tx0, ty0, lds, d1, d2);
+                stencil_tile_mfma<CT, RT, TH, TW, NTHR, PAD, TAIL_WHOLE, false, EXACT>(
+                    pp, a.taps, tapl, umul, a.rs, T, 0, T, H, W, tx0, ty0, lds, d1, d2);
                 d1 *= pp.ginv_in * pp.ginv_out;
                 d2 *= pp.ginv_out * pp.ginv_out;
                 const float m = block_max<NTHR>(pp.wmax, reinterpret_cast<float *>(red));

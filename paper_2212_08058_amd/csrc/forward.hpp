@@ -488,7 +488,8 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
             tapl[threadIdx.x] = g;
         }
         __syncthreads();
-        constexpr bool TAIL_APART = sizeof(ST) == 4, YACC_OUT = sizeof(ST) == 4 || TW == 64;
+        constexpr bool YACC_OUT = sizeof(ST) == 4 || TW == 64;
+        constexpr MfmaTail TAIL = sizeof(ST) == 4 ? TAIL_APART : !PF && TW == 64 ? TAIL_BY_LENGTH : TAIL_WHOLE;
         // staging multiplier umul = scale 2^S with |f x scale 2^S| < 2^10, output scale 2^-S
         float bound = __uint_as_float(a.state ? st.ubound : *a.ubound);
         if constexpr (PF) {
@@ -522,7 +523,7 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
                 pp.sg = ldexpf(1.f, ein - 10 - 2 * e);
                 umul = (float)(scale * ldexp(1.0, 10 - ein) * pp.ginv_in);
             }
-            stencil_tile_mfma<CT, RT, TH, TW, NTHR, PAD, TAIL_APART, YACC_OUT, EXACT>(
+            stencil_tile_mfma<CT, RT, TH, TW, NTHR, PAD, TAIL, YACC_OUT, EXACT>(
                 pp, a.taps, tapl, umul, a.rs, a.T, t0, t1, a.H, a.W, x0, y0, lds, d1, d2);
             d1 *= pp.ginv_in * pp.ginv_out;
             d2 *= pp.ginv_out * pp.ginv_out;
@@ -532,8 +533,8 @@ __global__ __launch_bounds__(NTHR, OCC) void fwd_step_kernel(FwdArgs<ST> a) {
             const int e = bound_exponent(bound, 100);
             const float umul = (float)(scale * ldexp(1.0, 10 - e));
             op.scale = ldexpf(1.f, e - 10);
-            stencil_tile_mfma<CT, RT, TH, TW, NTHR, PAD, TAIL_APART, YACC_OUT>(op, a.taps, tapl, umul, a.rs, a.T, t0,
-                                                                               t1, a.H, a.W, x0, y0, lds, d1, d2);
+            stencil_tile_mfma<CT, RT, TH, TW, NTHR, PAD, TAIL, YACC_OUT>(op, a.taps, tapl, umul, a.rs, a.T, t0, t1, a.H,
+                                                                         a.W, x0, y0, lds, d1, d2);
         }
     } else if constexpr (PIPE == 4) {
         int t = t0;

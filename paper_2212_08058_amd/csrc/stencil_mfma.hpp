@@ -38,10 +38,13 @@
 // A clip of few frames is mostly first and last phases. The first two, with no
 // frame to x-filter, run before the loop with what they have. Past the clip's
 // last frame only the epilogue is left: TAIL_APART branches around the rest (one
-// step, r = (15, 5), whole call: 5x49x100 36.6 -> 29.8 us, 7x411x326 56.6 -> 49.0;
+// step, r = (15, 5), whole call: 5x49x100 36.6 -> 29.4 us, 7x411x326 56.6 -> 49.0;
 // 12 iterations of 5x112x783 382 -> 335). In bfloat16 that branch makes every
 // phase wait for loads it need not wait for (20 iterations at 64x480x854 1720 ->
-// 2190 us), and the phases stay whole.
+// 2190 us), and the phases stay whole; a single step on the 32x64 tile has both
+// loops and takes the one with the branch where such phases are at least a
+// quarter of the input frames (5x177x141 31.7 -> 29.1 us, 4x274x69 29.0 -> 26.4,
+// 12x74x486 40.0 either way; on the 32x128 tile two loops spill: 38.5 -> 50.0).
 // Per frame:
 //   stage:  u' on the (TH + 2 PAD) x (TW + 2 PAD) slab around the tile (PAD =
 //           8 or 16, at least the space radius), split into
@@ -261,6 +264,10 @@ __device__ __forceinline__ float4_t mfma_xblock_mma(const _Float16 *Y, int b, in
     return acc;
 }
 
+// The phases past the clip's last frame: the whole phase, only the epilogue, or
+// the one of the two that suits the segment's length (two loops in the kernel).
+enum MfmaTail { TAIL_WHOLE, TAIL_APART, TAIL_BY_LENGTH };
+
 // Streams one tile through frames [t0, t1) (reading [t0 - RT, t1 + RT) clipped
 // to the clip). Op is the forward step's FwdOp; umul = scale * 2^S multiplies
 // f * x at staging and op.scale must be 2^-S. rs is the problem's space
@@ -278,7 +285,7 @@ __device__ __forceinline__ float4_t mfma_xblock_mma(const _Float16 *Y, int b, in
 // 32x64 tile (28 at 16x205x231, r = (15, 5): 0.90 against 0.98 ms), a phase's own
 // in the bfloat16 32x128 tile (20 at 64x480x854: 1720 against 1790 us) and the
 // batch (48 clips, 582 M voxels, 50 iterations: 99.6 against 105 ms).
-template <class CT, int RT, int TH, int TW, int NTHR, int PAD, bool TAIL_APART, bool YACC_OUT, bool EXACT = false,
+template <class CT, int RT, int TH, int TW, int NTHR, int PAD, MfmaTail TAIL, bool YACC_OUT, bool EXACT = false,
           class Op>
 __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &tp, const float *tapl, float umul,
                                                   int rs, int T, int t0, int t1, int H, int W, int x0, int y0,
@@ -423,8 +430,9 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
     float4_t yo[G::YPW];
     // ring step k: the phase that stages frame k + 2, y-filters frame k + 1 and
     // x-filters frame k
-    auto phase = [&](auto ring_pos, int k) __attribute__((always_inline)) {
+    auto phase = [&](auto ring_pos, int k, auto tail) __attribute__((always_inline)) {
         constexpr int J = decltype(ring_pos)::value;
+        constexpr bool APART = decltype(tail)::value;
         const int tout = fw.out(k);
         const bool emit = tout >= t0 && tout < t1;
         // the epilogue's loads go first: they have the whole phase to arrive.
@@ -433,7 +441,7 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
         // for the younger group instead of draining it.
         op.template fetch_out<XPW, 4>(tout, ooff, oraw, emit);
         CT v[XPW][4];
-        if (TAIL_APART && k >= nin) {  // v is not read
+        if (APART && k >= nin) {  // v is not read
             ring_step<J, CT, RT, XPW, 4>(acc, v, tp, false, emit, tout, op, ooff, oraw, d1, d2);
             return;
         }
@@ -454,7 +462,7 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
         for (int i = 0; i < XPW; ++i)
 #pragma unroll
             for (int q = 0; q < 4; ++q) v[i][q] = xa[i][q];
-        ring_step<J, CT, RT, XPW, 4>(acc, v, tp, TAIL_APART || k < nin, emit, tout, op, ooff, oraw, d1, d2);
+        ring_step<J, CT, RT, XPW, 4>(acc, v, tp, APART || k < nin, emit, tout, op, ooff, oraw, d1, d2);
         ystore(k + 1, ya);
         __syncthreads();
     };
@@ -464,7 +472,17 @@ __device__ __forceinline__ void stencil_tile_mfma(const Op &op, const Taps<CT> &
     stage(1);
     ystore(0, yo);
     __syncthreads();
-    ring_loop<NTS, 0>(fw.nstep, phase);
+    auto run = [&](auto tail) __attribute__((always_inline)) {
+        ring_loop<NTS, 0>(fw.nstep, [&](auto ring_pos, int k) __attribute__((always_inline)) { phase(ring_pos, k, tail); });
+    };
+    if constexpr (TAIL == TAIL_BY_LENGTH) {
+        if (4 * (fw.nstep - nin) >= nin)
+            run(std::true_type{});
+        else
+            run(std::false_type{});
+    } else {
+        run(std::bool_constant<TAIL == TAIL_APART>{});
+    }
 }
 
 }  // namespace stpi
