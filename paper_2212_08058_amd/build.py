@@ -45,15 +45,17 @@ def build(jobs: int | None = None) -> str:
     os.makedirs(BUILD, exist_ok=True)
     srcs = sources()
     jobs = jobs or min(len(srcs), max(1, (os.cpu_count() or 4)))
-    with cf.ThreadPoolExecutor(jobs) as ex:
-        objs = list(ex.map(_compile, srcs))
     # host-side check of the generated device code, loaded by path: importing the
     # package would load the library that is being built
     import importlib.util
     spec = importlib.util.spec_from_file_location("stpi_isa_check", os.path.join(HERE, "isa_check.py"))
     mod = importlib.util.module_from_spec(spec)
     spec.loader.exec_module(mod)
-    mod.check_device_code(srcs, jobs, HIPCC, FLAGS, BUILD)
+    # beside the compilation: each waits mostly for its one or two largest sources
+    with cf.ThreadPoolExecutor(jobs) as ex, cf.ThreadPoolExecutor(1) as beside:
+        check = beside.submit(mod.check_device_code, srcs, jobs, HIPCC, FLAGS, BUILD)
+        objs = list(ex.map(_compile, srcs))
+        check.result()
     tmp = LIB + ".tmp"
     cmd = [HIPCC, f"--offload-arch={ARCH}", "-shared", "-fPIC", "-o", tmp, *objs]
     r = subprocess.run(cmd, capture_output=True, text=True)
